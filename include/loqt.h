@@ -121,6 +121,8 @@ loqt_status nf4_dequantize(const uint8_t *codes, const float *absmax, int64_t ro
  *          V = s x deq(Q_q) (T x r bf16) and fp32 slices of dBp
  *   FWD_NQ, BWD_NQ: the unquantised variant below: U resp. Z (T x r bf16), the fp32 slices of dB and
  *          the folded weight (out x in bf16)
+ *   plus, in the forward and backward calls, fp32 slices of the products that would otherwise leave compute units idle
+ *   (few tokens, narrow outputs).  A workspace without room for those is accepted; the call then runs with fewer slices.
  */
 size_t loqt_workspace_bytes(int op, int64_t T, int64_t out, int64_t in, int64_t r);
 

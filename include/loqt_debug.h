@@ -46,8 +46,8 @@ int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in);
 /*
  * Tile-shape option (process-wide, not thread-safe; for tests and tuning).  The products of the
  * pre-pass family (every product of the layer calls of sec. 2.2 / 2.4 and the merge of Alg. 1 line 5
- * when it takes that path) run on work-group tiles of 256x256, 256x128 or 128x128 outputs, chosen from
- * the sizes.  LOQT_TILE_AUTO keeps that choice; the other values force one shape for every such product
+ * when it takes that path) run on work-group tiles of 256x256 outputs or less (loqt_plan_tiles lists the shapes),
+ * chosen from the sizes.  LOQT_TILE_AUTO keeps that choice; the other values force one shape for every such product
  * whatever its size (the compensation step of Alg. 2 and the dense merge always use 128x128).  All
  * shapes compute the same quantities; results differ only in summation order.  Returns
  * LOQT_INVALID_ARG for any other value.
@@ -63,6 +63,13 @@ loqt_status loqt_set_tile(int tile);
  * 256x256 tiles.  Either pointer may be NULL.  Returns LOQT_BAD_SHAPE for M, N <= 0 or Nx < 0.
  */
 loqt_status loqt_plan_product(int64_t M, int64_t N, int64_t Nx, int64_t *n_large, double *rounds);
+/*
+ * Diagnostic (host only): tile shape and number of slices of the contraction of an M x N product over K that does not
+ * run on 256x256 tiles by the plan above (fewer than 224 such tiles, or K < 2048), with at most max_splits slices.
+ * sliced != 0: the result is summed from fp32 slices in any case (dB).  *tile: 1 = 256x256, 2 = 256x128,
+ * 3 = 128x128, 4 = 128x128 with a ring of four stages, 5 = 64x128, 6 = 64x64.  Either pointer may be NULL.
+ */
+loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max_splits, int *tile, int *splits);
 
 /*
  * Optional per-kernel timing (diagnostics for benchmarks; off by default).

@@ -114,6 +114,8 @@ lib.loqt_set_path.restype = _i
 lib.loqt_set_path.argtypes = [_i]
 lib.loqt_plan_product.restype = _i
 lib.loqt_plan_product.argtypes = [_i64, _i64, _i64, _P(_i64), _P(C.c_double)]
+lib.loqt_plan_tiles.restype = _i
+lib.loqt_plan_tiles.argtypes = [_i64, _i64, _i64, _i, _i, _P(_i), _P(_i)]
 lib.loqt_set_tile.restype = _i
 lib.loqt_set_tile.argtypes = [_i]
 lib.loqt_resolved_path.restype = _i
@@ -415,6 +417,13 @@ def plan_product(M: int, N: int, Nx: int = 0):
     c = C.c_double(0.0)
     _check(lib.loqt_plan_product(M, N, Nx, C.byref(n), C.byref(c)), "loqt_plan_product")
     return int(n.value), float(c.value)
+
+
+def plan_tiles(M: int, N: int, K: int, sliced: bool = False, max_splits: int = 32):
+    """(tile shape, slices of the contraction) of a product that takes no 256x256 plan -- host only."""
+    t, n = _i(0), _i(0)
+    _check(lib.loqt_plan_tiles(M, N, K, 1 if sliced else 0, max_splits, C.byref(t), C.byref(n)), "loqt_plan_tiles")
+    return t.value, n.value
 
 
 def set_tile(tile: int) -> None:

@@ -132,13 +132,11 @@ size_t bwd_z_bytes(int64_t T, int64_t r) { return bf16_bytes(T, r); }
 // Workspace layouts of the pre-pass family.  Products take their operands in whichever orientation
 // they are stored (rows x K or K x rows), so nothing is ever transposed: the only pre-passes are NF4
 // expansions, one per NF4 operand and call.
-// Number of slices of the contraction for a product whose result is summed from fp32 slices (dB = Z^T x and its
-// relatives: M x N outputs, contraction K).  Estimated duration in k-tile steps: rounds of work-groups (256 tiles
-// of 256x128 with one work-group per compute unit from 512 rows up, 512 tiles of 128x128 with two per unit below;
-// the launcher makes the same choice) times the k-tiles per slice plus a fixed prologue / epilogue, plus the slices'
-// own traffic (each is written once and read once by the reduction: M N 8 bytes against the ~12 MB the chip moves
-// in one k-tile step when the slices stay in the Infinity Cache).  A slice is at least 512 deep.
-int choose_splits(int64_t M, int64_t N, int64_t K) {
+// A product that leaves compute units idle runs in fp32 slices of its contraction (plan_nt in gemm_nt.hip), and the
+// slices live in the workspace.  loqt_workspace_bytes counts room for the best plan; a call accepts less, down to
+// `least`, and then plans with the slices it has room for.  `least` holds the slices of dB (M x N outputs, contraction
+// K) that this older estimate asks for, in k-tile steps.
+int least_splits(int64_t M, int64_t N, int64_t K) {
     auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     const bool wide = M >= 512;
     const int64_t tiles = wide ? cdiv(M, 256) * cdiv(N, 128) : cdiv(M, 128) * cdiv(N, 128);
@@ -154,51 +152,55 @@ int choose_splits(int64_t M, int64_t N, int64_t K) {
     }
     return best;
 }
-
-// Z = s dy deq(P) (T x r outputs, contraction over `out`) in two fp32 slices of the contraction when its 256x128
-// tiles would fill no more than half of the compute units (1B block: 8192 x 512; 13B block: 4096 x 1024): twice
-// the work-groups at half the depth, then the fixed-order sum of the slices into bf16.  1 = one bf16 product.
-int z_splits(int64_t T, int64_t out, int64_t r) {
+// ... and, for Z = s dy deq(P) (T x r outputs, contraction over `out`), two slices where its 256x128 tiles number
+// 64 to 128
+int least_z_splits(int64_t T, int64_t out, int64_t r) {
     if (T < 512 || out < 2048) return 1;
     const int64_t tiles = ((T + 255) / 256) * ((r + 127) / 128);
     return (tiles >= 64 && tiles <= 128) ? 2 : 1;
 }
+// slices of an M x N sum over K of which `room` bytes hold the fp32 values (pitch ldp)
+int planned_splits(int64_t M, int64_t N, int64_t K, int64_t ldp, size_t room) {
+    const int64_t fit = (int64_t)(room / ((size_t)M * (size_t)ldp * 4));
+    return plan_nt(M, N, (K + 63) / 64, true, 1, (int)std::min<int64_t>(std::max<int64_t>(fit, 1), NT_MAX_SPLITS)).splits;
+}
+size_t slices_bytes(int64_t splits, int64_t M, int64_t ldp) { return round_up((size_t)splits * (size_t)M * (size_t)ldp * 4, 256); }
 
 // `saved`: the caller keeps W_eff in a buffer of its own (loqt_linear_fwd_save / loqt_linear_bwd_saved), so the
 // workspace holds no copy of the weight (and the forward pass, always folded then, no U)
 struct FwdWs {
-    size_t U, Wb, Pb, split, total;  // U = s x B^T; Wb = deq(W) or W_eff; Pb = deq(P); slices of y's column remainder
-    int64_t split_floats;
+    size_t U, Wb, Pb, split, least, total;  // U = s x B^T; Wb = deq(W) or W_eff; Pb = deq(P); slices of U, then of y
     FwdWs(int64_t T, int64_t out, int64_t in, int64_t r, bool saved = false) {
         U = 0;
         Wb = U + (saved ? 0 : bf16_bytes(T, r));
         Pb = Wb + (saved ? 0 : bf16_bytes(out, in));
         split = Pb + bf16_bytes(out, r);
-        split_floats = remainder_split_floats(T, out);
-        total = split + round_up((size_t)split_floats * 4, 256);
+        least = split + round_up((size_t)remainder_split_floats(T, out) * 4, 256);
+        // (whichever form runs: the size does not depend on the path option)
+        int64_t most = product_split_floats(T, out, in, 0);
+        if (!saved) most = std::max({most, product_split_floats(T, r, in, 0), product_split_floats(T, out, in, r)});
+        total = std::max(least, split + round_up((size_t)most * 4, 256));
     }
 };
 struct BwdWs {
-    size_t Z, Wb, Pb, partials, total;  // Z = s dy deq(P); Wb = deq(W) or W_eff; Pb = deq(P); fp32 slices
-    int splits, zsplits;                // slices of dB; slices of Z (1: none)
-    int64_t ldp, ldzp;
+    size_t Z, Wb, Pb, partials, least, total;  // Z = s dy deq(P); Wb = deq(W) or W_eff; Pb = deq(P); fp32 slices
+    int64_t ldp;
     BwdWs(int64_t T, int64_t out, int64_t in, int64_t r, bool saved = false) {
         Z = 0;
         Wb = Z + bf16_bytes(T, r);
         Pb = Wb + (saved ? 0 : bf16_bytes(out, in));
         partials = Pb + bf16_bytes(out, r);
         ldp = (int64_t)round_up(in, 4);
-        splits = choose_splits(r, in, T);
-        ldzp = (int64_t)round_up(r, 4);
-        zsplits = z_splits(T, out, r);
-        // the slices of Z are summed into Z before the dB product writes its own: one region serves both
-        const size_t db_bytes = (size_t)splits * (size_t)r * (size_t)ldp * 4;
-        const size_t z_bytes = zsplits > 1 ? (size_t)zsplits * (size_t)T * (size_t)ldzp * 4 : 0;
-        // ... and so can the slices of dx's column remainder, which are summed before dB starts
-        const size_t dx_bytes = (size_t)remainder_split_floats(T, in) * 4;
-        size_t most = db_bytes > z_bytes ? db_bytes : z_bytes;
-        if (dx_bytes > most) most = dx_bytes;
-        total = partials + round_up(most, 256);
+        const int64_t ldzp = (int64_t)round_up(r, 4);
+        // the slices of Z are summed into Z before those of dx are written, and both before the dB product writes
+        // its own: one region serves all three
+        const int least_z = least_z_splits(T, out, r);
+        least = partials + std::max({slices_bytes(least_splits(r, in, T), r, ldp),
+                                     least_z > 1 ? slices_bytes(least_z, T, ldzp) : (size_t)0,
+                                     round_up((size_t)remainder_split_floats(T, in) * 4, 256)});
+        const int64_t dx = std::max(product_split_floats(T, in, out, 0), product_split_floats(T, in, out, r));
+        total = std::max({least, partials + slices_bytes(planned_splits(r, in, T, ldp, ~(size_t)0), r, ldp),
+                          partials + round_up((size_t)std::max(dx, product_split_floats(T, r, out, 0)) * 4, 256)});
     }
 };
 struct MergeWs {
@@ -213,8 +215,7 @@ struct MergeWs {
 // compensation loop: Pb = bf16(P) (out x r), E = W - deq(Q_c) (out x round_up(in, 64), bf16),
 // fp32 slices of B = P^T E over the contraction along `out`
 struct InitWs {
-    size_t Pb, E, partials, total;
-    int splits;
+    size_t Pb, E, partials, least, total;
     int64_t ldp, lde, ldr;
     InitWs(int64_t out, int64_t in, int64_t r) {
         ldr = (int64_t)round_up(r, 8);
@@ -223,30 +224,52 @@ struct InitWs {
         Pb = 0;
         E = Pb + round_up((size_t)out * (size_t)ldr * 2, 256);
         partials = E + round_up((size_t)out * (size_t)lde * 2, 256);
-        splits = choose_splits(r, in, out);
-        total = partials + round_up((size_t)splits * (size_t)r * (size_t)ldp * 4, 256);
+        least = partials + slices_bytes(least_splits(r, in, out), r, ldp);
+        total = std::max(least, partials + slices_bytes(planned_splits(r, in, out, ldp, ~(size_t)0), r, ldp));
+    }
+};
+
+// LoQT-nq: U or Z (T x r) first, then the dB slices (backward), then room for the folded weight W_eff (out x in, bf16),
+// whether or not the path option makes this call fold, then the slices of U or Z and of y or dx
+struct NqWs {
+    size_t partials, We, split, total;
+    int64_t ldp;
+    NqWs(bool bwd, int64_t T, int64_t out, int64_t in, int64_t r) {
+        partials = bf16_bytes(T, r);
+        ldp = (int64_t)round_up(in, 4);
+        // the region of the dB slices is as large as loqt_linear_bwd's least workspace makes it
+        const BwdWs L(T, out, in, r);
+        We = partials + (bwd ? L.least - L.partials : 0);
+        split = We + bf16_bytes(out, in);
+        int64_t most;
+        if (bwd) most = std::max({product_split_floats(T, r, out, 0), product_split_floats(T, in, out, 0),
+                                  product_split_floats(T, in, out, r), planned_splits(r, in, T, ldp, ~(size_t)0) * r * ldp});
+        else most = std::max({product_split_floats(T, r, in, 0), product_split_floats(T, out, in, 0),
+                              product_split_floats(T, out, in, r)});
+        total = split + round_up((size_t)most * 4, 256);
     }
 };
 
 // right-side variant (W + s Bp Q^T): Qb = deq(Q) (in x r), We = folded weight (out x in), V = s x Qb
 // (T x r), fp32 slices of dBp = dy^T V over the contraction along T
 struct RightWs {
-    size_t Qb, We, V, partials, total;
-    int splits;
+    size_t Qb, We, V, partials, least, total;  // partials: slices of V, of y or dx, of dBp, one after the other
     int64_t ldr, ldw, ldp;
     RightWs(int op, int64_t T, int64_t out, int64_t in, int64_t r) {
         ldr = (int64_t)round_up(r, 8);
         ldw = (int64_t)round_up(in, 8);
         ldp = (int64_t)round_up(r, 4);
-        splits = 1;
         Qb = 0;
         We = Qb + bf16_bytes(in, r);
         V = We + (op == LOQT_OP_MERGE_RIGHT ? 0 : bf16_bytes(out, in));
         partials = V + (op == LOQT_OP_BWD_RIGHT ? bf16_bytes(T, r) : 0);
-        total = partials;
+        least = total = partials;
+        if (op == LOQT_OP_FWD_RIGHT) total += round_up((size_t)product_split_floats(T, out, in, 0) * 4, 256);
         if (op == LOQT_OP_BWD_RIGHT) {
-            splits = choose_splits(out, r, T);
-            total = partials + round_up((size_t)splits * (size_t)out * (size_t)ldp * 4, 256);
+            least = partials + slices_bytes(least_splits(out, r, T), out, ldp);
+            const int64_t v_dx = std::max(product_split_floats(T, r, in, 0), product_split_floats(T, in, out, 0));
+            total = std::max({least, partials + slices_bytes(planned_splits(out, r, T, ldp, ~(size_t)0), out, ldp),
+                              partials + round_up((size_t)v_dx * 4, 256)});
         }
     }
 };
@@ -459,14 +482,8 @@ size_t loqt_workspace_bytes(int op, int64_t T, int64_t out, int64_t in, int64_t 
             if (T <= 0) return 0;
             return RightWs(op, T, out, in, r).total;
         case LOQT_OP_MERGE_RIGHT: return RightWs(op, 0, out, in, r).total;
-        // LoQT-nq: U or Z (T x r) first, then the dB slices (backward), then room for the folded weight
-        // W_eff (out x in, bf16), whether or not the path option makes this call fold
-        case LOQT_OP_FWD_NQ: return T <= 0 ? 0 : bf16_bytes(T, r) + bf16_bytes(out, in);
-        case LOQT_OP_BWD_NQ: {
-            if (T <= 0) return 0;
-            const BwdWs L(T, out, in, r);
-            return bf16_bytes(T, r) + (L.total - L.partials) + bf16_bytes(out, in);
-        }
+        case LOQT_OP_FWD_NQ: return T <= 0 ? 0 : NqWs(false, T, out, in, r).total;
+        case LOQT_OP_BWD_NQ: return T <= 0 ? 0 : NqWs(true, T, out, in, r).total;
         default: return 0;
     }
 }
@@ -483,8 +500,8 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
     LOQT_TRY(check_bf16(y, T, out, ld_y));
     if (!ws) return LOQT_INVALID_ARG;
     if (!aligned(ws, 256)) return LOQT_MISALIGNED;
-    if (ws_bytes < loqt_workspace_bytes(save_weff ? LOQT_OP_FWD_SAVE : LOQT_OP_FWD, T, out, in, r))
-        return LOQT_WORKSPACE_TOO_SMALL;
+    const FwdWs L(T, out, in, r, save_weff != nullptr);
+    if (ws_bytes < L.least) return LOQT_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)hip_stream;
     const int64_t ld_u = (int64_t)round_up(r, 8);
     loqt_bf16* U = reinterpret_cast<loqt_bf16*>(ws);
@@ -492,7 +509,6 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
 
     if (save_weff) LOQT_TRY(check_bf16(save_weff, out, in, ld_save));
     if (save_weff || use_prepass(T)) {
-        const FwdWs L(T, out, in, r, save_weff != nullptr);
         char* base = reinterpret_cast<char*>(ws);
         uint16_t* Wb = save_weff ? save_weff : reinterpret_cast<uint16_t*>(base + L.Wb);
         uint16_t* Pb = reinterpret_cast<uint16_t*>(base + L.Pb);
@@ -513,6 +529,8 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
             p.alpha = s;
             p.C = U;
             p.ldc = ld_u;
+            p.split_ws = reinterpret_cast<float*>(base + L.split);
+            p.split_ws_floats = (int64_t)((ws_bytes - L.split) / 4);
             LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st));
         }
         // y = x Wb^T (+ U deq(P)^T when the rank-r term is not folded into Wb)
@@ -529,7 +547,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
         p.C = y;
         p.ldc = ld_y;
         p.split_ws = reinterpret_cast<float*>(base + L.split);
-        p.split_ws_floats = L.split_floats;
+        p.split_ws_floats = (int64_t)((ws_bytes - L.split) / 4);
         LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Y, EPI_BF16, false, false, p, st));
         return LOQT_OK;
     }
@@ -597,8 +615,10 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
     if (!aligned(dB, dB_dtype == LOQT_BF16 ? 2 : 4)) return LOQT_MISALIGNED;
     if (!ws) return LOQT_INVALID_ARG;
     if (!aligned(ws, 256)) return LOQT_MISALIGNED;
-    if (ws_bytes < loqt_workspace_bytes(saved ? LOQT_OP_BWD_SAVED : LOQT_OP_BWD, T, out, in, r))
-        return LOQT_WORKSPACE_TOO_SMALL;
+    const BwdWs L(T, out, in, r, saved != nullptr);
+    // (the fused form sums as many slices as it likes, in a workspace laid out Z, slices)
+    const size_t fused = bwd_z_bytes(T, r) + round_up((size_t)gemm_db_splits(T, r, in) * (size_t)r * (size_t)in * 4, 256);
+    if (ws_bytes < (saved ? L.least : std::max(L.least, fused))) return LOQT_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)hip_stream;
     const int64_t ld_z = (int64_t)round_up(r, 8);
     loqt_bf16* Z = reinterpret_cast<loqt_bf16*>(ws);
@@ -606,11 +626,11 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
 
     GemmParams p;
     if (saved || use_prepass(T)) {
-        const BwdWs L(T, out, in, r, saved != nullptr);
         char* base = reinterpret_cast<char*>(ws);
         const uint16_t* Wb = saved ? saved : reinterpret_cast<const uint16_t*>(base + L.Wb);
         uint16_t* Pb = reinterpret_cast<uint16_t*>(base + L.Pb);
         float* part = reinterpret_cast<float*>(base + L.partials);
+        const int64_t part_floats = (int64_t)((ws_bytes - L.partials) / 4);
         const int64_t ldw = saved ? ld_saved : (int64_t)round_up(in, 8);
         LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_z, st, SLOT_PREPASS));
         const bool folded = dx && (saved || use_folded_bwd(T, out, in));
@@ -618,16 +638,14 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         // take less time than the two launches: its tiles then fill a partly empty round of the dx product
         bool z_with_dx = false;
         if (folded) {
-            const int64_t tm = (T + 255) / 256, tm128 = (T + 127) / 128;
+            const int64_t tm = (T + 255) / 256;
             const int64_t t_dx = tm * ((in + 255) / 256), t_z = tm * ((r + 255) / 256);
-            // Z alone: 256x256 tiles when they fill the chip, else 128x128 in rounds of 512
-            // (with a long contraction and 224 .. 256 tiles of 256x128 it runs on those: about 0.55 of a round)
-            const int64_t t_z2 = tm * ((r + 127) / 128);
+            // Z alone, in rounds of 256x256 tiles (a k-tile of such a round: 1.56 us): on those when they fill the chip,
+            // else by plan_nt
             const double z_alone = t_z >= 224 ? plan_bf16_product(T, r, 0).cost
-                                   : (out >= 2048 && t_z2 >= 224 && t_z2 <= 256)
-                                       ? 0.55
-                                       : 0.68 * (double)((tm128 * ((r + 127) / 128) + 511) / 512);
-            z_with_dx = t_dx >= 224 && plan_bf16_product(T, in, r).cost < plan_bf16_product(T, in, 0).cost + z_alone;
+                                              : plan_nt(T, r, (out + 63) / 64, false, 1, NT_MAX_SPLITS).cost /
+                                                    (1.56 * (double)((out + 63) / 64) + 8.0);
+            z_with_dx = t_dx >= 224 && out >= 2048 && plan_bf16_product(T, in, r).cost < plan_bf16_product(T, in, 0).cost + z_alone;
         }
         if (!z_with_dx) {
             // Z = s dy deq(P): deq(P) is out x r, i.e. K x rows
@@ -637,17 +655,11 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
             p.M = (int)T;
             p.N = (int)r;
             p.alpha = s;
-            if (L.zsplits > 1 && g_nt_tile_override == 0) {  // (a forced tile shape keeps the single product)
-                p.C = part;
-                p.ldc = L.ldzp;
-                p.splits = L.zsplits;
-                LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_F32_SPLITK, false, true, p, st));
-                LOQT_HIP(launch_reduce_db(part, L.zsplits, T, r, L.ldzp, Z, LOQT_BF16, ld_z, 0, st));
-            } else {
-                p.C = Z;
-                p.ldc = ld_z;
-                LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
-            }
+            p.C = Z;
+            p.ldc = ld_z;
+            p.split_ws = part;
+            p.split_ws_floats = part_floats;
+            LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
         }
         if (dx) {
             // dx = dy Wb (+ Z B when the rank-r term is not folded into Wb); Wb is out x in: K x rows
@@ -678,7 +690,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
                 p.ldcx = ld_z;
             }
             p.split_ws = part;  // (the slices of Z, if any, have been summed by now; those of dB come later)
-            p.split_ws_floats = remainder_split_floats(T, in);
+            p.split_ws_floats = part_floats;
             LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
         }
         // dB = Z^T x: Z is T x r and x is T x in, both K x rows; contraction over T in slices
@@ -690,9 +702,9 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         p.alpha = 1.0f;
         p.C = part;
         p.ldc = L.ldp;
-        p.splits = L.splits;
+        p.splits = planned_splits(r, in, T, L.ldp, ws_bytes - L.partials);
         LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DB, EPI_F32_SPLITK, true, true, p, st));
-        LOQT_HIP(launch_reduce_db(part, L.splits, r, in, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
+        LOQT_HIP(launch_reduce_db(part, p.splits, r, in, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
         return LOQT_OK;
     }
     memset(&p, 0, sizeof(p));
@@ -840,7 +852,8 @@ loqt_status loqt_init_compensate(const float* W, int64_t ld_w, const float* P, i
     if (!ws) return LOQT_INVALID_ARG;
     if (!aligned(ws, 256)) return LOQT_MISALIGNED;
     const InitWs L(out, in, r);
-    if (ws_bytes < L.total) return LOQT_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < L.least) return LOQT_WORKSPACE_TOO_SMALL;
+    const int splits = planned_splits(r, in, out, L.ldp, ws_bytes - L.partials);
     hipStream_t st = (hipStream_t)hip_stream;
     char* base = reinterpret_cast<char*>(ws);
     uint16_t* Pb = reinterpret_cast<uint16_t*>(base + L.Pb);
@@ -876,9 +889,9 @@ loqt_status loqt_init_compensate(const float* W, int64_t ld_w, const float* P, i
         p.alpha = 1.0f / s;
         p.C = part;
         p.ldc = L.ldp;
-        p.splits = L.splits;
+        p.splits = splits;
         LOQT_HIP(launch_gemm_nt(SLOT_INIT_B, EPI_F32_SPLITK, true, true, p, st));
-        LOQT_HIP(launch_reduce_db(part, L.splits, r, in, L.ldp, B, LOQT_BF16, ld_B, 0, st));
+        LOQT_HIP(launch_reduce_db(part, splits, r, in, L.ldp, B, LOQT_BF16, ld_B, 0, st));
     }
     return LOQT_OK;
 }
@@ -923,7 +936,7 @@ loqt_status loqt_linear_fwd_right(const loqt_bf16* x, int64_t ld_x, int64_t T, c
     LOQT_TRY(check_bf16(x, T, in, ld_x));
     LOQT_TRY(check_bf16(y, T, out, ld_y));
     const RightWs L(LOQT_OP_FWD_RIGHT, T, out, in, r);
-    LOQT_TRY(check_ws(ws, ws_bytes, L.total));
+    LOQT_TRY(check_ws(ws, ws_bytes, L.least));
     hipStream_t st = (hipStream_t)hip_stream;
     char* base = reinterpret_cast<char*>(ws);
     uint16_t* Qb = reinterpret_cast<uint16_t*>(base + L.Qb);
@@ -939,6 +952,8 @@ loqt_status loqt_linear_fwd_right(const loqt_bf16* x, int64_t ld_x, int64_t T, c
     p.alpha = 1.0f;
     p.C = y;
     p.ldc = ld_y;
+    p.split_ws = reinterpret_cast<float*>(base + L.partials);
+    p.split_ws_floats = (int64_t)((ws_bytes - L.partials) / 4);
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Y, EPI_BF16, false, false, p, st));
     return LOQT_OK;
 }
@@ -957,7 +972,8 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     if (ld_dBp < r) return LOQT_BAD_SHAPE;
     if (!aligned(dBp, dBp_dtype == LOQT_BF16 ? 2 : 4)) return LOQT_MISALIGNED;
     const RightWs L(LOQT_OP_BWD_RIGHT, T, out, in, r);
-    LOQT_TRY(check_ws(ws, ws_bytes, L.total));
+    LOQT_TRY(check_ws(ws, ws_bytes, L.least));
+    const int64_t part_floats = (int64_t)((ws_bytes - L.partials) / 4);
     hipStream_t st = (hipStream_t)hip_stream;
     char* base = reinterpret_cast<char*>(ws);
     uint16_t* Qb = reinterpret_cast<uint16_t*>(base + L.Qb);
@@ -975,6 +991,8 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     p.alpha = s;
     p.C = V;
     p.ldc = L.ldr;
+    p.split_ws = part;
+    p.split_ws_floats = part_floats;
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, true, p, st));
     if (dx) {
         // dx = dy W_eff, W_eff out x in: K x rows
@@ -987,6 +1005,8 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
         p.alpha = 1.0f;
         p.C = dx;
         p.ldc = ld_dx;
+        p.split_ws = part;
+        p.split_ws_floats = part_floats;
         LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
     }
     // dBp = dy^T V: dy is T x out and V is T x r, both K x rows; contraction over T in slices
@@ -998,9 +1018,9 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     p.alpha = 1.0f;
     p.C = part;
     p.ldc = L.ldp;
-    p.splits = L.splits;
+    p.splits = planned_splits(out, r, T, L.ldp, ws_bytes - L.partials);
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DB, EPI_F32_SPLITK, true, true, p, st));
-    LOQT_HIP(launch_reduce_db(part, L.splits, out, r, L.ldp, dBp, dBp_dtype, ld_dBp, accumulate, st));
+    LOQT_HIP(launch_reduce_db(part, p.splits, out, r, L.ldp, dBp, dBp_dtype, ld_dBp, accumulate, st));
     return LOQT_OK;
 }
 
@@ -1140,6 +1160,10 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     const bool folded = use_folded(T, out, in);
     LOQT_TRY(check_ws(ws, ws_bytes, bf16_bytes(T, r) + (folded ? bf16_bytes(out, in) : 0)));
     hipStream_t st = (hipStream_t)hip_stream;
+    // slices of U and y: past the folded weight, or in its place when this call does not fold
+    const size_t split_off = bf16_bytes(T, r) + (folded ? bf16_bytes(out, in) : 0);
+    float* split = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + split_off);
+    const int64_t split_floats = (int64_t)((ws_bytes - split_off) / 4);
     uint16_t* U = reinterpret_cast<uint16_t*>(ws);
     const int64_t ld_u = (int64_t)round_up(r, 8);
     GemmParams p;
@@ -1155,6 +1179,8 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
         p.alpha = 1.0f;
         p.C = y;
         p.ldc = ld_y;
+        p.split_ws = split;
+        p.split_ws_floats = split_floats;
         LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Y, EPI_BF16, false, false, p, st));
         return LOQT_OK;
     }
@@ -1166,6 +1192,8 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     p.alpha = s;
     p.C = U;
     p.ldc = ld_u;
+    p.split_ws = split;
+    p.split_ws_floats = split_floats;
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st));
     memset(&p, 0, sizeof(p));  // y = [x | U] [W | P]^T
     p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
@@ -1177,6 +1205,8 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     p.alpha = 1.0f;
     p.C = y;
     p.ldc = ld_y;
+    p.split_ws = split;
+    p.split_ws_floats = split_floats;
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Y, EPI_BF16, false, false, p, st));
     return LOQT_OK;
 }
@@ -1194,14 +1224,19 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     if (dB_dtype != LOQT_F32 && dB_dtype != LOQT_BF16) return LOQT_INVALID_ARG;
     if (ld_dB < in) return LOQT_BAD_SHAPE;
     if (!aligned(dB, dB_dtype == LOQT_BF16 ? 2 : 4)) return LOQT_MISALIGNED;
-    const BwdWs L(T, out, in, r);  // only its split choice and slice pitch are used here
+    const NqWs L(true, T, out, in, r);
     const size_t z_bytes = bf16_bytes(T, r);
     const bool folded = dx && use_folded(T, out, in);
-    LOQT_TRY(check_ws(ws, ws_bytes, z_bytes + (L.total - L.partials) + (folded ? bf16_bytes(out, in) : 0)));
+    // slices of Z, dx and dB, one after the other: in the region of the dB slices, or past the folded weight (or in its
+    // place) where there is more room
+    const size_t end = folded ? L.split : L.We;
+    LOQT_TRY(check_ws(ws, ws_bytes, end));
     hipStream_t st = (hipStream_t)hip_stream;
     uint16_t* Z = reinterpret_cast<uint16_t*>(ws);
-    float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + z_bytes);
-    uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + z_bytes + (L.total - L.partials));
+    uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.We);
+    const bool at_end = folded && ws_bytes - L.split > L.We - L.partials;
+    float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + (at_end ? L.split : z_bytes));
+    const size_t part_bytes = at_end ? ws_bytes - L.split : folded ? L.We - L.partials : ws_bytes - L.partials;
     const int64_t ld_we = (int64_t)round_up(in, 8);
     if (folded) LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, st));
     const int64_t ld_z = (int64_t)round_up(r, 8);
@@ -1214,6 +1249,8 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     p.alpha = s;
     p.C = Z;
     p.ldc = ld_z;
+    p.split_ws = part;
+    p.split_ws_floats = (int64_t)(part_bytes / 4);
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
     if (dx) {  // dx = [dy | Z] [W ; B]: W is out x in and B is r x in, both K x rows; folded: dx = dy W_eff
         memset(&p, 0, sizeof(p));
@@ -1228,6 +1265,8 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
         p.alpha = 1.0f;
         p.C = dx;
         p.ldc = ld_dx;
+        p.split_ws = part;
+        p.split_ws_floats = (int64_t)(part_bytes / 4);
         LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
     }
     memset(&p, 0, sizeof(p));  // dB = Z^T x over slices of T
@@ -1238,9 +1277,9 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     p.alpha = 1.0f;
     p.C = part;
     p.ldc = L.ldp;
-    p.splits = L.splits;
+    p.splits = planned_splits(r, in, T, L.ldp, part_bytes);
     LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DB, EPI_F32_SPLITK, true, true, p, st));
-    LOQT_HIP(launch_reduce_db(part, L.splits, r, in, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
+    LOQT_HIP(launch_reduce_db(part, p.splits, r, in, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
     return LOQT_OK;
 }
 
@@ -1324,6 +1363,16 @@ loqt_status loqt_plan_product(int64_t M, int64_t N, int64_t Nx, int64_t* n_large
     const BF16Plan plan = plan_bf16_product(M, N, Nx);
     if (n_large) *n_large = plan.n1;
     if (rounds) *rounds = plan.cost;
+    return LOQT_OK;
+}
+
+loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max_splits, int* tile, int* splits) {
+    if (M <= 0 || N <= 0 || K <= 0 || max_splits < 1 || M > ((int64_t)1 << 30) || N > ((int64_t)1 << 30) ||
+        K > ((int64_t)1 << 30))
+        return LOQT_BAD_SHAPE;
+    const NtPlan plan = plan_nt(M, N, (K + 63) / 64, sliced != 0, 1, max_splits);
+    if (tile) *tile = plan.tile;
+    if (splits) *splits = plan.splits;
     return LOQT_OK;
 }
 

@@ -37,6 +37,7 @@
 // The 256x256 kernels use every vector register; tests/test_isa_guard.py checks their generated loop.
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "loqt_internal.h"
@@ -193,7 +194,11 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             return swz(row);
         }
     };
-    auto rc_swz = [](int kk) { return (4 * (kk & 3)) ^ (MF16 ? 2 * ((kk >> 3) & 1) : 0); };
+    //  A 64-row tile has rows of 128 bytes, half the banks: there k rows 2 and 3 of a group of four have to move to
+    // the other half of theirs, rows 0 and 1 already lie side by side.
+    auto rc_swz = [](int kk, int cpr) {
+        return cpr == 8 ? 4 * ((kk >> 1) & 1) : (4 * (kk & 3)) ^ (MF16 ? 2 * ((kk >> 3) & 1) : 0);
+    };
     auto tail_operand = [&](auto rc_tag, auto br_tag, const void* optr, int64_t old, int orows, int oK, int row0, int k0,
                             char* tile) {
         constexpr bool RC = decltype(rc_tag)::value;
@@ -234,7 +239,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             const char* sbase = reinterpret_cast<const char*>(optr) + ((int64_t)k0 * old + row0) * 2;
 #pragma unroll 1
             for (int i = 0; i < NC; ++i) {
-                const int logical = (tid % CPR) ^ rc_swz(i * KPI + kq);
+                const int logical = (tid % CPR) ^ rc_swz(i * KPI + kq, CPR);
                 const uint32_t off = (uint32_t)(i * KPI + kq) * ld2 + (uint32_t)min(logical * 8, clast) * 2u;
                 uint4 v = make_uint4(0, 0, 0, 0);
                 if (i * KPI + kq < kleft) v = *reinterpret_cast<const uint4*>(sbase + off);
@@ -277,12 +282,12 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int chunk = ((wm * Cfg::WTM + i * 32 + cb) >> 3) + (q >> 1);
-            a_rc[i] = (8 * h + jj) * (BM * 2) + ((chunk ^ (4 * jj)) << 4) + (q & 1) * 8;
+            a_rc[i] = (8 * h + jj) * (BM * 2) + ((chunk ^ rc_swz(jj, BM / 8)) << 4) + (q & 1) * 8;
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int chunk = ((wn * Cfg::WTN + j * 32 + cb) >> 3) + (q >> 1);
-            b_rc[j] = BM * ROWB + (8 * h + jj) * (BN * 2) + ((chunk ^ (4 * jj)) << 4) + (q & 1) * 8;
+            b_rc[j] = BM * ROWB + (8 * h + jj) * (BN * 2) + ((chunk ^ rc_swz(jj, BN / 8)) << 4) + (q & 1) * 8;
         }
     }
     typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -341,7 +346,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 const int clast = (((orows - 1) >> 3) << 3) - row0;
 #pragma unroll
                 for (int i = 0; i < NC; ++i) {
-                    const int logical = (tid % CPR) ^ rc_swz(kq + i * KPI);
+                    const int logical = (tid % CPR) ^ rc_swz(kq + i * KPI, CPR);
                     off[i] = (uint32_t)(kq + i * KPI) * ld2 + (uint32_t)min(logical * 8, clast) * 2u;
                 }
                 base = reinterpret_cast<const char*>(optr) + ((int64_t)k0 * old + row0) * 2;
@@ -470,14 +475,14 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                 for (int u = 0; u < TM2; ++u) {
                     const int chunk = ((wm * Cfg::WTM + u * 16) >> 3) + (q >> 1);
-                    a_rc16[u] = (8 * q4 + jj) * (BM * 2) + ((chunk ^ rc_swz(8 * q4 + jj)) << 4) + (q & 1) * 8;
+                    a_rc16[u] = (8 * q4 + jj) * (BM * 2) + ((chunk ^ rc_swz(8 * q4 + jj, BM / 8)) << 4) + (q & 1) * 8;
                 }
             }
             if constexpr (BRC) {
 #pragma unroll
                 for (int u = 0; u < TN2; ++u) {
                     const int chunk = ((wn * Cfg::WTN + u * 16) >> 3) + (q >> 1);
-                    b_rc16[u] = BM * ROWB + (8 * q4 + jj) * (BN * 2) + ((chunk ^ rc_swz(8 * q4 + jj)) << 4) + (q & 1) * 8;
+                    b_rc16[u] = BM * ROWB + (8 * q4 + jj) * (BN * 2) + ((chunk ^ rc_swz(8 * q4 + jj, BN / 8)) << 4) + (q & 1) * 8;
                 }
             }
         }
@@ -1168,6 +1173,76 @@ BF16Plan plan_bf16_product(int64_t M, int64_t N, int64_t Nx) {
     return plan;
 }
 
+// Products that do not fill the chip with 256x256 tiles over a long contraction (few tokens, narrow outputs, short
+// contractions) and the fp32 slices of dB and its relatives: tile shape and number of slices of the contraction from
+// an estimate in microseconds.  Per shape: work-groups per compute unit, the time of one k-tile when a few work-groups
+// have memory to themselves (a serial chain of loads, barrier and fragment reads), when every compute unit runs one and
+// when it runs two (shared L2, fabric and power), and the rest of a tile (first loads, epilogue).
+// Measured on contractions of 5120 and 13824 (M = 256), 2048 and 768 (M = 4096).  The two- and one-sided 64-wide
+// tiles carry rings of three and four stages, the deep 128x128 form four: with one work-group per compute unit the
+// distance of the prefetch is what counts (256 x 1024 x 13824, one slice, us: 133 with two stages, 95 with four, 64
+// on 64x64 tiles; eight stages of 64x64 were no better, 64).
+struct TileSpec {
+    int id, bm, bn, per_cu;
+    double alone, full, both, fix;
+};
+constexpr TileSpec kTiles[] = {
+    {NT_64x64, 64, 64, 2, 0.25, 0.27, 0.52, 2.0},
+    {NT_64x128, 64, 128, 2, 0.32, 0.38, 0.70, 2.2},
+    {NT_128x128_DEEP, 128, 128, 1, 0.36, 0.62, 0.62, 3.0},
+    {NT_128x128, 128, 128, 2, 0.60, 0.70, 1.06, 3.0},
+    {NT_256x128, 256, 128, 1, 0.55, 0.95, 0.95, 4.0},
+    {NT_256x256, 256, 256, 1, 1.20, 1.56, 1.56, 8.0},
+};
+
+double tile_cost(const TileSpec& t, int64_t M, int64_t N, int64_t nkt, int splits) {
+    auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int64_t wgs = cdiv(M, t.bm) * cdiv(N, t.bn) * splits, round = 256 * t.per_cu;
+    const double kt = (double)cdiv(nkt, splits);
+    auto one = [&](int64_t w) {
+        const double u = (double)w / 256.0;
+        return kt * (u <= 1.0 ? t.alone + (t.full - t.alone) * u : t.full + (t.both - t.full) * (u - 1.0)) + t.fix;
+    };
+    return (double)(wgs / round) * one(round) + (wgs % round ? one(wgs % round) : 0.0);
+}
+
+// slices > 1 (or `sliced`: the result is summed from fp32 slices in any case) cost their own traffic and the
+// reduction's: written at about 6 TB/s, read back at 7, and a launch
+double slices_cost(int64_t M, int64_t N, int splits) {
+    const double bytes = (double)M * (double)N * 4.0 * splits;
+    return bytes / 6.0e6 + 4.0 + (bytes + (double)M * (double)N * 2.0) / 7.0e6;
+}
+
+NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, int max_splits) {
+    NtPlan best{0, 1, 0.0};
+    for (const TileSpec& t : kTiles) {
+        if (sliced && t.id == NT_256x256) continue;  // no such kernel: its slices were slower than those of 256x128
+        for (int splits = min_splits; splits <= max_splits; ++splits) {
+            const int64_t per = (nkt + splits - 1) / splits;
+            if (min_splits < max_splits && splits > min_splits) {
+                if (per < 4 || t.id == NT_256x256) break;
+                if ((nkt + per - 1) / per != splits) continue;  // the last slices would be empty
+            }
+            double cost = tile_cost(t, M, N, nkt, splits);
+            if (sliced || splits > 1) cost += slices_cost(M, N, splits);
+            if (best.tile == 0 || cost < best.cost) best = NtPlan{t.id, splits, cost};
+        }
+    }
+    return best;
+}
+
+// whether a bf16-output product of M rows, N (+ Nx) columns and contraction K runs on 256x256 tiles by the plan above
+static bool large_product(int64_t M, int64_t N, int64_t Nx, int64_t K) {
+    auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    return K >= 2048 && cdiv(M, 256) * (cdiv(N, 256) + cdiv(Nx, 256)) >= 224;
+}
+
+int64_t product_split_floats(int64_t M, int64_t N, int64_t K0, int64_t K1) {
+    if (large_product(M, N, 0, K0 + K1)) return remainder_split_floats(M, N);
+    const NtPlan plan = plan_nt(M, N, (K0 + BK - 1) / BK + (K1 + BK - 1) / BK, false, 1, NT_MAX_SPLITS);
+    return plan.splits > 1 ? plan.splits * M * ((N + 3) / 4 * 4) : 0;
+}
+
 // Scratch (floats) for the column remainder of a bf16-output product of M rows and N columns in two fp32 slices
 // of the contraction: when the plan has a remainder and its 256x128 tiles number 64 to 128 (see launch_nt_sized).
 int64_t remainder_split_floats(int64_t M, int64_t N) {
@@ -1183,33 +1258,64 @@ int64_t remainder_split_floats(int64_t M, int64_t N) {
 
 namespace {
 
+// one launch on the given tile shape
+template <int EPI, bool ARC, bool BRC>
+hipError_t launch_nt_tile(int tile, const GemmParams& p, hipStream_t st) {
+    switch (tile) {
+        case NT_256x256:
+            if constexpr (EPI == EPI_BF16) return launch_nt<256, 256, EPI, ARC, BRC>(p, st);
+            break;
+        case NT_256x128: return launch_nt<256, 128, EPI, ARC, BRC>(p, st);
+        case NT_128x128: return launch_nt<128, 128, EPI, ARC, BRC>(p, st);
+        case NT_128x128_DEEP: return launch_nt<128, 128, EPI, ARC, BRC, 4>(p, st);
+        case NT_64x128: return launch_nt<64, 128, EPI, ARC, BRC, 3>(p, st);
+        case NT_64x64: return launch_nt<64, 64, EPI, ARC, BRC, 4>(p, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+int ktiles(const GemmParams& p) { return (p.A[0].K + BK - 1) / BK + (p.A[1].K + BK - 1) / BK; }
+
 template <int EPI, bool ARC, bool BRC>
 hipError_t launch_nt_sized(const GemmParams& p, hipStream_t st) {
-    // largest tile that still gives every compute unit a work-group
-    const int64_t z = EPI == EPI_F32_SPLITK ? p.splits : 1;
     auto tiles = [&](int bm, int bn) {
-        return z * ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn + (p.Nx + bn - 1) / bn);
+        return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn + (p.Nx + bn - 1) / bn);
     };
     // 256x256 tiles (one work-group per compute unit) have the best ratio of MFMA work to LDS and
     // global traffic and win on long contractions with a light epilogue.  With short contractions
-    // or a heavy epilogue (merge, fp32 slices; measured on real data, the fold is better off with the
+    // or a heavy epilogue (merge; measured on real data, the fold is better off with the
     // large tile) two or three resident 128x128 work-groups per
     // compute unit win: the epilogue and prologue of one overlap with the main loop of another.
     if constexpr (EPI == EPI_COMP || EPI == EPI_FOLD_F32) {
         return launch_nt<128, 128, EPI, ARC, BRC>(p, st);  // heavy epilogue: small tiles only
+    } else if constexpr (EPI == EPI_F32_SPLITK) {
+        // the number of slices was fixed with the workspace (plan_nt); the tile that goes with it
+        if (g_nt_tile_override == 1) return launch_nt<256, 256, EPI, ARC, BRC>(p, st);
+        if (g_nt_tile_override == 2) return launch_nt<256, 128, EPI, ARC, BRC>(p, st);
+        if (g_nt_tile_override == 3) return launch_nt<128, 128, EPI, ARC, BRC>(p, st);
+        return launch_nt_tile<EPI, ARC, BRC>(plan_nt(p.M, p.N, ktiles(p), true, p.splits, p.splits).tile, p, st);
     } else {
     int choice = g_nt_tile_override;
     if (choice == 0) {
-        const int K = p.A[0].K + p.A[1].K;
-        const bool light = (EPI == EPI_BF16 && K >= 2048) || EPI == EPI_FOLD || EPI == EPI_ACC_BF16;
-        choice = (light && tiles(256, 256) >= 224) ? 1 : 3;
-        // skinny bf16 products with a long contraction (Z = s dy deq(P) at rank 1024: 8192 x 1024 outputs) fill the
-        // chip with 256x128 tiles, one per compute unit, at half the LDS traffic per flop of the 128x128 ones.  With
-        // only half as many tiles (4096 x 1024 outputs: half the compute units stay idle) they are still ahead when
-        // the contraction is very long (13B gate / up, K = 13824: 180 -> 162 us) and behind at K = 5461.
-        if (EPI == EPI_BF16 && choice == 3 && K >= 2048 && p.Nx == 0 && tiles(256, 128) <= 256 &&
-            (tiles(256, 128) >= 224 || (tiles(256, 128) >= 128 && K >= 8192)))
-            choice = 2;
+        const bool light = EPI == EPI_BF16 ? large_product(p.M, p.N, p.Nx, p.A[0].K + p.A[1].K)
+                                           : (EPI == EPI_FOLD || EPI == EPI_ACC_BF16) && tiles(256, 256) >= 224;
+        choice = light ? 1 : 3;
+        if constexpr (EPI == EPI_BF16) {
+            if (!light && p.Nx == 0) {
+                const int64_t ldc = (p.N + 3) / 4 * 4;
+                const int64_t room = p.split_ws ? p.split_ws_floats / (p.M * ldc) : 0;
+                const NtPlan plan = plan_nt(p.M, p.N, ktiles(p), false, 1, (int)std::min<int64_t>(std::max<int64_t>(room, 1), NT_MAX_SPLITS));
+                if (plan.splits == 1) return launch_nt_tile<EPI, ARC, BRC>(plan.tile, p, st);
+                // fp32 slices of the contraction and their fixed-order sum
+                GemmParams c = p;
+                c.C = p.split_ws;
+                c.ldc = ldc;
+                c.splits = plan.splits;
+                hipError_t e = launch_nt_tile<EPI_F32_SPLITK, ARC, BRC>(plan.tile, c, st);
+                if (e != hipSuccess) return e;
+                return launch_reduce_db(p.split_ws, plan.splits, p.M, p.N, ldc, p.C, LOQT_BF16, p.ldc, 0, st, false);
+            }
+        }
     }
     if constexpr (EPI == EPI_BF16) {
         // 256x256 tiles run in rounds of one tile per compute unit.  When the last round would be mostly
@@ -1259,16 +1365,6 @@ hipError_t launch_nt_sized(const GemmParams& p, hipStream_t st) {
     }
     if (choice == 1) return launch_nt<256, 256, EPI, ARC, BRC>(p, st);
     if (choice == 2) return launch_nt<256, 128, EPI, ARC, BRC>(p, st);
-    if constexpr (EPI == EPI_F32_SPLITK) {
-        // The fp32 slices (dB and its relatives: short rows of 128 outputs, both operands stored K x rows) run on
-        // 256x128 tiles, one work-group per compute unit, from 512 output rows (rank 512) up (1B block, rank 512:
-        // dB 0.30 -> 0.24 ms against 128x128 tiles).  History of this choice: 128x128 with two stages waited for its
-        // loads more than for anything else (dB 0.78 ms on the 7B block); 256x128 with a ring of three stages in the
-        // 32x32x16 loop 0.66 ms; the 16x16x32 loop with two stages, whose loads run up to 1.5 k-tiles ahead and are
-        // spread over the tile, 0.60 ms (A/B on one machine: 79 -> 73 us for 1024 x 4096 x 8192).
-        if (g_nt_tile_override == 0 && p.M >= 512)
-            return launch_nt<256, 128, EPI, ARC, BRC, 2>(p, st);
-    }
     return launch_nt<128, 128, EPI, ARC, BRC>(p, st);
     }
 }
@@ -1319,13 +1415,23 @@ hipError_t prepare_nt_kernels() {
     LOQT_PREP3(EPI_ACC_BF16, false, true);
     LOQT_PREP3(EPI_F32_SPLITK, true, true);
     LOQT_PREP3(EPI_F32_SPLITK, false, true);
+    LOQT_PREP3(EPI_F32_SPLITK, false, false);
 #undef LOQT_PREP3
-    if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, true, true, 3>()) != hipSuccess) return e;
+    // the shapes of plan_nt
+#define LOQT_PREP_SMALL(EPI, ARC, BRC)                                              \
+    if ((e = ensure_attr<128, 128, EPI, ARC, BRC, 4>()) != hipSuccess) return e;    \
+    if ((e = ensure_attr<64, 128, EPI, ARC, BRC, 3>()) != hipSuccess) return e;     \
+    if ((e = ensure_attr<64, 64, EPI, ARC, BRC, 4>()) != hipSuccess) return e
+    LOQT_PREP_SMALL(EPI_BF16, false, false);
+    LOQT_PREP_SMALL(EPI_BF16, false, true);
+    LOQT_PREP_SMALL(EPI_F32_SPLITK, false, false);
+    LOQT_PREP_SMALL(EPI_F32_SPLITK, false, true);
+    LOQT_PREP_SMALL(EPI_F32_SPLITK, true, true);
+#undef LOQT_PREP_SMALL
     if ((e = ensure_attr<256, 256, EPI_BF16, false, false, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 256, EPI_BF16, false, true, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, true, true, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, false, true, 2, true>()) != hipSuccess) return e;
-    if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, false, false, 2, false>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, false, false, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_BF16, false, false, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_BF16, false, true, 2, true>()) != hipSuccess) return e;

@@ -255,6 +255,18 @@ struct GemmParams {
 };
 // floats of scratch a bf16-output product of M rows and N columns can use for its column remainder (0: none)
 int64_t remainder_split_floats(int64_t M, int64_t N);
+// ... and for all of it, with a contraction of K0 (+ K1, the second segment): the slices of plan_nt or the remainder's
+int64_t product_split_floats(int64_t M, int64_t N, int64_t K0, int64_t K1);
+
+// Tile shape and slices of the contraction of a product that is not run on 256x256 tiles by plan_bf16_product, the
+// best of min_splits .. max_splits slices.  sliced: the result is summed from fp32 slices in any case (dB).
+enum NtTile { NT_256x256 = 1, NT_256x128, NT_128x128, NT_128x128_DEEP, NT_64x128, NT_64x64 };
+constexpr int NT_MAX_SPLITS = 32;
+struct NtPlan {
+    int tile, splits;
+    double cost;  // microseconds, estimated
+};
+NtPlan plan_nt(int64_t M, int64_t N, int64_t ktiles, bool sliced, int min_splits, int max_splits);
 
 // which GEMM to run
 enum GemmId { GEMM_U = 0, GEMM_Y, GEMM_Z, GEMM_DX, GEMM_DB, GEMM_MERGE };
