@@ -29,8 +29,10 @@ extern "C" {
  *                      y = x W_eff^T and dx = dy W_eff.  The intermediate U is not formed; Z still is
  *                      (dB = Z^T x).  Cheaper than carrying the rank-r term through every token
  *                      (2 T r (in + out) flop per pass) from T = out in / (in + out) tokens up.
- *   LOQT_PATH_AUTO   : forward and backward always take the pre-pass family (measured ahead of the
- *                      fused form at every token count from 16 up), folded when T (in + out) >= out in --
+ *   LOQT_PATH_AUTO   : forward calls with at most 32 tokens (loqt_linear_fwd, loqt_linear_fwd_nq) stream the weight
+ *                      once and expand its codes in registers (a kernel of its own; reported as FUSED); otherwise
+ *                      forward and backward take the pre-pass family (measured ahead of the
+ *                      general fused form at every token count from 16 up), folded when T (in + out) >= out in --
  *                      except that the backward pass, which has Z = s dy deq(P_q) at hand anyway, keeps the
  *                      rank-r term as a second K segment of the dx product when out > 0.73 T (2 T r in flop at
  *                      the rate of the large products instead of 2 out in r at the rate of the fold);

@@ -97,6 +97,8 @@ int g_path = LOQT_PATH_AUTO;
 bool use_prepass(int64_t /*tokens*/) {
     return g_path != LOQT_PATH_FUSED;
 }
+// Forward with a handful of tokens: the codes are streamed once and expanded in registers (few.hip), no copy of the weight.
+bool use_few_tokens(int64_t tokens) { return g_path == LOQT_PATH_AUTO && tokens <= FEW_TOKENS_MAX; }
 // Merge: below 1024 columns the pre-pass of P costs as much as it saves.
 bool use_prepass_merge(int64_t in) {
     if (g_path == LOQT_PATH_FUSED) return false;
@@ -331,6 +333,17 @@ loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const lo
     return LOQT_OK;
 }
 
+// U = s x B^T for a handful of tokens.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
+// long contraction goes out in slices instead, which find room where a copy of the weight would be.  Whole forward calls
+// in us, one launch / slices: contraction 5461, 16 tokens 19 / 24, 32 tokens 26 / 28; contraction 11008, 16 tokens
+// 40 / 36, 32 tokens 60 / 43.
+hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipStream_t st) {
+    if (p.A[0].K <= (p.M <= 16 ? 8192 : 5504)) return launch_few_tokens(SLOT_GEMM_U, false, p, st);
+    p.split_ws = split_ws;
+    p.split_ws_floats = (int64_t)(split_bytes / 4);
+    return launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st);
+}
+
 loqt_status merge_fused(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absmax_out,
                         const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s, hipStream_t st) {
     const int out = (int)Wq->rows, in = (int)Wq->cols, r = (int)Pq->cols;
@@ -508,6 +521,29 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
     GemmParams p;
 
     if (save_weff) LOQT_TRY(check_bf16(save_weff, out, in, ld_save));
+    if (!save_weff && use_few_tokens(T)) {
+        memset(&p, 0, sizeof(p));  // U = s x B^T
+        p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
+        p.B[0] = bf16_operand(B, ld_B, (int)r, (int)in);
+        p.M = (int)T;
+        p.N = (int)r;
+        p.alpha = s;
+        p.C = U;
+        p.ldc = ld_u;
+        LOQT_HIP(launch_u_few(p, reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + L.Wb), ws_bytes - L.Wb, st));
+        memset(&p, 0, sizeof(p));  // y = x deq(W)^T + U deq(P)^T
+        p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
+        p.B[0] = nf4_operand(Wq, (int)out, (int)in);
+        p.A[1] = bf16_operand(U, ld_u, (int)T, (int)r);
+        p.B[1] = nf4_operand(Pq, (int)out, (int)r);
+        p.M = (int)T;
+        p.N = (int)out;
+        p.alpha = 1.0f;
+        p.C = y;
+        p.ldc = ld_y;
+        LOQT_HIP(launch_few_tokens(SLOT_GEMM_Y, true, p, st));
+        return LOQT_OK;
+    }
     if (save_weff || use_prepass(T)) {
         char* base = reinterpret_cast<char*>(ws);
         uint16_t* Wb = save_weff ? save_weff : reinterpret_cast<uint16_t*>(base + L.Wb);
@@ -830,7 +866,7 @@ size_t loqt_merge_batched_workspace_bytes(int n_layers, const loqt_merge_desc* d
 
 int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in) {
     if (op == LOQT_OP_MERGE) return use_prepass_merge(in) ? LOQT_PATH_PREPASS : LOQT_PATH_FUSED;
-    if (!use_prepass(T)) return LOQT_PATH_FUSED;
+    if (!use_prepass(T) || (op == LOQT_OP_FWD && use_few_tokens(T))) return LOQT_PATH_FUSED;
     if (op == LOQT_OP_BWD) return use_folded_bwd(T, out, in) ? LOQT_PATH_FOLDED : LOQT_PATH_PREPASS;
     return use_folded(T, out, in) ? LOQT_PATH_FOLDED : LOQT_PATH_PREPASS;
 }
@@ -1157,7 +1193,7 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     LOQT_TRY(check_layer_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r));
     LOQT_TRY(check_bf16(x, T, in, ld_x));
     LOQT_TRY(check_bf16(y, T, out, ld_y));
-    const bool folded = use_folded(T, out, in);
+    const bool few = use_few_tokens(T), folded = use_folded(T, out, in);
     LOQT_TRY(check_ws(ws, ws_bytes, bf16_bytes(T, r) + (folded ? bf16_bytes(out, in) : 0)));
     hipStream_t st = (hipStream_t)hip_stream;
     // slices of U and y: past the folded weight, or in its place when this call does not fold
@@ -1167,7 +1203,7 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     uint16_t* U = reinterpret_cast<uint16_t*>(ws);
     const int64_t ld_u = (int64_t)round_up(r, 8);
     GemmParams p;
-    if (folded) {  // y = x W_eff^T with the rank-r term folded into a transient copy of the weight
+    if (folded && !few) {  // y = x W_eff^T with the rank-r term folded into a transient copy of the weight
         uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + bf16_bytes(T, r));
         const int64_t ld_we = (int64_t)round_up(in, 8);
         LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, st));
@@ -1194,7 +1230,7 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     p.ldc = ld_u;
     p.split_ws = split;
     p.split_ws_floats = split_floats;
-    LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st));
+    LOQT_HIP(few ? launch_u_few(p, split, (size_t)split_floats * 4, st) : launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st));
     memset(&p, 0, sizeof(p));  // y = [x | U] [W | P]^T
     p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
     p.B[0] = bf16_operand(W, ld_W, (int)out, (int)in);
@@ -1207,7 +1243,7 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     p.ldc = ld_y;
     p.split_ws = split;
     p.split_ws_floats = split_floats;
-    LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Y, EPI_BF16, false, false, p, st));
+    LOQT_HIP(few ? launch_few_tokens(SLOT_GEMM_Y, false, p, st) : launch_gemm_nt(SLOT_GEMM_Y, EPI_BF16, false, false, p, st));
     return LOQT_OK;
 }
 

@@ -1,0 +1,269 @@
+// Forward products with few tokens (T <= 32): y = x deq(W)^T + U deq(P)^T and U = s x B^T, the weight streamed once.
+//
+// With a handful of tokens the product is a read of the weight: 0.5625 bytes per element from HBM, a few matrix
+// instructions on the way.  Expanding the weight to bf16 first moves 2.56 + 2 bytes per element and then feeds 64-row
+// tiles of which a quarter is tokens.  Here a lane reads 32 codes (16 bytes) of one weight row, looks their levels up
+// (bf16 table in LDS) and hands them to v_mfma_f32_16x16x32_bf16 as they are; a block of 64 is summed on its own and
+// then scaled by the block's absmax in fp32.  (The levels are rounded to bf16 before the scaling instead of after it:
+// 1.4e-3 rms of the weight against 1.7e-3.)  The matrix instruction wants the eight k from 32 j + 8 q on in lane group q;
+// the group has read 32 q .. 32 q + 31, so the four dwords of codes are transposed across the four groups of 16 lanes
+// first (two lane swaps per pair).  Neither operand passes through LDS.
+//
+// A work-group owns 16 * RT weight rows over the whole contraction; its 16 waves take every 16th chunk of 128 and their
+// sums meet in LDS in a fixed order, so there are no slices in memory and no second launch.  What bounds it is not the
+// codes (28 MB in 6.7 us, alone in the same access pattern) but x: every work-group reads all of it from L2, and the
+// compute units of an XCD ask for the same lines (16 tokens: 20 bytes per cycle and unit arrive).  So RT grows with
+// the number of rows.  Measured, us, 16 tokens, contraction 5120: 4096 rows 9.2 (RT 1), 12.9 (RT 2); 11008 rows 23
+// (RT 1), 26 (RT 2), 18.2 (RT 3); 8 waves and RT 1: 9.8 and 24.8.  The whole call at 16 x 11008 x 4096, rank 1024: 78 -> 28 (164 before the narrow tiles of gemm_nt.hip).
+// From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
+#include <type_traits>
+
+#include "loqt_internal.h"
+
+namespace loqt {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+constexpr int CH = 128;  // contraction of one chunk
+constexpr int NW = 16;   // waves of a work-group
+constexpr int NB = 2;    // chunks whose weights a wave has in flight
+
+typedef __attribute__((ext_vector_type(8))) short s16x8;
+
+// the bf16 levels of 8 codes (element e in byte e / 2, even e in the high nibble)
+__device__ __forceinline__ bf16x8 levels8(uint32_t w, const char* lut) {
+    const uint32_t odd = (w << 1) & 0x1e1e1e1eu, even = (w >> 3) & 0x1e1e1e1eu;  // byte offsets into the table
+    s16x8 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = *reinterpret_cast<const short*>(lut + ((even >> (8 * i)) & 0xffu));
+        v[2 * i + 1] = *reinterpret_cast<const short*>(lut + ((odd >> (8 * i)) & 0xffu));
+    }
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// elements k .. k+7 of a bf16 row (16-byte aligned pieces, the pitch a multiple of 8); MASK: those from K on as zero.
+// Always one unconditional load: a branch around it would make every load wait for the ones before.
+template <bool MASK>
+__device__ __forceinline__ bf16x8 load8(const uint16_t* row, int k, int K) {
+    if constexpr (!MASK) return *reinterpret_cast<const bf16x8*>(row + k);
+    uint4 v = *reinterpret_cast<const uint4*>(row + (k < K ? k : 0));
+    uint32_t* w = reinterpret_cast<uint32_t*>(&v);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) w[d] &= k + 2 * d + 1 < K ? 0xffffffffu : k + 2 * d < K ? 0xffffu : 0u;
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+// lanes 32-63 of a change places with lanes 0-31 of b; rows 1 and 3 of 16 lanes of a with rows 0 and 2 of b
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+    const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(a, b, false, false));
+    a = r[0], b = r[1];
+}
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+    const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(a, b, false, false));
+    a = r[0], b = r[1];
+}
+
+struct Seg {  // one K segment: x (bf16, T x K) and the weight rows (NF4 or bf16, N x K)
+    const uint16_t* a;
+    int64_t lda;
+    const void* w;
+    const float* absmax;
+    int64_t ldw;
+    int K;
+};
+
+template <bool NF4>
+struct Weights;  // one chunk of 16 rows: what a lane holds of its row; k0: start of the chunk
+template <>
+struct Weights<true> {
+    uint32_t d[4];
+    float am[2];
+    // Padding nibbles are levels like any other and meet zeros of x; a block wholly past K has no scale to rely on.
+    template <bool MASK>
+    __device__ __forceinline__ void load(const Seg& s, int row, int k0, int q) {
+        int k = k0 + 32 * q, k1 = k0 + 64;
+        if (MASK) k = k < s.ldw ? k : k0, k1 = k1 < s.K ? k1 : k0;
+        const uint4 c = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(s.w) + (int64_t)row * (s.ldw >> 1) + (k >> 1));
+        d[0] = c.x, d[1] = c.y, d[2] = c.z, d[3] = c.w;
+        const float* a = s.absmax + (int64_t)row * (s.ldw >> 6);
+        am[0] = a[k0 >> 6], am[1] = a[k1 >> 6];
+    }
+    __device__ __forceinline__ void ready() {  // dword j of lane group q becomes dword q of group j
+        swap32(d[0], d[2]);
+        swap32(d[1], d[3]);
+        swap16(d[0], d[1]);
+        swap16(d[2], d[3]);
+    }
+    __device__ __forceinline__ bf16x8 frag(int j, const char* lut) const { return levels8(d[j], lut); }
+    __device__ __forceinline__ float scale(int h) const { return am[h]; }
+};
+template <>
+struct Weights<false> {
+    bf16x8 v[4];
+    template <bool MASK>
+    __device__ __forceinline__ void load(const Seg& s, int row, int k0, int q) {
+        const uint16_t* r = reinterpret_cast<const uint16_t*>(s.w) + (int64_t)row * s.ldw;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = load8<MASK>(r, k0 + 32 * j + 8 * q, s.K);
+    }
+    __device__ __forceinline__ void ready() {}
+    __device__ __forceinline__ bf16x8 frag(int j, const char*) const { return v[j]; }
+    __device__ __forceinline__ float scale(int) const { return 1.f; }
+};
+
+// C[T x N] (bf16) = alpha * sum over both segments of A_seg[T x K_seg] * B_seg[N x K_seg]^T; A bf16, B NF4 or bf16
+template <bool NF4, int NT, int RT>
+__global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p) {
+    __shared__ f32x4 red[NW / 2][RT * NT][64];
+    uint16_t* lut = reinterpret_cast<uint16_t*>(red);  // until the sums need the place
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const char* lutc = reinterpret_cast<const char*>(lut);
+    const int q = lane >> 4, l16 = lane & 15;
+    const int n0 = blockIdx.x * (16 * RT);
+    int row[RT], tok[NT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) row[i] = min(n0 + 16 * i + l16, p.N - 1);  // rows and tokens past the end: any valid one
+#pragma unroll
+    for (int t = 0; t < NT; ++t) tok[t] = min(16 * t + l16, p.M - 1);
+    f32x4 acc[RT][NT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const Seg s0{reinterpret_cast<const uint16_t*>(p.A[0].ptr), p.A[0].ld, p.B[0].ptr, p.B[0].absmax, p.B[0].ld, p.A[0].K};
+    const Seg s1{reinterpret_cast<const uint16_t*>(p.A[1].ptr), p.A[1].ld, p.B[1].ptr, p.B[1].absmax, p.B[1].ld, p.A[1].K};
+    auto seg = [&](bool second) {  // (scalar selects; a run-time index would go through memory)
+        return Seg{second ? s1.a : s0.a, second ? s1.lda : s0.lda, second ? s1.w : s0.w, second ? s1.absmax : s0.absmax,
+                   second ? s1.ldw : s0.ldw, second ? s1.K : s0.K};
+    };
+    Weights<NF4> w[NB][RT];
+    bf16x8 x[NT][4];
+    auto load_w = [&](auto mask, int b, const Seg& s, int k0) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) w[b][i].template load<decltype(mask)::value>(s, row[i], k0, q);
+    };
+    auto load_x = [&](auto mask, const Seg& s, int k0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                x[t][j] = load8<decltype(mask)::value>(s.a + tok[t] * s.lda, k0 + 32 * j + 8 * q, s.K);
+    };
+    auto multiply = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            w[b][i].ready();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {  // blocks of 64
+                const bf16x8 f0 = w[b][i].frag(2 * h, lutc), f1 = w[b][i].frag(2 * h + 1, lutc);
+                const float sc = w[b][i].scale(h);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    f32x4 a = NF4 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][t];
+                    a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t][2 * h], f0, a, 0, 0, 0);
+                    a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t][2 * h + 1], f1, a, 0, 0, 0);
+                    if (NF4) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][t][e] = __builtin_fmaf(sc, a[e], acc[i][t][e]);
+                    } else {
+                        acc[i][t] = a;
+                    }
+                }
+            }
+        }
+    };
+    constexpr std::integral_constant<bool, false> WHOLE{};
+    constexpr std::integral_constant<bool, true> CUT{};
+    // whole chunks: batches of NB per wave; past the last one the loads repeat it and nothing is multiplied
+    const int f0 = s0.K / CH, full = f0 + s1.K / CH;
+    auto whole = [&](int c, auto&& f) {
+        c = min(c, full - 1);
+        const bool second = c >= f0;
+        f(seg(second), (second ? c - f0 : c) * CH);
+    };
+    auto batch = [&](int c0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) whole(c0 + b * NW, [&](const Seg& s, int k0) { load_w(WHOLE, b, s, k0); });
+        whole(c0, [&](const Seg& s, int k0) { load_x(WHOLE, s, k0); });
+    };
+    if (full > 0) batch(wave);
+    if (NF4) {
+        if (tid < 16) lut[tid] = (uint16_t)(pack_bf16(kNf4Levels[tid], 0.f) & 0xffffu);
+        __syncthreads();
+    }
+    for (int c0 = wave; c0 < full;) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (c0 + b * NW < full) multiply(b);
+            if (b + 1 < NB) whole(c0 + (b + 1) * NW, [&](const Seg& s, int k0) { load_x(WHOLE, s, k0); });
+        }
+        c0 += NB * NW;
+        if (c0 < full) batch(c0);
+    }
+    // what is left of a segment that does not end on a chunk
+#pragma unroll 1
+    for (int t = 0; t < 2; ++t) {
+        const Seg s = seg(t == 1);
+        if (s.K % CH == 0 || wave != (full + t) % NW) continue;
+        load_w(CUT, 0, s, s.K / CH * CH);
+        load_x(CUT, s, s.K / CH * CH);
+        multiply(0);
+    }
+    // lane: row 16 i + (lane & 15), tokens 16 t + 4 (lane >> 4) .. +3.  The upper half of the waves hands over to the
+    // lower half first (half the LDS).
+    auto put = [&](int slot, bool add) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) red[slot][i * NT + t][lane] = add ? red[slot][i * NT + t][lane] + acc[i][t] : acc[i][t];
+    };
+    __syncthreads();
+    if (wave >= NW / 2) put(wave - NW / 2, false);
+    __syncthreads();
+    if (wave < NW / 2) put(wave, true);
+    __syncthreads();
+    for (int u = tid; u < RT * NT * 64; u += 64 * NW) {
+        const int it = u >> 6, ln = u & 63;
+        f32x4 s = red[0][it][ln];
+#pragma unroll
+        for (int v = 1; v < NW / 2; ++v) s += red[v][it][ln];
+        const int m = 16 * (it % NT) + 4 * (ln >> 4), n = n0 + 16 * (it / NT) + (ln & 15);
+        if (n >= p.N) continue;
+        uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + (int64_t)m * p.ldc + n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (m + e < p.M) dst[e * p.ldc] = (uint16_t)(pack_bf16(p.alpha * s[e], 0.f) & 0xffffu);
+    }
+}
+
+template <bool NF4, int NT, int RT>
+hipError_t launch_rows(const GemmParams& p, hipStream_t st) {
+    hipLaunchKernelGGL((few_tokens_kernel<NF4, NT, RT>), dim3((p.N + 16 * RT - 1) / (16 * RT)), dim3(64 * NW), 0, st, p);
+    return hipGetLastError();
+}
+
+// rows per work-group: as few as leave at most one work-group of 16 waves for a compute unit
+template <bool NF4, int NT>
+hipError_t launch_tokens(const GemmParams& p, hipStream_t st) {
+    const int tiles = (p.N + 15) / 16;
+    if (tiles <= 256) return launch_rows<NF4, NT, 1>(p, st);
+    if (tiles <= 512) return launch_rows<NF4, NT, 2>(p, st);
+    if (tiles <= 768) return launch_rows<NF4, NT, 3>(p, st);
+    return launch_rows<NF4, NT, 4>(p, st);
+}
+
+}  // namespace
+
+hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_t st) {
+    if (p.M < 1 || p.M > FEW_TOKENS_MAX) return hipErrorInvalidValue;
+    TimedLaunch tl(slot, st);
+    if (p.M <= 16) return nf4 ? launch_tokens<true, 1>(p, st) : launch_tokens<false, 1>(p, st);
+    return nf4 ? launch_tokens<true, 2>(p, st) : launch_tokens<false, 2>(p, st);
+}
+
+}  // namespace loqt

@@ -268,6 +268,11 @@ struct NtPlan {
 };
 NtPlan plan_nt(int64_t M, int64_t N, int64_t ktiles, bool sliced, int min_splits, int max_splits);
 
+// forward products with at most FEW_TOKENS_MAX tokens (few.hip): C[M x N] = alpha * sum_seg A_seg B_seg^T, A bf16, B rows x K
+// in NF4 or bf16
+constexpr int FEW_TOKENS_MAX = 32;
+hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_t st);
+
 // which GEMM to run
 enum GemmId { GEMM_U = 0, GEMM_Y, GEMM_Z, GEMM_DX, GEMM_DB, GEMM_MERGE };
 hipError_t launch_gemm(GemmId id, const GemmParams& p, hipStream_t st);

@@ -1,0 +1,94 @@
+"""Forward calls with a handful of tokens (the codes are expanded in registers, no copy of the weight): sizes that end
+inside chunks, row tiles and token tiles, padding that holds NaN, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import loqt_oracle as O
+from paper_2405_16528_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # T, out, in, r
+    (1, 130, 40, 8),          # contractions shorter than a chunk of 128
+    (16, 512, 512, 128),      # whole chunks only
+    (17, 300, 1000, 72),      # second token tile with one token; chunk tails of both segments
+    (32, 100, 2176, 200),     # 17 whole chunks: one wave has two
+    (3, 4200, 136, 40),       # two row tiles per work-group
+    (31, 8300, 200, 64),      # three
+    (16, 12300, 328, 24),     # four, one token tile
+    (32, 12300, 72, 24),      # four, two token tiles
+    (9, 72, 8300, 40),        # U in slices of its contraction
+]
+
+
+def _nan_padded(bits, extra):
+    """bf16 bits (rows, cols) in a device buffer whose pitch padding is NaN."""
+    rows, cols = bits.shape
+    buf = np.full((rows, (cols + 7) // 8 * 8 + extra), 0x7FC0, dtype=np.uint16)
+    buf[:, :cols] = bits
+    return torch.from_numpy(buf.view(np.int16)).cuda().view(torch.bfloat16)[:, :cols]
+
+
+def _nan_scaled(q):
+    """NF4 on the device with 64 columns of padding, its codes arbitrary and its scales NaN."""
+    from tests import gpu_util as G
+    codes, absmax = q
+    t = G.nf4_dev(codes, absmax, G.rup(codes.shape[1], 64) + 64)
+    t.codes[:, -32:] = 0xF3
+    t.absmax[:, -1] = float("nan")
+    return t
+
+
+@pytest.mark.parametrize("T,out,inp,r", CASES)
+def test_forward_parity(T, out, inp, r):
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    assert L.resolved_path(L.OP_FWD, T, out, inp) == L.PATH_FUSED
+    rng = synth.rng_for(T, "few", out, inp)
+    s = 0.5
+    Wq = O.nf4_quantize(synth.normal_f32(rng, (out, inp), 0.02))
+    Pq = O.nf4_quantize(synth.normal_f32(rng, (out, r), out ** -0.5))
+    B, x = synth.normal_bf16(rng, (r, inp), 2e-2), synth.normal_bf16(rng, (T, inp), 1.0)
+    y = G.bf16_empty(T, out, fill=float("nan"))
+    L.loqt_linear_fwd(_nan_padded(x, 8), _nan_scaled(Wq), _nan_scaled(Pq), _nan_padded(B, 16), s, y,
+                      G.workspace(L.OP_FWD, T, out, inp, r))
+    torch.cuda.synchronize()
+    ref = O.loqt_linear_fwd(x, Wq, Pq, B, s)
+    # operands: the levels in bf16 instead of the scaled weights (each off by at most 2^-8), output in bf16
+    err = G.bf16_output_report(G.bf16_host(y), ref)[0]
+    print(f"few T={T} out={out} in={inp} r={r}: err/rms y {err:.2e}")
+    # and not less exact than the expanded weight
+    L.set_path(L.PATH_PREPASS)
+    try:
+        y2 = G.bf16_empty(T, out)
+        L.loqt_linear_fwd(_nan_padded(x, 8), _nan_scaled(Wq), _nan_scaled(Pq), _nan_padded(B, 16), s, y2,
+                          G.workspace(L.OP_FWD, T, out, inp, r))
+    finally:
+        L.set_path(L.PATH_AUTO)
+    rel = [np.linalg.norm(O.bf16_to_f64(G.bf16_host(t)) - ref) / np.linalg.norm(ref) for t in (y, y2)]
+    assert rel[0] <= rel[1] * 1.1 + 2e-4, rel  # (a few outputs of one token scatter by a tenth)
+
+
+@pytest.mark.parametrize("T,out,inp,r", CASES)
+def test_forward_nq_parity(T, out, inp, r):
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    rng = synth.rng_for(T, "few nq", out, inp)
+    s = 0.5
+    W, P = synth.normal_bf16(rng, (out, inp), 0.02), synth.normal_bf16(rng, (out, r), out ** -0.5)
+    B, x = synth.normal_bf16(rng, (r, inp), 2e-2), synth.normal_bf16(rng, (T, inp), 1.0)
+    y = G.bf16_empty(T, out, fill=float("nan"))
+    L.loqt_linear_fwd_nq(_nan_padded(x, 8), _nan_padded(W, 8), _nan_padded(P, 0), _nan_padded(B, 16), s, y,
+                         G.workspace(L.OP_FWD_NQ, T, out, inp, r))
+    torch.cuda.synchronize()
+    G.bf16_output_report(G.bf16_host(y), O.loqt_linear_fwd_nq(x, W, P, B, s))
+
+
+def test_the_line_between_the_forms():
+    """32 tokens are a handful, 33 are not; the backward pass and the pair that keeps the weight never are."""
+    from paper_2405_16528_amd import binding as L
+    assert L.resolved_path(L.OP_FWD, 32, 512, 512) == L.PATH_FUSED
+    assert L.resolved_path(L.OP_FWD, 33, 512, 512) == L.PATH_PREPASS
+    assert L.resolved_path(L.OP_BWD, 16, 512, 512) == L.PATH_PREPASS
