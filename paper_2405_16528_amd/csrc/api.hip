@@ -168,41 +168,70 @@ int planned_splits(int64_t M, int64_t N, int64_t K, int64_t ldp, size_t room) {
 }
 size_t slices_bytes(int64_t splits, int64_t M, int64_t ldp) { return round_up((size_t)splits * (size_t)M * (size_t)ldp * 4, 256); }
 
+// The layouts below take the size of the workspace at hand; ALL: the size that loqt_workspace_bytes asks for.
+constexpr size_t ALL = ~(size_t)0;
+
 // `saved`: the caller keeps W_eff in a buffer of its own (loqt_linear_fwd_save / loqt_linear_bwd_saved), so the
 // workspace holds no copy of the weight (and the forward pass, always folded then, no U)
+// Pitch of the bf16 copy of the weight: rows that start on a cache line (128 bytes) where the workspace has room for it.
+// (x of 5461 columns at a pitch of 5464 makes every 128-byte piece of a row span two lines; the weight need not as well.)
+struct Region {
+    size_t at, end;
+    int64_t ld;
+};
+Region weight_region(size_t at, int64_t rows, int64_t cols, size_t rest, size_t ws_bytes) {
+    const int64_t wide = (int64_t)round_up(cols, 64), ld = at + bf16_bytes(rows, wide) + rest <= ws_bytes ? wide : (int64_t)round_up(cols, 8);
+    return Region{at, at + bf16_bytes(rows, ld), ld};
+}
+
 struct FwdWs {
     size_t U, Wb, Pb, split, least, total;  // U = s x B^T; Wb = deq(W) or W_eff; Pb = deq(P); slices of U, then of y
-    FwdWs(int64_t T, int64_t out, int64_t in, int64_t r, bool saved = false) {
+    int64_t ldw;
+    FwdWs(int64_t T, int64_t out, int64_t in, int64_t r, bool saved, size_t ws_bytes) {
         U = 0;
         Wb = U + (saved ? 0 : bf16_bytes(T, r));
-        Pb = Wb + (saved ? 0 : bf16_bytes(out, in));
-        split = Pb + bf16_bytes(out, r);
-        least = split + round_up((size_t)remainder_split_floats(T, out) * 4, 256);
-        // (whichever form runs: the size does not depend on the path option)
-        int64_t most = product_split_floats(T, out, in, 0);
-        if (!saved) most = std::max({most, product_split_floats(T, r, in, 0), product_split_floats(T, out, in, r)});
-        total = std::max(least, split + round_up((size_t)most * 4, 256));
+        const size_t rest = bf16_bytes(out, r), remainder = round_up((size_t)remainder_split_floats(T, out) * 4, 256);
+        const Region w = weight_region(Wb, out, in, rest + remainder, ws_bytes);
+        ldw = w.ld;
+        Pb = saved ? Wb : w.end;
+        split = Pb + rest;
+        least = Wb + (saved ? 0 : bf16_bytes(out, in)) + rest + remainder;
+        total = least;
+        if (ws_bytes == ALL) {
+            // (whichever form runs: the size does not depend on the path option)
+            int64_t most = product_split_floats(T, out, in, 0);
+            if (!saved) most = std::max({most, product_split_floats(T, r, in, 0), product_split_floats(T, out, in, r)});
+            total = std::max(split + remainder, split + round_up((size_t)most * 4, 256));
+        }
     }
 };
 struct BwdWs {
     size_t Z, Wb, Pb, partials, least, total;  // Z = s dy deq(P); Wb = deq(W) or W_eff; Pb = deq(P); fp32 slices
-    int64_t ldp;
-    BwdWs(int64_t T, int64_t out, int64_t in, int64_t r, bool saved = false) {
+    int64_t ldw, ldp;
+    BwdWs(int64_t T, int64_t out, int64_t in, int64_t r, bool saved, size_t ws_bytes) {
         Z = 0;
         Wb = Z + bf16_bytes(T, r);
-        Pb = Wb + (saved ? 0 : bf16_bytes(out, in));
-        partials = Pb + bf16_bytes(out, r);
         ldp = (int64_t)round_up(in, 4);
         const int64_t ldzp = (int64_t)round_up(r, 4);
         // the slices of Z are summed into Z before those of dx are written, and both before the dB product writes
         // its own: one region serves all three
         const int least_z = least_z_splits(T, out, r);
-        least = partials + std::max({slices_bytes(least_splits(r, in, T), r, ldp),
-                                     least_z > 1 ? slices_bytes(least_z, T, ldzp) : (size_t)0,
-                                     round_up((size_t)remainder_split_floats(T, in) * 4, 256)});
-        const int64_t dx = std::max(product_split_floats(T, in, out, 0), product_split_floats(T, in, out, r));
-        total = std::max({least, partials + slices_bytes(planned_splits(r, in, T, ldp, ~(size_t)0), r, ldp),
-                          partials + round_up((size_t)std::max(dx, product_split_floats(T, r, out, 0)) * 4, 256)});
+        const size_t rest = bf16_bytes(out, r);
+        const size_t least_slices = std::max({slices_bytes(least_splits(r, in, T), r, ldp),
+                                              least_z > 1 ? slices_bytes(least_z, T, ldzp) : (size_t)0,
+                                              round_up((size_t)remainder_split_floats(T, in) * 4, 256)});
+        const Region w = weight_region(Wb, out, in, rest + least_slices, ws_bytes);
+        ldw = w.ld;
+        Pb = saved ? Wb : w.end;
+        partials = Pb + rest;
+        least = Wb + (saved ? 0 : bf16_bytes(out, in)) + rest + least_slices;
+        total = least;
+        if (ws_bytes == ALL) {
+            const int64_t most = std::max({product_split_floats(T, in, out, 0), product_split_floats(T, in, out, r),
+                                           product_split_floats(T, r, out, 0)});
+            total = partials + std::max({least_slices, slices_bytes(planned_splits(r, in, T, ldp, ALL), r, ldp),
+                                         round_up((size_t)most * 4, 256)});
+        }
     }
 };
 struct MergeWs {
@@ -227,28 +256,38 @@ struct InitWs {
         E = Pb + round_up((size_t)out * (size_t)ldr * 2, 256);
         partials = E + round_up((size_t)out * (size_t)lde * 2, 256);
         least = partials + slices_bytes(least_splits(r, in, out), r, ldp);
-        total = std::max(least, partials + slices_bytes(planned_splits(r, in, out, ldp, ~(size_t)0), r, ldp));
+        total = std::max(least, partials + slices_bytes(planned_splits(r, in, out, ldp, ALL), r, ldp));
     }
 };
 
 // LoQT-nq: U or Z (T x r) first, then the dB slices (backward), then room for the folded weight W_eff (out x in, bf16),
 // whether or not the path option makes this call fold, then the slices of U or Z and of y or dx
 struct NqWs {
-    size_t partials, We, split, total;
-    int64_t ldp;
-    NqWs(bool bwd, int64_t T, int64_t out, int64_t in, int64_t r) {
+    size_t partials, We, split, least, total;  // least: for a call that folds
+    int64_t ldw, ldp;
+    NqWs(bool bwd, int64_t T, int64_t out, int64_t in, int64_t r, size_t ws_bytes) {
         partials = bf16_bytes(T, r);
         ldp = (int64_t)round_up(in, 4);
         // the region of the dB slices is as large as loqt_linear_bwd's least workspace makes it
-        const BwdWs L(T, out, in, r);
-        We = partials + (bwd ? L.least - L.partials : 0);
-        split = We + bf16_bytes(out, in);
-        int64_t most;
-        if (bwd) most = std::max({product_split_floats(T, r, out, 0), product_split_floats(T, in, out, 0),
-                                  product_split_floats(T, in, out, r), planned_splits(r, in, T, ldp, ~(size_t)0) * r * ldp});
-        else most = std::max({product_split_floats(T, r, in, 0), product_split_floats(T, out, in, 0),
-                              product_split_floats(T, out, in, r)});
-        total = split + round_up((size_t)most * 4, 256);
+        size_t slices = 0;
+        if (bwd) {
+            const BwdWs L(T, out, in, r, true, 0);
+            slices = L.least - L.partials;
+        }
+        We = partials + slices;
+        const Region w = weight_region(We, out, in, 0, ws_bytes);
+        ldw = w.ld;
+        split = w.end;
+        least = We + bf16_bytes(out, in);
+        total = least;
+        if (ws_bytes == ALL) {
+            int64_t most;
+            if (bwd) most = std::max({product_split_floats(T, r, out, 0), product_split_floats(T, in, out, 0),
+                                      product_split_floats(T, in, out, r), planned_splits(r, in, T, ldp, ALL) * r * ldp});
+            else most = std::max({product_split_floats(T, r, in, 0), product_split_floats(T, out, in, 0),
+                                  product_split_floats(T, out, in, r)});
+            total = split + round_up((size_t)most * 4, 256);
+        }
     }
 };
 
@@ -257,21 +296,24 @@ struct NqWs {
 struct RightWs {
     size_t Qb, We, V, partials, least, total;  // partials: slices of V, of y or dx, of dBp, one after the other
     int64_t ldr, ldw, ldp;
-    RightWs(int op, int64_t T, int64_t out, int64_t in, int64_t r) {
+    RightWs(int op, int64_t T, int64_t out, int64_t in, int64_t r, size_t ws_bytes) {
         ldr = (int64_t)round_up(r, 8);
-        ldw = (int64_t)round_up(in, 8);
         ldp = (int64_t)round_up(r, 4);
         Qb = 0;
         We = Qb + bf16_bytes(in, r);
-        V = We + (op == LOQT_OP_MERGE_RIGHT ? 0 : bf16_bytes(out, in));
-        partials = V + (op == LOQT_OP_BWD_RIGHT ? bf16_bytes(T, r) : 0);
-        least = total = partials;
-        if (op == LOQT_OP_FWD_RIGHT) total += round_up((size_t)product_split_floats(T, out, in, 0) * 4, 256);
-        if (op == LOQT_OP_BWD_RIGHT) {
-            least = partials + slices_bytes(least_splits(out, r, T), out, ldp);
-            const int64_t v_dx = std::max(product_split_floats(T, r, in, 0), product_split_floats(T, in, out, 0));
-            total = std::max({least, partials + slices_bytes(planned_splits(out, r, T, ldp, ~(size_t)0), out, ldp),
-                              partials + round_up((size_t)v_dx * 4, 256)});
+        const bool weight = op != LOQT_OP_MERGE_RIGHT, bwd = op == LOQT_OP_BWD_RIGHT;
+        const size_t v = bwd ? bf16_bytes(T, r) : 0, least_slices = bwd ? slices_bytes(least_splits(out, r, T), out, ldp) : 0;
+        const Region w = weight_region(We, out, in, v + least_slices, ws_bytes);
+        ldw = w.ld;
+        V = weight ? w.end : We;
+        partials = V + v;
+        least = We + (weight ? bf16_bytes(out, in) : 0) + v + least_slices;
+        total = least;
+        if (ws_bytes == ALL && weight) {
+            int64_t most = bwd ? std::max(product_split_floats(T, r, in, 0), product_split_floats(T, in, out, 0))
+                               : product_split_floats(T, out, in, 0);
+            total = partials + std::max({least_slices, round_up((size_t)most * 4, 256),
+                                         bwd ? slices_bytes(planned_splits(out, r, T, ldp, ALL), out, ldp) : (size_t)0});
         }
     }
 };
@@ -478,25 +520,25 @@ size_t loqt_workspace_bytes(int op, int64_t T, int64_t out, int64_t in, int64_t 
     switch (op) {
         case LOQT_OP_FWD: {
             if (T <= 0) return 0;
-            return FwdWs(T, out, in, r).total;  // the fused path needs only its first part (U)
+            return FwdWs(T, out, in, r, false, ALL).total;  // the fused path needs only its first part (U)
         }
         case LOQT_OP_BWD: {
             if (T <= 0) return 0;
             const size_t fused = bwd_z_bytes(T, r) + round_up((size_t)gemm_db_splits(T, r, in) * (size_t)r * (size_t)in * 4, 256);
-            const size_t pre = BwdWs(T, out, in, r).total;
+            const size_t pre = BwdWs(T, out, in, r, false, ALL).total;
             return fused > pre ? fused : pre;
         }
-        case LOQT_OP_FWD_SAVE: return T <= 0 ? 0 : FwdWs(T, out, in, r, true).total;
-        case LOQT_OP_BWD_SAVED: return T <= 0 ? 0 : BwdWs(T, out, in, r, true).total;
+        case LOQT_OP_FWD_SAVE: return T <= 0 ? 0 : FwdWs(T, out, in, r, true, ALL).total;
+        case LOQT_OP_BWD_SAVED: return T <= 0 ? 0 : BwdWs(T, out, in, r, true, ALL).total;
         case LOQT_OP_MERGE: return merge_ws_bytes(out, in, r);
         case LOQT_OP_INIT: return InitWs(out, in, r).total;
         case LOQT_OP_FWD_RIGHT:
         case LOQT_OP_BWD_RIGHT:
             if (T <= 0) return 0;
-            return RightWs(op, T, out, in, r).total;
-        case LOQT_OP_MERGE_RIGHT: return RightWs(op, 0, out, in, r).total;
-        case LOQT_OP_FWD_NQ: return T <= 0 ? 0 : NqWs(false, T, out, in, r).total;
-        case LOQT_OP_BWD_NQ: return T <= 0 ? 0 : NqWs(true, T, out, in, r).total;
+            return RightWs(op, T, out, in, r, ALL).total;
+        case LOQT_OP_MERGE_RIGHT: return RightWs(op, 0, out, in, r, ALL).total;
+        case LOQT_OP_FWD_NQ: return T <= 0 ? 0 : NqWs(false, T, out, in, r, ALL).total;
+        case LOQT_OP_BWD_NQ: return T <= 0 ? 0 : NqWs(true, T, out, in, r, ALL).total;
         default: return 0;
     }
 }
@@ -513,7 +555,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
     LOQT_TRY(check_bf16(y, T, out, ld_y));
     if (!ws) return LOQT_INVALID_ARG;
     if (!aligned(ws, 256)) return LOQT_MISALIGNED;
-    const FwdWs L(T, out, in, r, save_weff != nullptr);
+    const FwdWs L(T, out, in, r, save_weff != nullptr, ws_bytes);
     if (ws_bytes < L.least) return LOQT_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)hip_stream;
     const int64_t ld_u = (int64_t)round_up(r, 8);
@@ -548,7 +590,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
         char* base = reinterpret_cast<char*>(ws);
         uint16_t* Wb = save_weff ? save_weff : reinterpret_cast<uint16_t*>(base + L.Wb);
         uint16_t* Pb = reinterpret_cast<uint16_t*>(base + L.Pb);
-        const int64_t ldw = save_weff ? ld_save : (int64_t)round_up(in, 8);
+        const int64_t ldw = save_weff ? ld_save : L.ldw;
         const bool folded = save_weff || use_folded(T, out, in);
         if (folded) {
             // y = x W_eff^T with W_eff = deq(W) + s deq(P) B folded once per call
@@ -651,7 +693,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
     if (!aligned(dB, dB_dtype == LOQT_BF16 ? 2 : 4)) return LOQT_MISALIGNED;
     if (!ws) return LOQT_INVALID_ARG;
     if (!aligned(ws, 256)) return LOQT_MISALIGNED;
-    const BwdWs L(T, out, in, r, saved != nullptr);
+    const BwdWs L(T, out, in, r, saved != nullptr, ws_bytes);
     // (the fused form sums as many slices as it likes, in a workspace laid out Z, slices)
     const size_t fused = bwd_z_bytes(T, r) + round_up((size_t)gemm_db_splits(T, r, in) * (size_t)r * (size_t)in * 4, 256);
     if (ws_bytes < (saved ? L.least : std::max(L.least, fused))) return LOQT_WORKSPACE_TOO_SMALL;
@@ -667,7 +709,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         uint16_t* Pb = reinterpret_cast<uint16_t*>(base + L.Pb);
         float* part = reinterpret_cast<float*>(base + L.partials);
         const int64_t part_floats = (int64_t)((ws_bytes - L.partials) / 4);
-        const int64_t ldw = saved ? ld_saved : (int64_t)round_up(in, 8);
+        const int64_t ldw = saved ? ld_saved : L.ldw;
         LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_z, st, SLOT_PREPASS));
         const bool folded = dx && (saved || use_folded_bwd(T, out, in));
         // Z rides along with dx (one product [dx | Z] over the shared operand dy) when that is estimated to
@@ -971,7 +1013,7 @@ loqt_status loqt_linear_fwd_right(const loqt_bf16* x, int64_t ld_x, int64_t T, c
     const int64_t out = Wq->rows, in = Wq->cols, r = Qq->cols;
     LOQT_TRY(check_bf16(x, T, in, ld_x));
     LOQT_TRY(check_bf16(y, T, out, ld_y));
-    const RightWs L(LOQT_OP_FWD_RIGHT, T, out, in, r);
+    const RightWs L(LOQT_OP_FWD_RIGHT, T, out, in, r, ws_bytes);
     LOQT_TRY(check_ws(ws, ws_bytes, L.least));
     hipStream_t st = (hipStream_t)hip_stream;
     char* base = reinterpret_cast<char*>(ws);
@@ -1007,7 +1049,7 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     if (dBp_dtype != LOQT_F32 && dBp_dtype != LOQT_BF16) return LOQT_INVALID_ARG;
     if (ld_dBp < r) return LOQT_BAD_SHAPE;
     if (!aligned(dBp, dBp_dtype == LOQT_BF16 ? 2 : 4)) return LOQT_MISALIGNED;
-    const RightWs L(LOQT_OP_BWD_RIGHT, T, out, in, r);
+    const RightWs L(LOQT_OP_BWD_RIGHT, T, out, in, r, ws_bytes);
     LOQT_TRY(check_ws(ws, ws_bytes, L.least));
     const int64_t part_floats = (int64_t)((ws_bytes - L.partials) / 4);
     hipStream_t st = (hipStream_t)hip_stream;
@@ -1068,7 +1110,7 @@ loqt_status loqt_merge_requant_right(const loqt_nf4_mat* Wq, uint8_t* codes_out,
     if (!aligned(codes_out, 16) || !aligned(absmax_out, 4)) return LOQT_MISALIGNED;
     LOQT_TRY(check_out_alias(Wq, codes_out, absmax_out));
     const int64_t out = Wq->rows, in = Wq->cols, r = Qq->cols;
-    const RightWs L(LOQT_OP_MERGE_RIGHT, 0, out, in, r);
+    const RightWs L(LOQT_OP_MERGE_RIGHT, 0, out, in, r, ws_bytes);
     LOQT_TRY(check_ws(ws, ws_bytes, L.total));
     hipStream_t st = (hipStream_t)hip_stream;
     uint16_t* Qb = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.Qb);
@@ -1194,18 +1236,19 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     LOQT_TRY(check_bf16(x, T, in, ld_x));
     LOQT_TRY(check_bf16(y, T, out, ld_y));
     const bool few = use_few_tokens(T), folded = use_folded(T, out, in);
-    LOQT_TRY(check_ws(ws, ws_bytes, bf16_bytes(T, r) + (folded ? bf16_bytes(out, in) : 0)));
+    const NqWs L(false, T, out, in, r, ws_bytes);
+    LOQT_TRY(check_ws(ws, ws_bytes, folded ? L.least : L.We));
     hipStream_t st = (hipStream_t)hip_stream;
     // slices of U and y: past the folded weight, or in its place when this call does not fold
-    const size_t split_off = bf16_bytes(T, r) + (folded ? bf16_bytes(out, in) : 0);
+    const size_t split_off = folded ? L.split : L.We;
     float* split = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + split_off);
     const int64_t split_floats = (int64_t)((ws_bytes - split_off) / 4);
     uint16_t* U = reinterpret_cast<uint16_t*>(ws);
     const int64_t ld_u = (int64_t)round_up(r, 8);
     GemmParams p;
     if (folded && !few) {  // y = x W_eff^T with the rank-r term folded into a transient copy of the weight
-        uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + bf16_bytes(T, r));
-        const int64_t ld_we = (int64_t)round_up(in, 8);
+        uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.We);
+        const int64_t ld_we = L.ldw;
         LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, st));
         memset(&p, 0, sizeof(p));
         p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
@@ -1260,20 +1303,19 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     if (dB_dtype != LOQT_F32 && dB_dtype != LOQT_BF16) return LOQT_INVALID_ARG;
     if (ld_dB < in) return LOQT_BAD_SHAPE;
     if (!aligned(dB, dB_dtype == LOQT_BF16 ? 2 : 4)) return LOQT_MISALIGNED;
-    const NqWs L(true, T, out, in, r);
+    const NqWs L(true, T, out, in, r, ws_bytes);
     const size_t z_bytes = bf16_bytes(T, r);
     const bool folded = dx && use_folded(T, out, in);
     // slices of Z, dx and dB, one after the other: in the region of the dB slices, or past the folded weight (or in its
     // place) where there is more room
-    const size_t end = folded ? L.split : L.We;
-    LOQT_TRY(check_ws(ws, ws_bytes, end));
+    LOQT_TRY(check_ws(ws, ws_bytes, folded ? L.least : L.We));
     hipStream_t st = (hipStream_t)hip_stream;
     uint16_t* Z = reinterpret_cast<uint16_t*>(ws);
     uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.We);
     const bool at_end = folded && ws_bytes - L.split > L.We - L.partials;
     float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + (at_end ? L.split : z_bytes));
     const size_t part_bytes = at_end ? ws_bytes - L.split : folded ? L.We - L.partials : ws_bytes - L.partials;
-    const int64_t ld_we = (int64_t)round_up(in, 8);
+    const int64_t ld_we = L.ldw;
     if (folded) LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, st));
     const int64_t ld_z = (int64_t)round_up(r, 8);
     GemmParams p;

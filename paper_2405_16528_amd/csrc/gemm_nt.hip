@@ -77,8 +77,7 @@ struct NtCfg {
 
 // One output tile.  L: index of the tile in the walk order described above (tiles past the end return at once);
 // split: slice of the contraction (EPI_F32_SPLITK), else 0.
-// NOTAIL (16x16x32 form only): every K segment is a whole number of k-tiles, so no tile ever takes the register path
-// and the loads need no mask -- see hot_load_live.
+// NOTAIL (16x16x32 form only): every K segment is a whole number of k-tiles, so no tile has to be cut (cut_tile).
 template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false>
 __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, const int split) {
     using Cfg = NtCfg<BM, BN, NS>;
@@ -324,8 +323,10 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         uint32_t offA[Cfg::NCHA], offB[Cfg::NCHB];
         const char *hotA = nullptr, *hotB = nullptr;  // operand bytes of the tile whose first half was issued last
         int64_t stepA = 0, stepB = 0;
+        // (kleft: what is left of the segment's contraction from k0 on.  The loads of a tile that is not full repeat a
+        // valid chunk or k row in place of those past the end; cut_tile then clears them.)
         auto hot_operand = [&](auto rc_tag, auto br_tag, const void* optr, int64_t old, int orows, int row0, int k0,
-                               uint32_t* off, const char*& base, int64_t& step) {
+                               int kleft, uint32_t* off, const char*& base, int64_t& step) {
             constexpr bool RC = decltype(rc_tag)::value;
             constexpr int BR = decltype(br_tag)::value;
             constexpr int NC = BR / 32;
@@ -335,8 +336,9 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 const int r0 = tid >> 3;
                 const int kc = (tid & 7) ^ kc_swz(r0);
                 const int rlast = orows - 1 - row0;
+                const uint32_t kb = NOTAIL || kc * 8 < kleft ? (uint32_t)kc * 16u : 0u;
 #pragma unroll
-                for (int i = 0; i < NC; ++i) off[i] = (uint32_t)min(i * 32 + r0, rlast) * ld2 + (uint32_t)kc * 16u;
+                for (int i = 0; i < NC; ++i) off[i] = (uint32_t)min(i * 32 + r0, rlast) * ld2 + kb;
                 base = reinterpret_cast<const char*>(optr) + ((int64_t)row0 * old + k0) * 2;
                 step = BK * 2;
             } else {
@@ -347,7 +349,8 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                 for (int i = 0; i < NC; ++i) {
                     const int logical = (tid % CPR) ^ rc_swz(kq + i * KPI, CPR);
-                    off[i] = (uint32_t)(kq + i * KPI) * ld2 + (uint32_t)min(logical * 8, clast) * 2u;
+                    const int kr = NOTAIL ? kq + i * KPI : min(kq + i * KPI, kleft - 1);
+                    off[i] = (uint32_t)kr * ld2 + (uint32_t)min(logical * 8, clast) * 2u;
                 }
                 base = reinterpret_cast<const char*>(optr) + ((int64_t)k0 * old + row0) * 2;
                 step = (int64_t)BK * old * 2;
@@ -356,13 +359,15 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         auto hot_setup = [&](int kt) {  // kt: a tile of the range
             const bool seg = kt >= nkt0;
             const int k0 = (kt - (seg ? nkt0 : 0)) * BK;
+            const int kleft = (seg ? p.A[1].K : p.A[0].K) - k0;
             hot_operand(std::integral_constant<bool, ARC>{}, std::integral_constant<int, BM>{}, a_ptr(seg), a_ld(seg),
-                        a_rows(seg), m0, k0, offA, hotA, stepA);
+                        a_rows(seg), m0, k0, kleft, offA, hotA, stepA);
             hot_operand(std::integral_constant<bool, BRC>{}, std::integral_constant<int, BN>{}, b_ptr(seg), b_ld(seg),
-                        b_rows(seg), n0, k0, offB, hotB, stepB);
+                        b_rows(seg), n0, k0, kleft, offB, hotB, stepB);
         };
+        auto is_tail = [&](int t) { return t == tail0 || t == tail1; };
         auto hot_advance = [&](int kt) {  // move on to tile kt, the successor of the current one (kt < kt_end)
-            if (kt == nkt0) hot_setup(kt);
+            if (kt == nkt0 || (MF16 && !NOTAIL && is_tail(kt))) hot_setup(kt);
             else hotA += stepA, hotB += stepB;
         };
         const uint32_t lds0 = (uint32_t)(uintptr_t)LOQT_LDS_PTR(smem);
@@ -396,8 +401,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             // tests/test_isa_guard.py checks that nothing else in the loop touches M0.  EXEC is restored to all
             // ones, the value it has in this uniform control flow.
         };
-        // The same load without the mask, for kernels whose tiles are all full (NOTAIL): two scalar instructions
-        // less per load.  A wave issues at most one instruction every four cycles, and the six-instruction form
+        // The same load without the mask (16x16x32 form): two scalar instructions less per load.  A wave issues at most one instruction every four cycles, and the six-instruction form
         // between two MFMAs of sixteen cycles each holds the second one back.  Tiles past the end of the contraction
         // are not masked either: the tile pointers stop advancing, so such a load fetches the last tile once more
         // into a stage nobody reads again (the loop's exit waits for them before LDS is reused).
@@ -413,6 +417,39 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 :
                 : "v"(o), "s"(base), "s"(dst)
                 : "memory");
+        };
+        // Tile kt of the range has landed in `stage` by direct loads and ends past its segment's contraction: clears
+        // everything from there on, in both operands (what came instead is finite, but the padding of a row need not be).
+        // The slots of LDS are those of the staging above.  A barrier has to follow.
+        auto cut_operand = [&](auto rc_tag, auto br_tag, int kleft, char* tile) {
+            constexpr bool RC = decltype(rc_tag)::value;
+            constexpr int BR = decltype(br_tag)::value;
+            constexpr int NC = BR / 32;
+            if constexpr (!RC) {
+                const int nv = kleft - 8 * ((tid & 7) ^ kc_swz(tid >> 3));  // valid elements of this thread's chunk column
+                if (nv < 8) {
+                    uint32_t keep[4];
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) keep[d] = 2 * d + 1 < nv ? 0xffffffffu : 2 * d < nv ? 0xffffu : 0u;
+#pragma unroll 1
+                    for (int i = 0; i < NC; ++i) {
+                        uint4* q = reinterpret_cast<uint4*>(tile + i * 4096 + tid * 16);
+                        const uint4 v = *q;
+                        *q = make_uint4(v.x & keep[0], v.y & keep[1], v.z & keep[2], v.w & keep[3]);
+                    }
+                }
+            } else {
+                constexpr int CPR = BR / 8, KPI = 256 / CPR;
+#pragma unroll 1
+                for (int i = 0; i < NC; ++i)
+                    if (i * KPI + tid / CPR >= kleft) *reinterpret_cast<uint4*>(tile + i * 4096 + tid * 16) = make_uint4(0, 0, 0, 0);
+            }
+        };
+        auto cut_tile = [&](int kt, char* stage) {
+            const bool seg = kt >= nkt0;
+            const int kleft = (seg ? p.A[1].K : p.A[0].K) - (kt - (seg ? nkt0 : 0)) * BK;
+            cut_operand(std::integral_constant<bool, ARC>{}, std::integral_constant<int, BM>{}, kleft, stage);
+            cut_operand(std::integral_constant<bool, BRC>{}, std::integral_constant<int, BN>{}, kleft, stage + BM * ROWB);
         };
         // fragment u (A fragments first) of k16 step ks of the tile at `stage` into buffer nb
         auto read_unit = [&](int ks, int nb, int u, const char* stage) {
@@ -498,20 +535,14 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             }
         };
         // slots S0..S1-1 (two MFMAs each) of a k32 step on fragment buffer CB.  RD > 0: the fragment reads of k32 step
-        // RKS of the tile at `rstage` into the other buffer, RD per slot from the first slot of the range on.  LD (0 / 1:
-        // that half of the tile at hotA / hotB, 2: all of it, -1: none): its loads into `lstage`, one per slot on the
-        // last slots of the range.
-        using I2tag = std::integral_constant<int, 2>;
+        // RKS of the tile at `rstage` into the other buffer, RD per slot from the first slot of the range on.  LD >= 0:
+        // this range starts at slot LD of the schedule of loads (of the tile at hotA / hotB, into `lstage`), one every
+        // LSP-th slot.
         auto slots16 = [&](auto cb_tag, auto s0_tag, auto s1_tag, auto rd_tag, auto rks_tag, auto ld_tag, const char* rstage,
-                           char* lstage, uint32_t live) {
+                           char* lstage) {
             constexpr int CB = decltype(cb_tag)::value, S0 = decltype(s0_tag)::value, S1 = decltype(s1_tag)::value;
             constexpr int RPS = decltype(rd_tag)::value;                 // fragment reads per slot
             constexpr int RKS = decltype(rks_tag)::value, LD = decltype(ld_tag)::value;
-            constexpr int NSL = S1 - S0;
-            constexpr int NLD = LD == 2 ? Cfg::NCH : NL;                 // loads to place ...
-            constexpr int LPS16 = (NLD + NSL - 1) / NSL;                 // ... LPS16 per slot ...
-            constexpr int LSL = (NLD + LPS16 - 1) / LPS16;               // ... on LSL slots ...
-            constexpr int LST = NSL >= 2 * LSL ? 2 : 1;                  // ... every LST-th of the last LST * LSL
 #pragma unroll
             for (int sl = S0; sl < S1; ++sl) {
 #pragma unroll
@@ -524,22 +555,9 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                     for (int u = t * RPS; u < (t + 1) * RPS && u < NU2; ++u) rd16(RKS, CB ^ 1, u, rstage);
                 }
-                if constexpr (LD >= 100) {
-                    // spread form without masks (schedule slot LD - 100 + t)
-                    const int g = LD - 100 + t;
+                if constexpr (LD >= 0) {
+                    const int g = LD + t;
                     if (g % LSP == 0 && g / LSP < Cfg::NCH) hot_load_live(g / LSP, lstage);
-                } else if constexpr (LD >= 10) {
-                    // spread form: the whole tile, one load every third slot from slot LD - 10 of the schedule on
-                    // (this range starts at schedule slot LD - 10)
-                    const int g = LD - 10 + t;
-                    if (g % LSP == 0 && g / LSP < Cfg::NCH) hot_load(I2tag{}, g / LSP, lstage, live);
-                } else if constexpr (LD >= 0) {
-                    const int tl = t - (NSL - LST * LSL);
-                    if (tl >= 0 && tl % LST == 0) {
-#pragma unroll
-                        for (int n = (tl / LST) * LPS16; n < (tl / LST + 1) * LPS16 && n < NLD; ++n)
-                            hot_load(ld_tag, n, lstage, live);
-                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -564,7 +582,6 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 : "scc");
             return m;
         };
-        auto is_tail = [&](int t) { return t == tail0 || t == tail1; };
         // The ring of NS stages: tile t lives in stage (t - kt_begin) % NS.  At the top of iteration kt the tiles
         // kt .. kt+NS-2 are in LDS or on their way, and so is the first half of tile kt+NS-1.
         auto wait_loads = [&](bool later_live) {
@@ -590,69 +607,45 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             // its wave cycles waiting where that kernel spent 6 %.
             using SH = std::integral_constant<int, NS2 / 2>;
             using SE = std::integral_constant<int, NS2>;
-            auto whole_tile = [&](int t, char* stage) -> bool {  // all of tile t into `stage`; true if by direct loads
-                if (is_tail(t)) {
-                    tail_tile(t, stage);
-                    return false;
-                }
-                const uint32_t live = live_mask(t);
-#pragma unroll
-                for (int n = 0; n < Cfg::NCH; ++n) hot_load(I2{}, n, stage, live);
-                return true;
-            };
             if (kt_begin < kt_end) {
                 hot_setup(kt_begin);
-                whole_tile(kt_begin, smem);
-                bool second = false;
-                if (kt_begin + 1 < kt_end) {
-                    hot_advance(kt_begin + 1);
-                    second = whole_tile(kt_begin + 1, smem + STAGE);
-                }
-                if (second) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(Cfg::NCH) : "memory");
-                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int n = 0; n < Cfg::NCH; ++n) hot_load_live(n, smem);
+                // (a range of one tile loads it twice; nobody reads the second copy)
+                if (kt_begin + 1 < kt_end) hot_advance(kt_begin + 1);
+#pragma unroll
+                for (int n = 0; n < Cfg::NCH; ++n) hot_load_live(n, smem + STAGE);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(Cfg::NCH) : "memory");
                 __syncthreads();
+                if (!NOTAIL && is_tail(kt_begin)) {
+                    cut_tile(kt_begin, smem);
+                    __syncthreads();
+                }
 #pragma unroll
                 for (int u = 0; u < NU2; ++u) rd16(0, 0, u, smem);
             }
-            if constexpr (NOTAIL) {
-                for (int kt = kt_begin; kt < kt_end; ++kt) {
-                    char* cur = smem + ((kt - kt_begin) & 1) * STAGE;
-                    char* nxt = smem + (((kt - kt_begin) & 1) ^ 1) * STAGE;
-                    slots16(I0{}, I0{}, SH{}, I2{}, I1{}, NOLD{}, cur, cur, 0);
-                    __syncthreads();  // X
-                    if (kt + 2 < kt_end) hot_advance(kt + 2);
-                    slots16(I0{}, SH{}, SE{}, I0{}, I0{}, std::integral_constant<int, 100>{}, cur, cur, 0);
-                    slots16(I1{}, I0{}, SH{}, I0{}, I0{}, std::integral_constant<int, 100 + NS2 / 2>{}, cur, cur, 0);
-                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LBY) : "memory");
-                    __syncthreads();  // Y
-                    slots16(I1{}, SH{}, SE{}, std::integral_constant<int, RPQ>{}, I0{}, std::integral_constant<int, 100 + NS2>{}, nxt, cur, 0);
-                }
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads past the end, before LDS is reused
-            } else
             for (int kt = kt_begin; kt < kt_end; ++kt) {
                 char* cur = smem + ((kt - kt_begin) & 1) * STAGE;
                 char* nxt = smem + (((kt - kt_begin) & 1) ^ 1) * STAGE;
-                const uint32_t live2 = live_mask(kt + 2);
-                slots16(I0{}, I0{}, SH{}, I2{}, I1{}, NOLD{}, cur, cur, 0);
+                slots16(I0{}, I0{}, SH{}, I2{}, I1{}, NOLD{}, cur, cur);
                 __syncthreads();  // X: nobody reads `cur` any more
-                if (kt + 2 < kt_end) {
-                    hot_advance(kt + 2);
-                    if (live2 == 0) tail_tile(kt + 2, cur);  // a tail tile (rare): through registers
-                }
-                // the 16 loads of tile kt+2 go out one every third slot over the remaining 48 slots of the tile: the
+                if (kt + 2 < kt_end) hot_advance(kt + 2);
+                // the loads of tile kt+2 go out one every LSP-th slot over the remaining three quarters of the tile: the
                 // memory pipeline limits the requests in flight per compute unit, and a burst of loads stalls the
                 // issue of the MFMAs behind it
-                slots16(I0{}, SH{}, SE{}, I0{}, I0{}, std::integral_constant<int, 10>{}, cur, cur, live2);
-                slots16(I1{}, I0{}, SH{}, I0{}, I0{}, std::integral_constant<int, 10 + NS2 / 2>{}, cur, cur, live2);
-                // tile kt+1 must have landed; the loads of tile kt+2 issued so far (schedule slots 0-31: 11 of them)
-                // came after it and may stay in flight, provided they went out as direct loads (a masked load may
-                // not count)
-                if (live2 != 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LBY) : "memory");
-                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                slots16(I0{}, SH{}, SE{}, I0{}, I0{}, I0{}, cur, cur);
+                slots16(I1{}, I0{}, SH{}, I0{}, I0{}, std::integral_constant<int, NS2 / 2>{}, cur, cur);
+                // tile kt+1 must have landed; the loads of tile kt+2 issued so far came after it and may stay in flight
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LBY) : "memory");
                 __syncthreads();  // Y
+                if (!NOTAIL && is_tail(kt + 1)) {
+                    cut_tile(kt + 1, nxt);
+                    __syncthreads();
+                }
                 // harmless stale reads after the last tile
-                slots16(I1{}, SH{}, SE{}, std::integral_constant<int, RPQ>{}, I0{}, std::integral_constant<int, 10 + NS2>{}, nxt, cur, live2);
+                slots16(I1{}, SH{}, SE{}, std::integral_constant<int, RPQ>{}, I0{}, std::integral_constant<int, NS2>{}, nxt, cur);
             }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads past the end, before LDS is reused
         } else {
         if (kt_begin < kt_end) {
             hot_setup(kt_begin);
