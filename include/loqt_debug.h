@@ -30,7 +30,10 @@ extern "C" {
  *                      (dB = Z^T x).  Cheaper than carrying the rank-r term through every token
  *                      (2 T r (in + out) flop per pass) from T = out in / (in + out) tokens up.
  *   LOQT_PATH_AUTO   : forward calls with at most 32 tokens (loqt_linear_fwd, loqt_linear_fwd_nq) stream the weight
- *                      once and expand its codes in registers (a kernel of its own; reported as FUSED); otherwise
+ *                      once and expand its codes in registers (a kernel of its own; reported as FUSED); calls with up
+ *                      to 64 tokens, or up to 256 on weights of 14 million elements or more, that do not fold keep the
+ *                      rank-r term beside the weight (reported as PREPASS) but expand the codes inside the products;
+ *                      otherwise
  *                      forward and backward take the pre-pass family (measured ahead of the
  *                      general fused form at every token count from 16 up), folded when T (in + out) >= out in --
  *                      except that the backward pass, which has Z = s dy deq(P_q) at hand anyway, keeps the

@@ -126,6 +126,15 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
     return (double)out <= 0.73 * (double)T;
 }
 
+// A few hundred tokens that do not fold: the codes are expanded inside the products (nf4_tile.hip) and no copy of the
+// weight is made.  Up to 64 tokens that is never behind (forward + backward, us, against copies: 2048 x 2048, rank 512, 67
+// and 68; 13824 x 5120, rank 1024, 164 and 272); up to 256 it takes a weight whose copy costs more than the slower loop
+// (256 tokens: 5461 x 2048 112 and 97, 4096 x 4096 126 and 133, 5120 x 5120 152 and 184; at 512 the copy is as good).
+bool use_nf4_tile(int64_t T, int64_t out, int64_t in) {
+    if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in)) return false;
+    return T <= 64 || (T <= 256 && out * in >= 14000000);
+}
+
 inline size_t bf16_bytes(int64_t rows, int64_t cols) {
     return round_up((size_t)rows * (size_t)round_up(cols, 8) * 2, 256);
 }
@@ -386,6 +395,22 @@ hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipS
     return launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st);
 }
 
+// Slices that fit: fp32 M x N at a pitch that is a multiple of 4
+int64_t slices_that_fit(int64_t M, int64_t N, size_t bytes) { return (int64_t)(bytes / ((size_t)M * round_up(N, 4) * 4)); }
+
+// C[M x N] (bf16) = alpha * the product that launch_nf4_tile makes of p, in slices at `ws`
+loqt_status nf4_product(int slot, bool b_rc, GemmParams p, uint16_t* C, int64_t ldc, float* ws, size_t ws_bytes,
+                        hipStream_t st) {
+    const int64_t nkt = (p.A[0].K + 63) / 64 + (b_rc ? 0 : (p.A[1].K + 63) / 64), ld = (int64_t)round_up(p.N, 4);
+    const int extra = b_rc && p.A[1].K > 0 ? 1 : 0;
+    p.splits = nf4_tile_splits(p.M, p.N, nkt, extra, slices_that_fit(p.M, p.N, ws_bytes) - extra);
+    p.C = ws;
+    p.ldc = ld;
+    LOQT_HIP(launch_nf4_tile(slot, b_rc, p, st));
+    LOQT_HIP(launch_reduce_db(ws, p.splits + extra, p.M, p.N, ld, C, LOQT_BF16, ldc, 0, st, false));
+    return LOQT_OK;
+}
+
 loqt_status merge_fused(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absmax_out,
                         const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s, hipStream_t st) {
     const int out = (int)Wq->rows, in = (int)Wq->cols, r = (int)Pq->cols;
@@ -586,6 +611,31 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
         LOQT_HIP(launch_few_tokens(SLOT_GEMM_Y, true, p, st));
         return LOQT_OK;
     }
+    // (the slices go where the copy of the weight would be)
+    char* const slices = reinterpret_cast<char*>(ws) + L.Wb;
+    const size_t slices_room = ws_bytes - L.Wb;
+    if (!save_weff && use_nf4_tile(T, out, in) && slices_that_fit(T, out, slices_room) >= 1) {
+        memset(&p, 0, sizeof(p));  // U = s x B^T
+        p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
+        p.B[0] = bf16_operand(B, ld_B, (int)r, (int)in);
+        p.M = (int)T;
+        p.N = (int)r;
+        p.alpha = s;
+        p.C = U;
+        p.ldc = ld_u;
+        p.split_ws = reinterpret_cast<float*>(slices);
+        p.split_ws_floats = (int64_t)(slices_room / 4);
+        LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st));
+        memset(&p, 0, sizeof(p));  // y = x deq(W)^T + U deq(P)^T
+        p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
+        p.B[0] = nf4_operand(Wq, (int)out, (int)in);
+        p.A[1] = bf16_operand(U, ld_u, (int)T, (int)r);
+        p.B[1] = nf4_operand(Pq, (int)out, (int)r);
+        p.M = (int)T;
+        p.N = (int)out;
+        p.alpha = 1.0f;
+        return nf4_product(SLOT_GEMM_Y, false, p, y, ld_y, reinterpret_cast<float*>(slices), slices_room, st);
+    }
     if (save_weff || use_prepass(T)) {
         char* base = reinterpret_cast<char*>(ws);
         uint16_t* Wb = save_weff ? save_weff : reinterpret_cast<uint16_t*>(base + L.Wb);
@@ -710,6 +760,28 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         float* part = reinterpret_cast<float*>(base + L.partials);
         const int64_t part_floats = (int64_t)((ws_bytes - L.partials) / 4);
         const int64_t ldw = saved ? ld_saved : L.ldw;
+        // a few hundred tokens: Z and dx straight from the codes, their slices where the copies of W and P would be
+        const size_t room = ws_bytes - L.Wb;
+        const bool tile = !saved && use_nf4_tile(T, out, in) && slices_that_fit(T, r, room) >= 1 &&
+                          slices_that_fit(T, in, room) >= 2;
+        if (tile) {
+            memset(&p, 0, sizeof(p));
+            p.A[0] = bf16_operand(dy, ld_dy, (int)T, (int)out);
+            p.B[0] = nf4_operand(Pq, (int)r, (int)out);
+            p.M = (int)T;
+            p.N = (int)r;
+            p.alpha = s;
+            float* const sl = reinterpret_cast<float*>(base + L.Wb);
+            LOQT_TRY(nf4_product(SLOT_GEMM_Z, true, p, Z, ld_z, sl, room, st));
+            if (dx) {
+                p.B[0] = nf4_operand(Wq, (int)in, (int)out);
+                p.N = (int)in;
+                p.alpha = 1.0f;
+                p.A[1] = bf16_operand(Z, ld_z, (int)T, (int)r);
+                p.B[1] = bf16_operand(B, ld_B, (int)in, (int)r);
+                LOQT_TRY(nf4_product(SLOT_GEMM_DX, true, p, dx, ld_dx, sl, room, st));
+            }
+        } else {
         LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_z, st, SLOT_PREPASS));
         const bool folded = dx && (saved || use_folded_bwd(T, out, in));
         // Z rides along with dx (one product [dx | Z] over the shared operand dy) when that is estimated to
@@ -770,6 +842,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
             p.split_ws = part;  // (the slices of Z, if any, have been summed by now; those of dB come later)
             p.split_ws_floats = part_floats;
             LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
+        }
         }
         // dB = Z^T x: Z is T x r and x is T x in, both K x rows; contraction over T in slices
         memset(&p, 0, sizeof(p));
@@ -1418,6 +1491,7 @@ loqt_status loqt_absmax_dq_expand(const uint8_t* codes8, const float* c1, const 
 loqt_status loqt_prepare(void) {
     LOQT_HIP(prepare_nt_kernels());
     LOQT_HIP(prepare_fused_kernels());
+    LOQT_HIP(prepare_nf4_tile_kernels());
     void* scratch_ptr = nullptr;
     LOQT_HIP(dq_static_scratch(&scratch_ptr));
     return LOQT_OK;
