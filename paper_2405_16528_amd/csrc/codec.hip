@@ -49,10 +49,10 @@ __global__ __launch_bounds__(256) void nf4_quantize_kernel(const float* __restri
         Nf4BlockEncoder be;
         be.set(m);
         uint32_t c[8];
-        uint32_t near = 0;
+        float nearest = __builtin_inff();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) c[e] = be.encode_fast(&enc, v[e], near);
-        if (__any(near)) {  // wave-uniform: some element sits within rounding of a decision point
+        for (int e = 0; e < 8; ++e) c[e] = be.encode_fast(&enc, v[e], nearest);
+        if (__any(be.near(nearest))) {  // wave-uniform: some element sits within rounding of a decision point
 #pragma unroll
             for (int e = 0; e < 8; ++e) c[e] = be.encode(&enc, v[e]);
         }

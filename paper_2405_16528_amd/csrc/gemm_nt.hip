@@ -56,11 +56,6 @@ constexpr int ROWB = 128;  // bytes of one LDS row (64 bf16)
 
 __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
-__device__ __forceinline__ uint32_t nib4(uint32_t word, int e) {
-    // element e (0..3) of a 2-byte group: byte e/2, even e in the high nibble
-    return (word >> (8 * (e >> 1) + ((e & 1) ? 0 : 4))) & 15u;
-}
-
 template <int BM, int BN, int NS = 2>
 struct NtCfg {
     static constexpr int TM = BM / 64, TN = BN / 64;   // 32x32 tiles per wave
@@ -72,7 +67,7 @@ struct NtCfg {
     static constexpr int EPITCH = WTN * 2 + 8;         // staging pitch of the bf16 epilogue
     static constexpr int SMEM_MAIN = NS * STAGE;       // NS stages: tiles kt .. kt+NS-1 are in LDS or in flight
     static constexpr int SMEM_EPI = 4 * WTM * EPITCH;
-    static constexpr int SMEM = (SMEM_MAIN > SMEM_EPI ? SMEM_MAIN : SMEM_EPI) + 64;
+    static constexpr int SMEM = SMEM_MAIN > SMEM_EPI ? SMEM_MAIN : SMEM_EPI;
 };
 
 // One output tile.  L: index of the tile in the walk order described above (tiles past the end return at once);
@@ -90,6 +85,25 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+
+    // tables of the epilogues that decode or encode NF4, in static LDS (their reads need no base register) and filled here:
+    // the barriers of the main loop lie between
+    constexpr bool ENCODES = EPI == EPI_MERGE || EPI == EPI_COMP, DECODES = ENCODES || EPI == EPI_FOLD || EPI == EPI_FOLD_F32;
+    __shared__ Nf4EncTables enc_tables;
+    __shared__ float level_table[16];
+    // the levels of four codes in the low half of hw (element e in byte e / 2, even e in the high nibble)
+    auto levels4 = [&](uint32_t hw, float* q) {
+        const uint32_t even = (hw >> 2) & 0x3c3cu, odd = (hw << 2) & 0x3c3cu;  // byte offsets into the table
+        const char* const t = reinterpret_cast<const char*>(level_table);
+        q[0] = *reinterpret_cast<const float*>(t + (even & 0xffu)), q[1] = *reinterpret_cast<const float*>(t + (odd & 0xffu));
+        q[2] = *reinterpret_cast<const float*>(t + (even >> 8)), q[3] = *reinterpret_cast<const float*>(t + (odd >> 8));
+    };
+    if constexpr (ENCODES) {
+        if (tid >= 64 && tid < 128) nf4_enc_tables_fill(&enc_tables, tid - 64);
+    }
+    if constexpr (DECODES) {
+        if (tid < 16) level_table[tid] = kNf4Levels[tid];
+    }
 
     // ---- tile of this work-group: contiguous range per XCD, groups of GM tile rows inside
     const int tiles_m = (p.M + BM - 1) / BM;
@@ -715,11 +729,6 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // column n = tj*32 + 8*g + 4*(lane >> 5) + j.
     if (EPI == EPI_BF16 || EPI == EPI_FOLD || EPI == EPI_ACC_BF16) {
         constexpr int EPITCH = Cfg::EPITCH, WTM = Cfg::WTM, WTN = Cfg::WTN;
-        float* lut = reinterpret_cast<float*>(smem + Cfg::SMEM - 64);
-        if (EPI == EPI_FOLD) {
-            if (tid < 16) lut[tid] = kNf4Levels[tid];
-            __syncthreads();
-        }
         // The fold stages 32 rows at a time (the same 32 rows of LDS for every block of rows: the LDS operations of a
         // wave complete in order), which leaves room for the old codes of the whole tile beside them.
         constexpr bool FOLD = EPI == EPI_FOLD;
@@ -838,11 +847,9 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                         }
                     }
                     if (EPI == EPI_FOLD) {
-                        const uint32_t cw = (cw4[g] >> (16 * h)) & 0xffffu;
-                        v0 += am * lut[nib4(cw, 0)];
-                        v1 += am * lut[nib4(cw, 1)];
-                        v2 += am * lut[nib4(cw, 2)];
-                        v3 += am * lut[nib4(cw, 3)];
+                        float q[4];
+                        levels4(cw4[g] >> (16 * h), q);
+                        v0 += am * q[0], v1 += am * q[1], v2 += am * q[2], v3 += am * q[3];
                     }
                     const uint2 v = make_uint2(pack_bf16(v0, v1), pack_bf16(v2, v3));
                     *reinterpret_cast<uint2*>(ebuf + ((FOLD ? 0 : ti * 32) + frow) * EPITCH + (tj * 32 + 8 * g + 4 * h) * 2) = v;
@@ -857,11 +864,6 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         // fma(alpha, acc, fl32(absmax * q[code])), the same expression the merge epilogue quantises.
         float* C = reinterpret_cast<float*>(p.C);
         if (EPI == EPI_F32_SPLITK) C += (int64_t)split * p.M * p.ldc;
-        float* lut = reinterpret_cast<float*>(smem);
-        if (EPI == EPI_FOLD_F32) {
-            if (tid < 16) lut[tid] = kNf4Levels[tid];
-            __syncthreads();
-        }
         const int64_t ldb = p.w_ld >> 1, lda = p.w_ld >> 6;
         if constexpr (MF16) {
             // 16x16 accumulator tiles: lane holds row ti*16 + (lane & 15), columns tj*16 + 4*(lane >> 4) .. +3
@@ -904,12 +906,12 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int n = n0 + wn * Cfg::WTN + tj * 32 + 8 * g + 4 * h;
-                    float v[4];
+                    float v[4], lev[4];
+                    if constexpr (EPI == EPI_FOLD_F32) levels4(cw4[g] >> (16 * h), lev);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        if (EPI == EPI_FOLD_F32) {
-                            const uint32_t cw = (cw4[g] >> (16 * h)) & 0xffffu;
-                            v[j] = __builtin_fmaf(p.alpha, acc[ti][tj][4 * g + j], am * lut[nib4(cw, j)]);
+                        if constexpr (EPI == EPI_FOLD_F32) {
+                            v[j] = __builtin_fmaf(p.alpha, acc[ti][tj][4 * g + j], am * lev[j]);
                         } else {
                             v[j] = p.alpha * acc[ti][tj][4 * g + j];
                         }
@@ -931,11 +933,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         // 64-block along n (Alg. 1 line 5).  A block of row m is 32 values in this lane and 32 in lane ^ 32.
         // compensation step (Alg. 2 lines 8-10): the same with W_hat = w_f32 + alpha * acc; the residual
         // w_f32 - deq(q(W_hat)) leaves as bf16.
-        Nf4EncTables* enc = reinterpret_cast<Nf4EncTables*>(smem);
-        float* lut = reinterpret_cast<float*>(smem + sizeof(Nf4EncTables));
-        if (tid < 64) nf4_enc_tables_fill(enc, tid);
-        else if (tid < 80) lut[tid - 64] = kNf4Levels[tid - 64];
-        __syncthreads();
+        const Nf4EncTables* const enc = &enc_tables;
         const int64_t ldb = p.w_ld >> 1, lda = p.w_ld >> 6;
 #pragma unroll
         for (int ti = 0; ti < TM; ++ti) {
@@ -966,12 +964,11 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                     }
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {  // q = 4*tt + g: tile tt of the pair, column group g
-                        const uint32_t cw =
-                            (reinterpret_cast<const uint32_t*>(&cw4[q >> 2])[q & 3] >> (16 * h)) & 0xffffu;
+                        float lev[4];
+                        levels4(reinterpret_cast<const uint32_t*>(&cw4[q >> 2])[q & 3] >> (16 * h), lev);
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
-                            v[4 * q + j] = __builtin_fmaf(p.alpha, acc[ti][2 * b + (q >> 2)][4 * (q & 3) + j],
-                                                          am_old * lut[nib4(cw, j)]);
+                            v[4 * q + j] = __builtin_fmaf(p.alpha, acc[ti][2 * b + (q >> 2)][4 * (q & 3) + j], am_old * lev[j]);
                     }
                 } else {
                     const float* wrow = p.w_f32 + (int64_t)m * p.w_f32_ld;
@@ -987,7 +984,10 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                                                           wsrc[4 * q + j]);
                     }
                 }
-                if (nb + 64 > p.w_cols) {  // ragged last block (wave-uniform): columns past the end count as 0
+                // ragged last block: columns past the end count as 0.  (The condition in scalar registers and the empty
+                // assembly keep it a branch: turned into selects it costs as much as the whole encoder.)
+                if (n0 + (wave_s & 1) * Cfg::WTN + b * 64 + 64 > p.w_cols) {
+                    asm volatile("");
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
                         const int nq = nb + (q >> 2) * 32 + 8 * (q & 3) + 4 * h;
@@ -1008,10 +1008,10 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 // single-precision encoder first; the exact one again for the whole block when any lane of the
                 // wave has an element within rounding of a decision point (about one block in 10^4)
                 uint32_t code[32];
-                uint32_t near = 0;
+                float nearest = __builtin_inff();
 #pragma unroll
-                for (int e = 0; e < 32; ++e) code[e] = be.encode_fast(enc, v[e], near);
-                if (__any(near)) {
+                for (int e = 0; e < 32; ++e) code[e] = be.encode_fast(enc, v[e], nearest);
+                if (__any(be.near(nearest))) {
 #pragma unroll
                     for (int e = 0; e < 32; ++e) code[e] = be.encode(enc, v[e]);
                 }
@@ -1028,7 +1028,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                             const int nq = nb + tt * 32 + 8 * g + 4 * h;
                             float e[4];
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) e[j] = wsrc[4 * q + j] - amax * lut[c[j]];
+                            for (int j = 0; j < 4; ++j) e[j] = wsrc[4 * q + j] - amax * level_table[c[j]];
                             if (mvalid && nq < p.e_ld)
                                 *reinterpret_cast<uint2*>(p.e_out + (int64_t)m * p.e_ld + nq) =
                                     make_uint2(pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3]));
