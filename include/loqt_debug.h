@@ -39,7 +39,8 @@ extern "C" {
  *                      except that the backward pass, which has Z = s dy deq(P_q) at hand anyway, keeps the
  *                      rank-r term as a second K segment of the dx product when out > 0.73 T (2 T r in flop at
  *                      the rate of the large products instead of 2 out in r at the rate of the fold);
- *                      the merge is fused below 1024 columns (`in`), pre-pass above.
+ *                      the merge takes the pre-pass form; below 1024 columns (`in`, reported as FUSED), where
+ *                      it may be called without a workspace, it is fused if that or too small a one was passed.
  * All compute the same quantities; results differ only in rounding order, within the stated
  * tolerance.
  */

@@ -99,7 +99,8 @@ bool use_prepass(int64_t /*tokens*/) {
 }
 // Forward with a handful of tokens: the codes are streamed once and expanded in registers (few.hip), no copy of the weight.
 bool use_few_tokens(int64_t tokens) { return g_path == LOQT_PATH_AUTO && tokens <= FEW_TOKENS_MAX; }
-// Merge: below 1024 columns the pre-pass of P costs as much as it saves.
+// Merge: a weight of 1024 columns or more always takes the pre-pass form (and so has to come with a workspace); a narrower
+// one takes it if the caller brought the workspace (narrow_merge_prepass).
 bool use_prepass_merge(int64_t in) {
     if (g_path == LOQT_PATH_FUSED) return false;
     if (g_path == LOQT_PATH_PREPASS || g_path == LOQT_PATH_FOLDED) return true;
@@ -384,6 +385,19 @@ loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const lo
     return LOQT_OK;
 }
 
+// bf16 copies of the weight and of P: one launch for both on small weights, where the launch is what they cost
+hipError_t expand_weight(const loqt_nf4_mat* Wq, uint16_t* Wb, int64_t ldw, const loqt_nf4_mat* Pq, uint16_t* Pb, int64_t ldp,
+                         hipStream_t st) {
+    if (Wq->rows * Wq->cols <= (int64_t)1 << 22) {
+        const DequantGroupItem both[2] = {{Wq->codes, Wq->absmax, Wb, Wq->rows, Wq->ld, ldw, (int)Wq->cols},
+                                          {Pq->codes, Pq->absmax, Pb, Pq->rows, Pq->ld, ldp, (int)Pq->cols}};
+        return launch_dequantize_grouped(both, 2, st, SLOT_PREPASS);
+    }
+    hipError_t e = launch_dequantize(Wq->codes, Wq->absmax, Wq->rows, Wq->cols, Wq->ld, Wb, LOQT_BF16, ldw, st, SLOT_PREPASS);
+    if (e != hipSuccess) return e;
+    return launch_dequantize(Pq->codes, Pq->absmax, Pq->rows, Pq->cols, Pq->ld, Pb, LOQT_BF16, ldp, st, SLOT_PREPASS);
+}
+
 // U = s x B^T for a handful of tokens.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
 // long contraction goes out in slices instead, which find room where a copy of the weight would be.  Whole forward calls
 // in us, one launch / slices: contraction 5461, 16 tokens 19 / 24, 32 tokens 26 / 28; contraction 11008, 16 tokens
@@ -393,6 +407,25 @@ hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipS
     p.split_ws = split_ws;
     p.split_ws_floats = (int64_t)(split_bytes / 4);
     return launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st);
+}
+
+// dB[M x N] (fp32 or bf16, pitch ld_dB) = sum of the planned slices of Z^T x and its relatives (both operands K x rows), or,
+// accumulating, that much more.  One slice that need not be added to anything goes straight to dB (rank 1024, 5120
+// columns, 256 tokens: a launch of 7 us less).
+hipError_t gradient_product(int slot, GemmParams p, float* part, size_t part_bytes, int64_t ldp, void* dB, int dB_dtype,
+                            int64_t ld_dB, int accumulate, hipStream_t st) {
+    p.splits = planned_splits(p.M, p.N, p.A[0].K, ldp, part_bytes);
+    const bool bf16 = dB_dtype == LOQT_BF16;
+    if (p.splits == 1 && !accumulate && g_nt_tile_override == 0 && ld_dB % (bf16 ? 8 : 4) == 0 && aligned(dB, 16)) {
+        p.C = dB;
+        p.ldc = ld_dB;
+        return launch_gemm_nt(slot, bf16 ? EPI_BF16 : EPI_F32_SPLITK, true, true, p, st);
+    }
+    p.C = part;
+    p.ldc = ldp;
+    hipError_t e = launch_gemm_nt(slot, EPI_F32_SPLITK, true, true, p, st);
+    if (e != hipSuccess) return e;
+    return launch_reduce_db(part, p.splits, p.M, p.N, ldp, dB, dB_dtype, ld_dB, accumulate, st);
 }
 
 // Slices that fit: fp32 M x N at a pitch that is a multiple of 4
@@ -460,10 +493,17 @@ loqt_status merge_prepass(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* abs
 
 size_t merge_ws_bytes(int64_t out, int64_t in, int64_t r) { return MergeWs(out, in, r).total; }
 
+// A narrow weight may come without a workspace (the fused form needs none); with one it takes the pre-pass form as well
+// (same bits; 2048 x 768, rank 256: 15.4 -> 11.8 us)
+bool narrow_merge_prepass(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const void* ws, size_t ws_bytes) {
+    return g_path == LOQT_PATH_AUTO && ws && aligned(ws, 256) && ws_bytes >= merge_ws_bytes(Wq->rows, Wq->cols, Pq->cols);
+}
+
 loqt_status merge_checked(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absmax_out,
-                          const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s, void* ws,
+                          const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s, void* ws, size_t ws_bytes,
                           hipStream_t st) {
-    if (use_prepass_merge(Wq->cols)) return merge_prepass(Wq, codes_out, absmax_out, Pq, B, ld_B, s, ws, st);
+    if (use_prepass_merge(Wq->cols) || narrow_merge_prepass(Wq, Pq, ws, ws_bytes))
+        return merge_prepass(Wq, codes_out, absmax_out, Pq, B, ld_B, s, ws, st);
     return merge_fused(Wq, codes_out, absmax_out, Pq, B, ld_B, s, st);
 }
 
@@ -646,8 +686,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
             // y = x W_eff^T with W_eff = deq(W) + s deq(P) B folded once per call
             LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wb, ldw, true, st));
         } else {
-            LOQT_HIP(launch_dequantize(Wq->codes, Wq->absmax, out, in, Wq->ld, Wb, LOQT_BF16, ldw, st, SLOT_PREPASS));
-            LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_u, st, SLOT_PREPASS));
+            LOQT_HIP(expand_weight(Wq, Wb, ldw, Pq, Pb, ld_u, st));
             // U = s x B^T
             memset(&p, 0, sizeof(p));
             p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
@@ -782,8 +821,9 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
                 LOQT_TRY(nf4_product(SLOT_GEMM_DX, true, p, dx, ld_dx, sl, room, st));
             }
         } else {
-        LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_z, st, SLOT_PREPASS));
         const bool folded = dx && (saved || use_folded_bwd(T, out, in));
+        if (dx && !folded) LOQT_HIP(expand_weight(Wq, reinterpret_cast<uint16_t*>(base + L.Wb), ldw, Pq, Pb, ld_z, st));
+        else LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_z, st, SLOT_PREPASS));
         // Z rides along with dx (one product [dx | Z] over the shared operand dy) when that is estimated to
         // take less time than the two launches: its tiles then fill a partly empty round of the dx product
         bool z_with_dx = false;
@@ -814,12 +854,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         if (dx) {
             // dx = dy Wb (+ Z B when the rank-r term is not folded into Wb); Wb is out x in: K x rows
             uint16_t* Wws = reinterpret_cast<uint16_t*>(base + L.Wb);
-            if (folded) {
-                if (!saved) LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wws, ldw, false, st));
-            } else {
-                LOQT_HIP(launch_dequantize(Wq->codes, Wq->absmax, out, in, Wq->ld, Wws, LOQT_BF16, ldw, st,
-                                           SLOT_PREPASS));
-            }
+            if (folded && !saved) LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wws, ldw, false, st));
             memset(&p, 0, sizeof(p));
             p.A[0] = bf16_operand(dy, ld_dy, (int)T, (int)out);
             p.B[0] = bf16_operand(Wb, ldw, (int)in, (int)out);
@@ -851,11 +886,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         p.M = (int)r;
         p.N = (int)in;
         p.alpha = 1.0f;
-        p.C = part;
-        p.ldc = L.ldp;
-        p.splits = planned_splits(r, in, T, L.ldp, ws_bytes - L.partials);
-        LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DB, EPI_F32_SPLITK, true, true, p, st));
-        LOQT_HIP(launch_reduce_db(part, p.splits, r, in, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
+        LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, ws_bytes - L.partials, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
         return LOQT_OK;
     }
     memset(&p, 0, sizeof(p));
@@ -918,7 +949,7 @@ loqt_status loqt_merge_requant(const loqt_nf4_mat* Wq, uint8_t* codes_out, float
                                size_t ws_bytes, void* hip_stream) {
     LOQT_TRY(check_merge(Wq, codes_out, absmax_out, Pq, B, ld_B));
     LOQT_TRY(check_merge_ws(Wq, Pq, ws, ws_bytes));
-    return merge_checked(Wq, codes_out, absmax_out, Pq, B, ld_B, s, ws, (hipStream_t)hip_stream);
+    return merge_checked(Wq, codes_out, absmax_out, Pq, B, ld_B, s, ws, ws_bytes, (hipStream_t)hip_stream);
 }
 
 loqt_status loqt_merge_requant_batched(int n_layers, const loqt_merge_desc* descs, void* ws, size_t ws_bytes,
@@ -936,9 +967,12 @@ loqt_status loqt_merge_requant_batched(int n_layers, const loqt_merge_desc* desc
     hipStream_t st = (hipStream_t)hip_stream;
     int i = 0;
     while (i < n_layers) {
-        if (!use_prepass_merge(descs[i].Wq.cols)) {
+        auto prepass = [&](const loqt_merge_desc& d) {
+            return use_prepass_merge(d.Wq.cols) || narrow_merge_prepass(&d.Wq, &d.Pq, ws, ws_bytes);
+        };
+        if (!prepass(descs[i])) {
             LOQT_TRY(merge_checked(&descs[i].Wq, descs[i].codes_out, descs[i].absmax_out, &descs[i].Pq, descs[i].B,
-                                   descs[i].ld_B, descs[i].s, ws, st));
+                                   descs[i].ld_B, descs[i].s, ws, ws_bytes, st));
             ++i;
             continue;
         }
@@ -946,7 +980,7 @@ loqt_status loqt_merge_requant_batched(int n_layers, const loqt_merge_desc* desc
         DequantGroupItem deq[MERGE_GROUP_MAX];
         int n = 0;
         size_t used = 0;
-        while (i + n < n_layers && n < MERGE_GROUP_MAX && use_prepass_merge(descs[i + n].Wq.cols)) {
+        while (i + n < n_layers && n < MERGE_GROUP_MAX && prepass(descs[i + n])) {
             const loqt_merge_desc& d = descs[i + n];
             const int64_t out = d.Wq.rows, in = d.Wq.cols, r = d.Pq.cols;
             const size_t need = merge_ws_bytes(out, in, r);
@@ -1167,11 +1201,7 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     p.M = (int)out;
     p.N = (int)r;
     p.alpha = 1.0f;
-    p.C = part;
-    p.ldc = L.ldp;
-    p.splits = planned_splits(out, r, T, L.ldp, ws_bytes - L.partials);
-    LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DB, EPI_F32_SPLITK, true, true, p, st));
-    LOQT_HIP(launch_reduce_db(part, p.splits, out, r, L.ldp, dBp, dBp_dtype, ld_dBp, accumulate, st));
+    LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, ws_bytes - L.partials, L.ldp, dBp, dBp_dtype, ld_dBp, accumulate, st));
     return LOQT_OK;
 }
 
@@ -1426,11 +1456,7 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     p.M = (int)r;
     p.N = (int)in;
     p.alpha = 1.0f;
-    p.C = part;
-    p.ldc = L.ldp;
-    p.splits = planned_splits(r, in, T, L.ldp, part_bytes);
-    LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DB, EPI_F32_SPLITK, true, true, p, st));
-    LOQT_HIP(launch_reduce_db(part, p.splits, r, in, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
+    LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, part_bytes, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
     return LOQT_OK;
 }
 

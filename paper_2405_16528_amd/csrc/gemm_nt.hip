@@ -16,10 +16,12 @@
 //    stalled load holds back the MFMAs behind it in the in-order wave).  The 16x16x32 loop has two barriers per
 //    k-tile -- one as soon as the tile's last fragments are in registers, which frees its stage for the tile after
 //    next, one that publishes the next tile -- so a load has 1.25 to 2 k-tiles to land; the 32x32x16 loop has one
-//    barrier and issues half a tile after it and half in the next k-step.  Loads past the end of the range are
-//    switched off through EXEC (or, in the kernel variants for contractions of whole k-tiles, fetch the last tile
-//    once more into a stage nobody reads), and a k-tile that is not full (the last one of a K segment that is not a
-//    multiple of 64) is staged through registers with zero fill instead;
+//    barrier and issues half a tile after it and half in the next k-step (tiles small enough for three or four
+//    stages keep as many tiles in flight).  Loads past the end of the range are switched off through EXEC in the
+//    32x32x16 loop and fetch the last tile once more, into a stage nobody reads, in the 16x16x32 loop.  A k-tile that
+//    is not full (the last one of a K segment that is not a multiple of 64) is staged through registers with zero fill
+//    in the former; in the latter it is loaded like any other, lanes past the end fetching a valid chunk, and what
+//    lies past the end is cleared in LDS (cut_tile);
 //  * 16-byte chunks of an LDS row are XOR-swizzled so that fragment reads are free of bank conflicts (the
 //    pattern depends on the MFMA shape); the swizzle is applied on the global side (which chunk a lane
 //    fetches), the LDS side of a direct load is lane-linear;
@@ -1259,7 +1261,7 @@ template <int EPI, bool ARC, bool BRC>
 hipError_t launch_nt_tile(int tile, const GemmParams& p, hipStream_t st) {
     switch (tile) {
         case NT_256x256:
-            if constexpr (EPI == EPI_BF16) return launch_nt<256, 256, EPI, ARC, BRC>(p, st);
+            if constexpr (EPI == EPI_BF16 && !ARC) return launch_nt<256, 256, EPI, ARC, BRC>(p, st);
             break;
         case NT_256x128: return launch_nt<256, 128, EPI, ARC, BRC>(p, st);
         case NT_128x128: return launch_nt<128, 128, EPI, ARC, BRC>(p, st);
@@ -1282,6 +1284,13 @@ hipError_t launch_nt_sized(const GemmParams& p, hipStream_t st) {
     // or a heavy epilogue (merge; measured on real data, the fold is better off with the
     // large tile) two or three resident 128x128 work-groups per
     // compute unit win: the epilogue and prologue of one overlap with the main loop of another.
+    // Epilogues that walk the weight, on weights that give 128x128 tiles for half the compute units at most: 64x128, twice
+    // the work-groups, since one round of 128x128 leaves half the chip idle.  Measured over whole calls, 128x128 -> this
+    // together with the gradient that skips its reduction: unquantised layer of 2048 x 768, rank 256, 4096 tokens 86 -> 82.5
+    // us; step of 512 x 512, rank 128, 256 tokens (also one expansion launch less and the merge's pre-pass) 53 -> 46.7 us.
+    if constexpr (EPI == EPI_COMP || EPI == EPI_FOLD || EPI == EPI_MERGE || EPI == EPI_ACC_BF16) {
+        if (g_nt_tile_override == 0 && tiles(128, 128) <= 128) return launch_nt<64, 128, EPI, ARC, BRC, 3>(p, st);
+    }
     if constexpr (EPI == EPI_COMP || EPI == EPI_FOLD_F32) {
         return launch_nt<128, 128, EPI, ARC, BRC>(p, st);  // heavy epilogue: small tiles only
     } else if constexpr (EPI == EPI_F32_SPLITK) {
@@ -1399,7 +1408,8 @@ hipError_t launch_merge_grouped(int slot, bool b_rc, const MergeGroupLayer* laye
 hipError_t prepare_nt_kernels() {
     hipError_t e;
 #define LOQT_PREP3(EPI, ARC, BRC)                                                   \
-    if ((e = ensure_attr<256, 256, EPI, ARC, BRC>()) != hipSuccess) return e;       \
+    if constexpr (EPI != EPI_BF16 || !ARC)                                          \
+        if ((e = ensure_attr<256, 256, EPI, ARC, BRC>()) != hipSuccess) return e;   \
     if ((e = ensure_attr<256, 128, EPI, ARC, BRC>()) != hipSuccess) return e;       \
     if ((e = ensure_attr<128, 128, EPI, ARC, BRC>()) != hipSuccess) return e
     LOQT_PREP3(EPI_BF16, false, false);
@@ -1412,7 +1422,6 @@ hipError_t prepare_nt_kernels() {
     LOQT_PREP3(EPI_F32_SPLITK, true, true);
     LOQT_PREP3(EPI_F32_SPLITK, false, true);
     LOQT_PREP3(EPI_F32_SPLITK, false, false);
-#undef LOQT_PREP3
     // the shapes of plan_nt
 #define LOQT_PREP_SMALL(EPI, ARC, BRC)                                              \
     if ((e = ensure_attr<128, 128, EPI, ARC, BRC, 4>()) != hipSuccess) return e;    \
@@ -1423,7 +1432,11 @@ hipError_t prepare_nt_kernels() {
     LOQT_PREP_SMALL(EPI_F32_SPLITK, false, false);
     LOQT_PREP_SMALL(EPI_F32_SPLITK, false, true);
     LOQT_PREP_SMALL(EPI_F32_SPLITK, true, true);
+    LOQT_PREP_SMALL(EPI_BF16, true, true);
+    LOQT_PREP3(EPI_BF16, true, true);
+    if ((e = ensure_attr<256, 128, EPI_BF16, true, true, 2, true>()) != hipSuccess) return e;
 #undef LOQT_PREP_SMALL
+#undef LOQT_PREP3
     if ((e = ensure_attr<256, 256, EPI_BF16, false, false, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 256, EPI_BF16, false, true, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, true, true, 2, true>()) != hipSuccess) return e;
@@ -1432,6 +1445,12 @@ hipError_t prepare_nt_kernels() {
     if ((e = ensure_attr<256, 128, EPI_BF16, false, false, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 128, EPI_BF16, false, true, 2, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<128, 128, EPI_COMP, false, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_COMP, false, true, 3>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_FOLD, false, false, 3>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_FOLD, false, true, 3>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_MERGE, false, false, 3>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_MERGE, false, true, 3>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_ACC_BF16, false, true, 3>()) != hipSuccess) return e;
     if ((e = ensure_attr<128, 128, EPI_FOLD_F32, false, true>()) != hipSuccess) return e;
     if ((e = ensure_attr_grouped<true>()) != hipSuccess) return e;
     return ensure_attr_grouped<false>();
@@ -1460,6 +1479,7 @@ hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmPar
         }
     } else if (a_rc && b_rc) {
         switch (epi) {
+            case EPI_BF16: return launch_nt_tile<EPI_BF16, true, true>(plan_nt(p.M, p.N, ktiles(p), true, 1, 1).tile, p, st);
             case EPI_F32_SPLITK: return launch_nt_sized<EPI_F32_SPLITK, true, true>(p, st);
             default: break;
         }
