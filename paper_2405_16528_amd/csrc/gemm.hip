@@ -383,6 +383,28 @@ __global__ __launch_bounds__(256) void loqt_gemm_kernel(const GemmParams p) {
     }
 }
 
+// Sum of one place over the slices, in slice order, from zero.  Four loads are in flight before the first addition: in the plain
+// loop every slice waits for the load of the one before it, and a small reduction is nothing but that chain.  Whole calls,
+// plain -> this: unquantised layer 2048 x 768, 4096 tokens (5 slices) 81.8 -> 79.7 us; 13824 x 5120, 256 tokens (2 to 24
+// slices) 206 -> 203.5 us.
+template <class V, class Add>
+__device__ __forceinline__ V sum_slices(const float* at, int splits, int64_t stride, Add add) {
+    const auto slice = [&](int k) { return *reinterpret_cast<const V*>(at + k * stride); };
+    V s{};
+    int k = 0;
+    for (; k + 4 <= splits; k += 4) {
+        const V a = slice(k), b = slice(k + 1), c = slice(k + 2), d = slice(k + 3);
+        add(s, a), add(s, b), add(s, c), add(s, d);
+    }
+    if (splits & 2) {
+        const V a = slice(k), b = slice(k + 1);
+        add(s, a), add(s, b);
+        k += 2;
+    }
+    if (splits & 1) add(s, slice(k));
+    return s;
+}
+
 // dB = (accumulate ? dB : 0) + sum over splits of the fp32 partials, then to the output dtype
 __global__ __launch_bounds__(256) void reduce_db_kernel(const float* __restrict__ partials, int splits,
                                                         int64_t M, int N, int64_t ldp, void* __restrict__ dB,
@@ -392,8 +414,7 @@ __global__ __launch_bounds__(256) void reduce_db_kernel(const float* __restrict_
          idx += (int64_t)gridDim.x * 256) {
         const int64_t m = idx / N;
         const int n = (int)(idx - m * N);
-        float s = 0.f;
-        for (int k = 0; k < splits; ++k) s += partials[((int64_t)k * M + m) * ldp + n];
+        float s = sum_slices<float>(partials + m * ldp + n, splits, M * ldp, [](float& a, float v) { a += v; });
         if (dB_bf16) {
             uint16_t* d = reinterpret_cast<uint16_t*>(dB) + m * ld_dB + n;
             if (accumulate) s += __uint_as_float((uint32_t)(*d) << 16);
@@ -416,11 +437,9 @@ __global__ __launch_bounds__(256) void reduce_db4_kernel(const float* __restrict
          idx += (int64_t)gridDim.x * 256) {
         const int64_t m = idx / N4;
         const int n = (int)(idx - m * N4) * 4;
-        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int k = 0; k < splits; ++k) {
-            const float4 v = *reinterpret_cast<const float4*>(partials + ((int64_t)k * M + m) * ldp + n);
-            s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
-        }
+        float4 s = sum_slices<float4>(partials + m * ldp + n, splits, M * ldp, [](float4& a, const float4& v) {
+            a.x += v.x, a.y += v.y, a.z += v.z, a.w += v.w;
+        });
         if (dB_bf16) {
             uint2* d = reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(dB) + m * ld_dB + n);
             if (accumulate) {
