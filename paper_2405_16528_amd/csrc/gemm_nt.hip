@@ -1190,15 +1190,17 @@ constexpr TileSpec kTiles[] = {
     {NT_256x256, 256, 256, 1, 1.20, 1.56, 1.56, 8.0},
 };
 
-double tile_cost(const TileSpec& t, int64_t M, int64_t N, int64_t nkt, int splits) {
-    auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-    const int64_t wgs = cdiv(M, t.bm) * cdiv(N, t.bn) * splits, round = 256 * t.per_cu;
-    const double kt = (double)cdiv(nkt, splits);
+// `tiles` of the output in `splits` slices of at most `per` k-tiles
+double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits) {
+    const int64_t wgs = tiles * splits;
+    const int log2_round = t.per_cu == 2 ? 9 : 8;  // work-groups of one round: 256 compute units
+    const int64_t rounds = wgs >> log2_round, rest = wgs & ((1 << log2_round) - 1);
+    const double kt = (double)per;
     auto one = [&](int64_t w) {
         const double u = (double)w / 256.0;
         return kt * (u <= 1.0 ? t.alone + (t.full - t.alone) * u : t.full + (t.both - t.full) * (u - 1.0)) + t.fix;
     };
-    return (double)(wgs / round) * one(round) + (wgs % round ? one(wgs % round) : 0.0);
+    return (rounds ? (double)rounds * one((int64_t)1 << log2_round) : 0.0) + (rest ? one(rest) : 0.0);
 }
 
 // slices > 1 (or `sliced`: the result is summed from fp32 slices in any case) cost their own traffic and the
@@ -1208,21 +1210,27 @@ double slices_cost(int64_t M, int64_t N, int splits) {
     return bytes / 6.0e6 + 4.0 + (bytes + (double)M * (double)N * 2.0) / 7.0e6;
 }
 
+// Runs once per product and call, so it is kept to about a microsecond (5.5 without the bound on the slices and with 64-bit
+// divisions in the loop, as much as a launch).
 NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, int max_splits) {
+    auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int kts = (int)nkt;  // dimensions are at most 2^30
     NtPlan best{0, 1, 0.0};
     for (const TileSpec& t : kTiles) {
         if (sliced && t.id == NT_256x256) continue;  // no such kernel: its slices were slower than those of 256x128
         // dB and its relatives from rank 512 up: operands come from HBM, and shorter tiles read the longer one more often
         // (512 x 5461 x 8192, us: 66 on 256x128, 80 on 128x128; 5461 x 512 x 4096 36 and 43; 1024 x 5120 x 256 14 and 21)
         if (sliced && M >= 512 && t.id == NT_128x128) continue;
+        const int64_t tiles = cdiv(M, t.bm) * cdiv(N, t.bn);
         for (int splits = min_splits; splits <= max_splits; ++splits) {
-            const int64_t per = (nkt + splits - 1) / splits;
+            const int per = (int)((unsigned)(kts + splits - 1) / (unsigned)splits);
             if (min_splits < max_splits && splits > min_splits) {
                 if (per < 4 || t.id == NT_256x256) break;
-                if ((nkt + per - 1) / per != splits) continue;  // the last slices would be empty
+                if ((int)((unsigned)(kts + per - 1) / (unsigned)per) != splits) continue;  // the last slices would be empty
             }
-            double cost = tile_cost(t, M, N, nkt, splits);
-            if (sliced || splits > 1) cost += slices_cost(M, N, splits);
+            const double extra = sliced || splits > 1 ? slices_cost(M, N, splits) : 0.0;
+            if (best.tile != 0 && extra >= best.cost) break;  // and more slices cost more still
+            const double cost = tile_cost(t, tiles, per, splits) + extra;
             if (best.tile == 0 || cost < best.cost) best = NtPlan{t.id, splits, cost};
         }
     }
