@@ -14,7 +14,8 @@
 // codes (28 MB in 6.7 us, alone in the same access pattern) but x: every work-group reads all of it from L2, and the
 // compute units of an XCD ask for the same lines (16 tokens: 20 bytes per cycle and unit arrive).  So RT grows with
 // the number of rows.  Measured, us, 16 tokens, contraction 5120: 4096 rows 9.2 (RT 1), 12.9 (RT 2); 11008 rows 23
-// (RT 1), 26 (RT 2), 18.2 (RT 3); 8 waves and RT 1: 9.8 and 24.8.  The whole call at 16 x 11008 x 4096, rank 1024: 78 -> 28 (164 before the narrow tiles of gemm_nt.hip).
+// (RT 1), 26 (RT 2), 18.2 (RT 3); 8 waves and RT 1: 9.8 and 24.8.  The whole call at 16 x 11008 x 4096, rank
+// 1024: 78 -> 27 (164 before the narrow tiles of gemm_nt.hip).
 // From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
 #include <type_traits>
 
