@@ -92,3 +92,53 @@ def test_the_line_between_the_forms():
     assert L.resolved_path(L.OP_FWD, 32, 512, 512) == L.PATH_FUSED
     assert L.resolved_path(L.OP_FWD, 33, 512, 512) == L.PATH_PREPASS
     assert L.resolved_path(L.OP_BWD, 16, 512, 512) == L.PATH_PREPASS
+
+
+def _us_per_call(forms, calls=20, runs=9):
+    """The fastest of several replays of each form (recorded, so that the host is not what is measured), taken in turn."""
+    graphs = []
+    for form in forms:
+        form()
+        torch.cuda.synchronize()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            for _ in range(calls):
+                form()
+    best = [float("inf")] * len(forms)
+    for _ in range(runs):
+        for j, graph in enumerate(graphs):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            graph.replay()
+            end.record()
+            end.synchronize()
+            best[j] = min(best[j], begin.elapsed_time(end) * 1e3 / calls)
+    return best
+
+
+@pytest.mark.parametrize("T,out,inp,r", [
+    (32, 7232, 128, 24),      # one chunk per product: fifteen of sixteen waves have none
+    (16, 2112, 128, 112),
+    (32, 512, 512, 128),      # four
+])
+def test_unquantised_forward_is_not_behind_the_plain_products(T, out, inp, r):
+    """With as good as no weight to stream the kernel has to cost no more than the products it stands in for."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    rng = synth.rng_for(T, "few time", out, inp)
+    W, P = G.bf16_dev(synth.normal_bf16(rng, (out, inp), 0.02)), G.bf16_dev(synth.normal_bf16(rng, (out, r), out ** -0.5))
+    B, x = G.bf16_dev(synth.normal_bf16(rng, (r, inp), 2e-2)), G.bf16_dev(synth.normal_bf16(rng, (T, inp), 1.0))
+    y, ws = G.bf16_empty(T, out), G.workspace(L.OP_FWD_NQ, T, out, inp, r)
+
+    def plain():
+        L.loqt_linear_fwd_nq(x, W, P, B, 0.5, y, ws)
+
+    def other():
+        L.set_path(L.PATH_PREPASS)
+        try:
+            plain()
+        finally:
+            L.set_path(L.PATH_AUTO)
+    few_us, other_us = _us_per_call([plain, other])
+    print(f"few T={T} out={out} in={inp} r={r}: {few_us:.1f} us, plain products {other_us:.1f}")
+    assert few_us <= 1.15 * other_us
