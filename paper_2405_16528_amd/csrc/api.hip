@@ -403,7 +403,7 @@ hipError_t expand_weight(const loqt_nf4_mat* Wq, uint16_t* Wb, int64_t ldw, cons
 // in us, one launch / slices: contraction 5461, 16 tokens 19 / 24, 32 tokens 26 / 28; contraction 11008, 16 tokens
 // 40 / 36, 32 tokens 60 / 43.
 hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipStream_t st) {
-    if (p.A[0].K <= (p.M <= 16 ? 8192 : 5504)) return launch_few_tokens(SLOT_GEMM_U, false, p, st);
+    if (p.A[0].K <= (p.M <= 16 ? 8192 : 5504) && p.N <= FEW_ROWS_MAX_BF16) return launch_few_tokens(SLOT_GEMM_U, false, p, st);
     p.split_ws = split_ws;
     p.split_ws_floats = (int64_t)(split_bytes / 4);
     return launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st);
@@ -1338,7 +1338,7 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     LOQT_TRY(check_layer_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r));
     LOQT_TRY(check_bf16(x, T, in, ld_x));
     LOQT_TRY(check_bf16(y, T, out, ld_y));
-    const bool few = use_few_tokens(T), folded = use_folded(T, out, in);
+    const bool few = use_few_tokens(T) && out <= FEW_ROWS_MAX_BF16, folded = use_folded(T, out, in);
     const NqWs L(false, T, out, in, r, ws_bytes);
     LOQT_TRY(check_ws(ws, ws_bytes, folded ? L.least : L.We));
     hipStream_t st = (hipStream_t)hip_stream;

@@ -29,7 +29,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int CH = 128;  // contraction of one chunk
 constexpr int NW = 16;   // waves of a work-group
-constexpr int NB = 2;    // chunks whose weights a wave has in flight
 
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 
@@ -142,6 +141,8 @@ __global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p)
         return Seg{second ? s1.a : s0.a, second ? s1.lda : s0.lda, second ? s1.w : s0.w, second ? s1.absmax : s0.absmax,
                    second ? s1.ldw : s0.ldw, second ? s1.K : s0.K};
     };
+    // chunks whose weights a wave has in flight
+    constexpr int NB = !NF4 && RT == 3 ? 1 : 2;
     Weights<NF4> w[NB][RT];
     bf16x8 x[NT][4];
     auto load_w = [&](auto mask, int b, const Seg& s, int k0) {
@@ -251,14 +252,18 @@ hipError_t launch_rows(const GemmParams& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// rows per work-group: as few as leave at most one work-group of 16 waves for a compute unit
+// Rows per work-group (16 RT): as few as leave at most one work-group of 16 waves for a compute unit.  Beyond that the one of
+// 48 and 64 whose rounds are cheaper by their rows (64 rows of two token tiles are 25 registers short and count for 80: 32
+// tokens on 13568 x 5376, us, 55 in two rounds of 48 and 45 in one of 64; on 18752 x 7872 61 and 82 in two rounds of either).
+// Rows in bf16 take 64 of the 128 registers at two chunks in flight; so 48 of them go with one chunk, and there is no form of 64.
 template <bool NF4, int NT>
 hipError_t launch_tokens(const GemmParams& p, hipStream_t st) {
     const int tiles = (p.N + 15) / 16;
     if (tiles <= 256) return launch_rows<NF4, NT, 1>(p, st);
     if (tiles <= 512) return launch_rows<NF4, NT, 2>(p, st);
-    if (tiles <= 768) return launch_rows<NF4, NT, 3>(p, st);
-    return launch_rows<NF4, NT, 4>(p, st);
+    if constexpr (NF4)
+        if ((tiles + 1023) / 1024 * (NT == 1 ? 4 : 5) < (tiles + 767) / 768 * 3) return launch_rows<NF4, NT, 4>(p, st);
+    return launch_rows<NF4, NT, 3>(p, st);
 }
 
 }  // namespace

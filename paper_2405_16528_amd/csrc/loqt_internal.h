@@ -272,6 +272,10 @@ NtPlan plan_nt(int64_t M, int64_t N, int64_t ktiles, bool sliced, int min_splits
 // forward products with at most FEW_TOKENS_MAX tokens (few.hip): C[M x N] = alpha * sum_seg A_seg B_seg^T, A bf16, B rows x K
 // in NF4 or bf16
 constexpr int FEW_TOKENS_MAX = 32;
+// Rows in bf16: up to one round of 48-row work-groups.  Further on the plain products are as good (whole unquantised calls over
+// 200 sizes of 12289 to 24000 rows, few-token kernel / plain: 16 tokens and fewer 0.88 of the time, 17 to 32 tokens 1.08, single
+// calls up to 1.55; up to 12288 rows 0.65 and 0.75).
+constexpr int FEW_ROWS_MAX_BF16 = 12288;
 hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_t st);
 
 // products of a few hundred tokens with NF4 weights (nf4_tile.hip) in p.splits fp32 slices at p.C (pitch p.ldc, a multiple

@@ -20,6 +20,8 @@ CASES = [
     (16, 12300, 328, 24),     # four, one token tile
     (32, 12300, 72, 24),      # four, two token tiles
     (9, 72, 8300, 40),        # U in slices of its contraction
+    (16, 12200, 2200, 24),    # three, whole chunks (one in flight in bf16), one wave has two
+    (32, 16500, 392, 16),     # three in two rounds; bf16 rows leave the kernel
 ]
 
 
@@ -120,6 +122,8 @@ def _us_per_call(forms, calls=20, runs=9):
     (32, 7232, 128, 24),      # one chunk per product: fifteen of sixteen waves have none
     (16, 2112, 128, 112),
     (32, 512, 512, 128),      # four
+    (32, 11904, 128, 8),      # three row tiles per work-group
+    (32, 17216, 192, 192),    # more rows than the kernel takes
 ])
 def test_unquantised_forward_is_not_behind_the_plain_products(T, out, inp, r):
     """With as good as no weight to stream the kernel has to cost no more than the products it stands in for."""

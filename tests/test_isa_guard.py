@@ -23,16 +23,25 @@ KERNELS = {
 }
 
 
-@pytest.fixture(scope="module")
-def assembly(tmp_path_factory):
+def _assembly(tmp_path_factory, source):
     from paper_2405_16528_amd import build as B
-    out = tmp_path_factory.mktemp("isa") / "gemm_nt.s"
+    out = tmp_path_factory.mktemp("isa") / (source + ".s")
     flags = [f for f in B.FLAGS if f not in ("-shared", "-fPIC")]
     cmd = [B.hipcc(), *flags, "-S", "--cuda-device-only", "-I", os.path.join(ROOT, "include"),
-           os.path.join(B.PKG, "csrc", "gemm_nt.hip"), "-o", str(out)]
+           os.path.join(B.PKG, "csrc", source), "-o", str(out)]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     return out.read_text()
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    return _assembly(tmp_path_factory, "gemm_nt.hip")
+
+
+@pytest.fixture(scope="module")
+def few_assembly(tmp_path_factory):
+    return _assembly(tmp_path_factory, "few.hip")
 
 
 def _loop_blocks(asm, mangled_part):
@@ -75,3 +84,15 @@ def test_main_loop_has_no_register_file_traffic(assembly, name):
             masked = nxt[0].startswith("s_mov_b32 exec_lo") and nxt[2].startswith("global_load_lds_dwordx4")
             plain = nxt[0].startswith("global_load_lds_dwordx4")
             assert masked or plain, (name, nxt)
+
+
+def test_few_token_kernels_keep_to_their_registers(few_assembly):
+    """16 waves leave 128 registers to a lane.  Only 64 rows of NF4 codes with two token tiles may spill (one round of those is
+    still ahead of two rounds of 48 rows), and not more than they do."""
+    spills = {}
+    for name, count in re.findall(r"\.name: +(\S*few_tokens_kernel\S*)\n(?:.*\n)*?.*\.vgpr_spill_count: +(\d+)", few_assembly):
+        nf4, token_tiles, row_tiles = re.search(r"ILb(\d)ELi(\d)ELi(\d)E", name).groups()
+        spills["NF4" if nf4 == "1" else "bf16", int(token_tiles), int(row_tiles)] = int(count)
+    assert set(spills) == {(w, t, n) for w in ("NF4", "bf16") for t in (1, 2) for n in (1, 2, 3, 4)} - {("bf16", 1, 4), ("bf16", 2, 4)}
+    assert spills.pop(("NF4", 2, 4)) <= 26
+    assert not any(spills.values()), spills
