@@ -1190,7 +1190,12 @@ constexpr TileSpec kTiles[] = {
     {NT_256x256, 256, 256, 1, 1.20, 1.56, 1.56, 8.0},
 };
 
-// `tiles` of the output in `splits` slices of at most `per` k-tiles
+// `tiles` of the output in `splits` slices of at most `per` k-tiles.  Between one and two work-groups per compute unit the
+// time per k-tile goes from `full` to `both` step by step, as measured on the small tiles and on slices (whole
+// unquantised backward calls, us: dx of 90 x 6528 x 13504 63 on slices of 128x128, 80 on what the rule below would take;
+// 312 x 7104 x 11776 116 and 141).  Whole contractions on
+// 128x128 tiles take as long as the unit that has two of them, however many others have one (1024 x 5120 x 13824: 320 tiles of
+// 128x128 231, 160 of 256x128 165; 600 x 10112 x 3520 59 and 50; 1816 x 2341 x 6546 126 and 95).
 double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits) {
     const int64_t wgs = tiles * splits;
     const int log2_round = t.per_cu == 2 ? 9 : 8;  // work-groups of one round: 256 compute units
@@ -1198,7 +1203,8 @@ double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits) {
     const double kt = (double)per;
     auto one = [&](int64_t w) {
         const double u = (double)w / 256.0;
-        return kt * (u <= 1.0 ? t.alone + (t.full - t.alone) * u : t.full + (t.both - t.full) * (u - 1.0)) + t.fix;
+        if (u <= 1.0) return kt * (t.alone + (t.full - t.alone) * u) + t.fix;
+        return kt * (t.id == NT_128x128 && splits == 1 ? t.both : t.full + (t.both - t.full) * (u - 1.0)) + t.fix;
     };
     return (rounds ? (double)rounds * one((int64_t)1 << log2_round) : 0.0) + (rest ? one(rest) : 0.0);
 }

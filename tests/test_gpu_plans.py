@@ -48,6 +48,14 @@ def test_plan_has_no_empty_slices_and_keeps_to_its_limit():
                         assert not (tile == T256x256 and (sliced or n > 1))
 
 
+@pytest.mark.parametrize("M,N,K", [(1024, 5120, 13824), (600, 10112, 3520), (1816, 2341, 6546)])
+def test_plan_counts_the_unit_that_has_two_tiles(M, N, K):
+    """257 to 512 tiles of 128x128 take as long as 512: these sizes are faster on 256x128."""
+    from paper_2405_16528_amd import binding as L
+    assert 256 < -(-M // 128) * -(-N // 128) < 512
+    assert L.plan_tiles(M, N, K, max_splits=1) == (T256x128, 1)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,out,inp,r,want", CASES)
 def test_fwd_bwd_parity(T, out, inp, r, want):
