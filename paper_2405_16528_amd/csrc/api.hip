@@ -830,12 +830,19 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         if (folded) {
             const int64_t tm = (T + 255) / 256;
             const int64_t t_dx = tm * ((in + 255) / 256), t_z = tm * ((r + 255) / 256);
-            // Z alone, in rounds of 256x256 tiles (a k-tile of such a round: 1.56 us): on those when they fill the chip,
-            // else by plan_nt
-            const double z_alone = t_z >= 224 ? plan_bf16_product(T, r, 0).cost
-                                              : plan_nt(T, r, (out + 63) / 64, false, 1, NT_MAX_SPLITS).cost /
-                                                    (1.56 * (double)((out + 63) / 64) + 8.0);
-            z_with_dx = t_dx >= 224 && out >= 2048 && plan_bf16_product(T, in, r).cost < plan_bf16_product(T, in, 0).cost + z_alone;
+            const int64_t kt = (out + 63) / 64;
+            const NtPlan z = plan_nt(T, r, kt, false, 1, NT_MAX_SPLITS);
+            if (out >= 2048) {
+                // in rounds of 256x256 tiles (a k-tile of such a round: 1.56 us); Z alone on those when they fill the chip,
+                // else by plan_nt
+                const double z_alone = t_z >= 224 ? plan_bf16_product(T, r, 0).cost : z.cost / (1.56 * (double)kt + 8.0);
+                z_with_dx = t_dx >= 224 && plan_bf16_product(T, in, r).cost < plan_bf16_product(T, in, 0).cost + z_alone;
+            } else {
+                // contractions too short for those tiles: [dx | Z] goes out on 128x128, and a Z that needs no further round of
+                // them costs nothing (saved backward, us, Z alone / beside dx: 3021 tokens, 81 x 6892, rank 21, 49.9 / 45.4;
+                // 1539 tokens, 128 x 8640, rank 128, 39.4 / 35.4)
+                z_with_dx = t_dx >= 224 && joint_cost_128(T, in, r, kt) < plan_nt(T, in, kt, false, 1, NT_MAX_SPLITS).cost + z.cost;
+            }
         }
         if (!z_with_dx) {
             // Z = s dy deq(P): deq(P) is out x r, i.e. K x rows

@@ -1243,6 +1243,14 @@ NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, i
     return best;
 }
 
+// a product of M rows and N columns with Nx extra columns beside them, on 128x128 tiles
+double joint_cost_128(int64_t M, int64_t N, int64_t Nx, int64_t nkt) {
+    auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    for (const TileSpec& t : kTiles)
+        if (t.id == NT_128x128) return tile_cost(t, cdiv(M, 128) * (cdiv(N, 128) + cdiv(Nx, 128)), (int)nkt, 1);
+    return 0.0;
+}
+
 // whether a bf16-output product of M rows, N (+ Nx) columns and contraction K runs on 256x256 tiles by the plan above
 static bool large_product(int64_t M, int64_t N, int64_t Nx, int64_t K) {
     auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };

@@ -268,6 +268,8 @@ struct NtPlan {
     double cost;  // microseconds, estimated
 };
 NtPlan plan_nt(int64_t M, int64_t N, int64_t ktiles, bool sliced, int min_splits, int max_splits);
+// ... and the cost of one launch of 128x128 tiles with Nx extra columns (the rows' other product) beside the N
+double joint_cost_128(int64_t M, int64_t N, int64_t Nx, int64_t ktiles);
 
 // forward products with at most FEW_TOKENS_MAX tokens (few.hip): C[M x N] = alpha * sum_seg A_seg B_seg^T, A bf16, B rows x K
 // in NF4 or bf16

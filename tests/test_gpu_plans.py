@@ -83,6 +83,30 @@ def test_fwd_bwd_parity(T, out, inp, r, want):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("T,out,inp,r", [(3021, 81, 6892, 21), (1539, 128, 8640, 128), (2305, 330, 5900, 136)])
+def test_z_rides_beside_dx_when_its_tiles_are_free(T, out, inp, r):
+    """Short contractions: Z adds no round of 128x128 tiles to those of dx, so it has no launch of its own."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    rounds = [-(-(-(-T // 128) * (-(-inp // 128) + extra)) // 512) for extra in (0, -(-r // 128))]
+    assert rounds[0] == rounds[1]
+    s = 0.5
+    lay, Wq, Pq, d = _setup(T, out, inp, r, seed=T + out, sigma_B=2e-2)
+    dx, ws = G.bf16_empty(T, inp, fill=float("nan")), G.workspace(L.OP_BWD, T, out, inp, r)
+    dB = torch.full((r, inp), float("nan"), dtype=torch.float32, device="cuda")
+    L.loqt_linear_bwd(d["dy"], d["x"], d["Wq"], d["Pq"], d["B"], s, dx, dB, False, ws)
+    L.timing_enable(True)
+    L.loqt_linear_bwd(d["dy"], d["x"], d["Wq"], d["Pq"], d["B"], s, dx, dB, False, ws)
+    torch.cuda.synchronize()
+    L.timing_enable(False)
+    launches = {name: n for name, (n, _) in L.timing_read().items()}
+    assert launches["gemm_z"] == 0 and launches["gemm_dx"] == 1
+    dx_ref, dB_ref = O.loqt_linear_bwd(lay.dy, lay.x, Wq, Pq, lay.B, s)
+    G.bf16_output_report(G.bf16_host(dx), dx_ref)
+    assert G.max_err_over_rms(dB.cpu().numpy().astype(np.float64), dB_ref) <= TOL
+
+
+@pytest.mark.gpu
 def test_smaller_workspace_means_fewer_slices():
     """A workspace with no room for the slices of U and y is still accepted, down to the operands' own copies."""
     from tests import gpu_util as G
