@@ -838,10 +838,12 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
                 const double z_alone = t_z >= 224 ? plan_bf16_product(T, r, 0).cost : z.cost / (1.56 * (double)kt + 8.0);
                 z_with_dx = t_dx >= 224 && plan_bf16_product(T, in, r).cost < plan_bf16_product(T, in, 0).cost + z_alone;
             } else {
-                // contractions too short for those tiles: [dx | Z] goes out on 128x128, and a Z that needs no further round of
-                // them costs nothing (saved backward, us, Z alone / beside dx: 3021 tokens, 81 x 6892, rank 21, 49.9 / 45.4;
-                // 1539 tokens, 128 x 8640, rank 128, 39.4 / 35.4)
-                z_with_dx = t_dx >= 224 && joint_cost_128(T, in, r, kt) < plan_nt(T, in, kt, false, 1, NT_MAX_SPLITS).cost + z.cost;
+                // contractions too short for those tiles: where dx runs on 128x128, a Z that needs no further round of them
+                // costs nothing beside it (saved backward, us, Z alone / beside dx: 3021 tokens, 81 x 6892, rank 21, 49.9 /
+                // 45.4; 1539 tokens, 128 x 8640, rank 128, 39.4 / 35.4; but 1605 tokens, 2029 x 10791, rank 8, whose dx is
+                // better off on 256x128, 123 / 128)
+                const NtPlan d = plan_nt(T, in, kt, false, 1, NT_MAX_SPLITS);
+                z_with_dx = t_dx >= 224 && d.tile == NT_128x128 && d.splits == 1 && joint_cost_128(T, in, r, kt) < d.cost + z.cost;
             }
         }
         if (!z_with_dx) {
