@@ -1184,27 +1184,29 @@ struct TileSpec {
 constexpr TileSpec kTiles[] = {
     {NT_64x64, 64, 64, 2, 0.25, 0.27, 0.52, 2.0},
     {NT_64x128, 64, 128, 2, 0.32, 0.38, 0.85, 2.2},
-    {NT_128x128_DEEP, 128, 128, 1, 0.36, 0.62, 0.62, 3.0},
+    {NT_128x128_DEEP, 128, 128, 1, 0.36, 0.62, 0.62, 3.5},
     {NT_128x128, 128, 128, 2, 0.60, 0.70, 1.06, 3.0},
     {NT_256x128, 256, 128, 1, 0.55, 0.95, 0.95, 4.0},
     {NT_256x256, 256, 256, 1, 1.20, 1.56, 1.56, 8.0},
 };
 
-// `tiles` of the output in `splits` slices of at most `per` k-tiles.  Between one and two work-groups per compute unit the
-// time per k-tile goes from `full` to `both` step by step, as measured on the small tiles and on slices (whole
-// unquantised backward calls, us: dx of 90 x 6528 x 13504 63 on slices of 128x128, 80 on what the rule below would take;
-// 312 x 7104 x 11776 116 and 141).  Whole contractions on
-// 128x128 tiles take as long as the unit that has two of them, however many others have one (1024 x 5120 x 13824: 320 tiles of
-// 128x128 231, 160 of 256x128 165; 600 x 10112 x 3520 59 and 50; 1816 x 2341 x 6546 126 and 95).
+// `tiles` of the output in `splits` slices of at most `per` k-tiles: the time of the fullest compute unit.  Each XCD takes an
+// eighth of the tiles, rounded up, of every slice: 84 tiles in three slices are 33 work-groups for each of seven XCDs with 32
+// compute units, two rounds, although they number 252 (256x128 tiles of 5209 x 480 x 6160, us: one slice 82, two 57, three 81).
+// And the first unit with a second work-group holds up the launch, though less than when all have two and share what is beyond
+// the unit: of the way from `full` to `both`, 0.3 at once (1024 x 5120 x 13824: 320 tiles of 128x128 231, 160 of 256x128 165;
+// 437 x 5062 x 5384: 280 of 64x128 82, 80 of 256x128 in three slices 48).  Over 350 products with every tile and 1 to 16 slices
+// timed, the plan takes 1.02 (y, dx), 1.01 (Z) and 1.14 (dB) of the time of the best; counting units as an average, 1.05, 1.04
+// and 1.17.
 double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits) {
-    const int64_t wgs = tiles * splits;
-    const int log2_round = t.per_cu == 2 ? 9 : 8;  // work-groups of one round: 256 compute units
+    const int64_t wgs = (tiles + 7) / 8 * splits;  // of the fullest XCD
+    const int log2_round = t.per_cu == 2 ? 6 : 5;  // ... and in one round of its 32 compute units
     const int64_t rounds = wgs >> log2_round, rest = wgs & ((1 << log2_round) - 1);
     const double kt = (double)per;
     auto one = [&](int64_t w) {
-        const double u = (double)w / 256.0;
+        const double u = (double)w / 32.0;
         if (u <= 1.0) return kt * (t.alone + (t.full - t.alone) * u) + t.fix;
-        return kt * (t.id == NT_128x128 && splits == 1 ? t.both : t.full + (t.both - t.full) * (u - 1.0)) + t.fix;
+        return kt * (t.full + (t.both - t.full) * (0.3 + 0.7 * (u - 1.0))) + t.fix;
     };
     return (rounds ? (double)rounds * one((int64_t)1 << log2_round) : 0.0) + (rest ? one(rest) : 0.0);
 }

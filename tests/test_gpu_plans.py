@@ -56,6 +56,16 @@ def test_plan_counts_the_unit_that_has_two_tiles(M, N, K):
     assert L.plan_tiles(M, N, K, max_splits=1) == (T256x128, 1)
 
 
+@pytest.mark.parametrize("M,N,K", [(5209, 480, 6160), (4238, 636, 6336), (7080, 267, 4544), (6685, 333, 7496)])
+def test_plan_counts_work_groups_by_xcd(M, N, K):
+    """81 to 85 tiles of 256x128 in three slices fit 256 compute units, but not the 32 of an XCD."""
+    from paper_2405_16528_amd import binding as L
+    tile, n = L.plan_tiles(M, N, K)
+    tiles = -(-M // 256) * -(-N // 128)
+    assert 3 * tiles <= 256 and 3 * -(-tiles // 8) > 32
+    assert (tile, n) != (T256x128, 3)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,out,inp,r,want", CASES)
 def test_fwd_bwd_parity(T, out, inp, r, want):
