@@ -30,6 +30,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int CH = 128;  // contraction of one chunk
 constexpr int NW = 16;   // waves of a work-group
 
+// The levels are kept in 64ths, and the sums of NF4 products with them: a block's 64 products, which have no scale yet, then
+// stay in fp32's range for every x that bf16 holds.  (A power of two: no other bit changes.)
+constexpr float UNIT = 64.f;
+
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 
 // the bf16 levels of 8 codes (element e in byte e / 2, even e in the high nibble)
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p)
     };
     batch(wave);
     if (NF4) {
-        if (tid < 16) lut[tid] = (uint16_t)(pack_bf16(kNf4Levels[tid], 0.f) & 0xffffu);
+        if (tid < 16) lut[tid] = (uint16_t)(pack_bf16(kNf4Levels[tid] / UNIT, 0.f) & 0xffffu);
         __syncthreads();
     }
     for (int c0 = wave; c0 < full;) {
@@ -242,7 +246,7 @@ __global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p)
         uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + (int64_t)m * p.ldc + n;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (m + e < p.M) dst[e * p.ldc] = (uint16_t)(pack_bf16(p.alpha * s[e], 0.f) & 0xffffu);
+            if (m + e < p.M) dst[e * p.ldc] = (uint16_t)(pack_bf16(p.alpha * (NF4 ? UNIT * s[e] : s[e]), 0.f) & 0xffffu);
     }
 }
 

@@ -88,6 +88,24 @@ def test_forward_nq_parity(T, out, inp, r):
     G.bf16_output_report(G.bf16_host(y), O.loqt_linear_fwd_nq(x, W, P, B, s))
 
 
+@pytest.mark.parametrize("T", [5, 20])
+@pytest.mark.parametrize("mag", [3e38, 1e-30])
+def test_inputs_at_the_ends_of_the_range(T, mag):
+    """A block's products are summed before they meet its scale: that must not leave fp32's range where y is inside it."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    out, inp, r, s = 520, 1100, 72, 1.0
+    rng = synth.rng_for(T, "few range")
+    Wq = O.nf4_quantize(synth.normal_f32(rng, (out, inp), 1e-3))
+    Pq = O.nf4_quantize(synth.normal_f32(rng, (out, r), 1e-3))
+    B = synth.normal_bf16(rng, (r, inp), 1e-3)
+    x = O.f32_to_bf16_rne((np.sign(rng.standard_normal((T, inp))) * mag * rng.uniform(0.5, 1.0, (T, inp))).astype(np.float32))
+    y = G.bf16_empty(T, out, fill=float("nan"))
+    L.loqt_linear_fwd(G.bf16_dev(x), G.nf4_dev(*Wq), G.nf4_dev(*Pq), G.bf16_dev(B), s, y, G.workspace(L.OP_FWD, T, out, inp, r))
+    torch.cuda.synchronize()
+    G.bf16_output_report(G.bf16_host(y), O.loqt_linear_fwd(x, Wq, Pq, B, s))
+
+
 def test_the_line_between_the_forms():
     """32 tokens are a handful, 33 are not; the backward pass and the pair that keeps the weight never are."""
     from paper_2405_16528_amd import binding as L
