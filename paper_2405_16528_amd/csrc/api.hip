@@ -439,7 +439,8 @@ loqt_status nf4_product(int slot, bool b_rc, GemmParams p, uint16_t* C, int64_t 
     p.splits = nf4_tile_splits(p.M, p.N, nkt, extra, slices_that_fit(p.M, p.N, ws_bytes) - extra);
     p.C = ws;
     p.ldc = ld;
-    LOQT_HIP(launch_nf4_tile(slot, b_rc, p, st));
+    TimedLaunch tl(slot, st);  // the product and the sum of its slices
+    LOQT_HIP(launch_nf4_tile(b_rc, p, st));
     LOQT_HIP(launch_reduce_db(ws, p.splits + extra, p.M, p.N, ld, C, LOQT_BF16, ldc, 0, st, false));
     return LOQT_OK;
 }

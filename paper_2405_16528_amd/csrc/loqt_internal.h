@@ -282,8 +282,8 @@ hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_
 
 // products of a few hundred tokens with NF4 weights (nf4_tile.hip) in p.splits fp32 slices at p.C (pitch p.ldc, a multiple
 // of 4): A bf16 M x K, B NF4 stored rows x K (both segments) or, b_rc, K x rows (the first; the second, if any, is bf16
-// stored K x rows and makes slice number p.splits, one more)
-hipError_t launch_nf4_tile(int slot, bool b_rc, const GemmParams& p, hipStream_t st);
+// stored K x rows and makes slice number p.splits, one more).  Not timed: the caller sums the slices under the same slot.
+hipError_t launch_nf4_tile(bool b_rc, const GemmParams& p, hipStream_t st);
 hipError_t prepare_nf4_tile_kernels();
 int nf4_tile_splits(int64_t M, int64_t N, int64_t ktiles, int extra, int64_t max_splits);
 

@@ -434,8 +434,7 @@ int nf4_tile_splits(int64_t M, int64_t N, int64_t nkt, int extra, int64_t max_sp
     return best;
 }
 
-hipError_t launch_nf4_tile(int slot, bool b_rc, const GemmParams& p, hipStream_t st) {
-    TimedLaunch tl(slot, st);
+hipError_t launch_nf4_tile(bool b_rc, const GemmParams& p, hipStream_t st) {
     if (p.M <= 64) return b_rc ? launch<64, true>(p, st) : launch<64, false>(p, st);
     if (p.M <= 128) return b_rc ? launch<128, true>(p, st) : launch<128, false>(p, st);
     return b_rc ? launch<256, true>(p, st) : launch<256, false>(p, st);

@@ -92,3 +92,43 @@ def test_without_dx_and_with_the_smallest_workspace():
             G.bf16_output_report(G.bf16_host(dx), dx_ref)
     with pytest.raises(L.LoqtError):
         L.loqt_linear_bwd(*d, None, dB, False, torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+
+
+def test_timers_cover_the_sum_of_the_slices():
+    """What the per-kernel timers leave out is the gaps between launches, in this form as in the one that has a launch per
+    product: the sums of the slices belong to their products."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    T, out, inp, r, s, calls = 256, 3840, 3712, 192, 0.5, 10
+    rng = synth.rng_for(T, "tile timers")
+    Wq = G.nf4_dev(*O.nf4_quantize(synth.normal_f32(rng, (out, inp), 0.02)))
+    Pq = G.nf4_dev(*O.nf4_quantize(synth.normal_f32(rng, (out, r), out ** -0.5)))
+    B, x = G.bf16_dev(synth.normal_bf16(rng, (r, inp), 2e-2)), G.bf16_dev(synth.normal_bf16(rng, (T, inp), 1.0))
+    dy, dx = G.bf16_dev(synth.normal_bf16(rng, (T, out), 1e-2)), G.bf16_empty(T, inp)
+    dB, ws = torch.empty((r, inp), dtype=torch.float32, device="cuda"), G.workspace(L.OP_BWD, T, out, inp, r)
+
+    def untimed_per_launch(path):
+        L.set_path(path)
+        try:
+            best = float("inf")
+            for _ in range(6):
+                begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                L.timing_enable(True)
+                for n in range(calls + 3):
+                    if n == 3:  # (the first ones fill the queue)
+                        torch.cuda.synchronize()
+                        L.timing_enable(False)
+                        L.timing_enable(True)
+                        begin.record()
+                    L.loqt_linear_bwd(dy, x, Wq, Pq, B, s, dx, dB, False, ws)
+                end.record()
+                end.synchronize()
+                L.timing_enable(False)
+                launches, ms = (sum(v) for v in zip(*L.timing_read().values()))
+                best = min(best, (begin.elapsed_time(end) - ms) * 1e3 / launches)
+            return best
+        finally:
+            L.set_path(L.PATH_AUTO)
+    tile, plain = untimed_per_launch(L.PATH_AUTO), untimed_per_launch(L.PATH_PREPASS)
+    print(f"outside of the timers, us per launch: {tile:.1f}, with a launch per product {plain:.1f}")
+    assert tile <= plain + 1.0
