@@ -1444,9 +1444,11 @@ hipError_t prepare_nt_kernels() {
     LOQT_PREP3(EPI_FOLD, false, true);
     LOQT_PREP3(EPI_ACC_BF16, false, true);
     LOQT_PREP3(EPI_F32_SPLITK, true, true);
-    LOQT_PREP3(EPI_F32_SPLITK, false, true);
-    LOQT_PREP3(EPI_F32_SPLITK, false, false);
-    // the shapes of plan_nt
+    // the shapes of plan_nt (slices of a bf16 product never run on 256x256 tiles)
+    if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, false, false>()) != hipSuccess) return e;
+    if ((e = ensure_attr<128, 128, EPI_F32_SPLITK, false, false>()) != hipSuccess) return e;
+    if ((e = ensure_attr<256, 128, EPI_F32_SPLITK, false, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<128, 128, EPI_F32_SPLITK, false, true>()) != hipSuccess) return e;
 #define LOQT_PREP_SMALL(EPI, ARC, BRC)                                              \
     if ((e = ensure_attr<128, 128, EPI, ARC, BRC, 4>()) != hipSuccess) return e;    \
     if ((e = ensure_attr<64, 128, EPI, ARC, BRC, 3>()) != hipSuccess) return e;     \
@@ -1498,7 +1500,6 @@ hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmPar
             case EPI_COMP: return launch_nt_sized<EPI_COMP, false, true>(p, st);
             case EPI_FOLD_F32: return launch_nt_sized<EPI_FOLD_F32, false, true>(p, st);
             case EPI_ACC_BF16: return launch_nt_sized<EPI_ACC_BF16, false, true>(p, st);
-            case EPI_F32_SPLITK: return launch_nt_sized<EPI_F32_SPLITK, false, true>(p, st);
             default: break;
         }
     } else if (a_rc && b_rc) {

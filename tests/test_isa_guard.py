@@ -96,3 +96,9 @@ def test_few_token_kernels_keep_to_their_registers(few_assembly):
     assert set(spills) == {(w, t, n) for w in ("NF4", "bf16") for t in (1, 2) for n in (1, 2, 3, 4)} - {("bf16", 1, 4), ("bf16", 2, 4)}
     assert spills.pop(("NF4", 2, 4)) <= 26
     assert not any(spills.values()), spills
+
+
+def test_no_kernel_that_nothing_launches(assembly):
+    """Slices of a product whose left operand is stored rows x K are planned on tiles of 256x128 and less only."""
+    assert "nt_gemm_kernelILi256ELi128ELi1ELb0E" in assembly  # (the name the next line would find)
+    assert "nt_gemm_kernelILi256ELi256ELi1ELb0E" not in assembly
