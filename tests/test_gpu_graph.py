@@ -108,3 +108,24 @@ def test_first_call_can_be_captured_after_prepare():
     res = subprocess.run([sys.executable, "-c", _COLD_CAPTURE.format(root=root)], capture_output=True, text=True,
                          timeout=240)
     assert res.returncode == 0 and "cold capture ok" in res.stdout, res.stdout[-2000:] + res.stderr[-4000:]
+
+
+_COLD_SIZES = "T, out, inp, r, s = 1100, 1280, 1024, 128, 0.5 "
+assert _COLD_SIZES in _COLD_CAPTURE
+
+
+@pytest.mark.parametrize("T,out,inp,r", [
+    (16, 512, 512, 128),       # forward from the codes in registers, backward from codes expanded inside the products
+    (16, 4200, 4096, 256),
+    (200, 1280, 1024, 128),    # copies of the weight, small tiles and slices
+    (200, 4200, 4096, 256),    # both directions from codes expanded inside the products
+])
+def test_first_call_with_few_tokens_can_be_captured_after_prepare(T, out, inp, r):
+    """The same for the forms that calls of a few or a few hundred tokens take."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    script = _COLD_CAPTURE.replace(_COLD_SIZES, f"T, out, inp, r, s = {T}, {out}, {inp}, {r}, 0.5 ").format(root=root)
+    res = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=240)
+    assert res.returncode == 0 and "cold capture ok" in res.stdout, res.stdout[-2000:] + res.stderr[-4000:]

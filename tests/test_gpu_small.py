@@ -34,6 +34,27 @@ def test_direct_gradient_has_the_bits_of_the_summed_one(T, out, inp, r, grad):
     assert G.max_err_over_rms(got[0].float().cpu().numpy().astype(np.float64), ref) <= TOL + (6 * 2.0 ** -8 if grad == torch.bfloat16 else 0)
 
 
+@pytest.mark.parametrize("grad", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,out,inp,r", [(100, 136, 129, 72), (256, 512, 333, 128), (70, 260, 1001, 256), (256, 1030, 2606, 1024)])
+def test_direct_gradient_keeps_to_its_columns(T, out, inp, r, grad):
+    """Columns that end inside the kernel's stores of 4 or 8, in a pitch with room past them."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    assert L.plan_tiles(r, inp, T, sliced=True)[1] == 1
+    _, _, _, d = _setup(T, out, inp, r, seed=T + r, sigma_B=2e-2)
+    got = []
+    for pitch in (G.rup(inp, 8), G.rup(inp, 8) + 8, inp + 3 if (inp + 3) % 4 else inp + 1):  # (the last one: summed)
+        buf = torch.full((r + 1, pitch), float("nan"), dtype=grad, device="cuda")
+        L.timing_enable(True)
+        L.loqt_linear_bwd(d["dy"], d["x"], d["Wq"], d["Pq"], d["B"], 0.5, None, buf[:r, :inp], False, G.workspace(L.OP_BWD, T, out, inp, r))
+        torch.cuda.synchronize()
+        L.timing_enable(False)
+        assert L.timing_read()["reduce_db"][0] == (0 if pitch % 8 == 0 else 1)  # the route the pitch is there for
+        assert buf[:, inp:].numel() > 0 and bool(torch.isnan(buf[:, inp:]).all()) and bool(torch.isnan(buf[r]).all())
+        got.append(buf[:r, :inp].clone())
+    assert not bool(torch.isnan(got[0]).any()) and torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
 @pytest.mark.parametrize("out,inp,r", [(512, 512, 128), (300, 456, 64), (1100, 333, 192), (2048, 768, 256), (40, 40, 8)])
 def test_narrow_merge_with_and_without_a_workspace(out, inp, r):
     from paper_2405_16528_amd import binding as L
