@@ -1173,10 +1173,12 @@ BF16Plan plan_bf16_product(int64_t M, int64_t N, int64_t Nx) {
 // an estimate in microseconds.  Per shape: work-groups per compute unit, the time of one k-tile when a few work-groups
 // have memory to themselves (a serial chain of loads, barrier and fragment reads), when every compute unit runs one and
 // when it runs two (shared L2, fabric and power), and the rest of a tile (first loads, epilogue).
-// Measured on contractions of 5120 and 13824 (M = 256), 2048 and 768 (M = 4096).  The two- and one-sided 64-wide
-// tiles carry rings of three and four stages, the deep 128x128 form four: with one work-group per compute unit the
-// distance of the prefetch is what counts (256 x 1024 x 13824, one slice, us: 133 with two stages, 95 with four, 64
-// on 64x64 tiles; eight stages of 64x64 were no better, 64).
+// Measured on contractions of 5120 and 13824 (M = 256), 2048 and 768 (M = 4096).  Two work-groups of 64x128 on a unit
+// were timed at 0.62 to 0.91 us per k-tile; with 0.75 to 0.85 the plan is nearest to the best choice over 350 products (1.021
+// of its time for y; 1.031 with 0.65, 1.024 with 0.95).  The two- and one-sided 64-wide tiles carry rings of three and four
+// stages, the deep 128x128 form four: with one work-group per compute unit the distance of the prefetch is what counts
+// (256 x 1024 x 13824, one slice, us: 133 with two stages, 95 with four, 64 on 64x64 tiles; eight stages of 64x64 were no
+// better, 64).
 struct TileSpec {
     int id, bm, bn, per_cu;
     double alone, full, both, fix;
@@ -1227,7 +1229,9 @@ NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, i
     for (const TileSpec& t : kTiles) {
         if (sliced && t.id == NT_256x256) continue;  // no such kernel: its slices were slower than those of 256x128
         // dB and its relatives from rank 512 up: operands come from HBM, and shorter tiles read the longer one more often
-        // (512 x 5461 x 8192, us: 66 on 256x128, 80 on 128x128; 5461 x 512 x 4096 36 and 43; 1024 x 5120 x 256 14 and 21)
+        // (512 x 5461 x 8192, us: 66 on 256x128, 80 on 128x128; 5461 x 512 x 4096 36 and 43; 1024 x 5120 x 256 14 and 21).
+        // The estimate does not see that: with 128x128 in it, 60 random products of 512 to 1024 rows take 1.01 of the time,
+        // single ones 0.94 to 1.16.
         if (sliced && M >= 512 && t.id == NT_128x128) continue;
         const int64_t tiles = cdiv(M, t.bm) * cdiv(N, t.bn);
         for (int splits = min_splits; splits <= max_splits; ++splits) {
@@ -1308,12 +1312,11 @@ hipError_t launch_nt_sized(const GemmParams& p, hipStream_t st) {
     // or a heavy epilogue (merge; measured on real data, the fold is better off with the
     // large tile) two or three resident 128x128 work-groups per
     // compute unit win: the epilogue and prologue of one overlap with the main loop of another.
-    // Epilogues that walk the weight, on weights that give 128x128 tiles for half the compute units at most: 64x128, twice
-    // the work-groups, since one round of 128x128 leaves half the chip idle.  Measured over whole calls, 128x128 -> this
-    // together with the gradient that skips its reduction: unquantised layer of 2048 x 768, rank 256, 4096 tokens 86 -> 82.5
-    // us; step of 512 x 512, rank 128, 256 tokens (also one expansion launch less and the merge's pre-pass) 53 -> 46.7 us.
+    // Epilogues that walk the weight, while 128x128 tiles leave compute units idle: 64x128, twice the work-groups.  Time of
+    // the launch, 64x128 / 128x128 (merge, unquantised merge, fold, compensation step): up to 127 tiles of 128x128 0.84, 0.80,
+    // 0.85, 0.76; 128 to 192 tiles 0.87, 0.90, 0.92, 0.87; 256 tiles, where every unit has one, 1.13, 1.08, 1.17, 1.02.
     if constexpr (EPI == EPI_COMP || EPI == EPI_FOLD || EPI == EPI_MERGE || EPI == EPI_ACC_BF16) {
-        if (g_nt_tile_override == 0 && tiles(128, 128) <= 128) return launch_nt<64, 128, EPI, ARC, BRC, 3>(p, st);
+        if (g_nt_tile_override == 0 && tiles(128, 128) <= 192) return launch_nt<64, 128, EPI, ARC, BRC, 3>(p, st);
     }
     if constexpr (EPI == EPI_COMP || EPI == EPI_FOLD_F32) {
         return launch_nt<128, 128, EPI, ARC, BRC>(p, st);  // heavy epilogue: small tiles only
