@@ -385,17 +385,14 @@ loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const lo
     return LOQT_OK;
 }
 
-// bf16 copies of the weight and of P: one launch for both on small weights, where the launch is what they cost
+// bf16 copies of the weight and of P in one launch (two cost a launch more and leave P, a small one, alone on the chip; whole
+// forward calls with 300 tokens, us, two / one: 512 x 512, rank 128, 17.2 / 16.7; 4096 x 4096, rank 1024, 64.1 / 60.2;
+// 13824 x 5120, rank 1024, 131.5 / 129.3)
 hipError_t expand_weight(const loqt_nf4_mat* Wq, uint16_t* Wb, int64_t ldw, const loqt_nf4_mat* Pq, uint16_t* Pb, int64_t ldp,
                          hipStream_t st) {
-    if (Wq->rows * Wq->cols <= (int64_t)1 << 22) {
-        const DequantGroupItem both[2] = {{Wq->codes, Wq->absmax, Wb, Wq->rows, Wq->ld, ldw, (int)Wq->cols},
-                                          {Pq->codes, Pq->absmax, Pb, Pq->rows, Pq->ld, ldp, (int)Pq->cols}};
-        return launch_dequantize_grouped(both, 2, st, SLOT_PREPASS);
-    }
-    hipError_t e = launch_dequantize(Wq->codes, Wq->absmax, Wq->rows, Wq->cols, Wq->ld, Wb, LOQT_BF16, ldw, st, SLOT_PREPASS);
-    if (e != hipSuccess) return e;
-    return launch_dequantize(Pq->codes, Pq->absmax, Pq->rows, Pq->cols, Pq->ld, Pb, LOQT_BF16, ldp, st, SLOT_PREPASS);
+    const DequantGroupItem both[2] = {{Wq->codes, Wq->absmax, Wb, Wq->rows, Wq->ld, ldw, (int)Wq->cols},
+                                      {Pq->codes, Pq->absmax, Pb, Pq->rows, Pq->ld, ldp, (int)Pq->cols}};
+    return launch_dequantize_grouped(both, 2, st, SLOT_PREPASS);
 }
 
 // U = s x B^T for a handful of tokens.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
