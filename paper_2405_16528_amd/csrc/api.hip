@@ -396,11 +396,15 @@ hipError_t expand_weight(const loqt_nf4_mat* Wq, uint16_t* Wb, int64_t ldw, cons
 }
 
 // U = s x B^T for a handful of tokens.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
-// long contraction goes out in slices instead, which find room where a copy of the weight would be.  Whole forward calls
-// in us, one launch / slices: contraction 5461, 16 tokens 19 / 24, 32 tokens 26 / 28; contraction 11008, 16 tokens
-// 40 / 36, 32 tokens 60 / 43.
+// long contraction goes out in slices instead, which find room where a copy of the weight would be.  Both forms timed in whole
+// calls of both layers (1024 and 4096 rows, rank 64 to 1024, contractions of 1024 to 13824): slices are ahead from 5500 (1
+// token), 4600 (8) and 3500 (16) on, with the second token tile from 2800 (17) and 2050 (32).  At 4096 and 16 tokens they save
+// 0.9 us of 24, at 8192 and 32 tokens 12.7 us.  A contraction that ends inside a k-tile costs them 2 to 4 us more (rows that
+// start off cache lines; 5461: -1.7 us at 4 tokens, -0.4 at 16, 2.6 at 32), which is 2000 of contraction.
 hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipStream_t st) {
-    if (p.A[0].K <= (p.M <= 16 ? 8192 : 5504) && p.N <= FEW_ROWS_MAX_BF16) return launch_few_tokens(SLOT_GEMM_U, false, p, st);
+    const int line = (p.M <= 16 ? 5632 - 128 * p.M : 3584 - 48 * p.M) + (p.A[0].K % 64 ? 2000 : 0);
+    const bool room = split_bytes >= (size_t)8 * p.M * round_up(p.N, 4) * 4;  // (one slice alone would be slower still)
+    if ((p.A[0].K <= line || !room) && p.N <= FEW_ROWS_MAX_BF16) return launch_few_tokens(SLOT_GEMM_U, false, p, st);
     p.split_ws = split_ws;
     p.split_ws_floats = (int64_t)(split_bytes / 4);
     return launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st);

@@ -164,3 +164,25 @@ def test_unquantised_forward_is_not_behind_the_plain_products(T, out, inp, r):
     few_us, other_us = _us_per_call([plain, other])
     print(f"few T={T} out={out} in={inp} r={r}: {few_us:.1f} us, plain products {other_us:.1f}")
     assert few_us <= 1.15 * other_us
+
+
+@pytest.mark.parametrize("T,inp", [(16, 8320), (3, 5760), (32, 4097)])
+def test_unquantised_forward_with_no_room_for_slices(T, inp):
+    """U over a long contraction goes out in slices where the workspace has room for them; one that holds U and nothing else
+    is accepted as well."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    out, r, s = 96, 40, 0.5
+    rng = synth.rng_for(T, "few room", inp)
+    W, P = synth.normal_bf16(rng, (out, inp), 0.02), synth.normal_bf16(rng, (out, r), out ** -0.5)
+    B, x = synth.normal_bf16(rng, (r, inp), 2e-2), synth.normal_bf16(rng, (T, inp), 1.0)
+    least = G.rup(T * G.rup(r, 8) * 2, 256)
+    assert least < L.loqt_workspace_bytes(L.OP_FWD_NQ, T, out, inp, r)
+    ref = O.loqt_linear_fwd_nq(x, W, P, B, s)
+    for size in (least, L.loqt_workspace_bytes(L.OP_FWD_NQ, T, out, inp, r)):
+        ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        y = G.bf16_empty(T, out, fill=float("nan"))
+        L.loqt_linear_fwd_nq(G.bf16_dev(x), G.bf16_dev(W), G.bf16_dev(P), G.bf16_dev(B), s, y, ws[:size])
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0xFF).all())
+        G.bf16_output_report(G.bf16_host(y), ref)
