@@ -54,7 +54,8 @@ int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in);
  * pre-pass family (every product of the layer calls of sec. 2.2 / 2.4 and the merge of Alg. 1 line 5
  * when it takes that path) run on work-group tiles of 256x256 outputs or less (loqt_plan_tiles lists the shapes),
  * chosen from the sizes.  LOQT_TILE_AUTO keeps that choice; the other values force one shape for every such product
- * whatever its size (the compensation step of Alg. 2 and the dense merge always use 128x128).  All
+ * whatever its size (the dense merge always uses 128x128, the compensation step of Alg. 2 does so under every value but
+ * AUTO, which gives small weights 64x128).  All
  * shapes compute the same quantities; results differ only in summation order.  Returns
  * LOQT_INVALID_ARG for any other value.
  */

@@ -181,8 +181,6 @@ size_t slices_bytes(int64_t splits, int64_t M, int64_t ldp) { return round_up((s
 // The layouts below take the size of the workspace at hand; ALL: the size that loqt_workspace_bytes asks for.
 constexpr size_t ALL = ~(size_t)0;
 
-// `saved`: the caller keeps W_eff in a buffer of its own (loqt_linear_fwd_save / loqt_linear_bwd_saved), so the
-// workspace holds no copy of the weight (and the forward pass, always folded then, no U)
 // Pitch of the bf16 copy of the weight: rows that start on a cache line (128 bytes) where the workspace has room for it.
 // (x of 5461 columns at a pitch of 5464 makes every 128-byte piece of a row span two lines; the weight need not as well.)
 struct Region {
@@ -194,6 +192,8 @@ Region weight_region(size_t at, int64_t rows, int64_t cols, size_t rest, size_t 
     return Region{at, at + bf16_bytes(rows, ld), ld};
 }
 
+// `saved`: the caller keeps W_eff in a buffer of its own (loqt_linear_fwd_save / loqt_linear_bwd_saved), so the
+// workspace holds no copy of the weight (and the forward pass, always folded then, no U)
 struct FwdWs {
     size_t U, Wb, Pb, split, least, total;  // U = s x B^T; Wb = deq(W) or W_eff; Pb = deq(P); slices of U, then of y
     int64_t ldw;
@@ -974,7 +974,8 @@ loqt_status loqt_merge_requant_batched(int n_layers, const loqt_merge_desc* desc
     // Layers that take the pre-pass form go out in groups: one launch expands the P_q of the group into the
     // workspace, one launch runs the merge tiles of all its layers.  A group holds as many consecutive layers as
     // the workspace has room for (at most MERGE_GROUP_MAX); with the minimum workspace that is one layer at a
-    // time, the same kernels, the same bits.  Layers on the fused form (narrow weights) run one by one.
+    // time, the same kernels, the same bits.  Layers on the fused form (narrow weights that come without room for
+    // their P_q) run one by one.
     hipStream_t st = (hipStream_t)hip_stream;
     int i = 0;
     while (i < n_layers) {

@@ -10,13 +10,18 @@
 // first (two lane swaps per pair).  Neither operand passes through LDS.
 //
 // A work-group owns 16 * RT weight rows over the whole contraction; its 16 waves take every 16th chunk of 128 and their
-// sums meet in LDS in a fixed order, so there are no slices in memory and no second launch.  What bounds it is not the
-// codes (28 MB in 6.7 us, alone in the same access pattern) but x: every work-group reads all of it from L2, and the
-// compute units of an XCD ask for the same lines (16 tokens: 20 bytes per cycle and unit arrive).  So RT grows with
-// the number of rows.  Measured, us, 16 tokens, contraction 5120: 4096 rows 9.2 (RT 1), 12.9 (RT 2); 11008 rows 23
-// (RT 1), 26 (RT 2), 18.2 (RT 3); 8 waves and RT 1: 9.8 and 24.8.  The whole call at 16 x 11008 x 4096, rank
-// 1024: 78 -> 27 (164 before the narrow tiles of gemm_nt.hip).
-// From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
+// sums meet in LDS in a fixed order, so there are no slices in memory and no second launch.  What bounds it is a chain inside
+// the wave, not a rate: a wave has two or three chunks and loads x of one only after the products of the one before, the
+// codes of the next two after both.  At 11008 x 5056 and 16 tokens a work-group of 48 rows reads 162 KB of x and 137 KB of
+// codes and scales in 13.8 us, 9 bytes per cycle and unit; by the counters (11008 x 4096) its waves wait for loads and barriers
+// in 43 % of their cycles and for a place to issue (look-ups and their addresses) in 40 %, the matrix units are busy in 6 %.
+// More rows per work-group share the chain, until the last work-groups start late: so RT grows with the number of rows.
+// Kernel, us, contraction 5056, the same weight each time / 24 weights in turn (by 750 MB at 11008 rows):
+//   16 tokens    RT 1          RT 2          RT 3          RT 4            32 tokens   RT 1          RT 2          RT 3          RT 4
+//   4096 rows     9.4 / 10.1   11.2 / 12.2   13.4 / 15.2   15.8 / 18.4                 12.7 / 14.1   14.3 / 16.1   16.7 / 18.9   24.6 / 27.3
+//   11008 rows   19.4 / 20.6   19.2 / 22.1   13.8 / 16.3   16.2 / 19.6                 36.6 / 37.3   28.8 / 31.1   18.2 / 20.4   26.7 / 30.2
+// The whole call at 16 x 11008 x 4096, rank 1024: 165 -> 24.0 (expanded weight -> this; 78 with the expanded weight on the
+// narrow tiles of gemm_nt.hip), 160 -> 56 on buffers that nothing has read before.  From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
 #include <type_traits>
 
 #include "loqt_internal.h"
