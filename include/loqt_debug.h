@@ -74,7 +74,7 @@ loqt_status loqt_plan_product(int64_t M, int64_t N, int64_t Nx, int64_t *n_large
  * Diagnostic (host only): tile shape and number of slices of the contraction of an M x N product over K that does not
  * run on 256x256 tiles by the plan above (fewer than 224 such tiles, or K < 2048), with at most max_splits slices.
  * sliced != 0: the result is summed from fp32 slices in any case (dB).  *tile: 1 = 256x256, 2 = 256x128,
- * 3 = 128x128, 4 = 128x128 with a ring of four stages, 5 = 64x128, 6 = 64x64.  Either pointer may be NULL.
+ * 3 = 128x128, 5 = 64x128, 6 = 64x64.  Either pointer may be NULL.
  */
 loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max_splits, int *tile, int *splits);
 

@@ -1,0 +1,160 @@
+// Products whose epilogue walks the weight (M = out, N = in): the fold of the rank-r term into a bf16 copy of the 4-bit or bf16
+// weight, the merge with requantisation, one step of the compensated initialisation, the dense merge.  The kernel is in
+// nt_tile.h.
+#include <string.h>
+
+#include "nt_tile.h"
+
+namespace loqt {
+
+namespace {
+
+// The merges of several layers (Alg. 1 line 5, one layer after the other) as ONE launch: the tiles of all layers
+// form one grid, so the prologue and epilogue of one layer's tiles overlap with the products of the next layer's
+// instead of every layer paying its own ramp-up, tail round and launch gap.  The per-layer descriptors travel in
+// the kernel argument block itself (no device-side table to fill, nothing to allocate, capture-safe), which
+// bounds a group at MERGE_GROUP_MAX layers.  per_xcd_end: running total of the tiles each XCD has walked when it
+// is through with this layer.
+struct MergeGroupItem {
+    const void* A;      // left operand of s * A B: deq(P) in bf16, out x r, K contiguous
+    const void* B;      // right operand: r x in stored K x rows (BRC) or in x r stored rows x K
+    int64_t lda, ldb;
+    const uint8_t* w_codes;
+    const float* w_absmax;
+    uint8_t* out_codes;
+    float* out_absmax;
+    int64_t w_ld;
+    int M, N, K, w_cols;
+    float alpha;
+    int per_xcd_end;
+};
+struct MergeGroupParams {
+    int n;
+    MergeGroupItem it[MERGE_GROUP_MAX];
+};
+static_assert(sizeof(MergeGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
+
+constexpr int GROUP_BM = 128, GROUP_BN = 128;
+using GroupCfg = NtCfg<GROUP_BM, GROUP_BN, 2>;
+
+template <bool BRC>
+__global__ __launch_bounds__(256, (GroupCfg::PER_CU)) void nt_merge_grouped_kernel(const MergeGroupParams g) {
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    int li = 0;
+    while (li + 1 < g.n && j >= g.it[li].per_xcd_end) ++li;  // wave-uniform
+    const int start = li ? g.it[li - 1].per_xcd_end : 0;
+    const MergeGroupItem& it = g.it[li];
+    GemmParams p;
+    p.A[0].ptr = it.A, p.A[0].absmax = nullptr, p.A[0].ld = it.lda, p.A[0].rows = it.M, p.A[0].K = it.K;
+    p.B[0].ptr = it.B, p.B[0].absmax = nullptr, p.B[0].ld = it.ldb, p.B[0].rows = it.w_cols, p.B[0].K = it.K;
+    p.A[1].ptr = nullptr, p.A[1].absmax = nullptr, p.A[1].ld = 0, p.A[1].rows = 0, p.A[1].K = 0;
+    p.B[1] = p.A[1];
+    p.Bx = p.A[1];
+    p.M = it.M, p.N = it.N, p.alpha = it.alpha;
+    p.C = nullptr, p.ldc = 0, p.splits = 1;
+    p.Cx = nullptr, p.ldcx = 0, p.Nx = 0, p.alphax = 0.f;
+    p.w_codes = it.w_codes, p.w_absmax = it.w_absmax, p.out_codes = it.out_codes, p.out_absmax = it.out_absmax;
+    p.w_ld = it.w_ld, p.w_cols = it.w_cols;
+    p.w_bf16 = nullptr, p.w_bf16_ld = 0, p.w_f32 = nullptr, p.w_f32_ld = 0, p.e_out = nullptr, p.e_ld = 0;
+    const int per_xcd = it.per_xcd_end - start;
+    nt_gemm_tile<GROUP_BM, GROUP_BN, EPI_MERGE, false, BRC>(p, xcd * per_xcd + (j - start), 0);
+}
+
+template <bool BRC>
+hipError_t ensure_attr_grouped() {
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_merge_grouped_kernel<BRC>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, GroupCfg::SMEM);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    return hipSuccess;
+}
+
+template <int EPI, bool BRC>
+hipError_t launch_sized(const GemmParams& p, hipStream_t st) {
+    auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
+    constexpr bool HEAVY = EPI == EPI_COMP || EPI == EPI_FOLD_F32;  // small tiles only
+    if constexpr (EPI != EPI_FOLD_F32) {
+        // While 128x128 tiles leave compute units idle: 64x128, twice the work-groups.  Time of
+        // the launch, 64x128 / 128x128 (merge, unquantised merge, fold, compensation step): up to 127 tiles of 128x128 0.84, 0.80,
+        // 0.85, 0.76; 128 to 192 tiles 0.87, 0.90, 0.92, 0.87; 256 tiles, where every unit has one, 1.13, 1.08, 1.17, 1.02.
+        if (g_nt_tile_override == 0 && tiles(128, 128) <= 192) return launch_nt<64, 128, EPI, false, BRC, 3>(p, st);
+    }
+    if constexpr (!HEAVY) {
+        // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its epilogue
+        // behind, which two resident 128x128 work-groups have: the fold's is short enough, the merge's is not.
+        int choice = g_nt_tile_override;
+        if (choice == 0 && (EPI == EPI_FOLD || EPI == EPI_ACC_BF16) && tiles(256, 256) >= 224) choice = NT_256x256;
+        if (choice == NT_256x256) return launch_nt<256, 256, EPI, false, BRC>(p, st);
+        if (choice == NT_256x128) return launch_nt<256, 128, EPI, false, BRC>(p, st);
+    }
+    return launch_nt<128, 128, EPI, false, BRC>(p, st);
+}
+
+template <int EPI, bool BRC>
+hipError_t prepare_sized() {
+    hipError_t e;
+    if constexpr (EPI != EPI_COMP && EPI != EPI_FOLD_F32) {
+        if ((e = ensure_attr<256, 256, EPI, false, BRC>()) != hipSuccess) return e;
+        if ((e = ensure_attr<256, 128, EPI, false, BRC>()) != hipSuccess) return e;
+    }
+    if constexpr (EPI != EPI_FOLD_F32)
+        if ((e = ensure_attr<64, 128, EPI, false, BRC, 3>()) != hipSuccess) return e;
+    return ensure_attr<128, 128, EPI, false, BRC>();
+}
+
+}  // namespace
+
+hipError_t launch_merge_grouped(int slot, bool b_rc, const MergeGroupLayer* layers, int n, hipStream_t st) {
+    if (n < 1 || n > MERGE_GROUP_MAX) return hipErrorInvalidValue;
+    TimedLaunch tl(slot, st);
+    MergeGroupParams g;
+    memset(&g, 0, sizeof(g));
+    g.n = n;
+    int per_xcd_total = 0;
+    for (int i = 0; i < n; ++i) {
+        const MergeGroupLayer& l = layers[i];
+        MergeGroupItem& it = g.it[i];
+        it.A = l.A, it.lda = l.lda, it.B = l.B, it.ldb = l.ldb;
+        it.w_codes = l.w_codes, it.w_absmax = l.w_absmax, it.out_codes = l.out_codes, it.out_absmax = l.out_absmax;
+        it.w_ld = l.w_ld, it.M = l.out, it.N = (int)l.w_ld, it.K = l.r, it.w_cols = l.in, it.alpha = l.s;
+        const int tiles = ((l.out + GROUP_BM - 1) / GROUP_BM) * (int)((l.w_ld + GROUP_BN - 1) / GROUP_BN);
+        per_xcd_total += (tiles + 7) / 8;
+        it.per_xcd_end = per_xcd_total;
+    }
+    constexpr int smem = GroupCfg::SMEM;
+    const dim3 grid((unsigned)per_xcd_total * 8u);
+    hipError_t e0 = b_rc ? ensure_attr_grouped<true>() : ensure_attr_grouped<false>();
+    if (e0 != hipSuccess) return e0;
+    if (b_rc) hipLaunchKernelGGL(nt_merge_grouped_kernel<true>, grid, dim3(256), smem, st, g);
+    else hipLaunchKernelGGL(nt_merge_grouped_kernel<false>, grid, dim3(256), smem, st, g);
+    return hipGetLastError();
+}
+
+hipError_t prepare_weight_kernels() {
+    hipError_t e;
+    if ((e = prepare_sized<EPI_MERGE, false>()) != hipSuccess) return e;
+    if ((e = prepare_sized<EPI_MERGE, true>()) != hipSuccess) return e;
+    if ((e = prepare_sized<EPI_FOLD, false>()) != hipSuccess) return e;
+    if ((e = prepare_sized<EPI_FOLD, true>()) != hipSuccess) return e;
+    if ((e = prepare_sized<EPI_ACC_BF16, true>()) != hipSuccess) return e;
+    if ((e = prepare_sized<EPI_COMP, true>()) != hipSuccess) return e;
+    if ((e = prepare_sized<EPI_FOLD_F32, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr_grouped<true>()) != hipSuccess) return e;
+    return ensure_attr_grouped<false>();
+}
+
+hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st) {
+    switch (epi) {
+        case EPI_MERGE: return b_rc ? launch_sized<EPI_MERGE, true>(p, st) : launch_sized<EPI_MERGE, false>(p, st);
+        case EPI_FOLD: return b_rc ? launch_sized<EPI_FOLD, true>(p, st) : launch_sized<EPI_FOLD, false>(p, st);
+        case EPI_COMP: return b_rc ? launch_sized<EPI_COMP, true>(p, st) : hipErrorInvalidValue;
+        case EPI_FOLD_F32: return b_rc ? launch_sized<EPI_FOLD_F32, true>(p, st) : hipErrorInvalidValue;
+        case EPI_ACC_BF16: return b_rc ? launch_sized<EPI_ACC_BF16, true>(p, st) : hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace loqt

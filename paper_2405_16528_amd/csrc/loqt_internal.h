@@ -261,7 +261,7 @@ int64_t product_split_floats(int64_t M, int64_t N, int64_t K0, int64_t K1);
 
 // Tile shape and slices of the contraction of a product that is not run on 256x256 tiles by plan_bf16_product, the
 // best of min_splits .. max_splits slices.  sliced: the result is summed from fp32 slices in any case (dB).
-enum NtTile { NT_256x256 = 1, NT_256x128, NT_128x128, NT_128x128_DEEP, NT_64x128, NT_64x64 };
+enum NtTile { NT_256x256 = 1, NT_256x128, NT_128x128, NT_64x128 = 5, NT_64x64 };
 constexpr int NT_MAX_SPLITS = 32;
 struct NtPlan {
     int tile, splits;
@@ -297,6 +297,8 @@ int gemm_db_splits(int64_t T, int64_t r, int64_t in);
 // large-token path (gemm_nt.hip): bf16 operands stored rows x K (K contiguous) or, with the
 // a_rc / b_rc flag, K x rows (rows contiguous; Operand::ld is the pitch of that stored matrix)
 hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st);
+// ... of which those whose epilogue walks the weight (gemm_weight.hip; A stored rows x K, not timed)
+hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st);
 // several merges as one launch of 128x128 tiles (EPI_MERGE over the tiles of all layers); at most MERGE_GROUP_MAX
 // layers per launch.  A: deq(P) in bf16 (out x r, pitch lda); B: the trainable factor, r x in stored K x rows
 // (b_rc) or in x r stored rows x K; the rest as in GemmParams.
@@ -326,6 +328,7 @@ hipError_t launch_merge_grouped(int slot, bool b_rc, const MergeGroupLayer* laye
 // raise the LDS size of every kernel configuration of gemm_nt.hip / gemm.hip above the default (otherwise done at the
 // first launch of each), so that a first call can be recorded into a HIP graph
 hipError_t prepare_nt_kernels();
+hipError_t prepare_weight_kernels();
 hipError_t prepare_fused_kernels();
 // tuning aid for benchmarks: 0 = choose by shape, 1 = 256x256, 2 = 256x128, 3 = 128x128 tiles
 extern int g_nt_tile_override;
