@@ -128,12 +128,14 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
 }
 
 // A few hundred tokens that do not fold: the codes are expanded inside the products (nf4_tile.hip) and no copy of the
-// weight is made.  Up to 64 tokens that is never behind (forward + backward, us, against copies: 2048 x 2048, rank 512, 67
-// and 68; 13824 x 5120, rank 1024, 164 and 272); up to 256 it takes a weight whose copy costs more than the slower loop
-// (256 tokens: 5461 x 2048 112 and 97, 4096 x 4096 126 and 133, 5120 x 5120 152 and 184; at 512 the copy is as good).
+// weight is made.  Up to 64 tokens that is never behind (forward + backward, us, against copies: 2048 x 2048, rank 512, 49
+// and 53; 13824 x 5120, rank 1024, 129 and 221); up to 256 it takes a weight whose copy costs more than the slower loop, the
+// more so the more tokens there are (96 / 128 / 192 / 256 tokens, time against copies: 2.8 million elements 1.08 / 1.13 / 1.31 /
+// 1.54, 4.2 million 1.00 / 1.04 / 1.11 / 1.21, 9 million 0.88 / 0.90 / 0.98 / 1.05, 11.2 million 0.90 to 0.98 / 0.93 to 1.00 /
+// 0.99 to 1.04 / 1.00 to 1.08, 16.8 million 0.80 / 0.82 / 0.92 / 0.98, 25 million 0.78 / 0.79 / 0.89 / 0.85).
 bool use_nf4_tile(int64_t T, int64_t out, int64_t in) {
     if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in)) return false;
-    return T <= 64 || (T <= 256 && out * in >= 14000000);
+    return T <= 64 || (T <= 256 && out * in >= 2500000 + 50000 * T);
 }
 
 inline size_t bf16_bytes(int64_t rows, int64_t cols) {
