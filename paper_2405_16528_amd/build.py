@@ -8,7 +8,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SOURCES = ["api.hip", "codec.hip", "few.hip", "gemm.hip", "gemm_nt.hip", "gemm_weight.hip", "nf4_tile.hip"]
+SOURCES = ["api.hip", "codec.hip", "few.hip", "gemm.hip", "gemm_nt.hip", "gemm_pair.hip", "gemm_weight.hip", "nf4_tile.hip"]
 LIB = os.path.join(PKG, "libloqt.so")
 
 FLAGS = [

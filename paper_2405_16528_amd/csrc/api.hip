@@ -364,8 +364,9 @@ Operand no_operand() {
 }
 
 // W_eff[out x in] (bf16, pitch ldw) = deq(Wq) + s * deq(Pq) B; Pb receives deq(Pq) in bf16
+// (dequant_p; else it is there).  z: a product that goes out with the fold, reading Pb too, or null
 loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s,
-                        uint16_t* Pb, uint16_t* We, int64_t ldw, bool dequant_p, hipStream_t st) {
+                        uint16_t* Pb, uint16_t* We, int64_t ldw, bool dequant_p, const GemmParams* z, hipStream_t st) {
     const int64_t out = Wq->rows, in = Wq->cols, r = Pq->cols;
     const int64_t ldr = (int64_t)round_up(r, 8);
     if (dequant_p)
@@ -383,7 +384,8 @@ loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const lo
     p.w_absmax = Wq->absmax;
     p.w_ld = Wq->ld;
     p.w_cols = (int)in;
-    LOQT_HIP(launch_gemm_nt(SLOT_FOLD, EPI_FOLD, false, true, p, st));
+    if (z) LOQT_HIP(launch_z_fold(SLOT_GEMM_Z, *z, SLOT_FOLD, EPI_FOLD, true, p, st));
+    else LOQT_HIP(launch_gemm_nt(SLOT_FOLD, EPI_FOLD, false, true, p, st));
     return LOQT_OK;
 }
 
@@ -414,19 +416,22 @@ hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipS
 
 // dB[M x N] (fp32 or bf16, pitch ld_dB) = sum of the planned slices of Z^T x and its relatives (both operands K x rows), or,
 // accumulating, that much more.  One slice that need not be added to anything goes straight to dB (rank 1024, 5120
-// columns, 256 tokens: a launch of 7 us less).
+// columns, 256 tokens: a launch of 7 us less).  dx: the product of dx, which goes out with it, or null.
 hipError_t gradient_product(int slot, GemmParams p, float* part, size_t part_bytes, int64_t ldp, void* dB, int dB_dtype,
-                            int64_t ld_dB, int accumulate, hipStream_t st) {
+                            int64_t ld_dB, int accumulate, const GemmParams* dx, hipStream_t st) {
+    auto go = [&](int epi) {
+        return dx ? launch_dx_gradient(SLOT_GEMM_DX, *dx, slot, epi, p, st) : launch_gemm_nt(slot, epi, true, true, p, st);
+    };
     p.splits = planned_splits(p.M, p.N, p.A[0].K, ldp, part_bytes);
     const bool bf16 = dB_dtype == LOQT_BF16;
     if (p.splits == 1 && !accumulate && g_nt_tile_override == 0 && ld_dB % (bf16 ? 8 : 4) == 0 && aligned(dB, 16)) {
         p.C = dB;
         p.ldc = ld_dB;
-        return launch_gemm_nt(slot, bf16 ? EPI_BF16 : EPI_F32_SPLITK, true, true, p, st);
+        return go(bf16 ? EPI_BF16 : EPI_F32_SPLITK);
     }
     p.C = part;
     p.ldc = ldp;
-    hipError_t e = launch_gemm_nt(slot, EPI_F32_SPLITK, true, true, p, st);
+    hipError_t e = go(EPI_F32_SPLITK);
     if (e != hipSuccess) return e;
     return launch_reduce_db(part, p.splits, p.M, p.N, ldp, dB, dB_dtype, ld_dB, accumulate, st);
 }
@@ -688,7 +693,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
         const bool folded = save_weff || use_folded(T, out, in);
         if (folded) {
             // y = x W_eff^T with W_eff = deq(W) + s deq(P) B folded once per call
-            LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wb, ldw, true, st));
+            LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wb, ldw, true, nullptr, st));
         } else {
             LOQT_HIP(expand_weight(Wq, Wb, ldw, Pq, Pb, ld_u, st));
             // U = s x B^T
@@ -795,7 +800,8 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
     loqt_bf16* Z = reinterpret_cast<loqt_bf16*>(ws);
     float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + bwd_z_bytes(T, r));
 
-    GemmParams p;
+    GemmParams p, pz, pdx;  // pz, pdx: products that go out together with a later one
+    bool dx_later = false;
     if (saved || use_prepass(T)) {
         char* base = reinterpret_cast<char*>(ws);
         const uint16_t* Wb = saved ? saved : reinterpret_cast<const uint16_t*>(base + L.Wb);
@@ -862,12 +868,13 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
             p.ldc = ld_z;
             p.split_ws = part;
             p.split_ws_floats = part_floats;
-            LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
+            pz = p;
+            if (!folded || saved) LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
         }
         if (dx) {
             // dx = dy Wb (+ Z B when the rank-r term is not folded into Wb); Wb is out x in: K x rows
             uint16_t* Wws = reinterpret_cast<uint16_t*>(base + L.Wb);
-            if (folded && !saved) LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wws, ldw, false, st));
+            if (folded && !saved) LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wws, ldw, false, z_with_dx ? nullptr : &pz, st));
             memset(&p, 0, sizeof(p));
             p.A[0] = bf16_operand(dy, ld_dy, (int)T, (int)out);
             p.B[0] = bf16_operand(Wb, ldw, (int)in, (int)out);
@@ -889,7 +896,8 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
             }
             p.split_ws = part;  // (the slices of Z, if any, have been summed by now; those of dB come later)
             p.split_ws_floats = part_floats;
-            LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
+            if (z_with_dx) LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
+            else pdx = p, dx_later = true;
         }
         }
         // dB = Z^T x: Z is T x r and x is T x in, both K x rows; contraction over T in slices
@@ -899,7 +907,8 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         p.M = (int)r;
         p.N = (int)in;
         p.alpha = 1.0f;
-        LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, ws_bytes - L.partials, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
+        LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, ws_bytes - L.partials, L.ldp, dB, dB_dtype, ld_dB, accumulate,
+                                  dx_later ? &pdx : nullptr, st));
         return LOQT_OK;
     }
     memset(&p, 0, sizeof(p));
@@ -1101,7 +1110,7 @@ loqt_status loqt_init_compensate(const float* W, int64_t ld_w, const float* P, i
 namespace {
 // Qb = deq(Qq) (bf16, in x r) and We = deq(Wq) + s Bp Qb^T (bf16, out x in, pitch ldw)
 loqt_status fold_weight_right(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Qq, const loqt_bf16* Bp, int64_t ld_Bp,
-                              float s, uint16_t* Qb, int64_t ldr, uint16_t* We, int64_t ldw, hipStream_t st) {
+                              float s, uint16_t* Qb, int64_t ldr, uint16_t* We, int64_t ldw, const GemmParams* v, hipStream_t st) {
     const int64_t out = Wq->rows, in = Wq->cols, r = Qq->cols;
     GemmParams p;
     memset(&p, 0, sizeof(p));
@@ -1116,7 +1125,8 @@ loqt_status fold_weight_right(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Qq, co
     p.w_absmax = Wq->absmax;
     p.w_ld = Wq->ld;
     p.w_cols = (int)in;
-    LOQT_HIP(launch_gemm_nt(SLOT_FOLD, EPI_FOLD, false, false, p, st));
+    if (v) LOQT_HIP(launch_z_fold(SLOT_GEMM_U, *v, SLOT_FOLD, EPI_FOLD, false, p, st));
+    else LOQT_HIP(launch_gemm_nt(SLOT_FOLD, EPI_FOLD, false, false, p, st));
     return LOQT_OK;
 }
 loqt_status check_ws(void* ws, size_t ws_bytes, size_t need) {
@@ -1141,7 +1151,7 @@ loqt_status loqt_linear_fwd_right(const loqt_bf16* x, int64_t ld_x, int64_t T, c
     uint16_t* Qb = reinterpret_cast<uint16_t*>(base + L.Qb);
     uint16_t* We = reinterpret_cast<uint16_t*>(base + L.We);
     LOQT_HIP(launch_dequantize(Qq->codes, Qq->absmax, in, r, Qq->ld, Qb, LOQT_BF16, L.ldr, st, SLOT_PREPASS));
-    LOQT_TRY(fold_weight_right(Wq, Qq, Bp, ld_Bp, s, Qb, L.ldr, We, L.ldw, st));
+    LOQT_TRY(fold_weight_right(Wq, Qq, Bp, ld_Bp, s, Qb, L.ldr, We, L.ldw, nullptr, st));
     GemmParams p;
     memset(&p, 0, sizeof(p));
     p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
@@ -1192,10 +1202,12 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     p.ldc = L.ldr;
     p.split_ws = part;
     p.split_ws_floats = part_floats;
-    LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, true, p, st));
-    if (dx) {
+    GemmParams pdx;
+    if (!dx) {
+        LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, true, p, st));
+    } else {
         // dx = dy W_eff, W_eff out x in: K x rows
-        LOQT_TRY(fold_weight_right(Wq, Qq, Bp, ld_Bp, s, Qb, L.ldr, We, L.ldw, st));
+        LOQT_TRY(fold_weight_right(Wq, Qq, Bp, ld_Bp, s, Qb, L.ldr, We, L.ldw, &p, st));
         memset(&p, 0, sizeof(p));
         p.A[0] = bf16_operand(dy, ld_dy, (int)T, (int)out);
         p.B[0] = bf16_operand(We, L.ldw, (int)in, (int)out);
@@ -1206,7 +1218,7 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
         p.ldc = ld_dx;
         p.split_ws = part;
         p.split_ws_floats = part_floats;
-        LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
+        pdx = p;
     }
     // dBp = dy^T V: dy is T x out and V is T x r, both K x rows; contraction over T in slices
     memset(&p, 0, sizeof(p));
@@ -1215,7 +1227,8 @@ loqt_status loqt_linear_bwd_right(const loqt_bf16* dy, int64_t ld_dy, const loqt
     p.M = (int)out;
     p.N = (int)r;
     p.alpha = 1.0f;
-    LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, ws_bytes - L.partials, L.ldp, dBp, dBp_dtype, ld_dBp, accumulate, st));
+    LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, ws_bytes - L.partials, L.ldp, dBp, dBp_dtype, ld_dBp, accumulate,
+                              dx ? &pdx : nullptr, st));
     return LOQT_OK;
 }
 
@@ -1330,7 +1343,7 @@ loqt_status check_layer_nq(const loqt_bf16* W, int64_t ld_W, const loqt_bf16* P,
 // instead of over W)
 static hipError_t fold_nq(const loqt_bf16* W, int64_t ld_W, const loqt_bf16* P, int64_t ld_P, const loqt_bf16* B,
                           int64_t ld_B, int64_t out, int64_t in, int64_t r, float s, uint16_t* We, int64_t ld_we,
-                          hipStream_t st) {
+                          const GemmParams* z, hipStream_t st) {
     GemmParams p;
     memset(&p, 0, sizeof(p));
     p.A[0] = bf16_operand(P, ld_P, (int)out, (int)r);
@@ -1342,6 +1355,7 @@ static hipError_t fold_nq(const loqt_bf16* W, int64_t ld_W, const loqt_bf16* P, 
     p.ldc = ld_we;
     p.w_bf16 = W;
     p.w_bf16_ld = ld_W;
+    if (z) return launch_z_fold(SLOT_GEMM_Z, *z, SLOT_FOLD, EPI_ACC_BF16, true, p, st);
     return launch_gemm_nt(SLOT_FOLD, EPI_ACC_BF16, false, true, p, st);
 }
 
@@ -1366,7 +1380,7 @@ loqt_status loqt_linear_fwd_nq(const loqt_bf16* x, int64_t ld_x, int64_t T, cons
     if (folded && !few) {  // y = x W_eff^T with the rank-r term folded into a transient copy of the weight
         uint16_t* We = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.We);
         const int64_t ld_we = L.ldw;
-        LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, st));
+        LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, nullptr, st));
         memset(&p, 0, sizeof(p));
         p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
         p.B[0] = bf16_operand(We, ld_we, (int)out, (int)in);
@@ -1433,7 +1447,6 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + (at_end ? L.split : z_bytes));
     const size_t part_bytes = at_end ? ws_bytes - L.split : folded ? L.We - L.partials : ws_bytes - L.partials;
     const int64_t ld_we = L.ldw;
-    if (folded) LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, st));
     const int64_t ld_z = (int64_t)round_up(r, 8);
     GemmParams p;
     memset(&p, 0, sizeof(p));  // Z = s dy P: P is out x r, i.e. K x rows
@@ -1446,7 +1459,9 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     p.ldc = ld_z;
     p.split_ws = part;
     p.split_ws_floats = (int64_t)(part_bytes / 4);
-    LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
+    if (folded) LOQT_HIP(fold_nq(W, ld_W, P, ld_P, B, ld_B, out, in, r, s, We, ld_we, &p, st));
+    else LOQT_HIP(launch_gemm_nt(SLOT_GEMM_Z, EPI_BF16, false, true, p, st));
+    GemmParams pdx;
     if (dx) {  // dx = [dy | Z] [W ; B]: W is out x in and B is r x in, both K x rows; folded: dx = dy W_eff
         memset(&p, 0, sizeof(p));
         p.A[0] = bf16_operand(dy, ld_dy, (int)T, (int)out);
@@ -1462,7 +1477,7 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
         p.ldc = ld_dx;
         p.split_ws = part;
         p.split_ws_floats = (int64_t)(part_bytes / 4);
-        LOQT_HIP(launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, p, st));
+        pdx = p;
     }
     memset(&p, 0, sizeof(p));  // dB = Z^T x over slices of T
     p.A[0] = bf16_operand(Z, ld_z, (int)r, (int)T);
@@ -1470,7 +1485,7 @@ loqt_status loqt_linear_bwd_nq(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf
     p.M = (int)r;
     p.N = (int)in;
     p.alpha = 1.0f;
-    LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, part_bytes, L.ldp, dB, dB_dtype, ld_dB, accumulate, st));
+    LOQT_HIP(gradient_product(SLOT_GEMM_DB, p, part, part_bytes, L.ldp, dB, dB_dtype, ld_dB, accumulate, dx ? &pdx : nullptr, st));
     return LOQT_OK;
 }
 

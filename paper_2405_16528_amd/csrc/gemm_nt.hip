@@ -160,16 +160,14 @@ hipError_t launch_nt_tile(int tile, const GemmParams& p, hipStream_t st) {
 
 int ktiles(const GemmParams& p) { return (p.A[0].K + BK - 1) / BK + (p.A[1].K + BK - 1) / BK; }
 
-// fp32 slices at p.C: the number of slices was fixed with the workspace (plan_nt); the tile that goes with it
-template <bool ARC, bool BRC>
-hipError_t launch_slices(const GemmParams& p, hipStream_t st) {
-    if (g_nt_tile_override != 0) {
-        if constexpr (ARC) {
-            if (g_nt_tile_override == NT_256x256) return launch_nt<256, 256, EPI_F32_SPLITK, ARC, BRC>(p, st);
-        }
-        return launch_nt_tile<EPI_F32_SPLITK, ARC, BRC>(g_nt_tile_override, p, st);
+// the gradient of a factor: fp32 slices at p.C, or bf16
+template <int EPI>
+hipError_t launch_gradient(const GemmParams& p, hipStream_t st) {
+    const int tile = gradient_tile(EPI, p);
+    if constexpr (EPI == EPI_F32_SPLITK) {
+        if (tile == NT_256x256) return launch_nt<256, 256, EPI, true, true>(p, st);  // (forced only)
     }
-    return launch_nt_tile<EPI_F32_SPLITK, ARC, BRC>(plan_nt(p.M, p.N, ktiles(p), true, p.splits, p.splits).tile, p, st);
+    return launch_nt_tile<EPI, true, true>(tile, p, st);
 }
 
 // C in bf16
@@ -181,18 +179,12 @@ hipError_t launch_product(const GemmParams& p, hipStream_t st) {
     // global traffic and win on long contractions.
     if (!large_product(p.M, p.N, p.Nx, p.A[0].K + p.A[1].K)) {
         if (p.Nx != 0) return launch_nt<128, 128, EPI, false, BRC>(p, st);
-        const int64_t ldc = (p.N + 3) / 4 * 4;
-        const int64_t room = p.split_ws ? p.split_ws_floats / (p.M * ldc) : 0;
-        const NtPlan plan = plan_nt(p.M, p.N, ktiles(p), false, 1, (int)std::min<int64_t>(std::max<int64_t>(room, 1), NT_MAX_SPLITS));
+        const NtPlan plan = product_plan(p);
         if (plan.splits == 1) return launch_nt_tile<EPI, false, BRC>(plan.tile, p, st);
-        // fp32 slices of the contraction and their fixed-order sum
-        GemmParams c = p;
-        c.C = p.split_ws;
-        c.ldc = ldc;
-        c.splits = plan.splits;
+        const GemmParams c = product_slices(p, plan.splits);
         hipError_t e = launch_nt_tile<EPI_F32_SPLITK, false, BRC>(plan.tile, c, st);
         if (e != hipSuccess) return e;
-        return launch_reduce_db(p.split_ws, plan.splits, p.M, p.N, ldc, p.C, LOQT_BF16, p.ldc, 0, st, false);
+        return launch_reduce_db(p.split_ws, plan.splits, p.M, p.N, c.ldc, p.C, LOQT_BF16, p.ldc, 0, st, false);
     }
     // 256x256 tiles run in rounds of one tile per compute unit.  When the last round would be mostly
     // empty, the tile columns that fill whole rounds go out as one launch and the remaining columns
@@ -251,6 +243,28 @@ hipError_t prepare_tiles() {
 
 int g_nt_tile_override = 0;
 
+NtPlan product_plan(const GemmParams& p) {
+    if (g_nt_tile_override != 0 || p.Nx != 0 || large_product(p.M, p.N, 0, p.A[0].K + p.A[1].K)) return NtPlan{0, 1, 0.0};
+    const int64_t room = p.split_ws ? p.split_ws_floats / (p.M * ((p.N + 3) / 4 * 4)) : 0;
+    return plan_nt(p.M, p.N, ktiles(p), false, 1, (int)std::min<int64_t>(std::max<int64_t>(room, 1), NT_MAX_SPLITS));
+}
+
+// fp32 slices of the contraction, for a fixed-order sum
+GemmParams product_slices(const GemmParams& p, int splits) {
+    GemmParams c = p;
+    c.C = p.split_ws;
+    c.ldc = (p.N + 3) / 4 * 4;
+    c.splits = splits;
+    return c;
+}
+
+// the number of slices was fixed with the workspace (plan_nt); the tile that goes with it
+int gradient_tile(int epi, const GemmParams& p) {
+    if (g_nt_tile_override != 0) return g_nt_tile_override;
+    const int n = epi == EPI_BF16 ? 1 : p.splits;
+    return plan_nt(p.M, p.N, ktiles(p), true, n, n).tile;
+}
+
 // every kernel configuration launch_gemm_nt / launch_merge_grouped can reach
 hipError_t prepare_nt_kernels() {
     hipError_t e;
@@ -261,6 +275,7 @@ hipError_t prepare_nt_kernels() {
     if ((e = prepare_tiles<EPI_F32_SPLITK, false, true>()) != hipSuccess) return e;
     if ((e = prepare_tiles<EPI_F32_SPLITK, true, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<256, 256, EPI_F32_SPLITK, true, true>()) != hipSuccess) return e;
+    if ((e = prepare_pair_kernels()) != hipSuccess) return e;
     return prepare_weight_kernels();
 }
 
@@ -270,8 +285,7 @@ hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmPar
     if (epi != EPI_BF16 && epi != EPI_F32_SPLITK) return a_rc ? hipErrorInvalidValue : launch_weight_product(epi, b_rc, p, st);
     if (!a_rc && epi == EPI_BF16) return b_rc ? launch_product<true>(p, st) : launch_product<false>(p, st);
     if (!a_rc || !b_rc) return hipErrorInvalidValue;
-    if (epi == EPI_F32_SPLITK) return launch_slices<true, true>(p, st);
-    return launch_nt_tile<EPI_BF16, true, true>(plan_nt(p.M, p.N, ktiles(p), true, 1, 1).tile, p, st);
+    return epi == EPI_BF16 ? launch_gradient<EPI_BF16>(p, st) : launch_gradient<EPI_F32_SPLITK>(p, st);
 }
 
 }  // namespace loqt

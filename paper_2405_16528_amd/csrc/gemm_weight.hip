@@ -74,21 +74,18 @@ hipError_t ensure_attr_grouped() {
 
 template <int EPI, bool BRC>
 hipError_t launch_sized(const GemmParams& p, hipStream_t st) {
-    auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
     constexpr bool HEAVY = EPI == EPI_COMP || EPI == EPI_FOLD_F32;  // small tiles only
-    if constexpr (EPI != EPI_FOLD_F32) {
-        // While 128x128 tiles leave compute units idle: 64x128, twice the work-groups.  Time of
-        // the launch, 64x128 / 128x128 (merge, unquantised merge, fold, compensation step): up to 127 tiles of 128x128 0.84, 0.80,
-        // 0.85, 0.76; 128 to 192 tiles 0.87, 0.90, 0.92, 0.87; 256 tiles, where every unit has one, 1.13, 1.08, 1.17, 1.02.
-        if (g_nt_tile_override == 0 && tiles(128, 128) <= 192) return launch_nt<64, 128, EPI, false, BRC, 3>(p, st);
-    }
-    if constexpr (!HEAVY) {
-        // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its epilogue
-        // behind, which two resident 128x128 work-groups have: the fold's is short enough, the merge's is not.
-        int choice = g_nt_tile_override;
-        if (choice == 0 && (EPI == EPI_FOLD || EPI == EPI_ACC_BF16) && tiles(256, 256) >= 224) choice = NT_256x256;
-        if (choice == NT_256x256) return launch_nt<256, 256, EPI, false, BRC>(p, st);
-        if (choice == NT_256x128) return launch_nt<256, 128, EPI, false, BRC>(p, st);
+    switch (weight_tile(EPI, p)) {
+        case NT_256x256:
+            if constexpr (!HEAVY) return launch_nt<256, 256, EPI, false, BRC>(p, st);
+            break;
+        case NT_256x128:
+            if constexpr (!HEAVY) return launch_nt<256, 128, EPI, false, BRC>(p, st);
+            break;
+        case NT_64x128:
+            if constexpr (EPI != EPI_FOLD_F32) return launch_nt<64, 128, EPI, false, BRC, 3>(p, st);
+            break;
+        default: break;
     }
     return launch_nt<128, 128, EPI, false, BRC>(p, st);
 }
@@ -144,6 +141,19 @@ hipError_t prepare_weight_kernels() {
     if ((e = prepare_sized<EPI_FOLD_F32, true>()) != hipSuccess) return e;
     if ((e = ensure_attr_grouped<true>()) != hipSuccess) return e;
     return ensure_attr_grouped<false>();
+}
+
+int weight_tile(int epi, const GemmParams& p) {
+    auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
+    if (g_nt_tile_override != 0) return g_nt_tile_override;
+    // While 128x128 tiles leave compute units idle: 64x128, twice the work-groups.  Time of
+    // the launch, 64x128 / 128x128 (merge, unquantised merge, fold, compensation step): up to 127 tiles of 128x128 0.84, 0.80,
+    // 0.85, 0.76; 128 to 192 tiles 0.87, 0.90, 0.92, 0.87; 256 tiles, where every unit has one, 1.13, 1.08, 1.17, 1.02.
+    if (epi != EPI_FOLD_F32 && tiles(128, 128) <= 192) return NT_64x128;
+    // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its epilogue
+    // behind, which two resident 128x128 work-groups have: the fold's is short enough, the others' are not.
+    if ((epi == EPI_FOLD || epi == EPI_ACC_BF16) && tiles(256, 256) >= 224) return NT_256x256;
+    return NT_128x128;
 }
 
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st) {

@@ -297,8 +297,20 @@ int gemm_db_splits(int64_t T, int64_t r, int64_t in);
 // large-token path (gemm_nt.hip): bf16 operands stored rows x K (K contiguous) or, with the
 // a_rc / b_rc flag, K x rows (rows contiguous; Operand::ld is the pitch of that stored matrix)
 hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st);
-// ... of which those whose epilogue walks the weight (gemm_weight.hip; A stored rows x K, not timed)
+// ... of which those whose epilogue walks the weight (gemm_weight.hip; A stored rows x K, not timed), and their tile
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st);
+int weight_tile(int epi, const GemmParams& p);
+// tile and slices of a bf16-output product (A stored rows x K) below the size of 256x256 rounds, as far as its scratch goes;
+// tile 0: larger, or with extra columns, or a tile is forced.  Its parameters when it runs in slices.  Tile of a gradient.
+NtPlan product_plan(const GemmParams& p);
+GemmParams product_slices(const GemmParams& p, int splits);
+int gradient_tile(int epi, const GemmParams& p);
+// dx (bf16, B stored K x rows) and the factor's gradient (epi: fp32 slices or bf16; both operands K x rows); Z (as dx) and
+// the fold (EPI_FOLD or EPI_ACC_BF16).  One launch where both run on small tiles (gemm_pair.hip), timed as dx and as the fold
+// then, else two, in this order
+hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int epi, const GemmParams& g, hipStream_t st);
+hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, bool b_rc, const GemmParams& fold, hipStream_t st);
+hipError_t prepare_pair_kernels();
 // several merges as one launch of 128x128 tiles (EPI_MERGE over the tiles of all layers); at most MERGE_GROUP_MAX
 // layers per launch.  A: deq(P) in bf16 (out x r, pitch lda); B: the trainable factor, r x in stored K x rows
 // (b_rc) or in x r stored rows x K; the rest as in GemmParams.
