@@ -85,7 +85,8 @@ loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max
  * it around a stream capture).  loqt_timing_read synchronises with the recorded events and returns,
  * for kernel slot `slot` (0 <= slot < loqt_timing_slots()), its name, launch count and summed
  * device time in milliseconds since the last loqt_timing_enable(1).  Products that share a launch are
- * timed as one of them: dx and the factor's gradient as dx, Z and the fold of the weight as the fold.  Not thread-safe; at most
+ * timed as one of them: dx and the factor's gradient as dx, Z and the fold of the weight as the fold, U and
+ * the copies of W and P as U.  Not thread-safe; at most
  * LOQT_TIMING_MAX_EVENTS launches are recorded per enable, later ones are not timed.
  */
 #define LOQT_TIMING_MAX_EVENTS 65536

@@ -392,11 +392,12 @@ loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const lo
 // bf16 copies of the weight and of P in one launch (two cost a launch more and leave P, a small one, alone on the chip; whole
 // forward calls with 300 tokens, us, two / one: 512 x 512, rank 128, 17.2 / 16.7; 4096 x 4096, rank 1024, 64.1 / 60.2;
 // 13824 x 5120, rank 1024, 131.5 / 129.3)
+// u: U = s x B^T, which goes out with them, or null.
 hipError_t expand_weight(const loqt_nf4_mat* Wq, uint16_t* Wb, int64_t ldw, const loqt_nf4_mat* Pq, uint16_t* Pb, int64_t ldp,
-                         hipStream_t st) {
+                         const GemmParams* u, hipStream_t st) {
     const DequantGroupItem both[2] = {{Wq->codes, Wq->absmax, Wb, Wq->rows, Wq->ld, ldw, (int)Wq->cols},
                                       {Pq->codes, Pq->absmax, Pb, Pq->rows, Pq->ld, ldp, (int)Pq->cols}};
-    return launch_dequantize_grouped(both, 2, st, SLOT_PREPASS);
+    return u ? launch_u_copies(SLOT_GEMM_U, *u, both, st) : launch_dequantize_grouped(both, 2, st, SLOT_PREPASS);
 }
 
 // U = s x B^T for a handful of tokens.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
@@ -695,7 +696,6 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
             // y = x W_eff^T with W_eff = deq(W) + s deq(P) B folded once per call
             LOQT_TRY(fold_weight(Wq, Pq, B, ld_B, s, Pb, Wb, ldw, true, nullptr, st));
         } else {
-            LOQT_HIP(expand_weight(Wq, Wb, ldw, Pq, Pb, ld_u, st));
             // U = s x B^T
             memset(&p, 0, sizeof(p));
             p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
@@ -707,7 +707,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
             p.ldc = ld_u;
             p.split_ws = reinterpret_cast<float*>(base + L.split);
             p.split_ws_floats = (int64_t)((ws_bytes - L.split) / 4);
-            LOQT_HIP(launch_gemm_nt(SLOT_GEMM_U, EPI_BF16, false, false, p, st));
+            LOQT_HIP(expand_weight(Wq, Wb, ldw, Pq, Pb, ld_u, &p, st));
         }
         // y = x Wb^T (+ U deq(P)^T when the rank-r term is not folded into Wb)
         memset(&p, 0, sizeof(p));
@@ -832,7 +832,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
             }
         } else {
         const bool folded = dx && (saved || use_folded_bwd(T, out, in));
-        if (dx && !folded) LOQT_HIP(expand_weight(Wq, reinterpret_cast<uint16_t*>(base + L.Wb), ldw, Pq, Pb, ld_z, st));
+        if (dx && !folded) LOQT_HIP(expand_weight(Wq, reinterpret_cast<uint16_t*>(base + L.Wb), ldw, Pq, Pb, ld_z, nullptr, st));
         else LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ld_z, st, SLOT_PREPASS));
         // Z rides along with dx (one product [dx | Z] over the shared operand dy) when that is estimated to
         // take less time than the two launches: its tiles then fill a partly empty round of the dx product

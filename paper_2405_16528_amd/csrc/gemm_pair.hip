@@ -1,5 +1,5 @@
-// Two products that do not need each other as one launch: the gradient of the factor beside dx, and Z = s dy deq(P) (or
-// V = s x deq(Q)) beside the fold of the weight.
+// Products that do not need each other as one launch: the gradient of the factor beside dx, Z = s dy deq(P) (or V = s x deq(Q))
+// beside the fold of the weight, U = s x B^T beside the bf16 copies of W and P.
 //
 // Below a few thousand tokens a product is one partly filled round of small tiles for 5 to 20 us, a launch costs 3 to 4 us of
 // them (2.6 of host time, 1.4 between kernels, the first loads of every work-group on top), and the small products (a few
@@ -93,6 +93,79 @@ hipError_t z_fold_kind(int epi, bool b_rc, int tb, const GemmParams* a, const Ge
     return b_rc ? z_fold<EPI_A, EPI_FOLD, true>(tb, a, b, st) : z_fold<EPI_A, EPI_FOLD, false>(tb, a, b, st);
 }
 
+// Bf16 copies of two NF4 matrices beside U = s x B^T, which does not need them.  A work-group of the copy takes eight codes per
+// thread and four such pieces at a time: the product's LDS leaves only two of them on a compute unit.
+struct CopyPair {
+    DequantGroupItem it[2];
+    int blocks[2];
+};
+constexpr int COPY_PIECES = 4;
+// ... which costs a large weight more than the launch saves.  Forward calls, us, two launches / one: 1.6 million elements (300
+// tokens) 19.4 / 14.8, 2.8 million 26.7 / 22.8, 6.4 million (500) 36.4 / 34.2, 9 million (300, 1000) 35.2 / 34.5 and 52.4 /
+// 52.0, 16.8 million 53.3 / 53.4 and 77.6 / 75.2, 25 million 58.6 / 61.6 and 67.8 / 70.9, 45 million (500) 90.2 / 98.4.
+constexpr int64_t COPY_BESIDE_MAX = 12000000;
+
+template <class A>
+__global__ __launch_bounds__(256, 2) void nt_copy_kernel(const GemmParams a, const CopyPair c, const int a_per, const int a_all) {
+    if ((int)blockIdx.x < a_all) {
+        A::run(a, blockIdx.x, a_per);
+        return;
+    }
+    __shared__ float lut[16];
+    if (threadIdx.x < 16) lut[threadIdx.x] = kNf4Levels[threadIdx.x];
+    __syncthreads();
+    const int b = (int)blockIdx.x - a_all, k = b >= c.blocks[0] ? 1 : 0;  // wave-uniform
+    const DequantGroupItem& it = c.it[k];
+    const int gpr = (it.cols + 7) >> 3;
+    const int64_t groups = it.rows * gpr, first = (int64_t)(k ? b - c.blocks[0] : b) * (256 * COPY_PIECES) + threadIdx.x;
+    uint32_t word[COPY_PIECES];
+    float m[COPY_PIECES];
+    int64_t row[COPY_PIECES];
+    int j0[COPY_PIECES];
+#pragma unroll
+    for (int i = 0; i < COPY_PIECES; ++i) {
+        const int64_t g = min(first + i * 256, groups - 1);  // (past the end: the last one again, not stored)
+        row[i] = g / gpr;
+        j0[i] = (int)(g - row[i] * gpr) * 8;
+        word[i] = *reinterpret_cast<const uint32_t*>(it.codes + row[i] * (it.ld_q >> 1) + (j0[i] >> 1));
+        m[i] = it.absmax[row[i] * (it.ld_q >> 6) + (j0[i] >> 6)];
+    }
+#pragma unroll
+    for (int i = 0; i < COPY_PIECES; ++i) {
+        if (first + i * 256 >= groups) break;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = m[i] * lut[(word[i] >> (8 * (e >> 1) + ((e & 1) ? 0 : 4))) & 15u];
+        uint16_t* dst = it.out + row[i] * it.ld_out + j0[i];
+        if (j0[i] + 8 <= it.cols) {
+            *reinterpret_cast<uint4*>(dst) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
+        } else {
+            for (int e = 0; e < 8 && j0[i] + e < it.cols; ++e) dst[e] = (uint16_t)(pack_bf16(v[e], 0.f) & 0xffffu);
+        }
+    }
+}
+
+template <class A>
+hipError_t launch_copy(const GemmParams* a, const DequantGroupItem* items, hipStream_t st) {
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_copy_kernel<A>), hipFuncAttributeMaxDynamicSharedMemorySize, A::SMEM);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    if (a == nullptr) return hipSuccess;
+    CopyPair c;
+    int64_t blocks = 0;
+    for (int i = 0; i < 2; ++i) {
+        c.it[i] = items[i];
+        c.blocks[i] = (int)((items[i].rows * ((items[i].cols + 7) / 8) + 256 * COPY_PIECES - 1) / (256 * COPY_PIECES));
+        blocks += c.blocks[i];
+    }
+    const int per = A::grid(*a), all = per * (A::EPI == EPI_F32_SPLITK ? a->splits : 1);
+    hipLaunchKernelGGL((nt_copy_kernel<A>), dim3((unsigned)(all + blocks)), dim3(256), A::SMEM, st, *a, c, per, all);
+    return hipGetLastError();
+}
+
 bool small_tile(int t) { return t == NT_64x64 || t == NT_64x128 || t == NT_128x128; }
 
 }  // namespace
@@ -125,8 +198,25 @@ hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, boo
     return launch_gemm_nt(slot, epi, false, b_rc, fold, st);
 }
 
+hipError_t launch_u_copies(int slot, const GemmParams& u, const DequantGroupItem* items, hipStream_t st) {
+    const NtPlan plan = product_plan(u);
+    if (plan.tile == NT_64x64 && items[0].rows * items[0].cols <= COPY_BESIDE_MAX) {
+        TimedLaunch tl(slot, st);
+        if (plan.splits == 1) return launch_copy<T64x64<EPI_BF16, false, false>>(&u, items, st);
+        const GemmParams c = product_slices(u, plan.splits);
+        hipError_t e = launch_copy<T64x64<EPI_F32_SPLITK, false, false>>(&c, items, st);
+        if (e != hipSuccess) return e;
+        return launch_reduce_db(u.split_ws, c.splits, u.M, u.N, c.ldc, u.C, LOQT_BF16, u.ldc, 0, st, false);
+    }
+    hipError_t e = launch_dequantize_grouped(items, 2, st, SLOT_PREPASS);
+    if (e != hipSuccess) return e;
+    return launch_gemm_nt(slot, EPI_BF16, false, false, u, st);
+}
+
 hipError_t prepare_pair_kernels() {
     hipError_t e;
+    if ((e = launch_copy<T64x64<EPI_BF16, false, false>>(nullptr, nullptr, nullptr)) != hipSuccess) return e;
+    if ((e = launch_copy<T64x64<EPI_F32_SPLITK, false, false>>(nullptr, nullptr, nullptr)) != hipSuccess) return e;
     for (int ta : {NT_64x64, NT_64x128, NT_128x128})
         for (int tb : {NT_64x64, NT_64x128}) {
             if ((e = dx_gradient<EPI_BF16>(ta, tb, nullptr, nullptr, nullptr)) != hipSuccess) return e;

@@ -336,6 +336,9 @@ struct DequantGroupItem {
     int cols;
 };
 hipError_t launch_dequantize_grouped(const DequantGroupItem* items, int n, hipStream_t st, int slot);
+// copies of two matrices and U = s x B^T (bf16, both operands rows x K), in one launch where U runs on small tiles, timed as U
+// then, else two
+hipError_t launch_u_copies(int slot, const GemmParams& u, const DequantGroupItem* items, hipStream_t st);
 hipError_t launch_merge_grouped(int slot, bool b_rc, const MergeGroupLayer* layers, int n, hipStream_t st);
 // raise the LDS size of every kernel configuration of gemm_nt.hip / gemm.hip above the default (otherwise done at the
 // first launch of each), so that a first call can be recorded into a HIP graph

@@ -85,3 +85,24 @@ def test_shared_launch_on_the_other_layers(T, out, inp, r):
     dx_ref = dy64 @ (W.double().cpu() + s * P64 @ B.double().cpu())
     assert G.max_err_over_rms(dx.double().cpu().numpy(), dx_ref.numpy()) <= TOL
     assert G.max_err_over_rms(dB[0].double().cpu().numpy(), (s * (dy64 @ P64).t() @ x64).numpy()) <= TOL
+
+
+@pytest.mark.parametrize("T,out,inp,r", [(70, 130, 136, 40), (100, 1030, 333, 72), (130, 1100, 1000, 264), (65, 24, 2600, 24)])
+def test_copies_beside_the_first_product(T, out, inp, r):
+    """bf16 copies of W and P in the launch of U: pieces that end inside a work-group's, rows that end inside a piece; U in one
+    slice and in several."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    lay, Wq, Pq, d = _setup(T, out, inp, r, seed=T + r, sigma_B=2e-2)
+    y = G.bf16_empty(T, out, fill=float("nan"))
+    L.set_path(L.PATH_PREPASS)
+    try:
+        L.timing_enable(True)
+        L.loqt_linear_fwd(d["x"], d["Wq"], d["Pq"], d["B"], 0.5, y, G.workspace(L.OP_FWD, T, out, inp, r))
+        torch.cuda.synchronize()
+        L.timing_enable(False)
+    finally:
+        L.set_path(L.PATH_AUTO)
+    n = {k: v[0] for k, v in L.timing_read().items()}
+    assert (n["prepass"], n["gemm_u"], n["gemm_y"]) == (0, 1, 1)
+    assert G.max_err_over_rms(O.bf16_to_f64(G.bf16_host(y)), O.loqt_linear_fwd(lay.x, Wq, Pq, lay.B, 0.5)) <= TOL
