@@ -21,7 +21,7 @@ template <int BM_, int BN_, int EPI_, bool ARC_, bool BRC_, int NS_>
 struct Part {
     static constexpr int BM = BM_, BN = BN_, EPI = EPI_, NS = NS_, SMEM = NtCfg<BM, BN, NS>::SMEM;
     static constexpr bool ARC = ARC_, BRC = BRC_;
-    static_assert(NtCfg<BM, BN, NS>::PER_CU == 2, "");
+    static_assert(NtCfg<BM, BN, NS>::PER_CU >= 2, "");
     static int grid(const GemmParams& p) { return (((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) + 7) / 8 * 8; }
     // `b`: work-group of this part; `per`: of them belong to a slice (a multiple of 8, so that b % 8 is the XCD)
     static __device__ __forceinline__ void run(const GemmParams& p, int b, int per) {
@@ -84,7 +84,7 @@ hipError_t dx_gradient(int ta, int tb, const GemmParams* a, const GemmParams* b,
 template <int EPI_A, int EPI_B, bool BRC>
 hipError_t z_fold(int tb, const GemmParams* a, const GemmParams* b, hipStream_t st) {
     using A = T64x64<EPI_A, false, true>;
-    if (tb == NT_64x128) return launch<A, T64x128<EPI_B, false, BRC>>(a, b, st);
+    if (tb == NT_64x128) return launch<A, Part<64, 128, EPI_B, false, BRC, 2>>(a, b, st);
     return launch<A, T128x128<EPI_B, false, BRC>>(a, b, st);
 }
 template <int EPI_A>
@@ -184,8 +184,9 @@ hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int e
 
 hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, bool b_rc, const GemmParams& fold, hipStream_t st) {
     const NtPlan plan = product_plan(z);
-    const int tb = weight_tile(epi, fold);
-    if (plan.tile == NT_64x64 && (tb == NT_64x128 || tb == NT_128x128)) {
+    if (plan.tile == NT_64x64 && small_tile(weight_tile(epi, fold))) {
+        // (a compute unit holds two of either here: 64x128 as long as 128x128 leave units idle)
+        const int tb = ((fold.M + 127) / 128) * (int64_t)((fold.N + 127) / 128) <= 192 ? NT_64x128 : NT_128x128;
         TimedLaunch tl(slot, st);
         if (plan.splits == 1) return z_fold_kind<EPI_BF16>(epi, b_rc, tb, &z, &fold, st);
         const GemmParams c = product_slices(z, plan.splits);

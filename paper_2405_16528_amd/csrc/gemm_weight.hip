@@ -83,7 +83,7 @@ hipError_t launch_sized(const GemmParams& p, hipStream_t st) {
             if constexpr (!HEAVY) return launch_nt<256, 128, EPI, false, BRC>(p, st);
             break;
         case NT_64x128:
-            if constexpr (EPI != EPI_FOLD_F32) return launch_nt<64, 128, EPI, false, BRC, 3>(p, st);
+            if constexpr (EPI != EPI_FOLD_F32) return launch_nt<64, 128, EPI, false, BRC>(p, st);
             break;
         default: break;
     }
@@ -98,7 +98,7 @@ hipError_t prepare_sized() {
         if ((e = ensure_attr<256, 128, EPI, false, BRC>()) != hipSuccess) return e;
     }
     if constexpr (EPI != EPI_FOLD_F32)
-        if ((e = ensure_attr<64, 128, EPI, false, BRC, 3>()) != hipSuccess) return e;
+        if ((e = ensure_attr<64, 128, EPI, false, BRC>()) != hipSuccess) return e;
     return ensure_attr<128, 128, EPI, false, BRC>();
 }
 
@@ -146,10 +146,16 @@ hipError_t prepare_weight_kernels() {
 int weight_tile(int epi, const GemmParams& p) {
     auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
     if (g_nt_tile_override != 0) return g_nt_tile_override;
-    // While 128x128 tiles leave compute units idle: 64x128, twice the work-groups.  Time of
-    // the launch, 64x128 / 128x128 (merge, unquantised merge, fold, compensation step): up to 127 tiles of 128x128 0.84, 0.80,
-    // 0.85, 0.76; 128 to 192 tiles 0.87, 0.90, 0.92, 0.87; 256 tiles, where every unit has one, 1.13, 1.08, 1.17, 1.02.
-    if (epi != EPI_FOLD_F32 && tiles(128, 128) <= 192) return NT_64x128;
+    // 64x128 tiles on two stages, of which a compute unit holds three: where 128x128, two to a unit, leave room for the 64x128
+    // to take no more rounds.  Time of the launch, 64x128 / 128x128, ranks of 96, 300 and 768, by tiles of 128x128:
+    //                        208 to 384       448, 512         560, 620        680, 760
+    //   fold                 0.86 to 1.02     1.10 to 1.24     0.86 to 1.02    0.99 to 1.16
+    //   merge                0.86 to 0.96     1.12 to 1.26     0.86 to 0.97    0.91 to 1.05
+    //   compensation step    0.81 to 0.92     1.04 to 1.19     0.87 to 0.96    0.94 to 1.08
+    //   unquantised merge    0.83 to 1.03     1.09 to 1.22     0.79 to 0.94    0.80 to 0.96
+    // (With three stages and two to a unit they took 1.03 to 1.28 of the time of two stages and three.)
+    const int64_t t = tiles(128, 128);
+    if (epi != EPI_FOLD_F32 && (t <= 384 || (t > 512 && t <= (epi == EPI_ACC_BF16 ? 768 : 640)))) return NT_64x128;
     // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its epilogue
     // behind, which two resident 128x128 work-groups have: the fold's is short enough, the others' are not.
     if ((epi == EPI_FOLD || epi == EPI_ACC_BF16) && tiles(256, 256) >= 224) return NT_256x256;

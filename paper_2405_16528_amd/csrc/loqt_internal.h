@@ -75,7 +75,7 @@ __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v 
 struct Nf4EncTables {
     double mid[64];
     uint32_t c0[64];
-    float2 fast[64];  // {fl32(mid[k]), c0[k] as bits}: one 8-byte read for the single-precision path
+    float2 fast[64];  // {fl32(mid[k]), c0[k] + 1 as bits}: one 8-byte read for the single-precision path
 };
 
 // one entry per calling thread, k = 0..63 (entries above 32 are never addressed by finite data
@@ -91,7 +91,7 @@ __device__ __forceinline__ void nf4_enc_tables_fill(Nf4EncTables* t, int k) {
         if (j == c) m = kNf4Mid[j];
     t->mid[k] = m;
     t->c0[k] = (uint32_t)c;
-    t->fast[k] = make_float2((float)m, __uint_as_float((uint32_t)c));
+    t->fast[k] = make_float2((float)m, __uint_as_float((uint32_t)c + 1u));
 }
 
 // Two ways to the same code.  encode(): everything in fp64, exact for every finite block.  encode_fast(): the same
@@ -122,13 +122,15 @@ struct Nf4BlockEncoder {
         return t->c0[k] + ((wd > th) ? 1u : 0u);
     }
     __device__ __forceinline__ uint32_t encode_fast(const Nf4EncTables* t, float w, float& nearest) const {
-        // 1.5 * 2^23 + 16 + 16 u, rounded to an integer by the addition itself: the low bits are k
-        const float xf = __builtin_fmaf(w, scf, 12582928.0f);
-        const uint32_t k = __float_as_uint(xf) & 63u;
-        const float2 e = t->fast[k];
+        // 1.5 * 2^20 + 16.5 + 16 u, rounded to eighths by the addition itself: k is the integer part, three bits up, where
+        // it is the byte offset into the table as well.  (An eighth is 2^-7 of u, so u can be taken for one up to 2^-8 = 0.0039
+        // away; the decision points are at least 0.00407 from every edge of a bucket.)
+        const float xf = __builtin_fmaf(w, scf, 1572880.5f);
+        const float2 e = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(t->fast) + (__float_as_uint(xf) & 0x1f8u));
         const float d = __builtin_fmaf(-e.x, Mf, w);
         nearest = fminf(nearest, __builtin_fabsf(d));
-        return __float_as_uint(e.y) + ((d > 0.f) ? 1u : 0u);
+        // one less where d is negative (a d of zero is near, and counts for nothing)
+        return __float_as_uint(e.y) + (uint32_t)((int32_t)__float_as_uint(d) >> 31);
     }
     __device__ __forceinline__ bool near(float nearest) const { return !(nearest > guard) || out_of_range; }
 };

@@ -65,7 +65,7 @@ struct NtCfg {
     static constexpr int SMEM_MAIN = NS * STAGE;       // NS stages: tiles kt .. kt+NS-1 are in LDS or in flight
     static constexpr int SMEM_EPI = 4 * WTM * EPITCH;
     static constexpr int SMEM = SMEM_MAIN > SMEM_EPI ? SMEM_MAIN : SMEM_EPI;
-    static constexpr int PER_CU = SMEM <= 78 * 1024 ? 2 : 1;  // work-groups that share a compute unit
+    static constexpr int PER_CU = SMEM <= 52 * 1024 ? 3 : SMEM <= 78 * 1024 ? 2 : 1;  // work-groups that share a compute unit
 };
 
 // the larger of a and of the value the lanes 16, 32 and 48 further on hold (all four lanes of a column of the wave get it)
@@ -103,19 +103,20 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // tables of the epilogues that decode or encode NF4, in static LDS (their reads need no base register) and filled here:
     // the barriers of the main loop lie between
     __shared__ Nf4EncTables enc_tables;
-    __shared__ float level_table[16];
-    // the levels of four codes in the low half of hw (element e in byte e / 2, even e in the high nibble)
-    auto levels4 = [&](uint32_t hw, float* q) {
-        const uint32_t even = (hw >> 2) & 0x3c3cu, odd = (hw << 2) & 0x3c3cu;  // byte offsets into the table
+    __shared__ float2 level_table[256];
+    // the levels of four codes in half `sh` (0 or 16) of cw (element e in byte e / 2, even e in the high nibble): a table entry
+    // holds both levels of a byte
+    auto levels4 = [&](uint32_t cw, int sh, float* q) {
+        const uint32_t hw = cw >> sh;
         const char* const t = reinterpret_cast<const char*>(level_table);
-        q[0] = *reinterpret_cast<const float*>(t + (even & 0xffu)), q[1] = *reinterpret_cast<const float*>(t + (odd & 0xffu));
-        q[2] = *reinterpret_cast<const float*>(t + (even >> 8)), q[3] = *reinterpret_cast<const float*>(t + (odd >> 8));
+        const float2 a = *reinterpret_cast<const float2*>(t + ((hw << 3) & 0x7f8u)), b = *reinterpret_cast<const float2*>(t + ((hw >> 5) & 0x7f8u));
+        q[0] = a.x, q[1] = a.y, q[2] = b.x, q[3] = b.y;
     };
     if constexpr (ENCODES) {
         if (tid >= 64 && tid < 128) nf4_enc_tables_fill(&enc_tables, tid - 64);
     }
     if constexpr (ENCODES || CODES) {
-        if (tid < 16) level_table[tid] = kNf4Levels[tid];
+        level_table[tid] = make_float2(kNf4Levels[tid >> 4], kNf4Levels[tid & 15]);
     }
 
     // ---- tile of this work-group: contiguous range per XCD, groups of GM tile rows inside
@@ -633,7 +634,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 if constexpr (EPI == EPI_FOLD) {  // folded weight (M = out, N = in)
                     const float am = am_old[i][j >> 2];
                     float q[4];
-                    levels4(cw[j >> 1] >> (j & 1 ? sh1 : sh0), q);
+                    levels4(cw[j >> 1], j & 1 ? sh1 : sh0, q);
                     v0 += am * q[0], v1 += am * q[1], v2 += am * q[2], v3 += am * q[3];
                 }
                 const uint2 v = make_uint2(pack_bf16(v0, v1), pack_bf16(v2, v3));
@@ -657,7 +658,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 if constexpr (EPI == EPI_FOLD_F32) {
                     float lev[4];
                     const uint32_t cw = *reinterpret_cast<const uint32_t*>(code_at(i, wn * (WTN / 32) + (j >> 1)));
-                    levels4(cw >> (j & 1 ? sh1 : sh0), lev);
+                    levels4(cw, j & 1 ? sh1 : sh0, lev);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(p.alpha, acc[i][j][e], am_old[i][j >> 2] * lev[e]);
                 } else {
@@ -686,12 +687,14 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         const Nf4EncTables* const enc = &enc_tables;
         const int64_t ldb = p.w_ld >> 1, lda = p.w_ld >> 6;
         constexpr int CPW = WTN / 32, RPS = 64 / CPW;  // chunks of codes per row of the wave; rows per store
-        float src[2][NB][16];  // old levels, or the weights (compensation), of the running 16 rows and of the next
+        // Old levels of the running 16 rows and of the next; compensation: the weights, from memory, of all rows at once.
+        constexpr int AHEAD = EPI == EPI_COMP ? TM : 2;
+        float src[AHEAD][NB][16];
         auto fetch = [&](int i) {
             const int m = m0 + wm * WTM + i * 16 + frow;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                float* const q = src[i & 1][b];
+                float* const q = src[i % AHEAD][b];
                 if constexpr (EPI == EPI_COMP) {
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
@@ -704,25 +707,26 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
                         const uint32_t cw = *reinterpret_cast<const uint32_t*>(code_at(i, wn * CPW + 2 * b + u));
-                        levels4(cw >> sh0, q + 8 * u);
-                        levels4(cw >> sh1, q + 8 * u + 4);
+                        levels4(cw, sh0, q + 8 * u);
+                        levels4(cw, sh1, q + 8 * u + 4);
                     }
                 }
             }
         };
         // columns of the wave from nlast on do not exist
         const int nlast = p.w_cols - (n0 + (wave_s & 1) * WTN);
-        fetch(0);
+#pragma unroll
+        for (int i = 0; i < AHEAD - 1; ++i) fetch(i);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int m = m0 + wm * WTM + i * 16 + frow;
-            if (i + 1 < TM) fetch(i + 1);
+            if (i + AHEAD - 1 < TM) fetch(i + AHEAD - 1);
             float v[NB][16];
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const float a = acc[i][4 * b + e / 4][e % 4], o = src[i & 1][b][e];
+                    const float a = acc[i][4 * b + e / 4][e % 4], o = src[i % AHEAD][b][e];
                     v[b][e] = __builtin_fmaf(p.alpha, a, EPI == EPI_COMP ? o : am_old[CODES ? i : 0][b] * o);
                 }
             // columns past the end count as 0.  (The condition in scalar registers and the empty
@@ -735,7 +739,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                     for (int e = 0; e < 16; ++e)
                         if (col_of(4 * b + e / 4) - wn * WTN + e % 4 >= nlast) {
                             v[b][e] = 0.f;
-                            if constexpr (EPI == EPI_COMP) src[i & 1][b][e] = 0.f;
+                            if constexpr (EPI == EPI_COMP) src[i % AHEAD][b][e] = 0.f;
                         }
             }
             Nf4BlockEncoder be[NB];
@@ -786,18 +790,20 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     *reinterpret_cast<uint32_t*>(code_at(i, wn * CPW + 2 * b + u)) = word[b][u];
-                    if constexpr (EPI == EPI_COMP) {
+                    if constexpr (EPI == EPI_COMP) {  // the residuals of the eight columns, 16 bytes
+                        uint2 half[2];
 #pragma unroll
-                        for (int t = 2 * u; t < 2 * u + 2; ++t) {
-                            const int n = n0 + col_of(4 * b + t);
+                        for (int t = 0; t < 2; ++t) {
                             float lev[4], e[4];
-                            levels4(word[b][u] >> (t & 1 ? sh1 : sh0), lev);
+                            levels4(word[b][u], t ? sh1 : sh0, lev);
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) e[k] = src[i & 1][b][4 * t + k] - amax[b] * lev[k];
-                            if (m < p.M && n < p.e_ld)
-                                *reinterpret_cast<uint2*>(p.e_out + (int64_t)m * p.e_ld + n) =
-                                    make_uint2(pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3]));
+                            for (int k = 0; k < 4; ++k) e[k] = src[i % AHEAD][b][8 * u + 4 * t + k] - amax[b] * lev[k];
+                            half[t] = make_uint2(pack_bf16(e[0], e[1]), pack_bf16(e[2], e[3]));
                         }
+                        const uint2 lo = sh0 ? half[1] : half[0], hi = sh0 ? half[0] : half[1];
+                        const int n = n0 + wn * WTN + 64 * b + 32 * u + 8 * g4;
+                        if (m < p.M && n < p.e_ld)
+                            *reinterpret_cast<uint4*>(p.e_out + (int64_t)m * p.e_ld + n) = make_uint4(lo.x, lo.y, hi.x, hi.y);
                     }
                 }
             }
