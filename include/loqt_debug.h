@@ -31,7 +31,7 @@ extern "C" {
  *                      (2 T r (in + out) flop per pass) from T = out in / (in + out) tokens up.
  *   LOQT_PATH_AUTO   : forward calls with at most 32 tokens (loqt_linear_fwd, loqt_linear_fwd_nq) stream the weight
  *                      once and expand its codes in registers (a kernel of its own; reported as FUSED); calls with up
- *                      to 64 tokens, or up to 256 on weights of 14 million elements or more, that do not fold keep the
+ *                      to 64 tokens, or T up to 256 on weights of 2.5 million + 50000 T elements or more, that do not fold keep the
  *                      rank-r term beside the weight (reported as PREPASS) but expand the codes inside the products;
  *                      otherwise
  *                      forward and backward take the pre-pass family (measured ahead of the
@@ -39,6 +39,8 @@ extern "C" {
  *                      except that the backward pass, which has Z = s dy deq(P_q) at hand anyway, keeps the
  *                      rank-r term as a second K segment of the dx product when out > 0.73 T (2 T r in flop at
  *                      the rate of the large products instead of 2 out in r at the rate of the fold);
+ *                      the fold of the forward pass and the merge of a weight of at most 512 tiles of 64x128 and
+ *                      rank 256 read P as its codes, without the streaming pass;
  *                      the merge takes the pre-pass form; below 1024 columns (`in`, reported as FUSED), where
  *                      it may be called without a workspace, it is fused if that or too small a one was passed.
  * All compute the same quantities; results differ only in rounding order, within the stated

@@ -369,11 +369,12 @@ loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const lo
                         uint16_t* Pb, uint16_t* We, int64_t ldw, bool dequant_p, const GemmParams* z, hipStream_t st) {
     const int64_t out = Wq->rows, in = Wq->cols, r = Pq->cols;
     const int64_t ldr = (int64_t)round_up(r, 8);
-    if (dequant_p)
+    const bool from_codes = dequant_p && g_path == LOQT_PATH_AUTO && weight_takes_codes(out, in, r);
+    if (dequant_p && !from_codes)
         LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ldr, st, SLOT_PREPASS));
     GemmParams p;
     memset(&p, 0, sizeof(p));
-    p.A[0] = bf16_operand(Pb, ldr, (int)out, (int)r);   // out x r, K contiguous
+    p.A[0] = from_codes ? nf4_operand(Pq, (int)out, (int)r) : bf16_operand(Pb, ldr, (int)out, (int)r);  // out x r, K contiguous
     p.B[0] = bf16_operand(B, ld_B, (int)in, (int)r);    // r x in: K x rows
     p.M = (int)out;
     p.N = (int)in;
@@ -483,10 +484,12 @@ loqt_status merge_prepass(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* abs
     const MergeWs L(out, in, r);
     uint16_t* Pb = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.Pb);
     const int64_t ldr = (int64_t)round_up(r, 8);
-    LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ldr, st, SLOT_PREPASS));
+    const bool from_codes = g_path == LOQT_PATH_AUTO && weight_takes_codes(out, Wq->ld, r);
+    if (!from_codes)
+        LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ldr, st, SLOT_PREPASS));
     GemmParams p;
     memset(&p, 0, sizeof(p));
-    p.A[0] = bf16_operand(Pb, ldr, (int)out, (int)r);  // rows of the tile are rows of W
+    p.A[0] = from_codes ? nf4_operand(Pq, (int)out, (int)r) : bf16_operand(Pb, ldr, (int)out, (int)r);  // rows of the tile are rows of W
     p.B[0] = bf16_operand(B, ld_B, (int)in, (int)r);   // r x in: K x rows, columns run along `in`
     p.M = (int)out;
     p.N = (int)Wq->ld;  // reach the padding columns (operand columns past `in` are never used)

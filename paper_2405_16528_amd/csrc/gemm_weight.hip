@@ -139,6 +139,8 @@ hipError_t prepare_weight_kernels() {
     if ((e = prepare_sized<EPI_ACC_BF16, true>()) != hipSuccess) return e;
     if ((e = prepare_sized<EPI_COMP, true>()) != hipSuccess) return e;
     if ((e = prepare_sized<EPI_FOLD_F32, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_MERGE, false, true, 2, false, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI_FOLD, false, true, 2, false, true>()) != hipSuccess) return e;
     if ((e = ensure_attr_grouped<true>()) != hipSuccess) return e;
     return ensure_attr_grouped<false>();
 }
@@ -162,7 +164,27 @@ int weight_tile(int epi, const GemmParams& p) {
     return NT_128x128;
 }
 
+// A small weight of low rank reads P as its codes: every work-group expands its 64 rows of P in LDS, which saves the launch that
+// would write them out.  That pays as long as all tiles of 64x128 are resident at once, two to a unit (the panel of P costs the
+// third); from there on the work-groups that follow each pay for their panel.  The call, us, rank 64 / 256, with the launch and
+// without, by tiles:
+//                      merge                              forward, 2048 tokens
+//   32  (512 x 512)    9.6 -> 6.6,   9.4 -> 7.9           13.0 -> 11.1, 14.1 -> 13.0
+//   192 (2048 x 768)   8.7 -> 6.1,   9.6 -> 8.0           20.1 -> 18.1, 20.5 -> 19.7
+//   512 (2048 x 2048)  9.1 -> 7.1,   11.0 -> 9.6          31.2 -> 29.2, 32.7 -> 31.6
+//   768 (2048 x 3072)  10.2 -> 10.8, 12.8 -> 15.3         42.0 -> 41.2, 44.2 -> 45.4
+//   2048 (4096 x 4096) 19.2 -> 19.3, 25.1 -> 25.0         74.5 -> 74.1, 79.2 -> 78.3
+bool weight_takes_codes(int64_t out, int64_t in, int64_t r) {
+    return g_nt_tile_override == 0 && r <= A_CODES_TILES * BK && ((out + 63) / 64) * ((in + 127) / 128) <= 512;
+}
+
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st) {
+    if (p.A[0].absmax) {
+        if (!b_rc || p.A[0].K > A_CODES_TILES * BK) return hipErrorInvalidValue;
+        if (epi == EPI_MERGE) return launch_nt<64, 128, EPI_MERGE, false, true, 2, false, true>(p, st);
+        if (epi == EPI_FOLD) return launch_nt<64, 128, EPI_FOLD, false, true, 2, false, true>(p, st);
+        return hipErrorInvalidValue;
+    }
     switch (epi) {
         case EPI_MERGE: return b_rc ? launch_sized<EPI_MERGE, true>(p, st) : launch_sized<EPI_MERGE, false>(p, st);
         case EPI_FOLD: return b_rc ? launch_sized<EPI_FOLD, true>(p, st) : launch_sized<EPI_FOLD, false>(p, st);

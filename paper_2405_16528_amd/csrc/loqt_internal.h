@@ -302,6 +302,8 @@ hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmPar
 // ... of which those whose epilogue walks the weight (gemm_weight.hip; A stored rows x K, not timed), and their tile
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st);
 int weight_tile(int epi, const GemmParams& p);
+// whether the fold and the merge of a weight out x in read P (rank r) as it is stored, A[0] with absmax
+bool weight_takes_codes(int64_t out, int64_t in, int64_t r);
 // tile and slices of a bf16-output product (A stored rows x K) below the size of 256x256 rounds, as far as its scratch goes;
 // tile 0: larger, or with extra columns, or a tile is forced.  Its parameters when it runs in slices.  Tile of a gradient.
 NtPlan product_plan(const GemmParams& p);

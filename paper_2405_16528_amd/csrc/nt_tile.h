@@ -5,7 +5,8 @@
 // with both operands bf16, each stored either rows x K (K contiguous) or K x rows (rows contiguous).
 // NF4 operands are dequantised to bf16 once per call (nf4_dequantize_kernel, or the fold epilogue
 // below) instead of once per output tile; at thousands of tokens that costs a few per cent of the
-// GEMM and keeps every VALU and LDS cycle of the inner loop for feeding the matrix cores.
+// GEMM and keeps every VALU and LDS cycle of the inner loop for feeding the matrix cores.  The exception is the A of
+// a small weight's fold or merge (ANF4), whose whole cost is its launches.
 //
 // Work-group: 256 threads = 4 waves (2 x 2), tile BM x BN x 64, v_mfma_f32_16x16x32_bf16: the same flops per cycle and the
 // same LDS bytes as v_mfma_f32_32x32x16_bf16, the same bits, but a quarter of the accumulator registers read and written per
@@ -53,16 +54,23 @@ constexpr int ROWB = 128;  // bytes of one LDS row (64 bf16)
 
 #define LOQT_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
-template <int BM, int BN, int NS = 2>
+// ANF4: A is NF4 and short (A_CODES_TILES k-tiles at most).  Its rows are expanded into a panel in LDS while the first tiles of B
+// are on their way (a few hundred cycles of look-ups per work-group at rank 256), and the loop loads B alone.
+constexpr int A_CODES_TILES = 4;
+
+template <int BM, int BN, int NS = 2, bool ANF4 = false>
 struct NtCfg {
     static constexpr int WTM = BM / 2, WTN = BN / 2;   // wave tile
     static constexpr int TM = WTM / 16, TN = WTN / 16; // 16x16 tiles per wave
-    static constexpr int STAGE = (BM + BN) * ROWB;
-    static constexpr int NCH = (BM + BN) / 32;         // 16-byte chunks per thread per stage
-    static constexpr int NCHA = BM / 32;               // of which belong to A
+    static constexpr int ASTAGE = ANF4 ? 0 : BM * ROWB; // bytes of A in a stage
+    static constexpr int STAGE = ASTAGE + BN * ROWB;
+    static constexpr int NCHA = ASTAGE / 4096;         // 16-byte chunks per thread per stage that belong to A
     static constexpr int NCHB = BN / 32;               // and to B
+    static constexpr int NCH = NCHA + NCHB;
+    static constexpr int PANEL = ANF4 ? A_CODES_TILES * BM * ROWB : 0;
+    static constexpr int HEAD = PANEL + (ANF4 ? BM * BN / 2 : 0);  // the panel and the old codes of the tile, ahead of the ring
     static constexpr int EPITCH = WTN * 2 + 8;         // staging pitch of the bf16 epilogue
-    static constexpr int SMEM_MAIN = NS * STAGE;       // NS stages: tiles kt .. kt+NS-1 are in LDS or in flight
+    static constexpr int SMEM_MAIN = HEAD + NS * STAGE; // NS stages: tiles kt .. kt+NS-1 are in LDS or in flight
     static constexpr int SMEM_EPI = 4 * WTM * EPITCH;
     static constexpr int SMEM = SMEM_MAIN > SMEM_EPI ? SMEM_MAIN : SMEM_EPI;
     static constexpr int PER_CU = SMEM <= 52 * 1024 ? 3 : SMEM <= 78 * 1024 ? 2 : 1;  // work-groups that share a compute unit
@@ -80,9 +88,9 @@ __device__ __forceinline__ float max_over_lane_groups(float a) {
 // One output tile.  L: index of the tile in the walk order described above (tiles past the end return at once);
 // split: slice of the contraction (EPI_F32_SPLITK), else 0.
 // NOTAIL (two stages only): every K segment is a whole number of k-tiles, so no tile has to be cut (cut_tile).
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
 __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, const int split) {
-    using Cfg = NtCfg<BM, BN, NS>;
+    using Cfg = NtCfg<BM, BN, NS, ANF4>;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, STAGE = Cfg::STAGE, WTM = Cfg::WTM, WTN = Cfg::WTN;
     constexpr bool ENCODES = EPI == EPI_MERGE || EPI == EPI_COMP;
     constexpr bool CODES = EPI == EPI_MERGE || EPI == EPI_FOLD || EPI == EPI_FOLD_F32;  // reads the old 4-bit weight
@@ -93,6 +101,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // same half of their 16-byte chunks, half of the banks.)
     constexpr bool WEIGHT = ENCODES || CODES || EPI == EPI_ACC_BF16;
     static_assert(!WEIGHT || WTN % 64 == 0, "");
+    static_assert(!ANF4 || (CODES && !ARC && NS == 2), "");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -216,7 +225,8 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 
     // The lane offsets of a thread's chunks are loop-invariant registers (per K segment) and the tile origin is a scalar
     // pointer that advances by a constant, so a load is one instruction plus scalar bookkeeping and can sit between MFMAs.
-    uint32_t offA[Cfg::NCHA], offB[Cfg::NCHB];
+    constexpr int CCPR = BN / 32, CRPP = 256 / CCPR, NCC = BM / CRPP;  // old codes: 16-byte chunks per row, rows per pass, passes
+    uint32_t offA[ANF4 ? NCC : Cfg::NCHA], offB[Cfg::NCHB];
     const char *hotA = nullptr, *hotB = nullptr;  // operand bytes of the tile that is loaded next
     int64_t stepA = 0, stepB = 0;
     // (kleft: what is left of the segment's contraction from k0 on.  The loads of a tile that is not full repeat a
@@ -259,20 +269,20 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         const bool seg = kt >= nkt0;
         const int k0 = (kt - (seg ? nkt0 : 0)) * BK;
         const int kleft = (seg ? p.A[1].K : p.A[0].K) - k0;
-        hot_operand(std::integral_constant<bool, ARC>{}, std::integral_constant<int, BM>{}, PlainTag{}, a_ptr(seg), a_ld(seg),
-                    a_rows(seg), m0, k0, kleft, offA, hotA, stepA);
+        if constexpr (!ANF4)
+            hot_operand(std::integral_constant<bool, ARC>{}, std::integral_constant<int, BM>{}, PlainTag{}, a_ptr(seg), a_ld(seg),
+                        a_rows(seg), m0, k0, kleft, offA, hotA, stepA);
         hot_operand(std::integral_constant<bool, BRC>{}, std::integral_constant<int, BN>{}, BTag{}, b_ptr(seg), b_ld(seg),
                     b_rows(seg), n0, k0, kleft, offB, hotB, stepB);
     };
     // The old codes of the tile (BN / 2 bytes a row) follow the last k-tile as if they were the next one's A: they land under
     // the last k-tiles' products and wait in LDS for the epilogue (fetched by it, they took as long as two or three k-tiles).
-    // Rows of CCPR 16-byte chunks; the swizzle keeps the reads of 16 rows apart.
-    constexpr int CCPR = BN / 32, CRPP = 256 / CCPR, NCC = BM / CRPP;
+    // The swizzle keeps the reads of 16 rows apart.
     auto code_swz = [](int row) { return CCPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
     auto codes_setup = [&]() {
         const uint32_t ldb = (uint32_t)(p.w_ld >> 1);
 #pragma unroll
-        for (int i = 0; i < Cfg::NCHA; ++i) {
+        for (int i = 0; i < (ANF4 ? NCC : Cfg::NCHA); ++i) {
             const int row = (i < NCC ? i : 0) * CRPP + tid / CCPR;
             const int ch = (tid % CCPR) ^ code_swz(row);
             offA[i] = (uint32_t)min(row, p.M - 1 - m0) * ldb + (n0 + ch * 32 < p.w_ld ? (uint32_t)ch * 16u : 0u);
@@ -281,7 +291,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     };
     auto hot_advance = [&](int kt) {  // move on to tile kt, the successor of the current one
         if (kt >= kt_end) {
-            if constexpr (CODES) {
+            if constexpr (CODES && !ANF4) {
                 if (kt == kt_end) codes_setup();
             }
             return;
@@ -290,6 +300,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         else hotA += stepA, hotB += stepB;
     };
     const uint32_t lds0 = (uint32_t)(uintptr_t)LOQT_LDS_PTR(smem);
+    char* const ring = smem + Cfg::HEAD;
     // Load n of a tile (chunks of A, then of B) into `stage`.  Inline assembly: the compiler cannot tell that the LDS reads of
     // the running tile never touch the stage the loads in flight are writing, and would wait for all of them (vmcnt(0))
     // before every group of transposing reads; written this way it does not see them, and the loop waits for them itself
@@ -300,18 +311,19 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // M0 cannot be named as a clobber (the compiler reserves it and warns that a clobber is not honoured): it
     // never keeps a value in M0 across other code, it writes M0 right in front of each of its own uses.
     // tests/test_isa_guard.py checks that nothing else in the loop touches M0.
-    auto hot_load = [&](int n, char* stage) {
-        const bool isA = n < Cfg::NCHA;
-        const int i = isA ? n : n - Cfg::NCHA;
-        const uint32_t o = isA ? offA[i] : offB[i];
-        const char* base = isA ? hotA : hotB;
-        const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)((isA ? 0 : BM * ROWB) + i * 4096 + wave_s * 1024);
+    auto direct_load = [&](uint32_t o, const char* base, uint32_t dst) {
         asm volatile(
             "s_mov_b32 m0, %2\n\t"
             "global_load_lds_dwordx4 %0, %1"
             :
             : "v"(o), "s"(base), "s"(dst)
             : "memory");
+    };
+    auto hot_load = [&](int n, char* stage) {
+        const bool isA = n < Cfg::NCHA;
+        const int i = isA ? n : n - Cfg::NCHA;
+        const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)((isA ? 0 : Cfg::ASTAGE) + i * 4096 + wave_s * 1024);
+        direct_load(isA ? offA[i] : offB[i], isA ? hotA : hotB, dst);
     };
     // Tile kt of the range has landed in `stage` by direct loads and ends past its segment's contraction: clears
     // everything from there on, in both operands (what came instead is finite, but the padding of a row need not be).
@@ -343,8 +355,46 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     auto cut_tile = [&](int kt, char* stage) {
         const bool seg = kt >= nkt0;
         const int kleft = (seg ? p.A[1].K : p.A[0].K) - (kt - (seg ? nkt0 : 0)) * BK;
-        cut_operand(std::integral_constant<bool, ARC>{}, std::integral_constant<int, BM>{}, PlainTag{}, kleft, stage);
-        cut_operand(std::integral_constant<bool, BRC>{}, std::integral_constant<int, BN>{}, BTag{}, kleft, stage + BM * ROWB);
+        if constexpr (!ANF4) cut_operand(std::integral_constant<bool, ARC>{}, std::integral_constant<int, BM>{}, PlainTag{}, kleft, stage);
+        cut_operand(std::integral_constant<bool, BRC>{}, std::integral_constant<int, BN>{}, BTag{}, kleft, stage + Cfg::ASTAGE);
+    };
+    // ANF4: the panel of A.  Chunk i of this thread is the same slot of the same tile layout as above; the codes of all k-tiles are
+    // asked for at once, ahead of the first tiles of B.
+    constexpr int PR = ANF4 ? BM / 32 : 1, PT = ANF4 ? A_CODES_TILES : 1;
+    uint32_t pcode[PR][PT];
+    float pscale[PR][PT];
+    const int pk = ((tid & 7) ^ kc_swz(PlainTag{}, tid >> 3)) * 8;  // first k of this thread's chunks in a k-tile
+    auto panel_load = [&]() {
+        const Operand& a = p.A[0];
+#pragma unroll
+        for (int i = 0; i < PR; ++i) {
+            const int64_t row = min(m0 + i * 32 + (tid >> 3), a.rows - 1);  // rows past the end: any valid row
+            const uint8_t* c = reinterpret_cast<const uint8_t*>(a.ptr) + row * (a.ld >> 1) + (pk >> 1);
+            const float* s = a.absmax + row * (a.ld >> 6);
+#pragma unroll
+            for (int t = 0; t < PT; ++t) {
+                const int kt = min(t, nkt0 - 1);
+                pcode[i][t] = *reinterpret_cast<const uint32_t*>(c + kt * (BK / 2));
+                pscale[i][t] = s[kt];
+            }
+        }
+    };
+    auto panel_expand = [&]() {  // (the same products and the same rounding as nf4_dequantize_kernel's)
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            if (t >= nkt0) break;
+            const int left = p.A[0].K - t * BK - pk;  // elements of this thread's chunks that exist
+#pragma unroll
+            for (int i = 0; i < PR; ++i) {
+                float q[8];
+                levels4(pcode[i][t], 0, q);
+                levels4(pcode[i][t], 16, q + 4);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) q[e] = e < left ? pscale[i][t] * q[e] : 0.f;
+                *reinterpret_cast<uint4*>(smem + t * (BM * ROWB) + i * 4096 + tid * 16) =
+                    make_uint4(pack_bf16(q[0], q[1]), pack_bf16(q[2], q[3]), pack_bf16(q[4], q[5]), pack_bf16(q[6], q[7]));
+            }
+        }
     };
 
     // ---- fragments.  A lane holds row (lane & 15) of a 16-row fragment and the 8 k-values 32*ks + 8*(lane >> 4) .. +7.
@@ -371,10 +421,10 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {  // even and odd tiles
                     const int row = 8 * g + 4 * ((t ^ g) & 1) + (frow & 3);
-                    b_ko[ks][t] = (uint32_t)(BM * ROWB + (wn * WTN + row) * ROWB + (((4 * ks + g4) ^ kc_swz(BTag{}, row)) << 4));
+                    b_ko[ks][t] = (uint32_t)(Cfg::ASTAGE + (wn * WTN + row) * ROWB + (((4 * ks + g4) ^ kc_swz(BTag{}, row)) << 4));
                 }
             } else {
-                b_ko[ks][0] = (uint32_t)(BM * ROWB + (wn * WTN + frow) * ROWB + (((4 * ks + g4) ^ kc_swz(BTag{}, frow)) << 4));
+                b_ko[ks][0] = (uint32_t)(Cfg::ASTAGE + (wn * WTN + frow) * ROWB + (((4 * ks + g4) ^ kc_swz(BTag{}, frow)) << 4));
             }
         }
         if constexpr (ARC) {
@@ -389,15 +439,16 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             for (int u = 0; u < TN; ++u) {
                 const int col = WEIGHT ? (u >> 2) * 64 + ((u >> 1) & 1) * 32 + 8 * q + 4 * ((u ^ q) & 1) : u * 16 + 4 * q;
                 const int chunk = (wn * WTN + col) >> 3;
-                b_rc[u] = BM * ROWB + (8 * g4 + jj) * (BN * 2) + ((chunk ^ rc_swz(BTag{}, 8 * g4 + jj, BN / 8)) << 4) + (col & 4) * 2;
+                b_rc[u] = Cfg::ASTAGE + (8 * g4 + jj) * (BN * 2) + ((chunk ^ rc_swz(BTag{}, 8 * g4 + jj, BN / 8)) << 4) + (col & 4) * 2;
             }
         }
     }
+    const char* panel = smem;  // ANF4: the running k-tile of A
     // fragment u (those of A first) of k32 step ks of the tile at `stage`
     auto read_frag = [&](int ks, int u, const char* stage) -> bf16x8 {
         if (u < TM) {
             if constexpr (ARC) return read_tr(stage + a_rc[u] + 32 * ks * (BM * 2), BM * 2);
-            else return *reinterpret_cast<const bf16x8*>(stage + a_ko[ks] + u * 16 * ROWB);
+            else return *reinterpret_cast<const bf16x8*>((ANF4 ? panel : stage) + a_ko[ks] + u * 16 * ROWB);
         } else {
             const int j = u - TM;
             if constexpr (BRC) return read_tr(stage + b_rc[j] + 32 * ks * (BN * 2), BN * 2);
@@ -464,24 +515,34 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         using RQ = std::integral_constant<int, RPQ>;
         using NOLD = std::integral_constant<int, -1>;
         if (kt_begin < kt_end) {
+            if constexpr (ANF4) {
+                panel_load();
+                codes_setup();
+#pragma unroll
+                for (int i = 0; i < NCC; ++i) direct_load(offA[i], hotA, lds0 + (uint32_t)(Cfg::PANEL + i * 4096 + wave_s * 1024));
+            }
             hot_setup(kt_begin);
 #pragma unroll
-            for (int n = 0; n < Cfg::NCH; ++n) hot_load(n, smem);
+            for (int n = 0; n < Cfg::NCH; ++n) hot_load(n, ring);
             hot_advance(kt_begin + 1);  // (a range of one tile loads it twice; nobody reads the second copy)
 #pragma unroll
-            for (int n = 0; n < Cfg::NCH; ++n) hot_load(n, smem + STAGE);
+            for (int n = 0; n < Cfg::NCH; ++n) hot_load(n, ring + STAGE);
+            if constexpr (ANF4) {
+                __syncthreads();  // the table of levels
+                panel_expand();
+            }
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(Cfg::NCH) : "memory");
             __syncthreads();
             if (is_tail(kt_begin)) {
-                cut_tile(kt_begin, smem);
+                cut_tile(kt_begin, ring);
                 __syncthreads();
             }
 #pragma unroll
-            for (int u = 0; u < NU; ++u) rd(0, 0, u, smem);
+            for (int u = 0; u < NU; ++u) rd(0, 0, u, ring);
         }
         for (int kt = kt_begin; kt < kt_end; ++kt) {
-            char* cur = smem + ((kt - kt_begin) & 1) * STAGE;
-            char* nxt = smem + (((kt - kt_begin) & 1) ^ 1) * STAGE;
+            char* cur = ring + ((kt - kt_begin) & 1) * STAGE;
+            char* nxt = ring + (((kt - kt_begin) & 1) ^ 1) * STAGE;
             slots(I0{}, I0{}, SH{}, RQ{}, I1{}, NOLD{}, cur, cur);
             __syncthreads();  // X: nobody reads `cur` any more
             hot_advance(kt + 2);
@@ -495,6 +556,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 __syncthreads();
             }
             // harmless stale reads after the last tile
+            if constexpr (ANF4) panel += BM * ROWB;
             slots(I1{}, SH{}, SE{}, RQ{}, I0{}, SE{}, nxt, cur);
         }
     } else {
@@ -567,8 +629,8 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // ------------------------------------------------------------------ epilogues
     // where the old codes are: the stage of the k-tile after the last one; the stage after that one is free
     const int nkt = kt_end - kt_begin;
-    char* const cbuf = smem + (CODES ? nkt % NS : 0) * STAGE;
-    char* const ebase = smem + (CODES ? (nkt + 1) % NS : ENCODES ? 1 : 0) * STAGE;
+    char* const cbuf = ANF4 ? smem + Cfg::PANEL : smem + (CODES ? nkt % NS : 0) * STAGE;
+    char* const ebase = ANF4 ? smem : smem + (CODES ? (nkt + 1) % NS : ENCODES ? 1 : 0) * STAGE;
     // byte offset of the dword of codes of this lane in row 16 i + frow of its wave, columns 32 c + 8 g4 .. +7 of the tile
     auto code_at = [&](int i, int c) {
         return cbuf + (wm * WTM + i * 16 + frow) * (BN / 2) + ((c ^ code_swz(frow)) << 4) + 4 * g4;
@@ -820,36 +882,36 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 }
 
 // Work-groups are dealt to the 8 XCDs round-robin by the hardware; each XCD walks a contiguous range of tiles.
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false>
-__global__ __launch_bounds__(256, (NtCfg<BM, BN, NS>::PER_CU)) void nt_gemm_kernel(const GemmParams p) {
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
+__global__ __launch_bounds__(256, (NtCfg<BM, BN, NS, ANF4>::PER_CU)) void nt_gemm_kernel(const GemmParams p) {
     const int per_xcd = gridDim.x >> 3;
-    nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, NOTAIL>(p, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), blockIdx.y);
+    nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>(p, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), blockIdx.y);
 }
 
 // the kernel's LDS size has to be raised above the default once per process (first launch, or loqt_prepare)
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
 hipError_t ensure_attr() {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, NtCfg<BM, BN, NS>::SMEM);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, NtCfg<BM, BN, NS, ANF4>::SMEM);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     return hipSuccess;
 }
 
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
 hipError_t launch_nt(const GemmParams& p, hipStream_t st) {
     if constexpr (BM == 256 && (EPI == EPI_BF16 || (EPI == EPI_F32_SPLITK && BN == 128)) && !NOTAIL) {
         // 256-row tiles of the plain products have a variant for contractions that are whole k-tiles
         if (p.A[0].K % BK == 0 && p.A[1].K % BK == 0) return launch_nt<BM, BN, EPI, ARC, BRC, NS, true>(p, st);
     }
-    hipError_t e0 = ensure_attr<BM, BN, EPI, ARC, BRC, NS, NOTAIL>();
+    hipError_t e0 = ensure_attr<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>();
     if (e0 != hipSuccess) return e0;
     const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN + (p.Nx + BN - 1) / BN);
     dim3 grid((tiles + 7) / 8 * 8, EPI == EPI_F32_SPLITK ? p.splits : 1);
-    hipLaunchKernelGGL((nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL>), grid, dim3(256), (NtCfg<BM, BN, NS>::SMEM), st, p);
+    hipLaunchKernelGGL((nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>), grid, dim3(256), (NtCfg<BM, BN, NS, ANF4>::SMEM), st, p);
     return hipGetLastError();
 }
 
