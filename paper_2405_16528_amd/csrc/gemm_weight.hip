@@ -154,13 +154,22 @@ int weight_tile(int epi, const GemmParams& p) {
     //   fold                 0.86 to 1.02     1.10 to 1.24     0.86 to 1.02    0.99 to 1.16
     //   merge                0.86 to 0.96     1.12 to 1.26     0.86 to 0.97    0.91 to 1.05
     //   compensation step    0.81 to 0.92     1.04 to 1.19     0.87 to 0.96    0.94 to 1.08
-    //   unquantised merge    0.83 to 1.03     1.09 to 1.22     0.79 to 0.94    0.80 to 0.96
+    //   unquantised merge    0.96 to 1.06     1.01 to 1.07     0.94 to 1.01    1.02 to 1.13
     // (With three stages and two to a unit they took 1.03 to 1.28 of the time of two stages and three.)
     const int64_t t = tiles(128, 128);
-    if (epi != EPI_FOLD_F32 && (t <= 384 || (t > 512 && t <= (epi == EPI_ACC_BF16 ? 768 : 640)))) return NT_64x128;
-    // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its epilogue
-    // behind, which two resident 128x128 work-groups have: the fold's is short enough, the others' are not.
-    if ((epi == EPI_FOLD || epi == EPI_ACC_BF16) && tiles(256, 256) >= 224) return NT_256x256;
+    if (epi != EPI_FOLD_F32 && (t <= 384 || (t > 512 && t <= 640))) return NT_64x128;
+    // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its prologue and
+    // epilogue behind, which two resident 128x128 work-groups have.  So it is ahead only where a product of some length fills
+    // the chip in one round, with the epilogues that are short.  Time of the launch, us, 256x256 / 128x128, by tiles of 256x256:
+    //                              fold, rank 96    300            512            1024           unquantised merge, rank 96 and 768
+    //   192  (4096 x 3072)         20.4 / 17.9      24.9 / 22.6    26.3 / 23.6    35.3 / 33.5    17.9 / 15.8   28.9 / 27.2
+    //   220  (5632 x 2560)         20.6 / 20.8      24.8 / 26.4    26.6 / 27.6    36.4 / 40.1    18.7 / 18.0   30.8 / 33.3
+    //   256  (4096 x 4096)         21.3 / 20.8      25.5 / 26.3    27.7 / 28.6    37.6 / 41.3    21.0 / 19.9   34.6 / 35.5
+    //   384  (8192 x 3072)         36.0 / 28.4      44.2 / 36.0    48.3 / 39.4    67.7 / 58.9    33.4 / 27.3   56.2 / 48.9
+    //   688  (11008 x 4096)        52.7 / 45.9      66.2 / 60.2    72.5 / 66.1    102.8 / 102.2  50.5 / 45.1   86.9 / 87.0
+    //   1080 (13824 x 5120)        83.1 / 66.6      104.5 / 88.8   116.3 / 102.3  167.8 / 159.4  78.7 / 65.0   138.6 / 133.2
+    const int64_t t256 = tiles(256, 256);
+    if (t256 >= 216 && t256 <= 256 && ((epi == EPI_FOLD && p.A[0].K > 128) || (epi == EPI_ACC_BF16 && p.A[0].K > 512))) return NT_256x256;
     return NT_128x128;
 }
 
