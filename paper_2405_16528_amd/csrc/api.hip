@@ -477,6 +477,18 @@ loqt_status merge_fused(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absma
     return LOQT_OK;
 }
 
+// A merge that reads P as its codes reads them while others of its work-groups store: none of what is written may be P's.
+bool outputs_apart(const uint8_t* codes_out, const float* absmax_out, const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq) {
+    auto apart = [](const void* a, size_t na, const void* b, size_t nb) {
+        const uintptr_t ua = (uintptr_t)a, ub = (uintptr_t)b;
+        return ua + na <= ub || ub + nb <= ua;
+    };
+    const size_t cw = (size_t)Wq->rows * (Wq->ld / 2), aw = (size_t)Wq->rows * (Wq->ld / 64) * 4;
+    const size_t cp = (size_t)Pq->rows * (Pq->ld / 2), ap = (size_t)Pq->rows * (Pq->ld / 64) * 4;
+    return apart(codes_out, cw, Pq->codes, cp) && apart(codes_out, cw, Pq->absmax, ap) && apart(absmax_out, aw, Pq->codes, cp) &&
+           apart(absmax_out, aw, Pq->absmax, ap);
+}
+
 loqt_status merge_prepass(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absmax_out,
                           const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s, void* ws,
                           hipStream_t st) {
@@ -484,7 +496,7 @@ loqt_status merge_prepass(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* abs
     const MergeWs L(out, in, r);
     uint16_t* Pb = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + L.Pb);
     const int64_t ldr = (int64_t)round_up(r, 8);
-    const bool from_codes = g_path == LOQT_PATH_AUTO && weight_takes_codes(out, Wq->ld, r);
+    const bool from_codes = g_path == LOQT_PATH_AUTO && weight_takes_codes(out, Wq->ld, r) && outputs_apart(codes_out, absmax_out, Wq, Pq);
     if (!from_codes)
         LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ldr, st, SLOT_PREPASS));
     GemmParams p;
@@ -1006,6 +1018,8 @@ loqt_status loqt_merge_requant_batched(int n_layers, const loqt_merge_desc* desc
         DequantGroupItem deq[MERGE_GROUP_MAX];
         int n = 0;
         size_t used = 0;
+        int64_t most_r = 0, tiles = 0;
+        bool apart = true;
         while (i + n < n_layers && n < MERGE_GROUP_MAX && prepass(descs[i + n])) {
             const loqt_merge_desc& d = descs[i + n];
             const int64_t out = d.Wq.rows, in = d.Wq.cols, r = d.Pq.cols;
@@ -1014,13 +1028,23 @@ loqt_status loqt_merge_requant_batched(int n_layers, const loqt_merge_desc* desc
             uint16_t* Pb = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + used);
             const int64_t ldr = (int64_t)round_up(r, 8);
             deq[n] = DequantGroupItem{d.Pq.codes, d.Pq.absmax, Pb, out, d.Pq.ld, ldr, (int)r};
-            layers[n] = MergeGroupLayer{Pb, d.B, ldr, d.ld_B, d.Wq.codes, d.Wq.absmax, d.codes_out, d.absmax_out,
+            layers[n] = MergeGroupLayer{Pb, nullptr, d.B, ldr, d.ld_B, d.Wq.codes, d.Wq.absmax, d.codes_out, d.absmax_out,
                                         d.Wq.ld, (int)out, (int)in, (int)r, d.s};
             used += need;
+            most_r = std::max(most_r, r);
+            tiles += codes_tiles(out, d.Wq.ld);
             ++n;
         }
-        LOQT_HIP(launch_dequantize_grouped(deq, n, st, SLOT_PREPASS));
-        LOQT_HIP(launch_merge_grouped(SLOT_MERGE, true, layers, n, st));
+        for (int a = 0; a < n; ++a)
+            for (int b = 0; b < n; ++b)
+                apart = apart && outputs_apart(descs[i + a].codes_out, descs[i + a].absmax_out, &descs[i + a].Wq, &descs[i + b].Pq);
+        if (apart && g_path == LOQT_PATH_AUTO && group_takes_codes(most_r, tiles)) {
+            for (int k = 0; k < n; ++k)
+                layers[k].A = deq[k].codes, layers[k].A_absmax = deq[k].absmax, layers[k].lda = deq[k].ld_q;
+        } else {
+            LOQT_HIP(launch_dequantize_grouped(deq, n, st, SLOT_PREPASS));
+        }
+        LOQT_HIP(launch_merge_grouped(SLOT_MERGE, layers, n, st));
         i += n;
     }
     return LOQT_OK;

@@ -410,10 +410,14 @@ hipError_t launch_dequantize_grouped(const DequantGroupItem* items, int n, hipSt
     DequantGroupParams g;
     memset(&g, 0, sizeof(g));
     g.n = n;
+    int64_t groups = 0;
+    for (int i = 0; i < n; ++i) groups += items[i].rows * ((items[i].cols + 7) >> 3);
+    // about four groups of 8 per lane; few of them are over sooner side by side
+    const int per_lane = groups <= 256 * 1024 ? 1 : 4;
     int total = 0;
     for (int i = 0; i < n; ++i) {
         g.it[i] = items[i];
-        total += grid_for(items[i].rows * ((items[i].cols + 7) >> 3), 256 * 4);  // about four groups of 8 per lane
+        total += grid_for(items[i].rows * ((items[i].cols + 7) >> 3), 256 * per_lane);
         g.block_end[i] = total;
     }
     hipLaunchKernelGGL(nf4_dequantize_grouped_kernel, dim3((unsigned)total), dim3(256), 0, st, g);

@@ -16,8 +16,9 @@ namespace {
 // bounds a group at MERGE_GROUP_MAX layers.  per_xcd_end: running total of the tiles each XCD has walked when it
 // is through with this layer.
 struct MergeGroupItem {
-    const void* A;      // left operand of s * A B: deq(P) in bf16, out x r, K contiguous
-    const void* B;      // right operand: r x in stored K x rows (BRC) or in x r stored rows x K
+    const void* A;          // left operand of s * A B: P, out x r, K contiguous, in bf16 or
+    const float* A_absmax;  // as its codes
+    const void* B;          // right operand: r x in stored K x rows
     int64_t lda, ldb;
     const uint8_t* w_codes;
     const float* w_absmax;
@@ -34,18 +35,18 @@ struct MergeGroupParams {
 };
 static_assert(sizeof(MergeGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
 
-constexpr int GROUP_BM = 128, GROUP_BN = 128;
-using GroupCfg = NtCfg<GROUP_BM, GROUP_BN, 2>;
+template <int BM, bool ANF4>
+using GroupCfg = NtCfg<BM, 128, 2, ANF4>;
 
-template <bool BRC>
-__global__ __launch_bounds__(256, (GroupCfg::PER_CU)) void nt_merge_grouped_kernel(const MergeGroupParams g) {
+template <int BM, bool ANF4>
+__global__ __launch_bounds__(256, (GroupCfg<BM, ANF4>::PER_CU)) void nt_merge_grouped_kernel(const MergeGroupParams g) {
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     int li = 0;
     while (li + 1 < g.n && j >= g.it[li].per_xcd_end) ++li;  // wave-uniform
     const int start = li ? g.it[li - 1].per_xcd_end : 0;
     const MergeGroupItem& it = g.it[li];
     GemmParams p;
-    p.A[0].ptr = it.A, p.A[0].absmax = nullptr, p.A[0].ld = it.lda, p.A[0].rows = it.M, p.A[0].K = it.K;
+    p.A[0].ptr = it.A, p.A[0].absmax = it.A_absmax, p.A[0].ld = it.lda, p.A[0].rows = it.M, p.A[0].K = it.K;
     p.B[0].ptr = it.B, p.B[0].absmax = nullptr, p.B[0].ld = it.ldb, p.B[0].rows = it.w_cols, p.B[0].K = it.K;
     p.A[1].ptr = nullptr, p.A[1].absmax = nullptr, p.A[1].ld = 0, p.A[1].rows = 0, p.A[1].K = 0;
     p.B[1] = p.A[1];
@@ -57,19 +58,29 @@ __global__ __launch_bounds__(256, (GroupCfg::PER_CU)) void nt_merge_grouped_kern
     p.w_ld = it.w_ld, p.w_cols = it.w_cols;
     p.w_bf16 = nullptr, p.w_bf16_ld = 0, p.w_f32 = nullptr, p.w_f32_ld = 0, p.e_out = nullptr, p.e_ld = 0;
     const int per_xcd = it.per_xcd_end - start;
-    nt_gemm_tile<GROUP_BM, GROUP_BN, EPI_MERGE, false, BRC>(p, xcd * per_xcd + (j - start), 0);
+    nt_gemm_tile<BM, 128, EPI_MERGE, false, true, 2, false, ANF4>(p, xcd * per_xcd + (j - start), 0);
 }
 
-template <bool BRC>
-hipError_t ensure_attr_grouped() {
+// g: null only raises the kernel's LDS size
+template <int BM, bool ANF4>
+hipError_t launch_grouped(MergeGroupParams* g, hipStream_t st) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_merge_grouped_kernel<BRC>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, GroupCfg::SMEM);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_merge_grouped_kernel<BM, ANF4>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (GroupCfg<BM, ANF4>::SMEM));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    return hipSuccess;
+    if (!g) return hipSuccess;
+    int per_xcd_total = 0;
+    for (int i = 0; i < g->n; ++i) {
+        MergeGroupItem& it = g->it[i];
+        const int tiles = ((it.M + BM - 1) / BM) * ((it.N + 127) / 128);
+        per_xcd_total += (tiles + 7) / 8;
+        it.per_xcd_end = per_xcd_total;
+    }
+    hipLaunchKernelGGL((nt_merge_grouped_kernel<BM, ANF4>), dim3((unsigned)per_xcd_total * 8u), dim3(256), (GroupCfg<BM, ANF4>::SMEM), st, *g);
+    return hipGetLastError();
 }
 
 template <int EPI, bool BRC>
@@ -104,30 +115,33 @@ hipError_t prepare_sized() {
 
 }  // namespace
 
-hipError_t launch_merge_grouped(int slot, bool b_rc, const MergeGroupLayer* layers, int n, hipStream_t st) {
+hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, hipStream_t st) {
     if (n < 1 || n > MERGE_GROUP_MAX) return hipErrorInvalidValue;
     TimedLaunch tl(slot, st);
     MergeGroupParams g;
     memset(&g, 0, sizeof(g));
     g.n = n;
-    int per_xcd_total = 0;
+    int64_t tiles = 0;  // of 128x128
     for (int i = 0; i < n; ++i) {
         const MergeGroupLayer& l = layers[i];
         MergeGroupItem& it = g.it[i];
-        it.A = l.A, it.lda = l.lda, it.B = l.B, it.ldb = l.ldb;
+        it.A = l.A, it.A_absmax = l.A_absmax, it.lda = l.lda, it.B = l.B, it.ldb = l.ldb;
         it.w_codes = l.w_codes, it.w_absmax = l.w_absmax, it.out_codes = l.out_codes, it.out_absmax = l.out_absmax;
         it.w_ld = l.w_ld, it.M = l.out, it.N = (int)l.w_ld, it.K = l.r, it.w_cols = l.in, it.alpha = l.s;
-        const int tiles = ((l.out + GROUP_BM - 1) / GROUP_BM) * (int)((l.w_ld + GROUP_BN - 1) / GROUP_BN);
-        per_xcd_total += (tiles + 7) / 8;
-        it.per_xcd_end = per_xcd_total;
+        tiles += ((l.out + 127) / 128) * ((l.w_ld + 127) / 128);
+        if (l.A_absmax && (l.r > A_CODES_TILES * BK || !layers[0].A_absmax)) return hipErrorInvalidValue;
+        if (!l.A_absmax && layers[0].A_absmax) return hipErrorInvalidValue;
     }
-    constexpr int smem = GroupCfg::SMEM;
-    const dim3 grid((unsigned)per_xcd_total * 8u);
-    hipError_t e0 = b_rc ? ensure_attr_grouped<true>() : ensure_attr_grouped<false>();
-    if (e0 != hipSuccess) return e0;
-    if (b_rc) hipLaunchKernelGGL(nt_merge_grouped_kernel<true>, grid, dim3(256), smem, st, g);
-    else hipLaunchKernelGGL(nt_merge_grouped_kernel<false>, grid, dim3(256), smem, st, g);
-    return hipGetLastError();
+    if (layers[0].A_absmax) return launch_grouped<64, true>(&g, st);
+    // 64x128 where they take no more rounds, as in weight_tile.  The call for a block of seven weights, us, 128x128 / 64x128 /
+    // 64x128 from the codes, by tiles of 128x128 (and of 64x128):
+    //         196 (392)           280 (528)             432 (864)             574 (1102)            784 (1552)            1210 (2420)
+    //   rank
+    //   64    12.8 / 11.7 / 8.4   13.6 / 12.3 / 11.0    14.6 / 15.3 / 12.9    19.0 / 17.1 / 16.4    21.4 / 20.5 / 21.2    26.4 / 26.2 / 28.3
+    //   128   13.9 / 12.8 / 9.4   15.5 / 13.8 / 12.5    16.0 / 16.8 / 14.9    20.5 / 18.6 / 18.7    23.0 / 22.2 / 23.9    28.5 / 28.5 / 32.0
+    //   256   15.7 / 14.5 / 11.1  17.4 / 15.2 / 15.6    17.9 / 19.1 / 18.3    24.8 / 22.7 / 22.9    28.0 / 27.2 / 30.0    35.1 / 35.1 / 40.3
+    //   384   16.6 / 15.2         21.1 / 18.3           21.8 / 23.3           28.0 / 25.9           31.8 / 31.5           40.1 / 40.8
+    return g_nt_tile_override == 0 && (tiles <= 384 || (tiles > 512 && tiles <= 800)) ? launch_grouped<64, false>(&g, st) : launch_grouped<128, false>(&g, st);
 }
 
 hipError_t prepare_weight_kernels() {
@@ -141,8 +155,9 @@ hipError_t prepare_weight_kernels() {
     if ((e = prepare_sized<EPI_FOLD_F32, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<64, 128, EPI_MERGE, false, true, 2, false, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<64, 128, EPI_FOLD, false, true, 2, false, true>()) != hipSuccess) return e;
-    if ((e = ensure_attr_grouped<true>()) != hipSuccess) return e;
-    return ensure_attr_grouped<false>();
+    if ((e = launch_grouped<64, true>(nullptr, nullptr)) != hipSuccess) return e;
+    if ((e = launch_grouped<64, false>(nullptr, nullptr)) != hipSuccess) return e;
+    return launch_grouped<128, false>(nullptr, nullptr);
 }
 
 int weight_tile(int epi, const GemmParams& p) {
@@ -184,7 +199,12 @@ int weight_tile(int epi, const GemmParams& p) {
 //   768 (2048 x 3072)  10.2 -> 10.8, 12.8 -> 15.3         42.0 -> 41.2, 44.2 -> 45.4
 //   2048 (4096 x 4096) 19.2 -> 19.3, 25.1 -> 25.0         74.5 -> 74.1, 79.2 -> 78.3
 bool weight_takes_codes(int64_t out, int64_t in, int64_t r) {
-    return g_nt_tile_override == 0 && r <= A_CODES_TILES * BK && ((out + 63) / 64) * ((in + 127) / 128) <= 512;
+    return !g_nt_tile_override && r <= A_CODES_TILES * BK && codes_tiles(out, in) <= 512;
+}
+int64_t codes_tiles(int64_t out, int64_t in) { return ((out + 63) / 64) * ((in + 127) / 128); }
+// (A group saves a longer launch; figures at launch_merge_grouped.)
+bool group_takes_codes(int64_t r, int64_t tiles) {
+    return !g_nt_tile_override && ((r <= A_CODES_TILES * BK && tiles <= 512) || (r <= 128 && tiles <= 900));
 }
 
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st) {

@@ -304,6 +304,9 @@ hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStr
 int weight_tile(int epi, const GemmParams& p);
 // whether the fold and the merge of a weight out x in read P (rank r) as it is stored, A[0] with absmax
 bool weight_takes_codes(int64_t out, int64_t in, int64_t r);
+// ... and those of a group: the largest rank, the sum of codes_tiles
+bool group_takes_codes(int64_t r, int64_t tiles);
+int64_t codes_tiles(int64_t out, int64_t in);
 // tile and slices of a bf16-output product (A stored rows x K) below the size of 256x256 rounds, as far as its scratch goes;
 // tile 0: larger, or with extra columns, or a tile is forced.  Its parameters when it runs in slices.  Tile of a gradient.
 NtPlan product_plan(const GemmParams& p);
@@ -321,6 +324,7 @@ hipError_t prepare_pair_kernels();
 constexpr int MERGE_GROUP_MAX = 24;
 struct MergeGroupLayer {
     const void* A;
+    const float* A_absmax;  // A is the codes of P (all layers of a group or none), else null
     const void* B;
     int64_t lda, ldb;
     const uint8_t* w_codes;
@@ -343,7 +347,7 @@ hipError_t launch_dequantize_grouped(const DequantGroupItem* items, int n, hipSt
 // copies of two matrices and U = s x B^T (bf16, both operands rows x K), in one launch where U runs on small tiles, timed as U
 // then, else two
 hipError_t launch_u_copies(int slot, const GemmParams& u, const DequantGroupItem* items, hipStream_t st);
-hipError_t launch_merge_grouped(int slot, bool b_rc, const MergeGroupLayer* layers, int n, hipStream_t st);
+hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, hipStream_t st);
 // raise the LDS size of every kernel configuration of gemm_nt.hip / gemm.hip above the default (otherwise done at the
 // first launch of each), so that a first call can be recorded into a HIP graph
 hipError_t prepare_nt_kernels();

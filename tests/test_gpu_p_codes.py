@@ -45,3 +45,50 @@ def test_same_bits_as_expanded(out, inp, r, codes):
         got.append((w_eff, y, merged[0].codes, merged[0].absmax))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("layers,codes", [
+    ([(65, 136, 63), (130, 72, 65), (300, 264, 256), (1, 8, 1)], True),
+    ([(1000, 333, 128), (63, 1030, 40), (2048, 2048, 64)], True),      # up to 900 tiles with ranks of 128 at most
+    ([(2048, 2048, 64), (64, 128, 129)], False),                       # 64x128, 513 tiles
+    ([(64, 128, 300), (190, 520, 255)], False),
+    ([(3000, 2048, 200), (512, 1030, 64)], False),                     # between: 128x128
+    ([(4096, 4096, 64), (64, 128, 64)], False),
+])
+def test_group_same_bits_as_one_by_one(layers, codes):
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = np.random.default_rng(len(layers))
+    sets = []
+    for out, inp, r in layers:
+        Wq, Pq = (G.nf4_dev(*O.nf4_quantize((g.standard_normal(n) * 0.02).astype(np.float32))) for n in ((out, inp), (out, r)))
+        B = (torch.from_numpy(g.standard_normal((r, G.rup(inp, 8)))) * 0.02).bfloat16().cuda()[:, :inp]
+        sets.append((Wq, L.NF4Tensor.empty(out, inp), Pq, B, 0.5))
+    descs = L.make_merge_descs(sets)
+    n = _launches(L, lambda: L.loqt_merge_requant_batched(descs, torch.empty(L.merge_descs_workspace_bytes(descs), dtype=torch.uint8, device="cuda")))
+    assert (n["prepass"], n["merge_requant"]) == (0 if codes else 1, 1)
+    L.set_path(L.PATH_FOLDED)
+    try:
+        for Wq, got, Pq, B, s in sets:
+            ref = L.loqt_merge_requant(Wq, Pq, B, s, out=L.NF4Tensor.empty(Wq.rows, Wq.cols))
+            assert torch.equal(ref.codes, got.codes) and torch.equal(ref.absmax, got.absmax)
+    finally:
+        L.set_path(L.PATH_AUTO)
+
+
+def test_output_over_the_codes_of_P():
+    """A merge that writes where P is reads all of P first."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = np.random.default_rng(3)
+    out, inp, r = 512, 512, 256
+    Wq, Pq = (G.nf4_dev(*O.nf4_quantize((g.standard_normal(n) * 0.02).astype(np.float32))) for n in ((out, inp), (out, r)))
+    B = (torch.from_numpy(g.standard_normal((r, inp))) * 0.02).bfloat16().cuda()
+    ref = L.loqt_merge_requant(Wq, Pq, B, 0.5, out=L.NF4Tensor.empty(out, inp))
+    got = L.NF4Tensor.empty(out, inp)
+    over = got.codes.view(-1)[:Pq.codes.numel()].view(Pq.codes.shape)
+    over.copy_(Pq.codes)
+    Pq.codes = over
+    n = _launches(L, lambda: L.loqt_merge_requant(Wq, Pq, B, 0.5, out=got))
+    assert n["prepass"] == 1
+    assert torch.equal(ref.codes, got.codes) and torch.equal(ref.absmax, got.absmax)
