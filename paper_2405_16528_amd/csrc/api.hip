@@ -401,7 +401,7 @@ hipError_t expand_weight(const loqt_nf4_mat* Wq, uint16_t* Wb, int64_t ldw, cons
     return u ? launch_u_copies(SLOT_GEMM_U, *u, both, st) : launch_dequantize_grouped(both, 2, st, SLOT_PREPASS);
 }
 
-// U = s x B^T for a handful of tokens.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
+// U = s x B^T for a handful of tokens, where it has a launch of its own.  Its r rows make few work-groups (64 at rank 1024), each reading all of x, so a
 // long contraction goes out in slices instead, which find room where a copy of the weight would be.  Both forms timed in whole
 // calls of both layers (1024 and 4096 rows, rank 64 to 1024, contractions of 1024 to 13824): slices are ahead from 5500 (1
 // token), 4600 (8) and 3500 (16) on, with the second token tile from 2800 (17) and 2050 (32).  At 4096 and 16 tokens they save
@@ -662,7 +662,25 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
         p.alpha = s;
         p.C = U;
         p.ldc = ld_u;
-        LOQT_HIP(launch_u_few(p, reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + L.Wb), ws_bytes - L.Wb, st));
+        float* const room = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + L.Wb);
+        if (few_layer_fits((int)T, (int)out, (int)r, ws_bytes - L.Wb)) {
+            GemmParams w, q;
+            memset(&w, 0, sizeof(w));
+            w.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
+            w.B[0] = nf4_operand(Wq, (int)out, (int)in);
+            w.M = (int)T;
+            w.N = (int)out;
+            w.split_ws = room;
+            q = w;
+            q.A[0] = bf16_operand(U, ld_u, (int)T, (int)r);
+            q.B[0] = nf4_operand(Pq, (int)out, (int)r);
+            q.alpha = 1.0f;
+            q.C = y;
+            q.ldc = ld_y;
+            LOQT_HIP(launch_few_layer(p, w, q, st));
+            return LOQT_OK;
+        }
+        LOQT_HIP(launch_u_few(p, room, ws_bytes - L.Wb, st));
         memset(&p, 0, sizeof(p));  // y = x deq(W)^T + U deq(P)^T
         p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
         p.B[0] = nf4_operand(Wq, (int)out, (int)in);

@@ -20,8 +20,10 @@
 //   16 tokens    RT 1          RT 2          RT 3          RT 4            32 tokens   RT 1          RT 2          RT 3          RT 4
 //   4096 rows     9.4 / 10.1   11.2 / 12.2   13.4 / 15.2   15.8 / 18.4                 12.7 / 14.1   14.3 / 16.1   16.7 / 18.9   24.6 / 27.3
 //   11008 rows   19.4 / 20.6   19.2 / 22.1   13.8 / 16.3   16.2 / 19.6                 36.6 / 37.3   28.8 / 31.1   18.2 / 20.4   26.7 / 30.2
-// The whole call at 16 x 11008 x 4096, rank 1024: 165 -> 24.0 (expanded weight -> this; 78 with the expanded weight on the
-// narrow tiles of gemm_nt.hip), 160 -> 56 on buffers that nothing has read before.  From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
+// U = s x B^T needs a launch before y, and the chip is nearly idle in it.  So where the work-groups of both fit on the chip at once U
+// goes out beside x deq(W)^T, which does not need it, whose sums wait in fp32 for the second launch, U deq(P)^T.
+// The whole call at 16 x 11008 x 4096, rank 1024: 165 -> 23.3 (expanded weight -> this; 78 with the expanded weight on the
+// narrow tiles of gemm_nt.hip), 160 -> 51 on buffers that nothing has read before.  From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
 #include <type_traits>
 
 #include "loqt_internal.h"
@@ -124,15 +126,20 @@ struct Weights<false> {
     __device__ __forceinline__ float scale(int) const { return 1.f; }
 };
 
-// C[T x N] (bf16) = alpha * sum over both segments of A_seg[T x K_seg] * B_seg[N x K_seg]^T; A bf16, B NF4 or bf16
-template <bool NF4, int NT, int RT>
-__global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p) {
-    __shared__ f32x4 red[NW / 2][RT * NT][64];
+// what becomes of the sums: bf16 result; fp32 sums for a later launch (four tokens of a row side by side: [T / 4][N]); bf16 result of
+// them and those of an earlier launch
+enum { TO_BF16, TO_SUMS, ADD_SUMS };
+
+// C[T x N] = alpha * sum over both segments of A_seg[T x K_seg] * B_seg[N x K_seg]^T; A bf16, B NF4 or bf16.  blk: which 16 RT rows of
+// B; lds: NW / 2 * RT * NT * 64 elements
+template <bool NF4, int NT, int RT, int OUT>
+__device__ __forceinline__ void few_tokens_rows(const GemmParams& p, const int blk, f32x4* const lds) {
+    f32x4(*const red)[RT * NT][64] = reinterpret_cast<f32x4(*)[RT * NT][64]>(lds);
     uint16_t* lut = reinterpret_cast<uint16_t*>(red);  // until the sums need the place
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const char* lutc = reinterpret_cast<const char*>(lut);
     const int q = lane >> 4, l16 = lane & 15;
-    const int n0 = blockIdx.x * (16 * RT);
+    const int n0 = blk * (16 * RT);
     int row[RT], tok[NT];
 #pragma unroll
     for (int i = 0; i < RT; ++i) row[i] = min(n0 + 16 * i + l16, p.N - 1);  // rows and tokens past the end: any valid one
@@ -143,6 +150,15 @@ __global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p)
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // the place in the result of this thread's four sums, in the end
+    const int um = 16 * ((tid >> 6) % NT) + 4 * q, un = n0 + 16 * ((tid >> 6) / NT) + l16;
+    static_assert(RT * NT <= NW, "one place per thread");
+    f32x4* const sums = reinterpret_cast<f32x4*>(p.split_ws) + (int64_t)(um >> 2) * p.N + un;
+    const bool mine = tid < RT * NT * 64 && un < p.N && um < p.M;
+    f32x4 before{0.f, 0.f, 0.f, 0.f};
+    if constexpr (OUT == ADD_SUMS)
+        if (mine) before = *sums;
 
     const Seg s0{reinterpret_cast<const uint16_t*>(p.A[0].ptr), p.A[0].ld, p.B[0].ptr, p.B[0].absmax, p.B[0].ld, p.A[0].K};
     const Seg s1{reinterpret_cast<const uint16_t*>(p.A[1].ptr), p.A[1].ld, p.B[1].ptr, p.B[1].absmax, p.B[1].ld, p.A[1].K};
@@ -241,23 +257,39 @@ __global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p)
     __syncthreads();
     if (wave < NW / 2) put(wave, true);
     __syncthreads();
-    for (int u = tid; u < RT * NT * 64; u += 64 * NW) {
-        const int it = u >> 6, ln = u & 63;
-        f32x4 s = red[0][it][ln];
+    if (!mine) return;
+    f32x4 s = red[0][tid >> 6][lane];
 #pragma unroll
-        for (int v = 1; v < NW / 2; ++v) s += red[v][it][ln];
-        const int m = 16 * (it % NT) + 4 * (ln >> 4), n = n0 + 16 * (it / NT) + (ln & 15);
-        if (n >= p.N) continue;
-        uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + (int64_t)m * p.ldc + n;
+    for (int v = 1; v < NW / 2; ++v) s += red[v][tid >> 6][lane];
+    if constexpr (NF4) s *= UNIT;
+    if constexpr (OUT == TO_SUMS) {
+        *sums = s;
+    } else {
+        if constexpr (OUT == ADD_SUMS) s += before;
+        uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + (int64_t)um * p.ldc + un;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (m + e < p.M) dst[e * p.ldc] = (uint16_t)(pack_bf16(p.alpha * (NF4 ? UNIT * s[e] : s[e]), 0.f) & 0xffffu);
+            if (um + e < p.M) dst[e * p.ldc] = (uint16_t)(pack_bf16(p.alpha * s[e], 0.f) & 0xffffu);
     }
 }
 
-template <bool NF4, int NT, int RT>
+template <bool NF4, int NT, int RT, int OUT>
+__global__ __launch_bounds__(64 * NW) void few_tokens_kernel(const GemmParams p) {
+    __shared__ f32x4 lds[NW / 2 * RT * NT * 64];
+    few_tokens_rows<NF4, NT, RT, OUT>(p, blockIdx.x, lds);
+}
+
+// U on the first u_blocks work-groups (16 RU rows each), the sums of x deq(W)^T on the others
+template <int NT, int RT, int RU>
+__global__ __launch_bounds__(64 * NW) void few_beside_kernel(const GemmParams u, const int u_blocks, const GemmParams w) {
+    __shared__ f32x4 lds[NW / 2 * (RT > RU ? RT : RU) * NT * 64];
+    if ((int)blockIdx.x < u_blocks) few_tokens_rows<false, NT, RU, TO_BF16>(u, blockIdx.x, lds);
+    else few_tokens_rows<true, NT, RT, TO_SUMS>(w, (int)blockIdx.x - u_blocks, lds);
+}
+
+template <bool NF4, int NT, int RT, int OUT>
 hipError_t launch_rows(const GemmParams& p, hipStream_t st) {
-    hipLaunchKernelGGL((few_tokens_kernel<NF4, NT, RT>), dim3((p.N + 16 * RT - 1) / (16 * RT)), dim3(64 * NW), 0, st, p);
+    hipLaunchKernelGGL((few_tokens_kernel<NF4, NT, RT, OUT>), dim3((p.N + 16 * RT - 1) / (16 * RT)), dim3(64 * NW), 0, st, p);
     return hipGetLastError();
 }
 
@@ -265,17 +297,67 @@ hipError_t launch_rows(const GemmParams& p, hipStream_t st) {
 // 48 and 64 whose rounds are cheaper by their rows (64 rows of two token tiles are 25 registers short and count for 80: 32
 // tokens on 13568 x 5376, us, 55 in two rounds of 48 and 45 in one of 64; on 18752 x 7872 61 and 82 in two rounds of either).
 // Rows in bf16 take 64 of the 128 registers at two chunks in flight; so 48 of them go with one chunk, and there is no form of 64.
-template <bool NF4, int NT>
+template <bool NF4, int NT, int OUT = TO_BF16>
 hipError_t launch_tokens(const GemmParams& p, hipStream_t st) {
     const int tiles = (p.N + 15) / 16;
-    if (tiles <= 256) return launch_rows<NF4, NT, 1>(p, st);
-    if (tiles <= 512) return launch_rows<NF4, NT, 2>(p, st);
+    if (tiles <= 256) return launch_rows<NF4, NT, 1, OUT>(p, st);
+    if (tiles <= 512) return launch_rows<NF4, NT, 2, OUT>(p, st);
     if constexpr (NF4)
-        if ((tiles + 1023) / 1024 * (NT == 1 ? 4 : 5) < (tiles + 767) / 768 * 3) return launch_rows<NF4, NT, 4>(p, st);
-    return launch_rows<NF4, NT, 3>(p, st);
+        if ((tiles + 1023) / 1024 * (NT == 1 ? 4 : 5) < (tiles + 767) / 768 * 3) return launch_rows<NF4, NT, 4, OUT>(p, st);
+    return launch_rows<NF4, NT, 3, OUT>(p, st);
+}
+
+// Rows per work-group of W and of U, 16 each: the fewest with which both together leave at most one work-group for a compute unit.
+// Whole calls, us, U first / U beside W, 1, 16 and 32 tokens:
+//   512 x 512, rank 128      14.0 / 10.1   14.1 / 10.2   13.8 / 9.8        11008 x 4096, rank 512    19.9 / 17.2   23.4 / 19.3   27.4 / 24.2
+//   4096 x 4096, rank 1024   13.7 / 12.9   19.3 / 15.0   23.7 / 19.7       13824 x 5120, rank 1024   26.0 / 22.7   29.4 / 25.5   (no room)
+//   5120 x 5120, rank 1024   18.6 / 13.9   22.9 / 17.0   28.3 / 22.8       4096 x 11008, rank 1024   23.3 / 19.6   30.1 / 26.6   39.6 / 36.7
+// U on 48 rows was no faster than U first (11008 x 4096, rank 1024: 20.1 / 21.0, 24.7 / 24.3, 29.3 / 29.5).  64 rows of W where 48 do
+// without U's work-groups pay from 9 tokens up (the same: 20.4 / 21.4 at one token, 22.2 / 22.5 at 8, 24.6 / 23.3 at 16).
+struct Beside {
+    int rt, ru;
+};
+Beside rows_beside(int T, int N, int r) {
+    const int tw = (N + 15) / 16, tu = (r + 15) / 16;
+    for (const Beside b : {Beside{1, 1}, Beside{2, 1}, Beside{3, 1}, Beside{3, 2}, Beside{4, 1}, Beside{4, 2}})
+        if ((b.rt < 4 || (T <= 16 && (tw > 768 || T > 8))) && (tw + b.rt - 1) / b.rt + (tu + b.ru - 1) / b.ru <= 256) return b;
+    return {0, 0};
+}
+
+template <int NT, int RT, int RU>
+hipError_t launch_beside(const GemmParams& u, const GemmParams& w, hipStream_t st) {
+    const int ub = (u.N + 16 * RU - 1) / (16 * RU);
+    hipLaunchKernelGGL((few_beside_kernel<NT, RT, RU>), dim3(ub + (w.N + 16 * RT - 1) / (16 * RT)), dim3(64 * NW), 0, st, u, ub, w);
+    return hipGetLastError();
+}
+
+template <int NT>
+hipError_t launch_beside(const GemmParams& u, const GemmParams& w, hipStream_t st) {
+    const Beside b = rows_beside(w.M, w.N, u.N);
+    if constexpr (NT == 1)
+        if (b.rt == 4) return b.ru == 1 ? launch_beside<NT, 4, 1>(u, w, st) : launch_beside<NT, 4, 2>(u, w, st);
+    if (b.rt == 1) return launch_beside<NT, 1, 1>(u, w, st);
+    if (b.rt == 2) return launch_beside<NT, 2, 1>(u, w, st);
+    if (b.rt == 3) return b.ru == 1 ? launch_beside<NT, 3, 1>(u, w, st) : launch_beside<NT, 3, 2>(u, w, st);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
+
+bool few_layer_fits(int T, int N, int r, size_t ws_bytes) {
+    return rows_beside(T, N, r).rt > 0 && ws_bytes >= (size_t)((T + 3) / 4) * N * 16;
+}
+
+hipError_t launch_few_layer(const GemmParams& u, const GemmParams& w, const GemmParams& q, hipStream_t st) {
+    if (w.M < 1 || w.M > FEW_TOKENS_MAX) return hipErrorInvalidValue;
+    {
+        TimedLaunch tl(SLOT_GEMM_U, st);
+        const hipError_t e = w.M <= 16 ? launch_beside<1>(u, w, st) : launch_beside<2>(u, w, st);
+        if (e != hipSuccess) return e;
+    }
+    TimedLaunch tl(SLOT_GEMM_Y, st);
+    return w.M <= 16 ? launch_tokens<true, 1, ADD_SUMS>(q, st) : launch_tokens<true, 2, ADD_SUMS>(q, st);
+}
 
 hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_t st) {
     if (p.M < 1 || p.M > FEW_TOKENS_MAX) return hipErrorInvalidValue;

@@ -281,6 +281,10 @@ constexpr int FEW_TOKENS_MAX = 32;
 // calls up to 1.55; up to 12288 rows 0.65 and 0.75).
 constexpr int FEW_ROWS_MAX_BF16 = 12288;
 hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_t st);
+// The same y in two launches, U = s x B^T (u) beside x deq(W)^T (w, its sums in fp32 to split_ws), then U deq(P)^T on top (q, from
+// split_ws to C); whether the sizes and the room for the sums allow it
+bool few_layer_fits(int T, int N, int r, size_t ws_bytes);
+hipError_t launch_few_layer(const GemmParams& u, const GemmParams& w, const GemmParams& q, hipStream_t st);
 
 // products of a few hundred tokens with NF4 weights (nf4_tile.hip) in p.splits fp32 slices at p.C (pitch p.ldc, a multiple
 // of 4): A bf16 M x K, B NF4 stored rows x K (both segments) or, b_rc, K x rows (the first; the second, if any, is bf16

@@ -186,3 +186,42 @@ def test_unquantised_forward_with_no_room_for_slices(T, inp):
         torch.cuda.synchronize()
         assert bool((ws[size:] == 0xFF).all())
         G.bf16_output_report(G.bf16_host(y), ref)
+
+
+@pytest.mark.parametrize("T,out,inp,r,beside", [
+    (4, 3600, 136, 40, True),      # rows of W and U per work-group (16 each): 1 and 1
+    (17, 3601, 264, 520, True),    # 2 and 1
+    (32, 8201, 200, 72, True),     # 3 and 1
+    (3, 11001, 136, 440, True),    # 3 and 2
+    (11, 11001, 136, 900, True),   # 4 and 1
+    (16, 13001, 136, 900, True),   # 4 and 2
+    (8, 11001, 136, 900, False),   # as many work-groups as the chip holds only with slower tiles
+    (18, 13001, 136, 40, False),
+    (31, 2000, 8, 8, False),       # no room for the sums
+])
+def test_u_beside_the_weight(T, out, inp, r, beside):
+    """U and the sums of x deq(W)^T in one launch, the rank-r term in the next: against the oracle, and nothing past the workspace."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    rng = synth.rng_for(T, "few beside", out, inp)
+    s = 0.5
+    Wq = O.nf4_quantize(synth.normal_f32(rng, (out, inp), 0.02))
+    Pq = O.nf4_quantize(synth.normal_f32(rng, (out, r), out ** -0.5))
+    B, x = synth.normal_bf16(rng, (r, inp), 2e-2), synth.normal_bf16(rng, (T, inp), 1.0)
+    size = L.loqt_workspace_bytes(L.OP_FWD, T, out, inp, r)
+    if inp == 8:  # U and the copies of W and P, the least that a call accepts
+        size = sum(G.rup(n * G.rup(k, 8) * 2, 256) for n, k in ((T, r), (out, inp), (out, r)))
+        assert size < 4 * T * out
+    ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    y = G.bf16_empty(T, out, fill=float("nan"))
+    L.timing_enable(True)
+    L.loqt_linear_fwd(_nan_padded(x, 8), _nan_scaled(Wq), _nan_scaled(Pq), _nan_padded(B, 16), s, y, ws[:size])
+    torch.cuda.synchronize()
+    L.timing_enable(False)
+    n = {k: v[0] for k, v in L.timing_read().items()}
+    assert (n["gemm_u"], n["gemm_y"]) == (1, 1)
+    assert bool((ws[size:] == 0xFF).all())
+    # the sums of the weight lie behind U
+    u_end = G.rup(T * G.rup(r, 8) * 2, 256)
+    assert bool((ws[u_end:u_end + 16 * out] != 0xFF).any()) == beside
+    G.bf16_output_report(G.bf16_host(y), O.loqt_linear_fwd(x, Wq, Pq, B, s))
