@@ -363,13 +363,21 @@ Operand no_operand() {
     return o;
 }
 
+// A fold or merge that reads P as its codes reads them while others of its work-groups store: none of the n bytes it writes may
+// be P's.
+bool apart_from(const void* p, size_t n, const loqt_nf4_mat* Pq) {
+    auto apart = [=](const void* q, size_t nq) { return (uintptr_t)p + n <= (uintptr_t)q || (uintptr_t)q + nq <= (uintptr_t)p; };
+    return apart(Pq->codes, (size_t)Pq->rows * (Pq->ld / 2)) && apart(Pq->absmax, (size_t)Pq->rows * (Pq->ld / 64) * 4);
+}
+
 // W_eff[out x in] (bf16, pitch ldw) = deq(Wq) + s * deq(Pq) B; Pb receives deq(Pq) in bf16
 // (dequant_p; else it is there).  z: a product that goes out with the fold, reading Pb too, or null
 loqt_status fold_weight(const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq, const loqt_bf16* B, int64_t ld_B, float s,
                         uint16_t* Pb, uint16_t* We, int64_t ldw, bool dequant_p, const GemmParams* z, hipStream_t st) {
     const int64_t out = Wq->rows, in = Wq->cols, r = Pq->cols;
     const int64_t ldr = (int64_t)round_up(r, 8);
-    const bool from_codes = dequant_p && g_path == LOQT_PATH_AUTO && weight_takes_codes(out, in, r);
+    const bool from_codes = dequant_p && g_path == LOQT_PATH_AUTO && weight_takes_codes(out, in, r) &&
+                            apart_from(We, (size_t)out * ldw * 2, Pq);
     if (dequant_p && !from_codes)
         LOQT_HIP(launch_dequantize(Pq->codes, Pq->absmax, out, r, Pq->ld, Pb, LOQT_BF16, ldr, st, SLOT_PREPASS));
     GemmParams p;
@@ -477,16 +485,8 @@ loqt_status merge_fused(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absma
     return LOQT_OK;
 }
 
-// A merge that reads P as its codes reads them while others of its work-groups store: none of what is written may be P's.
 bool outputs_apart(const uint8_t* codes_out, const float* absmax_out, const loqt_nf4_mat* Wq, const loqt_nf4_mat* Pq) {
-    auto apart = [](const void* a, size_t na, const void* b, size_t nb) {
-        const uintptr_t ua = (uintptr_t)a, ub = (uintptr_t)b;
-        return ua + na <= ub || ub + nb <= ua;
-    };
-    const size_t cw = (size_t)Wq->rows * (Wq->ld / 2), aw = (size_t)Wq->rows * (Wq->ld / 64) * 4;
-    const size_t cp = (size_t)Pq->rows * (Pq->ld / 2), ap = (size_t)Pq->rows * (Pq->ld / 64) * 4;
-    return apart(codes_out, cw, Pq->codes, cp) && apart(codes_out, cw, Pq->absmax, ap) && apart(absmax_out, aw, Pq->codes, cp) &&
-           apart(absmax_out, aw, Pq->absmax, ap);
+    return apart_from(codes_out, (size_t)Wq->rows * (Wq->ld / 2), Pq) && apart_from(absmax_out, (size_t)Wq->rows * (Wq->ld / 64) * 4, Pq);
 }
 
 loqt_status merge_prepass(const loqt_nf4_mat* Wq, uint8_t* codes_out, float* absmax_out,
