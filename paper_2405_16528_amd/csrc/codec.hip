@@ -66,7 +66,8 @@ __global__ __launch_bounds__(256) void nf4_quantize_kernel(const float* __restri
 // dequantise: 8 elements (4 code bytes) per lane.  (A form with 32 elements per lane -- one 16-byte code load, four
 // 16-byte stores -- measured 40 % slower: its stores leave the wave as four quarter-filled lines each.)
 // ---------------------------------------------------------------------------------------
-template <int OUT_BF16>
+// ENDS: rows end inside a group.
+template <int OUT_BF16, bool ENDS>
 __global__ __launch_bounds__(256) void nf4_dequantize_kernel(const uint8_t* __restrict__ codes,
                                                              const float* __restrict__ absmax,
                                                              int64_t rows, int cols, int64_t ld_q,
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(256) void nf4_dequantize_kernel(const uint8_t* __re
         }
         if (OUT_BF16) {
             uint16_t* dst = reinterpret_cast<uint16_t*>(out) + row * ld_out + j0;
-            if (j0 + 8 <= cols) {
+            if (!ENDS || j0 + 8 <= cols) {
                 uint4 o;
                 o.x = pack_bf16(v[0], v[1]);
                 o.y = pack_bf16(v[2], v[3]);
@@ -98,16 +99,27 @@ __global__ __launch_bounds__(256) void nf4_dequantize_kernel(const uint8_t* __re
                 o.w = pack_bf16(v[6], v[7]);
                 *reinterpret_cast<uint4*>(dst) = o;
             } else {
-                for (int e = 0; e < 8 && j0 + e < cols; ++e)
-                    dst[e] = (uint16_t)(pack_bf16(v[e], 0.f) & 0xffffu);
+                store_bf16_tail(dst, v, cols - j0);
             }
         } else {
             float* dst = reinterpret_cast<float*>(out) + row * ld_out + j0;
-            if (j0 + 8 <= cols) {
+            if (!ENDS || j0 + 8 <= cols) {
                 *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
                 *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
             } else {
-                for (int e = 0; e < 8 && j0 + e < cols; ++e) dst[e] = v[e];
+                const int n = cols - j0;
+                float4 r = make_float4(v[0], v[1], v[2], v[3]);
+                if (n & 4) {
+                    *reinterpret_cast<float4*>(dst) = r;
+                    dst += 4;
+                    r = make_float4(v[4], v[5], v[6], v[7]);
+                }
+                if (n & 2) {
+                    *reinterpret_cast<float2*>(dst) = make_float2(r.x, r.y);
+                    dst += 2;
+                    r.x = r.z;
+                }
+                if (n & 1) *dst = r.x;
             }
         }
     }
@@ -123,6 +135,7 @@ struct DequantGroupParams {
 };
 static_assert(sizeof(DequantGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
 
+template <bool ENDS>
 __global__ __launch_bounds__(256) void nf4_dequantize_grouped_kernel(const DequantGroupParams g) {
     __shared__ float lut[16];
     if (threadIdx.x < 16) lut[threadIdx.x] = kNf4Levels[threadIdx.x];
@@ -146,7 +159,7 @@ __global__ __launch_bounds__(256) void nf4_dequantize_grouped_kernel(const Dequa
             v[e] = m * lut[c];
         }
         uint16_t* dst = it.out + row * it.ld_out + j0;
-        if (j0 + 8 <= cols) {
+        if (!ENDS || j0 + 8 <= cols) {
             uint4 o;
             o.x = pack_bf16(v[0], v[1]);
             o.y = pack_bf16(v[2], v[3]);
@@ -154,7 +167,7 @@ __global__ __launch_bounds__(256) void nf4_dequantize_grouped_kernel(const Dequa
             o.w = pack_bf16(v[6], v[7]);
             *reinterpret_cast<uint4*>(dst) = o;
         } else {
-            for (int e = 0; e < 8 && j0 + e < cols; ++e) dst[e] = (uint16_t)(pack_bf16(v[e], 0.f) & 0xffffu);
+            store_bf16_tail(dst, v, cols - j0);
         }
     }
 }
@@ -395,12 +408,9 @@ hipError_t launch_dequantize(const uint8_t* codes, const float* absmax, int64_t 
     TimedLaunch tl(slot, st);
     const int64_t ngroups = rows * ((cols + 7) >> 3);
     const int grid = grid_for(ngroups, 256);
-    if (out_dtype == LOQT_BF16)
-        hipLaunchKernelGGL(nf4_dequantize_kernel<1>, dim3(grid), dim3(256), 0, st, codes, absmax, rows,
-                           (int)cols, ld_q, out, ld_out);
-    else
-        hipLaunchKernelGGL(nf4_dequantize_kernel<0>, dim3(grid), dim3(256), 0, st, codes, absmax, rows,
-                           (int)cols, ld_q, out, ld_out);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, codes, absmax, rows, (int)cols, ld_q, out, ld_out); };
+    if (cols % 8 == 0) go(out_dtype == LOQT_BF16 ? nf4_dequantize_kernel<1, false> : nf4_dequantize_kernel<0, false>);
+    else go(out_dtype == LOQT_BF16 ? nf4_dequantize_kernel<1, true> : nf4_dequantize_kernel<0, true>);
     return hipGetLastError();
 }
 
@@ -411,7 +421,8 @@ hipError_t launch_dequantize_grouped(const DequantGroupItem* items, int n, hipSt
     memset(&g, 0, sizeof(g));
     g.n = n;
     int64_t groups = 0;
-    for (int i = 0; i < n; ++i) groups += items[i].rows * ((items[i].cols + 7) >> 3);
+    bool ends = false;
+    for (int i = 0; i < n; ++i) groups += items[i].rows * ((items[i].cols + 7) >> 3), ends = ends || items[i].cols % 8 != 0;
     // about four groups of 8 per lane; few of them are over sooner side by side
     const int per_lane = groups <= 256 * 1024 ? 1 : 4;
     int total = 0;
@@ -420,7 +431,8 @@ hipError_t launch_dequantize_grouped(const DequantGroupItem* items, int n, hipSt
         total += grid_for(items[i].rows * ((items[i].cols + 7) >> 3), 256 * per_lane);
         g.block_end[i] = total;
     }
-    hipLaunchKernelGGL(nf4_dequantize_grouped_kernel, dim3((unsigned)total), dim3(256), 0, st, g);
+    const auto kernel = ends ? nf4_dequantize_grouped_kernel<true> : nf4_dequantize_grouped_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), 0, st, g);
     return hipGetLastError();
 }
 

@@ -14,7 +14,7 @@
 // the wave, not a rate: a wave has two or three chunks and loads x of one only after the products of the one before, the
 // codes of the next two after both.  At 11008 x 5056 and 16 tokens a work-group of 48 rows reads 162 KB of x and 137 KB of
 // codes and scales in 13.8 us, 9 bytes per cycle and unit; by the counters (11008 x 4096) its waves wait for loads and barriers
-// in 43 % of their cycles and for a place to issue (look-ups and their addresses) in 40 %, the matrix units are busy in 6 %.
+// in 46 % of their cycles and for a place to issue (look-ups and their addresses) in 40 %, the matrix units are busy in 5 %.
 // More rows per work-group share the chain, until the last work-groups start late: so RT grows with the number of rows.
 // Kernel, us, contraction 5056, the same weight each time / 24 weights in turn (by 750 MB at 11008 rows):
 //   16 tokens    RT 1          RT 2          RT 3          RT 4            32 tokens   RT 1          RT 2          RT 3          RT 4

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256, 2) void nt_copy_kernel(const GemmParams a, con
         if (j0[i] + 8 <= it.cols) {
             *reinterpret_cast<uint4*>(dst) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
         } else {
-            for (int e = 0; e < 8 && j0[i] + e < it.cols; ++e) dst[e] = (uint16_t)(pack_bf16(v[e], 0.f) & 0xffffu);
+            store_bf16_tail(dst, v, it.cols - j0[i]);
         }
     }
 }

@@ -50,6 +50,23 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     v[1] = (__bf16)b;
     return __builtin_bit_cast(uint32_t, v);
 }
+// the first n < 8 of v as bf16, in at most three stores (dst 16-byte aligned).  One store per element: expanding 5000 x 999 took
+// 6.5 us against 4.8 for 5000 x 1000; this way 5.9 against 5.7 (another machine).
+__device__ __forceinline__ void store_bf16_tail(uint16_t* dst, const float* v, int n) {
+    uint32_t lo = pack_bf16(v[0], v[1]);
+    if (n & 4) {
+        *reinterpret_cast<uint2*>(dst) = make_uint2(lo, pack_bf16(v[2], v[3]));
+        dst += 4;
+        lo = pack_bf16(v[4], v[5]);
+    }
+    const uint32_t hi = pack_bf16(n & 4 ? v[6] : v[2], 0.f);
+    if (n & 2) {
+        *reinterpret_cast<uint32_t*>(dst) = lo;
+        dst += 2;
+        lo = hi;
+    }
+    if (n & 1) *dst = (uint16_t)(lo & 0xffffu);
+}
 __device__ __forceinline__ float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
 

@@ -119,3 +119,20 @@ def test_round_trip_on_device_is_idempotent():
     q2 = L.nf4_quantize(deq)
     torch.cuda.synchronize()
     assert torch.equal(q1.codes, q2.codes) and torch.equal(q1.absmax, q2.absmax)
+
+
+@pytest.mark.parametrize("cols", [1, 2, 3, 4, 5, 6, 7, 9, 63, 66, 76, 133])
+def test_dequantize_row_ends(cols):
+    """The last group of a row is stored in pieces of four, two and one: every remainder, nothing past the last column."""
+    from tests import gpu_util as G
+    L = _L()
+    c, a = O.nf4_quantize(synth.normal_f32(synth.rng_for(cols, "row ends", cols, 1), (37, cols), 0.02))
+    q, ld = G.nf4_dev(c, a), G.rup(cols, 8) + 8
+    out16 = torch.full((37, ld), -7.0, dtype=torch.bfloat16, device="cuda")
+    out32 = torch.full((37, ld), -7.0, device="cuda")
+    L.nf4_dequantize(q, out16[:, :cols])
+    L.nf4_dequantize(q, out32[:, :cols])
+    torch.cuda.synchronize()
+    assert bool((out16[:, cols:] == -7.0).all()) and bool((out32[:, cols:] == -7.0).all())
+    assert np.array_equal(out32[:, :cols].cpu().numpy().view(np.uint32), O.nf4_dequantize_f32(c, a).view(np.uint32))
+    assert np.array_equal(G.bf16_host(out16[:, :cols]), O.nf4_dequantize_bf16(c, a))
