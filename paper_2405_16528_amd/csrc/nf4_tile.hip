@@ -168,25 +168,27 @@ __global__ __launch_bounds__(THREADS, 2) void nf4_tile_kernel(const GemmParams p
         else baseB += (int64_t)BK * p.B[1].ld * 2;
     };
     const uint32_t lds0 = LOQT_LDS_ADDR(smem), lwave = (uint32_t)wave * 1024u;
-    // Inline assembly (M0: the LDS address) for the reasons given in nt_tile.h: the compiler would wait for all of the loads in
-    // front of LDS reads.
+    // Inline assembly (M0: the LDS address, and one wait state between its write and the load) for the reasons given in nt_tile.h:
+    // the compiler would wait for all of the loads in front of LDS reads.
+    auto direct_load = [&](uint32_t o, const char* base, uint32_t dst, uint32_t at) {
+        asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o), "s"(base), "s"(dst), "i"(at) : "memory", "scc");
+    };
     auto load_a = [&](int n, const char* stage) {
-        const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)n * 8192u + lwave;
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offA[n]), "s"(baseA), "s"(dst) : "memory");
+        direct_load(offA[n], baseA, lds0 + (uint32_t)(stage - smem) + lwave, (uint32_t)(n * 8192));
     };
     auto load_b = [&](int i, const char* stage) {
-        const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)(BM * ROWB + i * 8192) + lwave;
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offB[i]), "s"(baseB), "s"(dst) : "memory");
+        direct_load(offB[i], baseB, lds0 + (uint32_t)(stage - smem) + lwave, (uint32_t)(BM * ROWB + i * 8192));
     };
     // codes and scales: two loads by half of the lanes (EXEC is all ones before and after: uniform control flow)
     auto load_q = [&](const char* slot) {
         const uint32_t dst = lds0 + (uint32_t)(slot - smem) + (uint32_t)wave * 512u;
         const uint32_t dsts = lds0 + (uint32_t)(slot - smem) + 4096u + (uint32_t)wave * 128u;
         asm volatile(
-            "s_mov_b32 exec_hi, 0\n\t"
             "s_mov_b32 m0, %2\n\t"
+            "s_mov_b32 exec_hi, 0\n\t"
             "global_load_lds_dwordx4 %0, %1\n\t"
             "s_mov_b32 m0, %5\n\t"
+            "s_nop 0\n\t"
             "global_load_lds_dword %3, %4\n\t"
             "s_mov_b32 exec_hi, -1"
             ::"v"(offQ), "s"(baseQ), "s"(dst), "v"(offS), "s"(baseS), "s"(dsts) : "memory");

@@ -308,22 +308,27 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // form between two MFMAs of sixteen cycles each holds the second one back.  Tiles past the end of the contraction
     // are not masked either: the tile pointers stop advancing, so such a load fetches the last tile once more
     // into a stage nobody reads again (the loop's exit waits for them before LDS is reused).
+    // A load that takes its LDS address from M0 may not be the very next instruction after the write of M0 (one wait state; the
+    // compiler keeps to it in its own code and does not look inside an assembly string).  So M0 gets the sum of the stage and the
+    // chunk's place in it, which would be an instruction anyway, and an s_nop follows: as many instructions as the sum, a move and
+    // the load.
     // M0 cannot be named as a clobber (the compiler reserves it and warns that a clobber is not honoured): it
     // never keeps a value in M0 across other code, it writes M0 right in front of each of its own uses.
-    // tests/test_isa_guard.py checks that nothing else in the loop touches M0.
-    auto direct_load = [&](uint32_t o, const char* base, uint32_t dst) {
+    // tests/test_isa_guard.py checks that nothing else in the loop touches M0, and the wait state.
+    auto direct_load = [&](uint32_t o, const char* base, uint32_t dst, uint32_t at) {
         asm volatile(
-            "s_mov_b32 m0, %2\n\t"
+            "s_add_u32 m0, %2, %3\n\t"
+            "s_nop 0\n\t"
             "global_load_lds_dwordx4 %0, %1"
             :
-            : "v"(o), "s"(base), "s"(dst)
-            : "memory");
+            : "v"(o), "s"(base), "s"(dst), "i"(at)
+            : "memory", "scc");
     };
     auto hot_load = [&](int n, char* stage) {
         const bool isA = n < Cfg::NCHA;
         const int i = isA ? n : n - Cfg::NCHA;
-        const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)((isA ? 0 : Cfg::ASTAGE) + i * 4096 + wave_s * 1024);
-        direct_load(isA ? offA[i] : offB[i], isA ? hotA : hotB, dst);
+        const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)(wave_s * 1024);
+        direct_load(isA ? offA[i] : offB[i], isA ? hotA : hotB, dst, (uint32_t)((isA ? 0 : Cfg::ASTAGE) + i * 4096));
     };
     // Tile kt of the range has landed in `stage` by direct loads and ends past its segment's contraction: clears
     // everything from there on, in both operands (what came instead is finite, but the padding of a row need not be).
@@ -519,7 +524,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 panel_load();
                 codes_setup();
 #pragma unroll
-                for (int i = 0; i < NCC; ++i) direct_load(offA[i], hotA, lds0 + (uint32_t)(Cfg::PANEL + i * 4096 + wave_s * 1024));
+                for (int i = 0; i < NCC; ++i) direct_load(offA[i], hotA, lds0 + (uint32_t)(wave_s * 1024), (uint32_t)(Cfg::PANEL + i * 4096));
             }
             hot_setup(kt_begin);
 #pragma unroll

@@ -75,14 +75,35 @@ def test_main_loop_has_no_register_file_traffic(assembly, name):
     n_loads = sum("global_load_lds_dwordx4" in x for x in text)
     assert n_loads == 16, f"{name}: {n_loads} direct loads in the loop blocks, expected 16"
     # M0 is written by the hand-written load sequence only (it cannot be declared as a clobber): every write of M0 in
-    # the loop is the s_mov of that sequence, directly followed by the load it serves.  (A mask in EXEC between the two holds
-    # back the next matrix instruction; neither variant has one.)
+    # the loop is the s_add of that sequence, followed by the wait state and the load it serves.  (A mask in EXEC between the two
+    # holds back the next matrix instruction; neither variant has one.)
     for i, x in enumerate(text):
-        if re.search(r"\bm0\b", x) and "s_mov_b32 m0" not in x:
+        if re.search(r"\bm0\b", x) and "s_add_u32 m0" not in x:
             raise AssertionError(f"{name}: M0 used outside the direct-load sequence: {x.strip()}")
-        if "s_mov_b32 m0" in x:
-            nxt = text[i + 1].strip()
-            assert nxt.startswith("global_load_lds_dwordx4"), (name, nxt)
+        if "s_add_u32 m0" in x:
+            assert text[i + 1].strip() == "s_nop 0" and text[i + 2].strip().startswith("global_load_lds_dwordx4"), (name, text[i + 1:i + 3])
+
+
+@pytest.mark.parametrize("source", ["gemm_nt.hip", "gemm_pair.hip", "gemm_weight.hip", "nf4_tile.hip"])
+def test_direct_loads_wait_for_M0(request, tmp_path_factory, source):
+    """gfx950 wants one wait state between a write of M0 and a load that takes its LDS address from there; the compiler puts an
+    s_nop into its own code and does not look inside inline assembly.  Every direct load of the library is inline assembly."""
+    asm = request.getfixturevalue("assembly") if source == "gemm_nt.hip" else _assembly(tmp_path_factory, source)
+    since, loads = None, 0  # instructions since the last write of M0 (None: none in this kernel yet)
+    for line in asm.split("\n"):
+        x = line.split(";")[0].strip()
+        if x.startswith("_Z") and x.endswith(":"):
+            since = None
+        if not re.match(r"(s|v|ds|global|buffer|flat|scratch)_", x):
+            continue
+        if x.startswith("global_load_lds"):
+            loads += 1
+            assert since is not None and since >= 1, f"{source}: {x} follows the write of M0 at once"
+        if re.match(r"s_\w+ m0\b", x):
+            since = 0
+        elif since is not None:
+            since += 1
+    assert loads > 0
 
 
 def test_few_token_kernels_keep_to_their_registers(few_assembly):
