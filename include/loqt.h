@@ -147,6 +147,8 @@ loqt_status loqt_linear_fwd(const loqt_bf16 *x, int64_t ld_x, int64_t T,
  *   dB = Z^T x                                   (r x in; dB_dtype LOQT_F32 or LOQT_BF16)
  *   accumulate != 0: dB_out = dB_in + dB (gradient accumulation), else dB_out = dB.
  * The full out x in gradient of W is never formed.  dB is summed in fp32 in a fixed order.
+ * dB may lie over an input of the call (a buffer that is not needed again): it is written when nothing reads that any more.  dx
+ * must not overlap an input, and nothing may overlap `ws`.  The same holds for the other backward calls below.
  */
 loqt_status loqt_linear_bwd(const loqt_bf16 *dy, int64_t ld_dy, const loqt_bf16 *x, int64_t ld_x,
                             int64_t T, const loqt_nf4_mat *Wq, const loqt_nf4_mat *Pq,

@@ -363,11 +363,19 @@ Operand no_operand() {
     return o;
 }
 
+// whether the n bytes at p and the nq at q have none in common
+bool apart(const void* p, size_t n, const void* q, size_t nq) {
+    return (uintptr_t)p + n <= (uintptr_t)q || (uintptr_t)q + nq <= (uintptr_t)p;
+}
+size_t span_bytes(int64_t rows, int64_t cols, int64_t ld, size_t size) { return (size_t)((rows - 1) * ld + cols) * size; }
+// ... the n bytes at p and a bf16 operand (rc: stored K x rows)
+bool apart_from(const void* p, size_t n, const Operand& o, bool rc) {
+    return o.K == 0 || apart(p, n, o.ptr, rc ? span_bytes(o.K, o.rows, o.ld, 2) : span_bytes(o.rows, o.K, o.ld, 2));
+}
 // A fold or merge that reads P as its codes reads them while others of its work-groups store: none of the n bytes it writes may
 // be P's.
 bool apart_from(const void* p, size_t n, const loqt_nf4_mat* Pq) {
-    auto apart = [=](const void* q, size_t nq) { return (uintptr_t)p + n <= (uintptr_t)q || (uintptr_t)q + nq <= (uintptr_t)p; };
-    return apart(Pq->codes, (size_t)Pq->rows * (Pq->ld / 2)) && apart(Pq->absmax, (size_t)Pq->rows * (Pq->ld / 64) * 4);
+    return apart(p, n, Pq->codes, (size_t)Pq->rows * (Pq->ld / 2)) && apart(p, n, Pq->absmax, (size_t)Pq->rows * (Pq->ld / 64) * 4);
 }
 
 // W_eff[out x in] (bf16, pitch ldw) = deq(Wq) + s * deq(Pq) B; Pb receives deq(Pq) in bf16
@@ -426,7 +434,8 @@ hipError_t launch_u_few(GemmParams& p, float* split_ws, size_t split_bytes, hipS
 
 // dB[M x N] (fp32 or bf16, pitch ld_dB) = sum of the planned slices of Z^T x and its relatives (both operands K x rows), or,
 // accumulating, that much more.  One slice that need not be added to anything goes straight to dB (rank 1024, 5120
-// columns, 256 tokens: a launch of 7 us less).  dx: the product of dx, which goes out with it, or null.
+// columns, 256 tokens: a launch of 7 us less).  dx: the product of dx, which goes out with it, or null.  The caller's dB may lie
+// over an input: it is written in a launch that reads it as well only where they have no byte in common.
 hipError_t gradient_product(int slot, GemmParams p, float* part, size_t part_bytes, int64_t ldp, void* dB, int dB_dtype,
                             int64_t ld_dB, int accumulate, const GemmParams* dx, hipStream_t st) {
     auto go = [&](int epi) {
@@ -434,7 +443,15 @@ hipError_t gradient_product(int slot, GemmParams p, float* part, size_t part_byt
     };
     p.splits = planned_splits(p.M, p.N, p.A[0].K, ldp, part_bytes);
     const bool bf16 = dB_dtype == LOQT_BF16;
-    if (p.splits == 1 && !accumulate && g_nt_tile_override == 0 && ld_dB % (bf16 ? 8 : 4) == 0 && aligned(dB, 16)) {
+    const size_t n = span_bytes(p.M, p.N, ld_dB, bf16 ? 2 : 4);
+    if (p.splits == 1 && !accumulate && g_nt_tile_override == 0 && ld_dB % (bf16 ? 8 : 4) == 0 && aligned(dB, 16) &&
+        apart_from(dB, n, p.A[0], true) && apart_from(dB, n, p.B[0], true)) {
+        if (dx && !(apart_from(dB, n, dx->A[0], false) && apart_from(dB, n, dx->A[1], false) && apart_from(dB, n, dx->B[0], true) &&
+                    apart_from(dB, n, dx->B[1], true) && apart(dB, n, dx->C, span_bytes(dx->M, dx->N, dx->ldc, 2)))) {
+            hipError_t e = launch_gemm_nt(SLOT_GEMM_DX, EPI_BF16, false, true, *dx, st);
+            if (e != hipSuccess) return e;
+            dx = nullptr;
+        }
         p.C = dB;
         p.ldc = ld_dB;
         return go(bf16 ? EPI_BF16 : EPI_F32_SPLITK);

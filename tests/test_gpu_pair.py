@@ -87,6 +87,64 @@ def test_shared_launch_on_the_other_layers(T, out, inp, r):
     assert G.max_err_over_rms(dB[0].double().cpu().numpy(), (s * (dy64 @ P64).t() @ x64).numpy()) <= TOL
 
 
+def _over(t):
+    """A fresh buffer with t's content at its start and room for a gradient of 2000 x 300 in fp32: t's copy, and the buffer."""
+    buf = torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")
+    whole = torch.as_strided(t, (t.shape[0], t.stride(0)), (t.stride(0), 1))
+    n = whole.numel() * 2
+    buf[:n].copy_(whole.reshape(-1).view(torch.uint8))
+    return buf[:n].view(torch.bfloat16).view(whole.shape)[:, :t.shape[1]], buf
+
+
+# (the launch that computes dx reads dy and the weight, without a fold B too; the gradient itself reads x, or x and dy)
+@pytest.mark.parametrize("grad", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("layer,T,out,inp,r,over", [
+    ("left", 130, 72, 72, 40, "dy"), ("left", 130, 72, 72, 40, "x"), ("left", 520, 300, 2600, 264, "dy"),
+    ("left", 100, 520, 264, 40, "B"), ("left", 100, 520, 264, 40, "dy"), ("saved", 130, 72, 72, 40, "w_eff"),
+    ("nq", 100, 520, 264, 40, "W"), ("nq", 100, 520, 264, 40, "B"), ("right", 130, 72, 72, 40, "dy"), ("right", 130, 72, 72, 40, "x")])
+def test_gradient_over_an_input(layer, T, out, inp, r, over, grad):
+    """dB in the place of an input: the bits that it and dx have with a buffer of its own."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + r)
+    rnd = lambda a, b, sg: (torch.randn(a, G.rup(b, 8), generator=g, device="cuda") * sg).bfloat16()[:, :b]
+    nf4 = lambda a, b, sg: L.nf4_quantize(torch.randn(a, G.rup(b, 4), generator=g, device="cuda") * sg, cols=b)
+    d = {"x": rnd(T, inp, 1.0), "dy": rnd(T, out, 1.0), "W": rnd(out, inp, 0.02), "w_eff": rnd(out, inp, 0.02), "P": rnd(out, r, 0.05),
+         "B": rnd(*((out, r) if layer == "right" else (r, inp)), 0.02)}
+    Wq, Pq, Qq = nf4(out, inp, 0.02), nf4(out, r, 0.05), nf4(inp, r, 0.05)
+    shape = (out, r) if layer == "right" else (r, inp)
+    op = {"left": L.OP_BWD, "saved": L.OP_BWD_SAVED, "nq": L.OP_BWD_NQ, "right": L.OP_BWD_RIGHT}[layer]
+    got = []
+    for shared in (False, True):
+        buf = torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")
+        a = dict(d)
+        if shared:
+            a[over], buf = _over(d[over])
+        ld = G.rup(shape[1], 8)
+        size = torch.empty(0, dtype=grad).element_size()
+        dB = buf[:shape[0] * ld * size].view(grad).view(shape[0], ld)[:, :shape[1]]
+        dx, ws = G.bf16_empty(T, inp, fill=float("nan")), G.workspace(op, T, out, inp, r)
+        L.timing_enable(True)
+        if layer == "left":
+            L.loqt_linear_bwd(a["dy"], a["x"], Wq, Pq, a["B"], 0.5, dx, dB, False, ws)
+        elif layer == "saved":
+            L.loqt_linear_bwd_saved(a["dy"], a["x"], Pq, 0.5, a["w_eff"], dx, dB, False, ws)
+        elif layer == "nq":
+            L.loqt_linear_bwd_nq(a["dy"], a["x"], a["W"], a["P"], a["B"], 0.5, dx, dB, False, ws)
+        else:
+            L.loqt_linear_bwd_right(a["dy"], a["x"], Wq, Qq, a["B"], 0.5, dx, dB, False, ws)
+        torch.cuda.synchronize()
+        L.timing_enable(False)
+        n = {k: v[0] for k, v in L.timing_read().items()}
+        # one launch without a sum of slices; over an operand of dx two, over one of the gradient a sum of its one slice
+        # (on the right side x went into V before)
+        own, read = over == ("dy" if layer == "right" else "x"), (layer, over) != ("right", "x")
+        assert (n["gemm_dx"], n["gemm_db"], n["reduce_db"]) == ((1, 0, 0) if not (shared and read) else (1, 0, 1) if own else (1, 1, 0))
+        got.append((dx.clone(), dB.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("T,out,inp,r", [(70, 130, 136, 40), (100, 1030, 333, 72), (130, 1100, 1000, 264), (65, 24, 2600, 24)])
 def test_copies_beside_the_first_product(T, out, inp, r):
     """bf16 copies of W and P in the launch of U: pieces that end inside a work-group's, rows that end inside a piece; U in one
