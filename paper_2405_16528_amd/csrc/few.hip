@@ -294,7 +294,7 @@ hipError_t launch_rows(const GemmParams& p, hipStream_t st) {
 }
 
 // Rows per work-group (16 RT): as few as leave at most one work-group of 16 waves for a compute unit.  Beyond that the one of
-// 48 and 64 whose rounds are cheaper by their rows (64 rows of two token tiles are 25 registers short and count for 80: 32
+// 48 and 64 whose rounds are cheaper by their rows (64 rows of two token tiles are 20 registers short and count for 80: 32
 // tokens on 13568 x 5376, us, 55 in two rounds of 48 and 45 in one of 64; on 18752 x 7872 61 and 82 in two rounds of either).
 // Rows in bf16 take 64 of the 128 registers at two chunks in flight; so 48 of them go with one chunk, and there is no form of 64.
 template <bool NF4, int NT, int OUT = TO_BF16>
@@ -302,7 +302,7 @@ hipError_t launch_tokens(const GemmParams& p, hipStream_t st) {
     const int tiles = (p.N + 15) / 16;
     if (tiles <= 256) return launch_rows<NF4, NT, 1, OUT>(p, st);
     if (tiles <= 512) return launch_rows<NF4, NT, 2, OUT>(p, st);
-    if constexpr (NF4)
+    if constexpr (NF4 && (NT == 1 || OUT != ADD_SUMS))  // (sums of two token tiles come from 768 tiles of rows at most: rows_beside)
         if ((tiles + 1023) / 1024 * (NT == 1 ? 4 : 5) < (tiles + 767) / 768 * 3) return launch_rows<NF4, NT, 4, OUT>(p, st);
     return launch_rows<NF4, NT, 3, OUT>(p, st);
 }

@@ -108,13 +108,21 @@ def test_direct_loads_wait_for_M0(request, tmp_path_factory, source):
 
 def test_few_token_kernels_keep_to_their_registers(few_assembly):
     """16 waves leave 128 registers to a lane.  Only 64 rows of NF4 codes with two token tiles may spill (one round of those is
-    still ahead of two rounds of 48 rows), and not more than they do."""
+    still ahead of two rounds of 48 rows), and not more than they do.  Every variant that a launch selects, and no other."""
     spills = {}
-    for name, count in re.findall(r"\.name: +(\S*few_tokens_kernel\S*)\n(?:.*\n)*?.*\.vgpr_spill_count: +(\d+)", few_assembly):
-        nf4, token_tiles, row_tiles = re.search(r"ILb(\d)ELi(\d)ELi(\d)E", name).groups()
-        spills["NF4" if nf4 == "1" else "bf16", int(token_tiles), int(row_tiles)] = int(count)
-    assert set(spills) == {(w, t, n) for w in ("NF4", "bf16") for t in (1, 2) for n in (1, 2, 3, 4)} - {("bf16", 1, 4), ("bf16", 2, 4)}
-    assert spills.pop(("NF4", 2, 4)) <= 26
+    for name, count in re.findall(r"\.name: +(\S*few_(?:tokens|beside)_kernel\S*)\n(?:.*\n)*?.*\.vgpr_spill_count: +(\d+)", few_assembly):
+        key = re.search(r"few_(?:tokens_kernelILb(?P<nf4>\d)ELi(?P<t>\d)ELi(?P<n>\d)ELi(?P<to>\d)E|beside_kernelILi(?P<bt>\d)ELi(?P<rt>\d)ELi(?P<ru>\d)E)", name)
+        assert key, name
+        key = (("beside", *(int(key[k]) for k in ("bt", "rt", "ru"))) if key["bt"]
+               else ("NF4" if key["nf4"] == "1" else "bf16", int(key["t"]), int(key["n"]), {"0": "result", "2": "on sums"}[key["to"]]))
+        assert key not in spills, name
+        spills[key] = int(count)
+    expected = {(w, t, n, "result") for w in ("NF4", "bf16") for t in (1, 2) for n in (1, 2, 3, 4)} - {("bf16", t, 4, "result") for t in (1, 2)}
+    # the rank-r term on top of the weight's sums, and U beside the weight: of 64 rows of the weight with one token tile only
+    expected |= {("NF4", t, n, "on sums") for t in (1, 2) for n in (1, 2, 3, 4)} - {("NF4", 2, 4, "on sums")}
+    expected |= {("beside", t, *n) for t in (1, 2) for n in ((1, 1), (2, 1), (3, 1), (3, 2), (4, 1), (4, 2)) if t == 1 or n[0] < 4}
+    assert set(spills) == expected, set(spills) ^ expected
+    assert spills.pop(("NF4", 2, 4, "result")) <= 20
     assert not any(spills.values()), spills
 
 
