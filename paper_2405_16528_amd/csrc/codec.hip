@@ -66,7 +66,8 @@ __global__ __launch_bounds__(256) void nf4_quantize_kernel(const float* __restri
 // dequantise: 8 elements (4 code bytes) per lane.  (A form with 32 elements per lane -- one 16-byte code load, four
 // 16-byte stores -- measured 40 % slower: its stores leave the wave as four quarter-filled lines each.)
 // ---------------------------------------------------------------------------------------
-// ENDS: rows end inside a group.
+// ENDS: rows end inside a group.  (Whole rows through that form, us: 11008 x 4096 27.15 -> 27.5 in bf16 and 51.4 -> 52.1 in fp32,
+// 5461 x 2048 7.31 -> 7.50 and 14.0 -> 14.3.)
 template <int OUT_BF16, bool ENDS>
 __global__ __launch_bounds__(256) void nf4_dequantize_kernel(const uint8_t* __restrict__ codes,
                                                              const float* __restrict__ absmax,

@@ -50,16 +50,18 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     v[1] = (__bf16)b;
     return __builtin_bit_cast(uint32_t, v);
 }
-// the first n < 8 of v as bf16, in at most three stores (dst 16-byte aligned).  One store per element: expanding 5000 x 999 took
-// 6.5 us against 4.8 for 5000 x 1000; this way 5.9 against 5.7 (another machine).
+// the first n < 8 of v as bf16, in at most three stores (dst 16-byte aligned).  Packed first, selected then: a choice between
+// elements of v by n is an index into an array in scratch memory, through which every group of the kernel goes.  Expanding, us:
+// 5000 x 999 5.45 that way, 4.73 this way (5000 x 1000 4.59; one store per element took 6.5 against 4.8, another machine);
+// 11008 x 4095 33.0 and 28.8.
 __device__ __forceinline__ void store_bf16_tail(uint16_t* dst, const float* v, int n) {
-    uint32_t lo = pack_bf16(v[0], v[1]);
+    const uint32_t p0 = pack_bf16(v[0], v[1]), p1 = pack_bf16(v[2], v[3]), p2 = pack_bf16(v[4], v[5]), p3 = pack_bf16(v[6], v[7]);
+    uint32_t lo = p0, hi = p1;
     if (n & 4) {
-        *reinterpret_cast<uint2*>(dst) = make_uint2(lo, pack_bf16(v[2], v[3]));
+        *reinterpret_cast<uint2*>(dst) = make_uint2(p0, p1);
         dst += 4;
-        lo = pack_bf16(v[4], v[5]);
+        lo = p2, hi = p3;
     }
-    const uint32_t hi = pack_bf16(n & 4 ? v[6] : v[2], 0.f);
     if (n & 2) {
         *reinterpret_cast<uint32_t*>(dst) = lo;
         dst += 2;

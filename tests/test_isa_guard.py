@@ -35,13 +35,24 @@ def _assembly(tmp_path_factory, source):
 
 
 @pytest.fixture(scope="module")
-def assembly(tmp_path_factory):
-    return _assembly(tmp_path_factory, "gemm_nt.hip")
+def assembly_of(tmp_path_factory):
+    made = {}
+
+    def of(source):
+        if source not in made:
+            made[source] = _assembly(tmp_path_factory, source)
+        return made[source]
+    return of
 
 
 @pytest.fixture(scope="module")
-def few_assembly(tmp_path_factory):
-    return _assembly(tmp_path_factory, "few.hip")
+def assembly(assembly_of):
+    return assembly_of("gemm_nt.hip")
+
+
+@pytest.fixture(scope="module")
+def few_assembly(assembly_of):
+    return assembly_of("few.hip")
 
 
 def _loop_blocks(asm, mangled_part):
@@ -85,10 +96,10 @@ def test_main_loop_has_no_register_file_traffic(assembly, name):
 
 
 @pytest.mark.parametrize("source", ["gemm_nt.hip", "gemm_pair.hip", "gemm_weight.hip", "nf4_tile.hip"])
-def test_direct_loads_wait_for_M0(request, tmp_path_factory, source):
+def test_direct_loads_wait_for_M0(assembly_of, source):
     """gfx950 wants one wait state between a write of M0 and a load that takes its LDS address from there; the compiler puts an
     s_nop into its own code and does not look inside inline assembly.  Every direct load of the library is inline assembly."""
-    asm = request.getfixturevalue("assembly") if source == "gemm_nt.hip" else _assembly(tmp_path_factory, source)
+    asm = assembly_of(source)
     since, loads = None, 0  # instructions since the last write of M0 (None: none in this kernel yet)
     for line in asm.split("\n"):
         x = line.split(";")[0].strip()
@@ -124,6 +135,15 @@ def test_few_token_kernels_keep_to_their_registers(few_assembly):
     assert set(spills) == expected, set(spills) ^ expected
     assert spills.pop(("NF4", 2, 4, "result")) <= 20
     assert not any(spills.values()), spills
+
+
+@pytest.mark.parametrize("source,kernel", [("codec.hip", "nf4_dequantize_kernel"), ("gemm_pair.hip", "nt_copy_kernel")])
+def test_streaming_kernels_keep_out_of_scratch_memory(assembly_of, source, kernel):
+    """The expansions of codes with rows that end inside a group of eight, and their neighbours: an array indexed at run time
+    would live in scratch memory, and every group would go through it."""
+    size = dict(re.findall(r"\.name: +(_Z\S+)\n(?:.*\n)*?.*\.private_segment_fixed_size: +(\d+)", assembly_of(source)))
+    assert any(kernel in k for k in size)
+    assert not {k: n for k, n in size.items() if int(n)}
 
 
 def test_no_kernel_that_nothing_launches(assembly):
