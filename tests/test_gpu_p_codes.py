@@ -92,3 +92,52 @@ def test_output_over_the_codes_of_P():
     n = _launches(L, lambda: L.loqt_merge_requant(Wq, Pq, B, 0.5, out=got))
     assert n["prepass"] == 1
     assert torch.equal(ref.codes, got.codes) and torch.equal(ref.absmax, got.absmax)
+
+
+def _in_place_of(t, buf):
+    """t's content at the start of the buffer `buf`, as a view of it."""
+    over = buf.view(torch.uint8).reshape(-1)[:t.numel() * t.element_size()].view(t.dtype).view(t.shape)
+    over.copy_(t)
+    return over
+
+
+@pytest.mark.parametrize("part", ["codes", "absmax"])
+def test_saved_weight_over_P(part):
+    """A forward call that leaves W_eff where P is reads all of P first."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = np.random.default_rng(4)
+    T, out, inp, r = 64, 512, 512, 256
+    Wq, Pq = (G.nf4_dev(*O.nf4_quantize((g.standard_normal(n) * 0.02).astype(np.float32))) for n in ((out, inp), (out, r)))
+    x, B = ((torch.from_numpy(g.standard_normal((n, inp))) * 0.02).bfloat16().cuda() for n in (T, r))
+    got = []
+    for over in (False, True):
+        w_eff = torch.zeros((out, inp), dtype=torch.bfloat16, device="cuda")
+        y = G.bf16_empty(T, out, fill=float("nan"))
+        if over:
+            setattr(Pq, part, _in_place_of(getattr(Pq, part), w_eff))
+        n = _launches(L, lambda: L.loqt_linear_fwd_save(x, Wq, Pq, B, 0.5, y, w_eff, G.workspace(L.OP_FWD_SAVE, T, out, inp, r)))
+        assert n["prepass"] == over
+        got.append((w_eff, y))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("target,part", [("codes", "codes"), ("codes", "absmax"), ("absmax", "absmax")])
+def test_group_that_writes_over_another_layers_P(target, part):
+    """The merges of a group share a launch: an output of one in the place of another's P, and every P is read first."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = np.random.default_rng(5)
+    sets = []
+    for out, inp, r in ((512, 512, 128), (300, 264, 64)):
+        Wq, Pq = (G.nf4_dev(*O.nf4_quantize((g.standard_normal(n) * 0.02).astype(np.float32))) for n in ((out, inp), (out, r)))
+        B = (torch.from_numpy(g.standard_normal((r, inp))) * 0.02).bfloat16().cuda()
+        sets.append((Wq, L.NF4Tensor.empty(out, inp), Pq, B, 0.5))
+    refs = [L.loqt_merge_requant(Wq, Pq, B, s, out=L.NF4Tensor.empty(Wq.rows, Wq.cols)) for Wq, _, Pq, B, s in sets]
+    torch.cuda.synchronize()
+    setattr(sets[1][2], part, _in_place_of(getattr(sets[1][2], part), getattr(sets[0][1], target)))
+    descs = L.make_merge_descs(sets)
+    n = _launches(L, lambda: L.loqt_merge_requant_batched(descs, torch.empty(L.merge_descs_workspace_bytes(descs), dtype=torch.uint8, device="cuda")))
+    assert (n["prepass"], n["merge_requant"]) == (1, 1)
+    for ref, (_, got, *_) in zip(refs, sets):
+        assert torch.equal(ref.codes, got.codes) and torch.equal(ref.absmax, got.absmax)
