@@ -3,6 +3,8 @@
 // nt_tile.h.
 #include <string.h>
 
+#include <algorithm>
+
 #include "nt_tile.h"
 
 namespace loqt {
@@ -121,7 +123,7 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
     MergeGroupParams g;
     memset(&g, 0, sizeof(g));
     g.n = n;
-    int64_t tiles = 0;  // of 128x128
+    int64_t tiles = 0, rank = 0;  // of 128x128; the largest
     for (int i = 0; i < n; ++i) {
         const MergeGroupLayer& l = layers[i];
         MergeGroupItem& it = g.it[i];
@@ -129,6 +131,7 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
         it.w_codes = l.w_codes, it.w_absmax = l.w_absmax, it.out_codes = l.out_codes, it.out_absmax = l.out_absmax;
         it.w_ld = l.w_ld, it.M = l.out, it.N = (int)l.w_ld, it.K = l.r, it.w_cols = l.in, it.alpha = l.s;
         tiles += ((l.out + 127) / 128) * ((l.w_ld + 127) / 128);
+        rank = std::max<int64_t>(rank, l.r);
         if (l.A_absmax && (l.r > A_CODES_TILES * BK || !layers[0].A_absmax)) return hipErrorInvalidValue;
         if (!l.A_absmax && layers[0].A_absmax) return hipErrorInvalidValue;
     }
@@ -141,7 +144,14 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
     //   128   13.9 / 12.8 / 9.4   15.5 / 13.8 / 12.5    16.0 / 16.8 / 14.9    20.5 / 18.6 / 18.7    23.0 / 22.2 / 23.9    28.5 / 28.5 / 32.0
     //   256   15.7 / 14.5 / 11.1  17.4 / 15.2 / 15.6    17.9 / 19.1 / 18.3    24.8 / 22.7 / 22.9    28.0 / 27.2 / 30.0    35.1 / 35.1 / 40.3
     //   384   16.6 / 15.2         21.1 / 18.3           21.8 / 23.3           28.0 / 25.9           31.8 / 31.5           40.1 / 40.8
-    return g_nt_tile_override == 0 && (tiles <= 384 || (tiles > 512 && tiles <= 800)) ? launch_grouped<64, false>(&g, st) : launch_grouped<128, false>(&g, st);
+    // Higher ranks, another machine:
+    //         196           360           540           616           721           760           784
+    //   384   19.6 / 18.2   25.2 / 22.4   31.3 / 28.2   31.8 / 29.1   33.5 / 31.1   34.2 / 31.8   35.4 / 34.7
+    //   512   22.5 / 21.1   27.4 / 24.4   34.1 / 31.2   34.5 / 32.0   38.0 / 35.6   37.5 / 35.7   38.8 / 39.1
+    //   768   26.0 / 24.0   32.3 / 28.4   41.2 / 37.8   40.9 / 38.4   43.3 / 42.7   43.6 / 42.6   47.1 / 47.4
+    //   1024  27.8 / 26.3   36.1 / 32.7   46.6 / 43.5   46.2 / 44.0   49.1 / 49.4   50.2 / 49.7   54.4 / 55.6
+    // 768 are two rounds of 64x128, three to a unit; a third one of a few tiles is made up for where the rank is small.
+    return g_nt_tile_override == 0 && (tiles <= 384 || (tiles > 512 && tiles <= (rank <= 384 ? 800 : 768))) ? launch_grouped<64, false>(&g, st) : launch_grouped<128, false>(&g, st);
 }
 
 hipError_t prepare_weight_kernels() {

@@ -54,6 +54,7 @@ def test_same_bits_as_expanded(out, inp, r, codes):
     ([(64, 128, 300), (190, 520, 255)], False),
     ([(3000, 2048, 200), (512, 1030, 64)], False),                     # between: 128x128
     ([(4096, 4096, 64), (64, 128, 64)], False),
+    ([(2048, 2048, 520), (2048, 4224, 512)], False),                   # a little over two rounds of 64x128, high ranks: 128x128
 ])
 def test_group_same_bits_as_one_by_one(layers, codes):
     from tests import gpu_util as G
