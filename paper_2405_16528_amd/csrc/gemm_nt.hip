@@ -162,8 +162,8 @@ int ktiles(const GemmParams& p) { return (p.A[0].K + BK - 1) / BK + (p.A[1].K + 
 
 // the gradient of a factor: fp32 slices at p.C, or bf16
 template <int EPI>
-hipError_t launch_gradient(const GemmParams& p, hipStream_t st) {
-    const int tile = gradient_tile(EPI, p);
+hipError_t launch_gradient(const GemmParams& p, hipStream_t st, const NtPlan* planned) {
+    const int tile = planned ? planned->tile : gradient_tile(EPI, p);
     if constexpr (EPI == EPI_F32_SPLITK) {
         if (tile == NT_256x256) return launch_nt<256, 256, EPI, true, true>(p, st);  // (forced only)
     }
@@ -172,14 +172,14 @@ hipError_t launch_gradient(const GemmParams& p, hipStream_t st) {
 
 // C in bf16
 template <bool BRC>
-hipError_t launch_product(const GemmParams& p, hipStream_t st) {
+hipError_t launch_product(const GemmParams& p, hipStream_t st, const NtPlan* planned) {
     constexpr int EPI = EPI_BF16;
     if (g_nt_tile_override != 0) return launch_nt_tile<EPI, false, BRC>(g_nt_tile_override, p, st);
     // 256x256 tiles (one work-group per compute unit) have the best ratio of MFMA work to LDS and
     // global traffic and win on long contractions.
     if (!large_product(p.M, p.N, p.Nx, p.A[0].K + p.A[1].K)) {
         if (p.Nx != 0) return launch_nt<128, 128, EPI, false, BRC>(p, st);
-        const NtPlan plan = product_plan(p);
+        const NtPlan plan = planned ? *planned : product_plan(p);
         if (plan.splits == 1) return launch_nt_tile<EPI, false, BRC>(plan.tile, p, st);
         const GemmParams c = product_slices(p, plan.splits);
         hipError_t e = launch_nt_tile<EPI_F32_SPLITK, false, BRC>(plan.tile, c, st);
@@ -280,12 +280,12 @@ hipError_t prepare_nt_kernels() {
 }
 
 // a_rc / b_rc: the operand is stored K x rows (rows contiguous) instead of rows x K
-hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st) {
+hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st, const NtPlan* plan) {
     TimedLaunch tl(slot, st);
     if (epi != EPI_BF16 && epi != EPI_F32_SPLITK) return a_rc ? hipErrorInvalidValue : launch_weight_product(epi, b_rc, p, st);
-    if (!a_rc && epi == EPI_BF16) return b_rc ? launch_product<true>(p, st) : launch_product<false>(p, st);
+    if (!a_rc && epi == EPI_BF16) return b_rc ? launch_product<true>(p, st, plan) : launch_product<false>(p, st, plan);
     if (!a_rc || !b_rc) return hipErrorInvalidValue;
-    return epi == EPI_BF16 ? launch_gradient<EPI_BF16>(p, st) : launch_gradient<EPI_F32_SPLITK>(p, st);
+    return epi == EPI_BF16 ? launch_gradient<EPI_BF16>(p, st, plan) : launch_gradient<EPI_F32_SPLITK>(p, st, plan);
 }
 
 }  // namespace loqt

@@ -177,9 +177,10 @@ hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int e
         TimedLaunch tl(slot_dx, st);
         return epi == EPI_BF16 ? dx_gradient<EPI_BF16>(plan.tile, tb, &dx, &g, st) : dx_gradient<EPI_F32_SPLITK>(plan.tile, tb, &dx, &g, st);
     }
-    hipError_t e = launch_gemm_nt(slot_dx, EPI_BF16, false, true, dx, st);
+    hipError_t e = launch_gemm_nt(slot_dx, EPI_BF16, false, true, dx, st, &plan);
     if (e != hipSuccess) return e;
-    return launch_gemm_nt(slot, epi, true, true, g, st);
+    const NtPlan gradient{tb, g.splits, 0.0};
+    return launch_gemm_nt(slot, epi, true, true, g, st, &gradient);
 }
 
 hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, bool b_rc, const GemmParams& fold, hipStream_t st) {
@@ -194,7 +195,7 @@ hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, boo
         if (e != hipSuccess) return e;
         return launch_reduce_db(z.split_ws, c.splits, z.M, z.N, c.ldc, z.C, LOQT_BF16, z.ldc, 0, st, false);
     }
-    hipError_t e = launch_gemm_nt(slot_z, EPI_BF16, false, true, z, st);
+    hipError_t e = launch_gemm_nt(slot_z, EPI_BF16, false, true, z, st, &plan);
     if (e != hipSuccess) return e;
     return launch_gemm_nt(slot, epi, false, b_rc, fold, st);
 }
@@ -211,7 +212,7 @@ hipError_t launch_u_copies(int slot, const GemmParams& u, const DequantGroupItem
     }
     hipError_t e = launch_dequantize_grouped(items, 2, st, SLOT_PREPASS);
     if (e != hipSuccess) return e;
-    return launch_gemm_nt(slot, EPI_BF16, false, false, u, st);
+    return launch_gemm_nt(slot, EPI_BF16, false, false, u, st, &plan);
 }
 
 hipError_t prepare_pair_kernels() {

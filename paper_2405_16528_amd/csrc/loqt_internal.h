@@ -320,8 +320,9 @@ hipError_t launch_reduce_db(const float* partials, int splits, int64_t M, int64_
 int gemm_db_splits(int64_t T, int64_t r, int64_t in);
 
 // large-token path (gemm_nt.hip): bf16 operands stored rows x K (K contiguous) or, with the
-// a_rc / b_rc flag, K x rows (rows contiguous; Operand::ld is the pitch of that stored matrix)
-hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st);
+// a_rc / b_rc flag, K x rows (rows contiguous; Operand::ld is the pitch of that stored matrix).  plan: product_plan(p), or the
+// tile of gradient_tile(epi, p), where the caller has it already (a plan takes 0.1 to 0.8 us of host time)
+hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st, const NtPlan* plan = nullptr);
 // ... of which those whose epilogue walks the weight (gemm_weight.hip; A stored rows x K, not timed), and their tile
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st);
 int weight_tile(int epi, const GemmParams& p);
