@@ -133,10 +133,17 @@ def _check(st: int, where: str) -> None:
         raise LoqtError(st, where)
 
 
+# (torch's private names: a build without them goes through the public call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     """The caller's current stream on the current device.  Asked for as a number: a small call is host time and little else,
     and torch.cuda.current_stream() spends 2.7 us on an object around the 0.2 us that the handle takes."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

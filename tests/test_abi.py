@@ -251,3 +251,17 @@ def test_auto_rule_on_the_paper_workloads(lib):
     assert r(L.OP_FWD, 256, 4096, 4096) == L.PATH_PREPASS and r(L.OP_BWD, 256, 4096, 4096) == L.PATH_PREPASS
     # the boundary T (in + out) = out in
     assert r(L.OP_FWD, 2048, 4096, 4096) == L.PATH_FOLDED and r(L.OP_FWD, 2047, 4096, 4096) == L.PATH_PREPASS
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
+def test_stream_without_torch_private_names(lib, monkeypatch, missing):
+    """The stream handle comes from two private functions of torch; without one of them, from the public call."""
+    import torch
+    from paper_2405_16528_amd import binding
+    public = type("Stream", (), {"cuda_stream": 4711})()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: public)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 100 + device, raising=False)
+    monkeypatch.setattr(binding, "_device", lambda: 3, raising=False)
+    assert binding._stream() == 103
+    monkeypatch.setattr(binding, missing, None)
+    assert binding._stream() == 4711
