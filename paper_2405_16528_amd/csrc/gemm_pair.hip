@@ -4,8 +4,9 @@
 // Below a few thousand tokens a product is one partly filled round of small tiles for 5 to 20 us, a launch costs 3 to 4 us of
 // them (2.6 of host time, 1.4 between kernels, the first loads of every work-group on top), and the small products (a few
 // dozen work-groups with long contractions) leave most of the chip idle.  One grid over the tiles of both: the first work-groups
-// belong to the product with the longer tiles, the others follow it onto whatever compute unit is free.  Both keep the tile
-// shape and slices they have alone, so the results are the same bits.  Only tiles of which a compute unit holds two take part;
+// belong to the product with the longer tiles, the others follow it onto whatever compute unit is free.  Both keep the slices
+// they have alone, and but for the fold, which has two work-groups to a unit here and a rule for that in launch_z_fold, their tiles.
+// Any tile sums k in the same order, so the results are the same bits.  Only tiles of which a compute unit holds two take part;
 // larger products run for hundreds of microseconds, and their tiles have a compute unit and its registers to themselves.
 #include <string.h>
 

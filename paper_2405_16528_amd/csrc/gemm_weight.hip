@@ -85,6 +85,7 @@ hipError_t launch_grouped(MergeGroupParams* g, hipStream_t st) {
     return hipGetLastError();
 }
 
+// (256x128 tiles, and merges on 256x256, were behind wherever they were timed: loqt_set_tile alone selects them.)
 template <int EPI, bool BRC>
 hipError_t launch_sized(const GemmParams& p, hipStream_t st) {
     constexpr bool HEAVY = EPI == EPI_COMP || EPI == EPI_FOLD_F32;  // small tiles only

@@ -342,9 +342,9 @@ int gradient_tile(int epi, const GemmParams& p);
 hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int epi, const GemmParams& g, hipStream_t st);
 hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, bool b_rc, const GemmParams& fold, hipStream_t st);
 hipError_t prepare_pair_kernels();
-// several merges as one launch of 128x128 tiles (EPI_MERGE over the tiles of all layers); at most MERGE_GROUP_MAX
-// layers per launch.  A: deq(P) in bf16 (out x r, pitch lda); B: the trainable factor, r x in stored K x rows
-// (b_rc) or in x r stored rows x K; the rest as in GemmParams.
+// several merges as one launch (EPI_MERGE over the tiles of all layers, 64x128 or 128x128); at most MERGE_GROUP_MAX layers per
+// launch.  A: deq(P) in bf16 or the codes of P (out x r, pitch lda); B: the trainable factor, r x in stored K x rows; the rest as in
+// GemmParams.
 constexpr int MERGE_GROUP_MAX = 24;
 struct MergeGroupLayer {
     const void* A;
