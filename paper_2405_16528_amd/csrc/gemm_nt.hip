@@ -34,21 +34,27 @@ BF16Plan plan_bf16_product(int64_t M, int64_t N, int64_t Nx) {
 // an estimate in microseconds.  Per shape: work-groups per compute unit, the time of one k-tile when a few work-groups
 // have memory to themselves (a serial chain of barrier, fragment reads and matrix instructions), when every compute unit runs
 // one and when it runs two (shared LDS, L2, fabric and power), and the rest of a tile (first loads, epilogue).
-// Measured on contractions of 768 to 5461 with 1 to 1024 work-groups; over 60 random products of all three operand orders
-// with every tile and 1 to 16 slices timed, the plan takes 1.03 of the time of the best choice.  The 64-row tiles have rings of
+// Over 15300 random products of all three operand orders, every tile and 1 to 32 slices timed by themselves, the plan takes 1.03 of the
+// time of the best choice (y 1.032, dx and Z 1.027, gradients 1.030).  In whole calls (33700 products of
+// forward and backward calls of random sizes, each on the tiles and slices that come near the best, the others as planned) the plan
+// makes the call 1.017 times as long as the best choice.  Two things come from there.  A tile of 256x128 costs 5.0 beside its loop:
+// with 4.0 they were taken, often in two or three slices, where 256x256 or 128x128 in one are ahead (y of 7817 x 13467 x 1856 350 us
+// against 308).  And `cold`: operands of more than 128 MB do not stay in the Infinity Cache, and the smaller the tile the more often they
+// are read (y of 4417 x 2135 x 12381 329 us on 256x128 in three slices and 216 on 256x256, of 7621 x 1465 x 9856 234 in two and 177).
+// With both, 122 of those products make their call 1.05 times as fast or more, 15 as slow.  The 64-row tiles have rings of
 // three and four stages (256 x 128 x 4096 on 64x64, us: 17.8 with three, 18.0 with four, 21.6 with eight; 1024 x 1024 x 4096
 // 21.1, 18.8 and 23.3).  128x128 tiles have two, which lets a compute unit hold two of them; alone on it, three or four are no
 // faster (1024 x 2048 x 2048: 20.5 us with two and with four).
 struct TileSpec {
     int id, bm, bn, per_cu;
-    double alone, full, both, fix;
+    double alone, full, both, fix, cold;
 };
 constexpr TileSpec kTiles[] = {
-    {NT_64x64, 64, 64, 2, 0.22, 0.24, 0.48, 1.99},
-    {NT_64x128, 64, 128, 2, 0.27, 0.34, 0.79, 2.24},
-    {NT_128x128, 128, 128, 2, 0.47, 0.61, 1.08, 3.0},
-    {NT_256x128, 256, 128, 1, 0.60, 0.78, 0.78, 4.0},
-    {NT_256x256, 256, 256, 1, 1.20, 1.49, 1.49, 7.95},
+    {NT_64x64, 64, 64, 2, 0.22, 0.24, 0.48, 1.99, 1.15},
+    {NT_64x128, 64, 128, 2, 0.27, 0.34, 0.79, 2.24, 1.1},
+    {NT_128x128, 128, 128, 2, 0.47, 0.61, 1.08, 3.0, 1.1},
+    {NT_256x128, 256, 128, 1, 0.60, 0.78, 0.78, 5.0, 1.25},
+    {NT_256x256, 256, 256, 1, 1.20, 1.49, 1.49, 7.95, 1.0},
 };
 
 // `tiles` of the output in `splits` slices of at most `per` k-tiles: the time of the fullest compute unit.  Each XCD takes an
@@ -56,14 +62,12 @@ constexpr TileSpec kTiles[] = {
 // compute units, two rounds, although they number 252 (256x128 tiles of 5209 x 480 x 6160, us: one slice 82, two 57, three 81).
 // And the first unit with a second work-group holds up the launch, though less than when all have two and share what is beyond
 // the unit: of the way from `full` to `both`, 0.3 at once (1024 x 5120 x 13824: 320 tiles of 128x128 231, 160 of 256x128 165;
-// 437 x 5062 x 5384: 280 of 64x128 82, 80 of 256x128 in three slices 48).  Over 350 products with every tile and 1 to 16 slices
-// timed, the plan takes 1.02 (y, dx), 1.01 (Z) and 1.14 (dB) of the time of the best; counting units as an average, 1.05, 1.04
-// and 1.17.
-double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits) {
+// 437 x 5062 x 5384: 280 of 64x128 82, 80 of 256x128 in three slices 48).
+double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits, bool cold) {
     const int64_t wgs = (tiles + 7) / 8 * splits;  // of the fullest XCD
     const int log2_round = t.per_cu == 2 ? 6 : 5;  // ... and in one round of its 32 compute units
     const int64_t rounds = wgs >> log2_round, rest = wgs & ((1 << log2_round) - 1);
-    const double kt = (double)per;
+    const double kt = (double)per * (cold ? t.cold : 1.0);
     auto one = [&](int64_t w) {
         const double u = (double)w / 32.0;
         if (u <= 1.0) return kt * (t.alone + (t.full - t.alone) * u) + t.fix;
@@ -71,6 +75,9 @@ double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits) {
     };
     return (rounds ? (double)rounds * one((int64_t)1 << log2_round) : 0.0) + (rest ? one(rest) : 0.0);
 }
+
+// `rows` of both operands together
+bool cold_operands(int64_t rows, int64_t nkt) { return rows * nkt > (int64_t)1000000; }  // 128 bytes to a k-tile
 
 // slices > 1 (or `sliced`: the result is summed from fp32 slices in any case) cost their own traffic and the
 // reduction's: written at about 6 TB/s, read back at 7, and a launch
@@ -84,24 +91,27 @@ double slices_cost(int64_t M, int64_t N, int splits) {
 NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, int max_splits) {
     auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     const int kts = (int)nkt;  // dimensions are at most 2^30
+    const bool cold = cold_operands(M + N, nkt);
     NtPlan best{0, 1, 0.0};
     for (const TileSpec& t : kTiles) {
         if (sliced && t.id == NT_256x256) continue;  // no such kernel: its slices were slower than those of 256x128
         // dB and its relatives from rank 512 up: operands come from HBM, and shorter tiles read the longer one more often
         // (512 x 5461 x 8192, us: 66 on 256x128, 80 on 128x128; 5461 x 512 x 4096 36 and 43; 1024 x 5120 x 256 14 and 21).
         // The estimate does not see that: with 128x128 in it, 60 random products of 512 to 1024 rows take 1.01 of the time,
-        // single ones 0.94 to 1.16.
-        if (sliced && M >= 512 && t.id == NT_128x128) continue;
+        // single ones 0.94 to 1.16.  One work-group to a unit at most is another matter (8141 x 384 x 1774 23 us on 128x128 in one
+        // slice, 27 and a sum of 9 on 256x128 in two; 896 x 4480 x 3337 35 and 47 in one slice of either).
         const int64_t tiles = cdiv(M, t.bm) * cdiv(N, t.bn);
+        const bool crowds = sliced && M >= 512 && t.id == NT_128x128;
         for (int splits = min_splits; splits <= max_splits; ++splits) {
             const int per = (int)((unsigned)(kts + splits - 1) / (unsigned)splits);
             if (min_splits < max_splits && splits > min_splits) {
                 if (per < 4 || t.id == NT_256x256) break;
                 if ((int)((unsigned)(kts + per - 1) / (unsigned)per) != splits) continue;  // the last slices would be empty
             }
+            if (crowds && (tiles + 7) / 8 * splits > 32) break;
             const double extra = sliced || splits > 1 ? slices_cost(M, N, splits) : 0.0;
             if (best.tile != 0 && extra >= best.cost) break;  // and more slices cost more still
-            const double cost = tile_cost(t, tiles, per, splits) + extra;
+            const double cost = tile_cost(t, tiles, per, splits, cold) + extra;
             if (best.tile == 0 || cost < best.cost) best = NtPlan{t.id, splits, cost};
         }
     }
@@ -112,7 +122,7 @@ NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, i
 double joint_cost_128(int64_t M, int64_t N, int64_t Nx, int64_t nkt) {
     auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     for (const TileSpec& t : kTiles)
-        if (t.id == NT_128x128) return tile_cost(t, cdiv(M, 128) * (cdiv(N, 128) + cdiv(Nx, 128)), (int)nkt, 1);
+        if (t.id == NT_128x128) return tile_cost(t, cdiv(M, 128) * (cdiv(N, 128) + cdiv(Nx, 128)), (int)nkt, 1, cold_operands(M + N + Nx, nkt));
     return 0.0;
 }
 

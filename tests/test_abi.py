@@ -265,3 +265,16 @@ def test_stream_without_torch_private_names(lib, monkeypatch, missing):
     assert binding._stream() == 103
     monkeypatch.setattr(binding, missing, None)
     assert binding._stream() == 4711
+
+
+@pytest.mark.parametrize("M,N,K,sliced,want", [
+    # one slice on 256x256 tiles, which read operands of more than 128 MB less often, not two or three on 256x128
+    (4417, 2135, 12381, False, (1, 1)), (7621, 1465, 9856, False, (1, 1)), (2238, 4936, 10630, False, (1, 1)), (1735, 5278, 10240, False, (1, 1)),
+    (7817, 13467, 1856, False, (1, 1)), (8108, 12480, 472, False, (1, 1)),  # rounds of 256x128 that cost more beside the loop
+    (8141, 384, 1774, True, (3, 1)), (896, 4480, 3337, True, (3, 1)),       # a gradient of one 128x128 tile to a unit at most
+    (5461, 512, 4096, True, (2, 2)), (512, 5461, 8192, True, (2, 2)),       # ... and of more
+])
+def test_plan_of_products_that_were_slower_on_256x128(lib, M, N, K, sliced, want):
+    """Host code.  (tile, slices) as timed in whole calls; 1 = 256x256, 2 = 256x128, 3 = 128x128."""
+    from paper_2405_16528_amd import binding as L
+    assert L.plan_tiles(M, N, K, sliced) == want
