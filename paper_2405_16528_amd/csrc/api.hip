@@ -680,7 +680,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
         p.C = U;
         p.ldc = ld_u;
         float* const room = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + L.Wb);
-        if (few_layer_fits((int)T, (int)out, (int)r, ws_bytes - L.Wb)) {
+        if (few_layer_fits((int)T, (int)out, (int)in, (int)r, ws_bytes - L.Wb)) {
             GemmParams w, q;
             memset(&w, 0, sizeof(w));
             w.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);

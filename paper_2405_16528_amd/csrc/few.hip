@@ -20,7 +20,7 @@
 //   16 tokens    RT 1          RT 2          RT 3          RT 4            32 tokens   RT 1          RT 2          RT 3          RT 4
 //   4096 rows     9.4 / 10.1   11.2 / 12.2   13.4 / 15.2   15.8 / 18.4                 12.7 / 14.1   14.3 / 16.1   16.7 / 18.9   24.6 / 27.3
 //   11008 rows   19.4 / 20.6   19.2 / 22.1   13.8 / 16.3   16.2 / 19.6                 36.6 / 37.3   28.8 / 31.1   18.2 / 20.4   26.7 / 30.2
-// U = s x B^T needs a launch before y, and the chip is nearly idle in it.  So where the work-groups of both fit on the chip at once U
+// U = s x B^T needs a launch before y, and the chip is nearly idle in it.  So where the work-groups of both fit on the chip at once and the contraction is long U
 // goes out beside x deq(W)^T, which does not need it, whose sums wait in fp32 for the second launch, U deq(P)^T.
 // The whole call at 16 x 11008 x 4096, rank 1024: 165 -> 23.3 (expanded weight -> this; 78 with the expanded weight on the
 // narrow tiles of gemm_nt.hip), 160 -> 51 on buffers that nothing has read before.  From 33 tokens on x costs more than the expanded weight (4096 x 11008, 64 tokens: 98 against 79).
@@ -309,7 +309,7 @@ hipError_t launch_tokens(const GemmParams& p, hipStream_t st) {
 
 // Rows per work-group of W and of U, 16 each: the fewest with which both together leave at most one work-group for a compute unit.
 // Whole calls, us, U first / U beside W, 1, 16 and 32 tokens:
-//   512 x 512, rank 128      14.0 / 10.1   14.1 / 10.2   13.8 / 9.8        11008 x 4096, rank 512    19.9 / 17.2   23.4 / 19.3   27.4 / 24.2
+//   11008 x 4096, rank 512   19.9 / 17.2   23.4 / 19.3   27.4 / 24.2
 //   4096 x 4096, rank 1024   13.7 / 12.9   19.3 / 15.0   23.7 / 19.7       13824 x 5120, rank 1024   26.0 / 22.7   29.4 / 25.5   (no room)
 //   5120 x 5120, rank 1024   18.6 / 13.9   22.9 / 17.0   28.3 / 22.8       4096 x 11008, rank 1024   23.3 / 19.6   30.1 / 26.6   39.6 / 36.7
 // U on 48 rows was no faster than U first (11008 x 4096, rank 1024: 20.1 / 21.0, 24.7 / 24.3, 29.3 / 29.5).  64 rows of W where 48 do
@@ -344,8 +344,16 @@ hipError_t launch_beside(const GemmParams& u, const GemmParams& w, hipStream_t s
 
 }  // namespace
 
-bool few_layer_fits(int T, int N, int r, size_t ws_bytes) {
-    return rows_beside(T, N, r).rt > 0 && ws_bytes >= (size_t)((T + 3) / 4) * N * 16;
+// It pays where U's chain over the contraction is long against the work-groups' other costs, the more rows the later: random calls of 1 to
+// 32 tokens, beside / first, by contraction:
+//                          800 to 1100    1400 to 1800    1800 to 2300    2300 to 3000    4000 to 5500
+//   to 4096 rows           1.01           0.94 to 1.01    0.88 to 1.00    0.83 to 0.96    0.81 to 0.83
+//   to 8192                1.03 to 1.08   0.99 to 1.03    0.95 to 1.00    0.87 to 0.93    0.83 to 0.84
+//   beyond                 1.11 to 1.12   1.04 to 1.08    1.00 to 1.04    0.95 to 0.98    0.88 to 0.90
+// Beside at any length, 4832 of 45000 calls were slower by more than 3 % than with U first (11600 x 218, 21 tokens, 8.6 / 10.7 us); with
+// these lines 354 are.
+bool few_layer_fits(int T, int N, int K, int r, size_t ws_bytes) {
+    return K >= (N <= 4096 ? 1300 : N <= 8192 ? 1800 : 2300) && rows_beside(T, N, r).rt > 0 && ws_bytes >= (size_t)((T + 3) / 4) * N * 16;
 }
 
 hipError_t launch_few_layer(const GemmParams& u, const GemmParams& w, const GemmParams& q, hipStream_t st) {

@@ -302,7 +302,7 @@ constexpr int FEW_ROWS_MAX_BF16 = 12288;
 hipError_t launch_few_tokens(int slot, bool nf4, const GemmParams& p, hipStream_t st);
 // The same y in two launches, U = s x B^T (u) beside x deq(W)^T (w, its sums in fp32 to split_ws), then U deq(P)^T on top (q, from
 // split_ws to C); whether the sizes and the room for the sums allow it
-bool few_layer_fits(int T, int N, int r, size_t ws_bytes);
+bool few_layer_fits(int T, int N, int K, int r, size_t ws_bytes);
 hipError_t launch_few_layer(const GemmParams& u, const GemmParams& w, const GemmParams& q, hipStream_t st);
 
 // products of a few hundred tokens with NF4 weights (nf4_tile.hip) in p.splits fp32 slices at p.C (pitch p.ldc, a multiple

@@ -189,15 +189,19 @@ def test_unquantised_forward_with_no_room_for_slices(T, inp):
 
 
 @pytest.mark.parametrize("T,out,inp,r,beside", [
-    (4, 3600, 136, 40, True),      # rows of W and U per work-group (16 each): 1 and 1
-    (17, 3601, 264, 520, True),    # 2 and 1
-    (32, 8201, 200, 72, True),     # 3 and 1
-    (3, 11001, 136, 440, True),    # 3 and 2
-    (11, 11001, 136, 900, True),   # 4 and 1
-    (16, 13001, 136, 900, True),   # 4 and 2
-    (8, 11001, 136, 900, False),   # as many work-groups as the chip holds only with slower tiles
-    (18, 13001, 136, 40, False),
-    (31, 2000, 8, 8, False),       # no room for the sums
+    # (contractions from 1300, 1800 and 2300 on, by rows: the lines from which U goes beside the weight; shorter ones come last)
+    (4, 3600, 1304, 40, True),      # rows of W and U per work-group (16 each): 1 and 1
+    (17, 3601, 1336, 520, True),    # 2 and 1
+    (32, 8201, 2312, 72, True),     # 3 and 1
+    (3, 11001, 2312, 440, True),    # 3 and 2
+    (11, 11001, 2312, 900, True),   # 4 and 1
+    (16, 13001, 2312, 900, True),   # 4 and 2
+    (8, 11001, 2312, 900, False),   # as many work-groups as the chip holds only with slower tiles
+    (18, 13001, 2312, 40, False),
+    (31, 2000, 8, 8, False),        # no room for the sums
+    (4, 3600, 1296, 40, False),     # U first
+    (17, 4112, 1792, 72, False),
+    (3, 8208, 2288, 40, False),
 ])
 def test_u_beside_the_weight(T, out, inp, r, beside):
     """U and the sums of x deq(W)^T in one launch, the rank-r term in the next: against the oracle, and nothing past the workspace."""
