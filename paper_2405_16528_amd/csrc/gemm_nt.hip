@@ -160,10 +160,12 @@ hipError_t launch_nt_tile(int tile, const GemmParams& p, hipStream_t st) {
         case NT_256x256:
             if constexpr (EPI == EPI_BF16 && !ARC) return launch_nt<256, 256, EPI, ARC, BRC>(p, st);
             break;
-        case NT_256x128: return launch_nt<256, 128, EPI, ARC, BRC>(p, st);
-        case NT_128x128: return launch_nt<128, 128, EPI, ARC, BRC>(p, st);
-        case NT_64x128: return launch_nt<64, 128, EPI, ARC, BRC, 3>(p, st);
-        case NT_64x64: return launch_nt<64, 64, EPI, ARC, BRC, 4>(p, st);
+        case NT_256x128: return launch_nt<256, 128, EPI, ARC, BRC, 3, false, false, true>(p, st);
+        case NT_128x128:
+            if (one_to_a_unit<EPI>(p)) return launch_nt<128, 128, EPI, ARC, BRC, 3, false, false, true>(p, st);
+            return launch_nt<128, 128, EPI, ARC, BRC>(p, st);
+        case NT_64x128: return launch_nt<64, 128, EPI, ARC, BRC, 3, false, false, true>(p, st);
+        case NT_64x64: return launch_nt<64, 64, EPI, ARC, BRC, 4, false, false, true>(p, st);
     }
     return hipErrorInvalidValue;
 }
@@ -188,7 +190,7 @@ hipError_t launch_product(const GemmParams& p, hipStream_t st, const NtPlan* pla
     // 256x256 tiles (one work-group per compute unit) have the best ratio of MFMA work to LDS and
     // global traffic and win on long contractions.
     if (!large_product(p.M, p.N, p.Nx, p.A[0].K + p.A[1].K)) {
-        if (p.Nx != 0) return launch_nt<128, 128, EPI, false, BRC>(p, st);
+        if (p.Nx != 0) return launch_nt_tile<EPI, false, BRC>(NT_128x128, p, st);
         const NtPlan plan = planned ? *planned : product_plan(p);
         if (plan.splits == 1) return launch_nt_tile<EPI, false, BRC>(plan.tile, p, st);
         const GemmParams c = product_slices(p, plan.splits);
@@ -224,15 +226,15 @@ hipError_t launch_product(const GemmParams& p, hipStream_t st, const NtPlan* pla
         c.C = p.split_ws;
         c.ldc = (b.N + 3) / 4 * 4;
         c.splits = 2;
-        e = launch_nt<256, 128, EPI_F32_SPLITK, false, BRC>(c, st);
+        e = launch_nt_tile<EPI_F32_SPLITK, false, BRC>(NT_256x128, c, st);
         if (e != hipSuccess) return e;
         return launch_reduce_db(p.split_ws, 2, b.M, b.N, c.ldc, b.C, LOQT_BF16, b.ldc, 0, st, false);
     }
     // between 129 and 256 tiles of 256x128 (7B gate / up forward: 768 of 11008 columns; 13B gate / up
     // forward: 1536 of 13824): that shape, one work-group per compute unit
     const int64_t t2 = ((int64_t)(b.M + 255) / 256) * ((b.N + 127) / 128);
-    if (b.Nx == 0 && t2 > 128 && t2 <= 256) return launch_nt<256, 128, EPI, false, BRC>(b, st);
-    return launch_nt<128, 128, EPI, false, BRC>(b, st);
+    if (b.Nx == 0 && t2 > 128 && t2 <= 256) return launch_nt_tile<EPI, false, BRC>(NT_256x128, b, st);
+    return launch_nt_tile<EPI, false, BRC>(NT_128x128, b, st);
 }
 
 template <int EPI, bool ARC, bool BRC>
@@ -242,11 +244,12 @@ hipError_t prepare_tiles() {
         if ((e = ensure_attr<256, 256, EPI, ARC, BRC>()) != hipSuccess) return e;
         if ((e = ensure_attr<256, 256, EPI, ARC, BRC, 2, true>()) != hipSuccess) return e;
     }
-    if ((e = ensure_attr<256, 128, EPI, ARC, BRC>()) != hipSuccess) return e;
-    if ((e = ensure_attr<256, 128, EPI, ARC, BRC, 2, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<256, 128, EPI, ARC, BRC, 3, false, false, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<256, 128, EPI, ARC, BRC, 3, true, false, true>()) != hipSuccess) return e;
     if ((e = ensure_attr<128, 128, EPI, ARC, BRC>()) != hipSuccess) return e;
-    if ((e = ensure_attr<64, 128, EPI, ARC, BRC, 3>()) != hipSuccess) return e;
-    return ensure_attr<64, 64, EPI, ARC, BRC, 4>();
+    if ((e = ensure_attr<128, 128, EPI, ARC, BRC, 3, false, false, true>()) != hipSuccess) return e;
+    if ((e = ensure_attr<64, 128, EPI, ARC, BRC, 3, false, false, true>()) != hipSuccess) return e;
+    return ensure_attr<64, 64, EPI, ARC, BRC, 4, false, false, true>();
 }
 
 }  // namespace

@@ -86,8 +86,9 @@ __device__ __forceinline__ float max_over_lane_groups(float a) {
 
 // One output tile.  L: index of the tile in the walk order described above (tiles past the end return at once);
 // split: slice of the contraction (EPI_F32_SPLITK), else 0.
-// NOTAIL (two stages only): every K segment is a whole number of k-tiles, so no tile has to be cut (cut_tile).
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
+// NOTAIL: every K segment is a whole number of k-tiles, so no tile has to be cut (cut_tile).
+// LOADERS: eight waves, of which four load.
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
 __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, const int split) {
     using Cfg = NtCfg<BM, BN, NS, ANF4>;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, STAGE = Cfg::STAGE, WTM = Cfg::WTM, WTN = Cfg::WTN;
@@ -101,9 +102,11 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     constexpr bool WEIGHT = ENCODES || CODES || EPI == EPI_ACC_BF16;
     static_assert(!WEIGHT || WTN % 64 == 0, "");
     static_assert(!ANF4 || (CODES && !ARC && NS == 2), "");
+    static_assert(!LOADERS || (!WEIGHT && NS > 2), "");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // (LOADERS: the second four waves load, with the indexes of the first four)
+    const int tid = LOADERS ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const int frow = lane & 15, g4 = lane >> 4;  // lane = 16 g4 + frow
@@ -463,7 +466,128 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     constexpr int NM = TM * TN, NU = TM + TN;  // MFMAs and fragments of a k32 step
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    if constexpr (NS == 2) {
+    if constexpr (LOADERS) {
+        // ---- waves of their own for the loads.  A wave issues in order, and a direct load holds it up while the memory pipeline of the
+        // compute unit is busy, so of the 1031 to 1100 cycles per k-tile of a 128x128 tile with one wave to a SIMD the matrix units were
+        // busy for 512; the products alone took 620, the loads alone 570, the fragment reads alone 420.  Here one wave of a SIMD
+        // multiplies and another one loads, with one barrier per k-tile between them: 670 and 760 cycles (B rows x K, K x rows), 256x128
+        // 1160 and 1210 instead of 1390 and 1430 (1024 of products), 64x128 590 instead of 720, 64x64 460 instead of 500.  The
+        // accumulators of 256x256 leave no registers for a second wave.  Four waves of products, fragments of one k32 step ahead: the
+        // barrier of k-tile kt, between its two steps, says that its fragments are in registers, which frees its stage for tile
+        // kt + NS, and that tile kt + 1 has landed.
+        constexpr int NCH = Cfg::NCH;
+        const int nkt = kt_end - kt_begin;
+        // all but `later` of the tiles asked for have landed
+        auto landed = [&](int later) {
+            if (later >= NS - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * NCH) : "memory");
+            else if (NS > 3 && later == NS - 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NCH) : "memory");
+            else if (NS > 4 && later == NS - 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 3) * NCH) : "memory");
+            else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCH) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        };
+        if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 8)) {
+            if (nkt > 0) {
+                hot_setup(kt_begin);
+                for (int t = 0; t < NS && t < nkt; ++t) {
+                    if (t > 0) hot_advance(kt_begin + t);
+#pragma unroll
+                    for (int n = 0; n < NCH; ++n) hot_load(n, smem + t * STAGE);
+                }
+                landed(min(NS, nkt) - 1);
+                __syncthreads();
+                if (is_tail(kt_begin)) {
+                    cut_tile(kt_begin, smem);
+                    __syncthreads();
+                }
+                int si = 0;
+                for (int kt = kt_begin; kt < kt_end; ++kt) {
+                    char* const cur = smem + si * STAGE;
+                    si = si + 1 == NS ? 0 : si + 1;
+                    landed(min(kt_end - 2 - kt, NS - 2));
+                    __syncthreads();
+                    if (is_tail(kt + 1)) {
+                        cut_tile(kt + 1, smem + si * STAGE);
+                        __syncthreads();
+                    }
+                    if (kt + NS < kt_end) {
+                        hot_advance(kt + NS);
+#pragma unroll
+                        for (int n = 0; n < NCH; ++n) hot_load(n, cur);
+                    }
+                }
+            }
+            __syncthreads();
+            return;
+        }
+        // 64x64: a k32 step is four products, less than the latency of a read, so the fragments of a whole k-tile are kept ahead and the
+        // barrier is between the k-tiles (64 x 64 x 4096 15.0 -> 14.6 us, 1024 x 1024 x 2048 10.5 -> 10.2)
+        constexpr bool WHOLE = NM < 8;
+        if (nkt > 0) {
+            __syncthreads();
+            if (is_tail(kt_begin)) __syncthreads();
+        }
+        int si = 0;
+        if constexpr (WHOLE) {
+            constexpr int NSL = 2 * NM, RSL = NSL * 3 / 4;  // slots of one MFMA; those that carry fragment reads
+            bf16x8 f[2][2][NU];
+            if (nkt > 0) {
+#pragma unroll
+                for (int u = 0; u < 2 * NU; ++u) f[0][u / NU][u % NU] = read_frag(u / NU, u % NU, smem);
+            }
+            auto ktile = [&](auto par_tag, int kt) {
+                constexpr int P = decltype(par_tag)::value;
+                si = si + 1 == NS ? 0 : si + 1;
+                const char* const nxt = smem + si * STAGE;
+                __syncthreads();
+                if (is_tail(kt + 1)) __syncthreads();
+#pragma unroll
+                for (int sl = 0; sl < NSL; ++sl) {
+                    const int ks = sl / NM, i = sl % NM / TN, j = sl % TN;
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[P][ks][TM + j], f[P][ks][i], acc[i][j], 0, 0, 0);
+                    if (sl < RSL) {
+#pragma unroll
+                        for (int u = sl * 2 * NU / RSL; u < (sl + 1) * 2 * NU / RSL; ++u) f[P ^ 1][u / NU][u % NU] = read_frag(u / NU, u % NU, nxt);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            for (int kt = kt_begin; kt < kt_end; ++kt) {
+                ktile(I0{}, kt);
+                if (++kt >= kt_end) break;
+                ktile(I1{}, kt);
+            }
+        } else {
+            constexpr int RSL = NM * 5 / 8;  // slots (of one MFMA) that carry fragment reads: the last ones have time to arrive
+            bf16x8 f[2][NU];
+            // the order in which a step's products ask for the fragments: A's first, B's, the rest of A's
+            auto nth = [](int n) { return n == 0 ? 0 : n <= TN ? TM + n - 1 : n - TN; };
+            auto step = [&](auto cb_tag, const char* rstage) {  // the MFMAs of k32 step CB, under them the reads of the next step
+                constexpr int CB = decltype(cb_tag)::value;
+#pragma unroll
+                for (int sl = 0; sl < NM; ++sl) {
+                    const int i = sl / TN, j = sl % TN;
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[CB][TM + j], f[CB][i], acc[i][j], 0, 0, 0);
+                    if (sl < RSL) {
+#pragma unroll
+                        for (int n = sl * NU / RSL; n < (sl + 1) * NU / RSL; ++n) f[CB ^ 1][nth(n)] = read_frag(CB ^ 1, nth(n), rstage);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if (nkt > 0) {
+#pragma unroll
+                for (int n = 0; n < NU; ++n) f[0][nth(n)] = read_frag(0, nth(n), smem);
+            }
+            for (int kt = kt_begin; kt < kt_end; ++kt) {
+                const char* const cur = smem + si * STAGE;
+                si = si + 1 == NS ? 0 : si + 1;
+                step(I0{}, cur);
+                __syncthreads();
+                if (is_tail(kt + 1)) __syncthreads();
+                step(I1{}, smem + si * STAGE);
+            }
+        }
+    } else if constexpr (NS == 2) {
         // ---- two stages.  A stage is free as soon as the fragments of its second k32 step sit in
         // registers, a quarter of the way into its tile, so its refill does not have to wait for the barrier
         // that publishes the next tile.  Per k-tile kt, in slots of two MFMAs:
@@ -925,18 +1049,27 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 }
 
 // Work-groups are dealt to the 8 XCDs round-robin by the hardware; each XCD walks a contiguous range of tiles.
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
-__global__ __launch_bounds__(256, (NtCfg<BM, BN, NS, ANF4>::PER_CU)) void nt_gemm_kernel(const GemmParams p) {
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
+__global__ __launch_bounds__(LOADERS ? 512 : 256, (LOADERS ? 2 : 1) * (NtCfg<BM, BN, NS, ANF4>::PER_CU)) void nt_gemm_kernel(const GemmParams p) {
     const int per_xcd = gridDim.x >> 3;
-    nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>(p, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), blockIdx.y);
+    nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>(p, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), blockIdx.y);
+}
+
+// 128x128 tiles: with waves of their own for the loads a compute unit holds one work-group, without two.  One is enough, and faster, while
+// no XCD (an eighth of the tiles of every slice, rounded up) has more than its 32 units: 4096 x 768 x 2048 21.4 -> 17.5 us, 2048 x 2048 x
+// 4096 36.8 -> 31.3.  From there on two hide each other's first loads and results (512 tiles of 4096 x 2048 x 5461: 103.7 either way).
+template <int EPI>
+bool one_to_a_unit(const GemmParams& p) {
+    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128 + (p.Nx + 127) / 128);
+    return (tiles + 7) / 8 * (EPI == EPI_F32_SPLITK ? p.splits : 1) <= 32;
 }
 
 // the kernel's LDS size has to be raised above the default once per process (first launch, or loqt_prepare)
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
 hipError_t ensure_attr() {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, NtCfg<BM, BN, NS, ANF4>::SMEM);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -944,17 +1077,17 @@ hipError_t ensure_attr() {
     return hipSuccess;
 }
 
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
 hipError_t launch_nt(const GemmParams& p, hipStream_t st) {
     if constexpr (BM == 256 && (EPI == EPI_BF16 || (EPI == EPI_F32_SPLITK && BN == 128)) && !NOTAIL) {
         // 256-row tiles of the plain products have a variant for contractions that are whole k-tiles
-        if (p.A[0].K % BK == 0 && p.A[1].K % BK == 0) return launch_nt<BM, BN, EPI, ARC, BRC, NS, true>(p, st);
+        if (p.A[0].K % BK == 0 && p.A[1].K % BK == 0) return launch_nt<BM, BN, EPI, ARC, BRC, NS, true, ANF4, LOADERS>(p, st);
     }
-    hipError_t e0 = ensure_attr<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>();
+    hipError_t e0 = ensure_attr<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>();
     if (e0 != hipSuccess) return e0;
     const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN + (p.Nx + BN - 1) / BN);
     dim3 grid((tiles + 7) / 8 * 8, EPI == EPI_F32_SPLITK ? p.splits : 1);
-    hipLaunchKernelGGL((nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4>), grid, dim3(256), (NtCfg<BM, BN, NS, ANF4>::SMEM), st, p);
+    hipLaunchKernelGGL((nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>), grid, dim3(LOADERS ? 512 : 256), (NtCfg<BM, BN, NS, ANF4>::SMEM), st, p);
     return hipGetLastError();
 }
 
