@@ -128,14 +128,21 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
 }
 
 // A few hundred tokens that do not fold: the codes are expanded inside the products (nf4_tile.hip) and no copy of the
-// weight is made.  Up to 64 tokens that is never behind (forward + backward, us, against copies: 2048 x 2048, rank 512, 49
-// and 53; 13824 x 5120, rank 1024, 129 and 221); up to 256 it takes a weight whose copy costs more than the slower loop, the
-// more so the more tokens there are (96 / 128 / 192 / 256 tokens, time against copies: 2.8 million elements 1.08 / 1.13 / 1.31 /
-// 1.54, 4.2 million 1.00 / 1.04 / 1.11 / 1.21, 9 million 0.88 / 0.90 / 0.98 / 1.05, 11.2 million 0.90 to 0.98 / 0.93 to 1.00 /
-// 0.99 to 1.04 / 1.00 to 1.08, 16.8 million 0.80 / 0.82 / 0.92 / 0.98, 25 million 0.78 / 0.79 / 0.89 / 0.85).
-bool use_nf4_tile(int64_t T, int64_t out, int64_t in) {
-    if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in)) return false;
-    return T <= 64 || (T <= 256 && out * in >= 2500000 + 50000 * T);
+// weight is made.  That pays for a weight whose copy costs more than the slower loop, the more so the more tokens there are, and
+// less in the backward pass, where the copies go out beside nothing else but the products of dx fill the chip and the gradient
+// shares their launch.  Time against copies, forward / backward, by elements of the weight (millions):
+//   tokens     40            64            96            128           192           256
+//   0.7        1.25 / 1.04   1.33 / 1.08   1.42 / 1.12   1.42 / 1.32   1.67 / 1.50   1.67 / 1.64
+//   1.6        1.14 / 0.96   1.21 / 1.04   1.29 / 1.12   1.36 / 1.15   1.57 / 1.30   1.79 / 1.39
+//   2.8, 2.9   1.06 / 0.94   1.05 / 0.88   1.10 / 1.06   1.25 / 1.09   1.40 / 1.21   1.50 / 1.47
+//   4.2        0.91 / 0.87   0.91 / 0.88   1.00 / 1.00   1.04 / 1.03   1.15 / 1.28   1.18 / 1.38
+//   11.2       0.64 / 0.84   0.71 / 0.87   0.79 / 1.00   0.91 / 1.05   0.97 / 1.17   1.00 / 1.26
+//   16.8       0.68 / 0.84   0.78 / 0.88   0.81 / 0.96   0.86 / 0.98   0.84 / 1.16   0.93 / 1.19
+//   26         0.65 / 0.81   0.71 / 0.85   0.77 / 0.93   0.77 / 0.91   0.86 / 0.98   0.68 / 0.87
+//   45         0.73 / 0.73   0.80 / 0.72   0.79 / 0.78   0.81 / 0.81   0.80 / 0.82   0.85 / 0.84
+bool use_nf4_tile(int64_t T, int64_t out, int64_t in, bool backward) {
+    if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in) || T > 256) return false;
+    return out * in >= (backward ? std::max<int64_t>(1500000, 130000 * T - 6000000) : 1500000 + 38000 * T);
 }
 
 inline size_t bf16_bytes(int64_t rows, int64_t cols) {
@@ -714,7 +721,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
     // (the slices go where the copy of the weight would be)
     char* const slices = reinterpret_cast<char*>(ws) + L.Wb;
     const size_t slices_room = ws_bytes - L.Wb;
-    if (!save_weff && use_nf4_tile(T, out, in) && slices_that_fit(T, out, slices_room) >= 1) {
+    if (!save_weff && use_nf4_tile(T, out, in, false) && slices_that_fit(T, out, slices_room) >= 1) {
         memset(&p, 0, sizeof(p));  // U = s x B^T
         p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
         p.B[0] = bf16_operand(B, ld_B, (int)r, (int)in);
@@ -861,7 +868,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         const int64_t ldw = saved ? ld_saved : L.ldw;
         // a few hundred tokens: Z and dx straight from the codes, their slices where the copies of W and P would be
         const size_t room = ws_bytes - L.Wb;
-        const bool tile = !saved && use_nf4_tile(T, out, in) && slices_that_fit(T, r, room) >= 1 &&
+        const bool tile = !saved && use_nf4_tile(T, out, in, true) && slices_that_fit(T, r, room) >= 1 &&
                           slices_that_fit(T, in, room) >= 2;
         if (tile) {
             memset(&p, 0, sizeof(p));

@@ -38,3 +38,38 @@ def test_contractions_around_the_stages(tile, K):
     assert G.max_err_over_rms(O.bf16_to_f64(G.bf16_host(y)), y_ref) <= TOL
     assert G.max_err_over_rms(O.bf16_to_f64(G.bf16_host(dx)), dx_ref) <= TOL
     assert G.max_err_over_rms(dB.cpu().numpy().astype(np.float64), dB_ref) <= TOL + few
+
+
+@pytest.mark.parametrize("T,out,inp,r", [(33, 300, 64 * n - cut, 24) for n in range(1, 7) for cut in (0, 40) if n > 1 or not cut] +
+                         [(64, 13900, 1100, 72), (64, 13824, 1024, 64), (256, 13900, 1720, 136), (128, 13824, 1536, 128)])
+def test_fed_by_the_expansion(T, out, inp, r):
+    """Products that expand the codes (a few hundred tokens): slices of one to seven k-tiles, and of ten to fourteen, where the feeding
+    waves have a form without branches for k-tiles that are neither cut nor the first of a segment.  Against the products on expanded
+    weights, which round the same operands: sums in another order, so a bf16 result moves by one step at most, and rarely."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + inp)
+
+    def bf16(rows, cols, sigma):
+        return (torch.randn((rows, G.rup(cols, 8)), generator=g, device="cuda") * sigma).bfloat16()[:, :cols]
+    Wq = L.nf4_quantize(torch.randn((out, G.rup(inp, 4)), generator=g, device="cuda")[:, :inp] * 0.02)
+    Pq = L.nf4_quantize(torch.randn((out, G.rup(r, 4)), generator=g, device="cuda")[:, :r] * out ** -0.5)
+    x, dy, B = bf16(T, inp, 1.0), bf16(T, out, 1e-2), bf16(r, inp, 2e-2)
+    got = []
+    try:
+        for path in (L.PATH_AUTO, L.PATH_PREPASS):
+            L.set_path(path)
+            y, dx = G.bf16_empty(T, out, fill=float("nan")), G.bf16_empty(T, inp, fill=float("nan"))
+            dB = torch.full((r, inp), float("nan"), device="cuda")
+            L.loqt_linear_fwd(x, Wq, Pq, B, 0.5, y, G.workspace(L.OP_FWD, T, out, inp, r))
+            L.loqt_linear_bwd(dy, x, Wq, Pq, B, 0.5, dx, dB, False, G.workspace(L.OP_BWD, T, out, inp, r))
+            got.append((y.float(), dx.float(), dB))
+    finally:
+        L.set_path(L.PATH_AUTO)
+    # y, dx: a step of the result is up to 2^-7 of it, and U or Z may round to the other side too, which moves a small term of the sum.
+    # dB is not rounded, but a step of one entry of Z, 2^-8 of it, times an entry of x goes into it: both up to 4.5 times their
+    # rms, and rms(dB) = sqrt(T) rms(Z) rms(x)
+    for (a, b), own, rest in zip(zip(*got), (2.0 ** -7, 2.0 ** -7, 0.0), (2.0 ** -9, 2.0 ** -9, 2.0 ** -8 * 4.5 ** 2 / T ** 0.5)):
+        assert torch.isfinite(a).all()
+        assert ((a - b).abs() <= own * b.abs() + rest * b.pow(2).mean().sqrt()).all()
