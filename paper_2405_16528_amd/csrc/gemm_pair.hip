@@ -203,7 +203,10 @@ hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int e
 
 hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, bool b_rc, const GemmParams& fold, hipStream_t st) {
     const NtPlan plan = product_plan(z);
-    if (plan.tile == NT_64x64 && small_tile(weight_tile(epi, fold))) {
+    // (a fold that is ahead on 256x256 tiles by a few per cent only still shares: it has to fill the chip with them, at some rank)
+    const int64_t t256 = ((fold.M + 255) / 256) * (int64_t)((fold.N + 255) / 256);
+    const bool alone = weight_tile(epi, fold) == NT_256x256 && t256 >= 216 && t256 <= 256 && fold.A[0].K > (epi == EPI_FOLD ? 128 : 512);
+    if (plan.tile == NT_64x64 && !alone && (g_nt_tile_override == 0 || small_tile(weight_tile(epi, fold)))) {
         // (a compute unit holds two of either here: 64x128 as long as 128x128 leave units idle)
         const int tb = ((fold.M + 127) / 128) * (int64_t)((fold.N + 127) / 128) <= 192 ? NT_64x128 : NT_128x128;
         TimedLaunch tl(slot, st);

@@ -37,11 +37,13 @@ struct MergeGroupParams {
 };
 static_assert(sizeof(MergeGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
 
+template <int BM>
+constexpr int GROUP_BN = BM == 256 ? 256 : 128;
 template <int BM, bool ANF4>
-using GroupCfg = NtCfg<BM, 128, 2, ANF4>;
+using GroupCfg = NtCfg<BM, GROUP_BN<BM>, 2, ANF4, BM == 256 ? 8 : 4>;
 
 template <int BM, bool ANF4>
-__global__ __launch_bounds__(256, (GroupCfg<BM, ANF4>::PER_CU)) void nt_merge_grouped_kernel(const MergeGroupParams g) {
+__global__ __launch_bounds__((GroupCfg<BM, ANF4>::THREADS), (GroupCfg<BM, ANF4>::THREADS / 256 * GroupCfg<BM, ANF4>::PER_CU)) void nt_merge_grouped_kernel(const MergeGroupParams g) {
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     int li = 0;
     while (li + 1 < g.n && j >= g.it[li].per_xcd_end) ++li;  // wave-uniform
@@ -60,7 +62,7 @@ __global__ __launch_bounds__(256, (GroupCfg<BM, ANF4>::PER_CU)) void nt_merge_gr
     p.w_ld = it.w_ld, p.w_cols = it.w_cols;
     p.w_bf16 = nullptr, p.w_bf16_ld = 0, p.w_f32 = nullptr, p.w_f32_ld = 0, p.e_out = nullptr, p.e_ld = 0;
     const int per_xcd = it.per_xcd_end - start;
-    nt_gemm_tile<BM, 128, EPI_MERGE, false, true, 2, false, ANF4>(p, xcd * per_xcd + (j - start), 0);
+    nt_gemm_tile<BM, GROUP_BN<BM>, EPI_MERGE, false, true, 2, false, ANF4, false, GroupCfg<BM, ANF4>::THREADS / 64>(p, xcd * per_xcd + (j - start), 0);
 }
 
 // g: null only raises the kernel's LDS size
@@ -77,21 +79,21 @@ hipError_t launch_grouped(MergeGroupParams* g, hipStream_t st) {
     int per_xcd_total = 0;
     for (int i = 0; i < g->n; ++i) {
         MergeGroupItem& it = g->it[i];
-        const int tiles = ((it.M + BM - 1) / BM) * ((it.N + 127) / 128);
+        const int tiles = ((it.M + BM - 1) / BM) * ((it.N + GROUP_BN<BM> - 1) / GROUP_BN<BM>);
         per_xcd_total += (tiles + 7) / 8;
         it.per_xcd_end = per_xcd_total;
     }
-    hipLaunchKernelGGL((nt_merge_grouped_kernel<BM, ANF4>), dim3((unsigned)per_xcd_total * 8u), dim3(256), (GroupCfg<BM, ANF4>::SMEM), st, *g);
+    hipLaunchKernelGGL((nt_merge_grouped_kernel<BM, ANF4>), dim3((unsigned)per_xcd_total * 8u), dim3((GroupCfg<BM, ANF4>::THREADS)), (GroupCfg<BM, ANF4>::SMEM), st, *g);
     return hipGetLastError();
 }
 
-// (256x128 tiles, and merges on 256x256, were behind wherever they were timed: loqt_set_tile alone selects them.)
+// (256x128 tiles were behind wherever they were timed: loqt_set_tile alone selects them.)
 template <int EPI, bool BRC>
 hipError_t launch_sized(const GemmParams& p, hipStream_t st) {
     constexpr bool HEAVY = EPI == EPI_COMP || EPI == EPI_FOLD_F32;  // small tiles only
     switch (weight_tile(EPI, p)) {
         case NT_256x256:
-            if constexpr (!HEAVY) return launch_nt<256, 256, EPI, false, BRC>(p, st);
+            if constexpr (!HEAVY) return launch_nt<256, 256, EPI, false, BRC, 2, false, false, false, 8>(p, st);
             break;
         case NT_256x128:
             if constexpr (!HEAVY) return launch_nt<256, 128, EPI, false, BRC>(p, st);
@@ -108,7 +110,8 @@ template <int EPI, bool BRC>
 hipError_t prepare_sized() {
     hipError_t e;
     if constexpr (EPI != EPI_COMP && EPI != EPI_FOLD_F32) {
-        if ((e = ensure_attr<256, 256, EPI, false, BRC>()) != hipSuccess) return e;
+        if ((e = ensure_attr<256, 256, EPI, false, BRC, 2, false, false, false, 8>()) != hipSuccess) return e;
+        if ((e = ensure_attr<256, 256, EPI, false, BRC, 2, true, false, false, 8>()) != hipSuccess) return e;
         if ((e = ensure_attr<256, 128, EPI, false, BRC>()) != hipSuccess) return e;
     }
     if constexpr (EPI != EPI_FOLD_F32)
@@ -124,7 +127,7 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
     MergeGroupParams g;
     memset(&g, 0, sizeof(g));
     g.n = n;
-    int64_t tiles = 0, rank = 0;  // of 128x128; the largest
+    int64_t tiles = 0, tiles256 = 0, rank = 0;  // of 128x128, of 256x256; the largest
     for (int i = 0; i < n; ++i) {
         const MergeGroupLayer& l = layers[i];
         MergeGroupItem& it = g.it[i];
@@ -132,6 +135,7 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
         it.w_codes = l.w_codes, it.w_absmax = l.w_absmax, it.out_codes = l.out_codes, it.out_absmax = l.out_absmax;
         it.w_ld = l.w_ld, it.M = l.out, it.N = (int)l.w_ld, it.K = l.r, it.w_cols = l.in, it.alpha = l.s;
         tiles += ((l.out + 127) / 128) * ((l.w_ld + 127) / 128);
+        tiles256 += ((l.out + 255) / 256) * ((l.w_ld + 255) / 256);
         rank = std::max<int64_t>(rank, l.r);
         if (l.A_absmax && (l.r > A_CODES_TILES * BK || !layers[0].A_absmax)) return hipErrorInvalidValue;
         if (!l.A_absmax && layers[0].A_absmax) return hipErrorInvalidValue;
@@ -152,6 +156,10 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
     //   768   26.0 / 24.0   32.3 / 28.4   41.2 / 37.8   40.9 / 38.4   43.3 / 42.7   43.6 / 42.6   47.1 / 47.4
     //   1024  27.8 / 26.3   36.1 / 32.7   46.6 / 43.5   46.2 / 44.0   49.1 / 49.4   50.2 / 49.7   54.4 / 55.6
     // 768 are two rounds of 64x128, three to a unit; a third one of a few tiles is made up for where the rank is small.
+    // 256x256 where a high rank makes the loop count and the last round of 256 tiles is nearly full.  The call, us, 128x128 / 256x256, by
+    // rounds: 518 / 508 (rank 1024, 12.06), 784 / 723 (1024, 18.9), 289 / 277 (800, 7.8), 238 / 230 (768, 6.75), 140 / 139 (512, 4.7),
+    // 331 / 330 (512, 12.06); 239 / 241 (256, 12.06), 153 / 155 (128, 9.1); 101 / 109 (512, 3.06), 74 / 78 (448, 2.3).
+    if (g_nt_tile_override == 0 && rank >= 512 && tiles256 >= 1024 && tiles256 * 100 >= (tiles256 + 255) / 256 * 256 * 92) return launch_grouped<256, false>(&g, st);
     return g_nt_tile_override == 0 && (tiles <= 384 || (tiles > 512 && tiles <= (rank <= 384 ? 800 : 768))) ? launch_grouped<64, false>(&g, st) : launch_grouped<128, false>(&g, st);
 }
 
@@ -168,12 +176,37 @@ hipError_t prepare_weight_kernels() {
     if ((e = ensure_attr<64, 128, EPI_FOLD, false, true, 2, false, true>()) != hipSuccess) return e;
     if ((e = launch_grouped<64, true>(nullptr, nullptr)) != hipSuccess) return e;
     if ((e = launch_grouped<64, false>(nullptr, nullptr)) != hipSuccess) return e;
+    if ((e = launch_grouped<256, false>(nullptr, nullptr)) != hipSuccess) return e;
     return launch_grouped<128, false>(nullptr, nullptr);
 }
 
 int weight_tile(int epi, const GemmParams& p) {
     auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
     if (g_nt_tile_override != 0) return g_nt_tile_override;
+    // One 256x256 tile per compute unit, eight waves, moves the least data per product, but has nothing to hide its first loads and its
+    // last stores behind, which two resident 128x128 work-groups have: it is ahead where its rounds of 256 tiles are nearly full.
+    // Time of the launch, 256x256 / 128x128, by tiles of 256x256 (2048 rows):
+    //                      160    192    224    256    320    384    448    512    640    768
+    //   fold, rank 64      1.03   0.97   0.93   0.88   1.23   1.12   1.00   1.16   1.08   0.98
+    //         256          0.98   0.97   0.88   0.87   1.21   1.08   0.98   1.07   1.02   0.92
+    //         512          0.98   0.97   0.89   0.89   1.22   1.07   0.97   1.04   1.00   0.89
+    //         1024         0.95   0.96   0.86   0.87   1.16   1.05   0.91   0.94   0.94   0.83
+    //   merge, rank 64     1.17   1.07   0.95   0.91   1.20   1.09   0.97   0.95   1.03   0.94
+    //         256          1.09   1.01   0.93   0.90   1.15   1.06   0.94   0.90   0.98   0.90
+    //         512          1.07   0.95   0.90   0.86   1.15   1.05   0.92   0.89   0.97   0.90
+    //         1024         1.00   0.97   0.87   0.86   1.16   1.04   0.94   0.86   0.98   0.86
+    //   unquantised merge, rank 256 / 1024
+    //                      1.07 / 1.02   0.99 / 0.98   0.96 / 0.89   0.95 / 0.91   1.16   1.10 / 1.06   1.06 / 0.98   1.16 / 0.97   1.07 / 0.96   0.98 / 0.86
+    // and, us, 11008 x 4096, rank 1024 (688 tiles): fold 114 -> 100, merge 120 -> 111; 4096 x 4096 (256): merge 46 -> 39.8; 2048 x 5461,
+    // rank 512 (176): fold 22.4 -> 21.5.  (With four waves the merge was never ahead, the fold in one round, 36.2 against 35.4.)
+    if (epi == EPI_FOLD || epi == EPI_MERGE || epi == EPI_ACC_BF16) {
+        const int64_t t256 = tiles(256, 256), rounds = (t256 + 255) / 256;
+        const int K = p.A[0].K;
+        const int64_t least = rounds == 1 ? (epi == EPI_FOLD ? (K >= 256 ? 160 : 192) : K >= 512 ? 192 : 208)
+                              : epi == EPI_MERGE || K > 768 ? rounds * (K >= 256 ? 208 : 220)
+                                                            : rounds * 256 + 1;  // (never: folds of low rank are bound by their stores)
+        if (t256 >= least) return NT_256x256;
+    }
     // 64x128 tiles on two stages, of which a compute unit holds three: where 128x128, two to a unit, leave room for the 64x128
     // to take no more rounds.  Time of the launch, 64x128 / 128x128, ranks of 96, 300 and 768, by tiles of 128x128:
     //                        208 to 384       448, 512         560, 620        680, 760
@@ -184,18 +217,6 @@ int weight_tile(int epi, const GemmParams& p) {
     // (With three stages and two to a unit they took 1.03 to 1.28 of the time of two stages and three.)
     const int64_t t = tiles(128, 128);
     if (epi != EPI_FOLD_F32 && (t <= 384 || (t > 512 && t <= 640))) return NT_64x128;
-    // One 256x256 tile per compute unit has the best ratio of MFMA work to LDS traffic, but nothing to hide its prologue and
-    // epilogue behind, which two resident 128x128 work-groups have.  So it is ahead only where a product of some length fills
-    // the chip in one round, with the epilogues that are short.  Time of the launch, us, 256x256 / 128x128, by tiles of 256x256:
-    //                              fold, rank 96    300            512            1024           unquantised merge, rank 96 and 768
-    //   192  (4096 x 3072)         20.4 / 17.9      24.9 / 22.6    26.3 / 23.6    35.3 / 33.5    17.9 / 15.8   28.9 / 27.2
-    //   220  (5632 x 2560)         20.6 / 20.8      24.8 / 26.4    26.6 / 27.6    36.4 / 40.1    18.7 / 18.0   30.8 / 33.3
-    //   256  (4096 x 4096)         21.3 / 20.8      25.5 / 26.3    27.7 / 28.6    37.6 / 41.3    21.0 / 19.9   34.6 / 35.5
-    //   384  (8192 x 3072)         36.0 / 28.4      44.2 / 36.0    48.3 / 39.4    67.7 / 58.9    33.4 / 27.3   56.2 / 48.9
-    //   688  (11008 x 4096)        52.7 / 45.9      66.2 / 60.2    72.5 / 66.1    102.8 / 102.2  50.5 / 45.1   86.9 / 87.0
-    //   1080 (13824 x 5120)        83.1 / 66.6      104.5 / 88.8   116.3 / 102.3  167.8 / 159.4  78.7 / 65.0   138.6 / 133.2
-    const int64_t t256 = tiles(256, 256);
-    if (t256 >= 216 && t256 <= 256 && ((epi == EPI_FOLD && p.A[0].K > 128) || (epi == EPI_ACC_BF16 && p.A[0].K > 512))) return NT_256x256;
     return NT_128x128;
 }
 

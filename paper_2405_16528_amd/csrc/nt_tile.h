@@ -58,20 +58,21 @@ constexpr int ROWB = 128;  // bytes of one LDS row (64 bf16)
 // are on their way (a few hundred cycles of look-ups per work-group at rank 256), and the loop loads B alone.
 constexpr int A_CODES_TILES = 4;
 
-template <int BM, int BN, int NS = 2, bool ANF4 = false>
+template <int BM, int BN, int NS = 2, bool ANF4 = false, int NW = 4>
 struct NtCfg {
-    static constexpr int WTM = BM / 2, WTN = BN / 2;   // wave tile
+    static constexpr int THREADS = NW * 64, WAVES_N = NW / 2;  // that multiply; waves along the columns of the tile
+    static constexpr int WTM = BM / 2, WTN = BN / WAVES_N;     // wave tile
     static constexpr int TM = WTM / 16, TN = WTN / 16; // 16x16 tiles per wave
     static constexpr int ASTAGE = ANF4 ? 0 : BM * ROWB; // bytes of A in a stage
     static constexpr int STAGE = ASTAGE + BN * ROWB;
-    static constexpr int NCHA = ASTAGE / 4096;         // 16-byte chunks per thread per stage that belong to A
-    static constexpr int NCHB = BN / 32;               // and to B
+    static constexpr int NCHA = ASTAGE / (THREADS * 16);         // 16-byte chunks per thread per stage that belong to A
+    static constexpr int NCHB = BN * ROWB / (THREADS * 16);               // and to B
     static constexpr int NCH = NCHA + NCHB;
     static constexpr int PANEL = ANF4 ? A_CODES_TILES * BM * ROWB : 0;
     static constexpr int HEAD = PANEL + (ANF4 ? BM * BN / 2 : 0);  // the panel and the old codes of the tile, ahead of the ring
     static constexpr int EPITCH = WTN * 2 + 16;        // staging pitch of the bf16 epilogue: 16-byte rows, no bank conflicts beyond two lanes
     static constexpr int SMEM = HEAD + NS * STAGE;     // NS stages: tiles kt .. kt+NS-1 are in LDS or in flight
-    static_assert(STAGE >= 4 * 32 * EPITCH || HEAD >= 4 * 32 * EPITCH, "room to stage 32 rows of each wave");
+    static_assert(STAGE >= NW * 32 * EPITCH || HEAD >= NW * 32 * EPITCH, "room to stage 32 rows of each wave");
     static constexpr int PER_CU = SMEM <= 52 * 1024 ? 3 : SMEM <= 78 * 1024 ? 2 : 1;  // work-groups that share a compute unit
 };
 
@@ -88,9 +89,14 @@ __device__ __forceinline__ float max_over_lane_groups(float a) {
 // split: slice of the contraction (EPI_F32_SPLITK), else 0.
 // NOTAIL: every K segment is a whole number of k-tiles, so no tile has to be cut (cut_tile).
 // LOADERS: eight waves, of which four load.
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
+// NW: waves that multiply, 2 x NW / 2 of them over the tile.  Eight: the 256x256 tiles whose epilogue walks the weight.  The loop is no
+// faster for the second wave on a SIMD, the epilogue is: 28900 cycles with four waves, 13700 with eight (merge), 12300 and 9000
+// (fold), of 65000 to 80000 in all at rank 1024.
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false, int NW = 4>
 __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, const int split) {
-    using Cfg = NtCfg<BM, BN, NS, ANF4>;
+    using Cfg = NtCfg<BM, BN, NS, ANF4, NW>;
+    constexpr int NT = Cfg::THREADS, PASS = NT * 16;  // bytes of one chunk per thread
+    static_assert(NW == 4 || (!LOADERS && !ANF4), "");
     constexpr int TM = Cfg::TM, TN = Cfg::TN, STAGE = Cfg::STAGE, WTM = Cfg::WTM, WTN = Cfg::WTN;
     constexpr bool ENCODES = EPI == EPI_MERGE || EPI == EPI_COMP;
     constexpr bool CODES = EPI == EPI_MERGE || EPI == EPI_FOLD || EPI == EPI_FOLD_F32;  // reads the old 4-bit weight
@@ -107,7 +113,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 
     // (LOADERS: the second four waves load, with the indexes of the first four)
     const int tid = LOADERS ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / Cfg::WAVES_N, wn = wave % Cfg::WAVES_N;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const int frow = lane & 15, g4 = lane >> 4;  // lane = 16 g4 + frow
 
@@ -127,7 +133,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         if (tid >= 64 && tid < 128) nf4_enc_tables_fill(&enc_tables, tid - 64);
     }
     if constexpr (ENCODES || CODES) {
-        level_table[tid] = make_float2(kNf4Levels[tid >> 4], kNf4Levels[tid & 15]);
+        if (NT == 256 || tid < 256) level_table[tid] = make_float2(kNf4Levels[tid >> 4], kNf4Levels[tid & 15]);
     }
 
     // ---- tile of this work-group: contiguous range per XCD, groups of GM tile rows inside
@@ -227,7 +233,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 
     // The lane offsets of a thread's chunks are loop-invariant registers (per K segment) and the tile origin is a scalar
     // pointer that advances by a constant, so a load is one instruction plus scalar bookkeeping and can sit between MFMAs.
-    constexpr int CCPR = BN / 32, CRPP = 256 / CCPR, NCC = BM / CRPP;  // old codes: 16-byte chunks per row, rows per pass, passes
+    constexpr int CCPR = BN / 32, CRPP = NT / CCPR, NCC = BM / CRPP;  // old codes: 16-byte chunks per row, rows per pass, passes
     uint32_t offA[ANF4 ? NCC : Cfg::NCHA], offB[Cfg::NCHB];
     const char *hotA = nullptr, *hotB = nullptr;  // operand bytes of the tile that is loaded next
     int64_t stepA = 0, stepB = 0;
@@ -237,7 +243,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                            int kleft, uint32_t* off, const char*& base, int64_t& step) {
         constexpr bool RC = decltype(rc_tag)::value;
         constexpr int BR = decltype(br_tag)::value;
-        constexpr int NC = BR / 32;
+        constexpr int NC = BR * ROWB / PASS;
         // a tile that lies wholly past the operand's last row (the merge walks the padding columns of the
         // code matrix, which can exceed `in` by more than a tile) reads the operand's first rows instead:
         // its products are never used, and the clamps below then never go negative
@@ -249,12 +255,12 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             const int rlast = orows - 1 - row0;  // rows past the end: any valid row
             const uint32_t kb = NOTAIL || kc * 8 < kleft ? (uint32_t)kc * 16u : 0u;
 #pragma unroll
-            for (int i = 0; i < NC; ++i) off[i] = (uint32_t)min(i * 32 + r0, rlast) * ld2 + kb;
+            for (int i = 0; i < NC; ++i) off[i] = (uint32_t)min(i * (NT / 8) + r0, rlast) * ld2 + kb;
             base = reinterpret_cast<const char*>(optr) + ((int64_t)row0 * old + k0) * 2;
             step = BK * 2;
         } else {
             constexpr int CPR = BR / 8;     // chunks per k row
-            constexpr int KPI = 256 / CPR;  // k rows covered by one pass of the 256 threads
+            constexpr int KPI = NT / CPR;   // k rows covered by one pass of the threads
             const int kq = tid / CPR;
             const int clast = (((orows - 1) >> 3) << 3) - row0;  // columns past the end: any valid chunk
 #pragma unroll
@@ -282,6 +288,8 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     // The swizzle keeps the reads of 16 rows apart.
     auto code_swz = [](int row) { return CCPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
     auto codes_setup = [&]() {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // (else its results are worked out ahead of the loop and copied, or reloaded, in every iteration)
         const uint32_t ldb = (uint32_t)(p.w_ld >> 1);
 #pragma unroll
         for (int i = 0; i < (ANF4 ? NCC : Cfg::NCHA); ++i) {
@@ -330,7 +338,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         const bool isA = n < Cfg::NCHA;
         const int i = isA ? n : n - Cfg::NCHA;
         const uint32_t dst = lds0 + (uint32_t)(stage - smem) + (uint32_t)(wave_s * 1024);
-        direct_load(isA ? offA[i] : offB[i], isA ? hotA : hotB, dst, (uint32_t)((isA ? 0 : Cfg::ASTAGE) + i * 4096));
+        direct_load(isA ? offA[i] : offB[i], isA ? hotA : hotB, dst, (uint32_t)((isA ? 0 : Cfg::ASTAGE) + i * PASS));
     };
     // Tile kt of the range has landed in `stage` by direct loads and ends past its segment's contraction: clears
     // everything from there on, in both operands (what came instead is finite, but the padding of a row need not be).
@@ -338,7 +346,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     auto cut_operand = [&](auto rc_tag, auto br_tag, auto dealt_tag, int kleft, char* tile) {
         constexpr bool RC = decltype(rc_tag)::value;
         constexpr int BR = decltype(br_tag)::value;
-        constexpr int NC = BR / 32;
+        constexpr int NC = BR * ROWB / PASS;
         if constexpr (!RC) {
             const int nv = kleft - 8 * ((tid & 7) ^ kc_swz(dealt_tag, tid >> 3));  // valid elements of this thread's chunk column
             if (nv < 8) {
@@ -347,16 +355,16 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
                 for (int d = 0; d < 4; ++d) keep[d] = 2 * d + 1 < nv ? 0xffffffffu : 2 * d < nv ? 0xffffu : 0u;
 #pragma unroll 1
                 for (int i = 0; i < NC; ++i) {
-                    uint4* q = reinterpret_cast<uint4*>(tile + i * 4096 + tid * 16);
+                    uint4* q = reinterpret_cast<uint4*>(tile + i * PASS + tid * 16);
                     const uint4 v = *q;
                     *q = make_uint4(v.x & keep[0], v.y & keep[1], v.z & keep[2], v.w & keep[3]);
                 }
             }
         } else {
-            constexpr int CPR = BR / 8, KPI = 256 / CPR;
+            constexpr int CPR = BR / 8, KPI = NT / CPR;
 #pragma unroll 1
             for (int i = 0; i < NC; ++i)
-                if (i * KPI + tid / CPR >= kleft) *reinterpret_cast<uint4*>(tile + i * 4096 + tid * 16) = make_uint4(0, 0, 0, 0);
+                if (i * KPI + tid / CPR >= kleft) *reinterpret_cast<uint4*>(tile + i * PASS + tid * 16) = make_uint4(0, 0, 0, 0);
         }
     };
     auto cut_tile = [&](int kt, char* stage) {
@@ -943,7 +951,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
             }
         };
         // columns of the wave from nlast on do not exist
-        const int nlast = p.w_cols - (n0 + (wave_s & 1) * WTN);
+        const int nlast = p.w_cols - (n0 + (wave_s % Cfg::WAVES_N) * WTN);
 #pragma unroll
         for (int i = 0; i < AHEAD - 1; ++i) fetch(i);
 #pragma unroll
@@ -1049,10 +1057,10 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 }
 
 // Work-groups are dealt to the 8 XCDs round-robin by the hardware; each XCD walks a contiguous range of tiles.
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
-__global__ __launch_bounds__(LOADERS ? 512 : 256, (LOADERS ? 2 : 1) * (NtCfg<BM, BN, NS, ANF4>::PER_CU)) void nt_gemm_kernel(const GemmParams p) {
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false, int NW = 4>
+__global__ __launch_bounds__(LOADERS ? 512 : 64 * NW, (LOADERS ? 2 : NW / 4) * (NtCfg<BM, BN, NS, ANF4, NW>::PER_CU)) void nt_gemm_kernel(const GemmParams p) {
     const int per_xcd = gridDim.x >> 3;
-    nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>(p, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), blockIdx.y);
+    nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS, NW>(p, (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), blockIdx.y);
 }
 
 // 128x128 tiles: with waves of their own for the loads a compute unit holds one work-group, without two.  One is enough, and faster, while
@@ -1065,29 +1073,29 @@ bool one_to_a_unit(const GemmParams& p) {
 }
 
 // the kernel's LDS size has to be raised above the default once per process (first launch, or loqt_prepare)
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false, int NW = 4>
 hipError_t ensure_attr() {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, NtCfg<BM, BN, NS, ANF4>::SMEM);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS, NW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, NtCfg<BM, BN, NS, ANF4, NW>::SMEM);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     return hipSuccess;
 }
 
-template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false>
+template <int BM, int BN, int EPI, bool ARC, bool BRC, int NS = 2, bool NOTAIL = false, bool ANF4 = false, bool LOADERS = false, int NW = 4>
 hipError_t launch_nt(const GemmParams& p, hipStream_t st) {
-    if constexpr (BM == 256 && (EPI == EPI_BF16 || (EPI == EPI_F32_SPLITK && BN == 128)) && !NOTAIL) {
-        // 256-row tiles of the plain products have a variant for contractions that are whole k-tiles
-        if (p.A[0].K % BK == 0 && p.A[1].K % BK == 0) return launch_nt<BM, BN, EPI, ARC, BRC, NS, true, ANF4, LOADERS>(p, st);
+    if constexpr (BM == 256 && (EPI == EPI_BF16 || (EPI == EPI_F32_SPLITK && BN == 128) || NW == 8) && !NOTAIL) {
+        // 256-row tiles have a variant for contractions that are whole k-tiles
+        if (p.A[0].K % BK == 0 && p.A[1].K % BK == 0) return launch_nt<BM, BN, EPI, ARC, BRC, NS, true, ANF4, LOADERS, NW>(p, st);
     }
-    hipError_t e0 = ensure_attr<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>();
+    hipError_t e0 = ensure_attr<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS, NW>();
     if (e0 != hipSuccess) return e0;
     const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN + (p.Nx + BN - 1) / BN);
     dim3 grid((tiles + 7) / 8 * 8, EPI == EPI_F32_SPLITK ? p.splits : 1);
-    hipLaunchKernelGGL((nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS>), grid, dim3(LOADERS ? 512 : 256), (NtCfg<BM, BN, NS, ANF4>::SMEM), st, p);
+    hipLaunchKernelGGL((nt_gemm_kernel<BM, BN, EPI, ARC, BRC, NS, NOTAIL, ANF4, LOADERS, NW>), grid, dim3(LOADERS ? 512 : 64 * NW), (NtCfg<BM, BN, NS, ANF4, NW>::SMEM), st, p);
     return hipGetLastError();
 }
 
