@@ -6,8 +6,8 @@
 // dozen work-groups with long contractions) leave most of the chip idle.  One grid over the tiles of both: the first work-groups
 // belong to the product with the longer tiles, the others follow it onto whatever compute unit is free.  Both keep the slices
 // they have alone, and but for the fold, which has two work-groups to a unit here and a rule for that in launch_z_fold, their tiles.
-// Any tile sums k in the same order, so the results are the same bits.  Only tiles of which a compute unit holds two take part;
-// larger products run for hundreds of microseconds, and their tiles have a compute unit and its registers to themselves.
+// Any tile sums k in the same order, so the results are the same bits.  Only tiles of up to 128x128 take
+// part; larger products run for hundreds of microseconds.
 #include <string.h>
 
 #include <algorithm>
@@ -18,16 +18,16 @@ namespace loqt {
 
 namespace {
 
-template <int BM_, int BN_, int EPI_, bool ARC_, bool BRC_, int NS_>
+template <int BM_, int BN_, int EPI_, bool ARC_, bool BRC_, int NS_, bool LOADERS_ = false>
 struct Part {
-    static constexpr int BM = BM_, BN = BN_, EPI = EPI_, NS = NS_, SMEM = NtCfg<BM, BN, NS>::SMEM;
-    static constexpr bool ARC = ARC_, BRC = BRC_;
-    static_assert(NtCfg<BM, BN, NS>::PER_CU >= 2, "");
+    static constexpr int BM = BM_, BN = BN_, EPI = EPI_, NS = NS_, SMEM = NtCfg<BM, BN, NS>::SMEM, PER_CU = NtCfg<BM, BN, NS>::PER_CU;
+    static constexpr bool ARC = ARC_, BRC = BRC_, LOADERS = LOADERS_;
+    static_assert(PER_CU >= 2 || LOADERS, "");
     static int grid(const GemmParams& p) { return (((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) + 7) / 8 * 8; }
     // `b`: work-group of this part; `per`: of them belong to a slice (a multiple of 8, so that b % 8 is the XCD)
     static __device__ __forceinline__ void run(const GemmParams& p, int b, int per) {
         const int split = EPI == EPI_F32_SPLITK ? b / per : 0, r = b - split * per;
-        nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS>(p, (r & 7) * (per >> 3) + (r >> 3), split);
+        nt_gemm_tile<BM, BN, EPI, ARC, BRC, NS, false, false, LOADERS>(p, (r & 7) * (per >> 3) + (r >> 3), split);
     }
 };
 template <int EPI, bool ARC, bool BRC>
@@ -37,12 +37,25 @@ using T64x128 = Part<64, 128, EPI, ARC, BRC, 3>;
 template <int EPI, bool ARC, bool BRC>
 using T128x128 = Part<128, 128, EPI, ARC, BRC, 2>;
 
-template <class A, class B>
-constexpr int pair_smem = A::SMEM > B::SMEM ? A::SMEM : B::SMEM;
+// with waves of their own for the loads (nt_tile.h), as they have alone
+template <int EPI, bool ARC, bool BRC>
+using L64x64 = Part<64, 64, EPI, ARC, BRC, 4, true>;
+template <int EPI, bool ARC, bool BRC>
+using L64x128 = Part<64, 128, EPI, ARC, BRC, 3, true>;
+template <int EPI, bool ARC, bool BRC>
+using L128x128 = Part<128, 128, EPI, ARC, BRC, 3, true>;
 
 template <class A, class B>
-__global__ __launch_bounds__(256, 2) void nt_pair_kernel(const GemmParams a, const GemmParams b, const int a_per, const int a_all,
+constexpr int pair_smem = A::SMEM > B::SMEM ? A::SMEM : B::SMEM;
+template <class A, class B>
+constexpr int pair_threads = A::LOADERS ? 512 : 256;
+template <class A, class B>
+constexpr int pair_per_simd = (A::LOADERS ? 2 : 1) * (A::PER_CU >= 2 && B::PER_CU >= 2 ? 2 : 1);  // waves
+
+template <class A, class B>
+__global__ __launch_bounds__((pair_threads<A, B>), (pair_per_simd<A, B>)) void nt_pair_kernel(const GemmParams a, const GemmParams b, const int a_per, const int a_all,
                                                          const int b_per) {
+    static_assert(A::LOADERS == B::LOADERS, "");
     if ((int)blockIdx.x < a_all) A::run(a, blockIdx.x, a_per);
     else B::run(b, blockIdx.x - a_all, b_per);
 }
@@ -66,19 +79,22 @@ hipError_t launch(const GemmParams* a, const GemmParams* b, hipStream_t st) {
     if (e != hipSuccess || a == nullptr) return e;
     const int a_per = A::grid(*a), b_per = B::grid(*b);
     const int a_all = a_per * (A::EPI == EPI_F32_SPLITK ? a->splits : 1), b_all = b_per * (B::EPI == EPI_F32_SPLITK ? b->splits : 1);
-    hipLaunchKernelGGL((nt_pair_kernel<A, B>), dim3(a_all + b_all), dim3(256), (pair_smem<A, B>), st, *a, *b, a_per, a_all, b_per);
+    hipLaunchKernelGGL((nt_pair_kernel<A, B>), dim3(a_all + b_all), dim3(pair_threads<A, B>), (pair_smem<A, B>), st, *a, *b, a_per, a_all, b_per);
     return hipGetLastError();
 }
 
-// dx on tile `ta`, the gradient on tile `tb` (fp32 slices, or, BF16, straight to its destination)
+// dx on tile `ta`, the gradient on tile `tb` (fp32 slices, or, BF16, straight to its destination).  Waves of their own for the loads
+// but beside 128x128 tiles that a unit has to share (`crowded`).
 template <int EPI_B>
-hipError_t dx_gradient(int ta, int tb, const GemmParams* a, const GemmParams* b, hipStream_t st) {
-    using B64 = T64x64<EPI_B, true, true>;
-    using B128 = T64x128<EPI_B, true, true>;
+hipError_t dx_gradient(int ta, int tb, bool crowded, const GemmParams* a, const GemmParams* b, hipStream_t st) {
+    using B64 = L64x64<EPI_B, true, true>;
+    using B128 = L64x128<EPI_B, true, true>;
     const bool wide = tb == NT_64x128;
-    if (ta == NT_64x64) return wide ? launch<T64x64<EPI_BF16, false, true>, B128>(a, b, st) : launch<T64x64<EPI_BF16, false, true>, B64>(a, b, st);
-    if (ta == NT_64x128) return wide ? launch<T64x128<EPI_BF16, false, true>, B128>(a, b, st) : launch<T64x128<EPI_BF16, false, true>, B64>(a, b, st);
-    return wide ? launch<T128x128<EPI_BF16, false, true>, B128>(a, b, st) : launch<T128x128<EPI_BF16, false, true>, B64>(a, b, st);
+    if (ta == NT_64x64) return wide ? launch<L64x64<EPI_BF16, false, true>, B128>(a, b, st) : launch<L64x64<EPI_BF16, false, true>, B64>(a, b, st);
+    if (ta == NT_64x128) return wide ? launch<L64x128<EPI_BF16, false, true>, B128>(a, b, st) : launch<L64x128<EPI_BF16, false, true>, B64>(a, b, st);
+    if (!crowded) return wide ? launch<L128x128<EPI_BF16, false, true>, B128>(a, b, st) : launch<L128x128<EPI_BF16, false, true>, B64>(a, b, st);
+    using A = T128x128<EPI_BF16, false, true>;
+    return wide ? launch<A, T64x128<EPI_B, true, true>>(a, b, st) : launch<A, T64x64<EPI_B, true, true>>(a, b, st);
 }
 
 // Z (bf16 or fp32 slices, always 64x64 tiles) and the fold on tile `tb`
@@ -176,7 +192,13 @@ hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int e
     const int tb = gradient_tile(epi, g);
     if (small_tile(plan.tile) && plan.splits == 1 && (tb == NT_64x64 || tb == NT_64x128)) {
         TimedLaunch tl(slot_dx, st);
-        return epi == EPI_BF16 ? dx_gradient<EPI_BF16>(plan.tile, tb, &dx, &g, st) : dx_gradient<EPI_F32_SPLITK>(plan.tile, tb, &dx, &g, st);
+        // 128x128 tiles with waves of their own for the loads have a unit to themselves, and so has every work-group of the gradient
+        // then: only where all of both find one (4096 x 768 x 2048 with a gradient of 256 x 768 x 4096 in 240 work-groups 25.7 us in twos,
+        // 29 one by one).
+        const int gw = tb == NT_64x64 ? 64 : 128;
+        const int64_t gradient = (int64_t)((g.M + 63) / 64) * ((g.N + gw - 1) / gw), dxs = (int64_t)((dx.M + 127) / 128) * ((dx.N + 127) / 128);
+        const bool crowded = (dxs + 7) / 8 + (gradient + 7) / 8 * (epi == EPI_F32_SPLITK ? g.splits : 1) > 32;
+        return epi == EPI_BF16 ? dx_gradient<EPI_BF16>(plan.tile, tb, crowded, &dx, &g, st) : dx_gradient<EPI_F32_SPLITK>(plan.tile, tb, crowded, &dx, &g, st);
     }
     hipError_t e = launch_gemm_nt(slot_dx, EPI_BF16, false, true, dx, st, &plan);
     if (e != hipSuccess) return e;
@@ -188,8 +210,8 @@ hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, boo
     const NtPlan plan = product_plan(z);
     // (a fold that is ahead on 256x256 tiles by a few per cent only still shares: it has to fill the chip with them, at some rank)
     const int64_t t256 = ((fold.M + 255) / 256) * (int64_t)((fold.N + 255) / 256);
-    const bool alone = weight_tile(epi, fold) == NT_256x256 && t256 >= 216 && t256 <= 256 && fold.A[0].K > (epi == EPI_FOLD ? 128 : 512);
-    if (plan.tile == NT_64x64 && !alone && (g_nt_tile_override == 0 || small_tile(weight_tile(epi, fold)))) {
+    const bool alone = weight_tile(epi, b_rc, fold) == NT_256x256 && t256 >= 216 && t256 <= 256 && fold.A[0].K > (epi == EPI_FOLD ? 128 : 512);
+    if (plan.tile == NT_64x64 && !alone && (g_nt_tile_override == 0 || small_tile(weight_tile(epi, b_rc, fold)))) {
         // (a compute unit holds two of either here: 64x128 as long as 128x128 leave units idle)
         const int tb = ((fold.M + 127) / 128) * (int64_t)((fold.N + 127) / 128) <= 192 ? NT_64x128 : NT_128x128;
         TimedLaunch tl(slot, st);
@@ -225,8 +247,10 @@ hipError_t prepare_pair_kernels() {
     if ((e = launch_copy<T64x64<EPI_F32_SPLITK, false, false>>(nullptr, nullptr, nullptr)) != hipSuccess) return e;
     for (int ta : {NT_64x64, NT_64x128, NT_128x128})
         for (int tb : {NT_64x64, NT_64x128}) {
-            if ((e = dx_gradient<EPI_BF16>(ta, tb, nullptr, nullptr, nullptr)) != hipSuccess) return e;
-            if ((e = dx_gradient<EPI_F32_SPLITK>(ta, tb, nullptr, nullptr, nullptr)) != hipSuccess) return e;
+            for (bool crowded : {false, true}) {
+                if ((e = dx_gradient<EPI_BF16>(ta, tb, crowded, nullptr, nullptr, nullptr)) != hipSuccess) return e;
+                if ((e = dx_gradient<EPI_F32_SPLITK>(ta, tb, crowded, nullptr, nullptr, nullptr)) != hipSuccess) return e;
+            }
         }
     for (int tb : {NT_64x128, NT_128x128})
         for (int k = 0; k < 3; ++k) {
