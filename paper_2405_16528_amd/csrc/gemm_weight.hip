@@ -91,7 +91,7 @@ hipError_t launch_grouped(MergeGroupParams* g, hipStream_t st) {
 template <int EPI, bool BRC>
 hipError_t launch_sized(const GemmParams& p, hipStream_t st) {
     constexpr bool HEAVY = EPI == EPI_COMP || EPI == EPI_FOLD_F32;  // small tiles only
-    switch (weight_tile(EPI, p)) {
+    switch (weight_tile(EPI, BRC, p)) {
         case NT_256x256:
             if constexpr (!HEAVY) return launch_nt<256, 256, EPI, false, BRC, 2, false, false, false, 8>(p, st);
             break;
@@ -180,7 +180,7 @@ hipError_t prepare_weight_kernels() {
     return launch_grouped<128, false>(nullptr, nullptr);
 }
 
-int weight_tile(int epi, const GemmParams& p) {
+int weight_tile(int epi, bool b_rc, const GemmParams& p) {
     auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
     if (g_nt_tile_override != 0) return g_nt_tile_override;
     // One 256x256 tile per compute unit, eight waves, moves the least data per product, but has nothing to hide its first loads and its
@@ -197,15 +197,19 @@ int weight_tile(int epi, const GemmParams& p) {
     //         1024         1.00   0.97   0.87   0.86   1.16   1.04   0.94   0.86   0.98   0.86
     //   unquantised merge, rank 256 / 1024
     //                      1.07 / 1.02   0.99 / 0.98   0.96 / 0.89   0.95 / 0.91   1.16   1.10 / 1.06   1.06 / 0.98   1.16 / 0.97   1.07 / 0.96   0.98 / 0.86
-    // and, us, 11008 x 4096, rank 1024 (688 tiles): fold 114 -> 100, merge 120 -> 111; 4096 x 4096 (256): merge 46 -> 39.8; 2048 x 5461,
+    // With B stored rows x K (the projection on the input side) about 0.03 more each: merge, rank 256, 416 to 704 tiles 0.93 to 1.02, fold,
+    // rank 512, 160 to 192 tiles 1.00, 5461 x 2048 20.6 -> 21.4.  And not where the larger tiles are padded by more than 4 % beyond
+    // the smaller ones (merge, 1152 x 11378, rank 192: 22.8 -> 29.9; 1152 x 12984, rank 896: 50.6 -> 54.1) or the contraction is
+    // shorter than a k-tile (merge, 1600 x 8768, rank 8: 23.4 -> 28.9).
+    // And, us, 11008 x 4096, rank 1024 (688 tiles): fold 114 -> 100, merge 120 -> 111; 4096 x 4096 (256): merge 46 -> 39.8; 2048 x 5461,
     // rank 512 (176): fold 22.4 -> 21.5.  (With four waves the merge was never ahead, the fold in one round, 36.2 against 35.4.)
     if (epi == EPI_FOLD || epi == EPI_MERGE || epi == EPI_ACC_BF16) {
         const int64_t t256 = tiles(256, 256), rounds = (t256 + 255) / 256;
         const int K = p.A[0].K;
-        const int64_t least = rounds == 1 ? (epi == EPI_FOLD ? (K >= 256 ? 160 : 192) : K >= 512 ? 192 : 208)
-                              : epi == EPI_MERGE || K > 768 ? rounds * (K >= 256 ? 208 : 220)
-                                                            : rounds * 256 + 1;  // (never: folds of low rank are bound by their stores)
-        if (t256 >= least) return NT_256x256;
+        int64_t least = rounds * 256 + 1;  // (never: folds of low rank over more than one round are bound by their stores)
+        if (rounds == 1) least = epi == EPI_FOLD && b_rc ? (K >= 256 ? 160 : 192) : K >= 512 && epi != EPI_FOLD ? 192 : 208;
+        else if (epi == EPI_MERGE || K > 768) least = rounds * (K < 256 ? 244 : b_rc || K > 768 ? 208 : 220);
+        if (t256 >= least && K >= 64 && tiles(128, 128) * 26 >= t256 * 100) return NT_256x256;
     }
     // 64x128 tiles on two stages, of which a compute unit holds three: where 128x128, two to a unit, leave room for the 64x128
     // to take no more rounds.  Time of the launch, 64x128 / 128x128, ranks of 96, 300 and 768, by tiles of 128x128:

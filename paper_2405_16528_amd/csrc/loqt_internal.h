@@ -325,7 +325,7 @@ int gemm_db_splits(int64_t T, int64_t r, int64_t in);
 hipError_t launch_gemm_nt(int slot, int epi, bool a_rc, bool b_rc, const GemmParams& p, hipStream_t st, const NtPlan* plan = nullptr);
 // ... of which those whose epilogue walks the weight (gemm_weight.hip; A stored rows x K, not timed), and their tile
 hipError_t launch_weight_product(int epi, bool b_rc, const GemmParams& p, hipStream_t st);
-int weight_tile(int epi, const GemmParams& p);
+int weight_tile(int epi, bool b_rc, const GemmParams& p);
 // whether the fold and the merge of a weight out x in read P (rank r) as it is stored, A[0] with absmax
 bool weight_takes_codes(int64_t out, int64_t in, int64_t r);
 // ... and those of a group: the largest rank, the sum of codes_tiles
