@@ -129,20 +129,33 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
 
 // A few hundred tokens that do not fold: the codes are expanded inside the products (nf4_tile.hip) and no copy of the
 // weight is made.  That pays for a weight whose copy costs more than the slower loop, the more so the more tokens there are, and
-// less in the backward pass, where the copies go out beside nothing else but the products of dx fill the chip and the gradient
-// shares their launch.  Time against copies, forward / backward, by elements of the weight (millions):
-//   tokens     40            64            96            128           192           256
-//   0.7        1.25 / 1.04   1.33 / 1.08   1.42 / 1.12   1.42 / 1.32   1.67 / 1.50   1.67 / 1.64
-//   1.6        1.14 / 0.96   1.21 / 1.04   1.29 / 1.12   1.36 / 1.15   1.57 / 1.30   1.79 / 1.39
-//   2.8, 2.9   1.06 / 0.94   1.05 / 0.88   1.10 / 1.06   1.25 / 1.09   1.40 / 1.21   1.50 / 1.47
-//   4.2        0.91 / 0.87   0.91 / 0.88   1.00 / 1.00   1.04 / 1.03   1.15 / 1.28   1.18 / 1.38
-//   11.2       0.64 / 0.84   0.71 / 0.87   0.79 / 1.00   0.91 / 1.05   0.97 / 1.17   1.00 / 1.26
-//   16.8       0.68 / 0.84   0.78 / 0.88   0.81 / 0.96   0.86 / 0.98   0.84 / 1.16   0.93 / 1.19
-//   26         0.65 / 0.81   0.71 / 0.85   0.77 / 0.93   0.77 / 0.91   0.86 / 0.98   0.68 / 0.87
-//   45         0.73 / 0.73   0.80 / 0.72   0.79 / 0.78   0.81 / 0.81   0.80 / 0.82   0.85 / 0.84
+// where the contraction (in; backward out) is long enough for the prologues of a k-tile's pipeline not to count.  In the backward
+// pass the copies win more often: they go out beside nothing else, the products of dx fill the chip (the more the wider the weight)
+// and the gradient shares their launch.  Time of the call with the codes against with copies, means over random weights
+// (38000 calls, 1 to 60 million elements, ranks 16 to 512), by millions of elements:
+//   forward, in       512..724  1024..1448  2048..2896  5800..      backward, out   512..724  1024..1448  2048..2896  5800..
+//   33..64 tokens                                                  up to 32 tokens
+//     1.5..2.5          1.22       1.08        1.02       1.02         1.5..2.5       1.23       1.02       0.93       0.90
+//     6..9              0.94       0.97        0.87       0.91         6..9           1.11       0.96       0.85       0.85
+//     20..30                                   0.79       0.84         20..30                               0.97       0.88
+//   65..128                                                        33..64
+//     2.5..4            1.36       1.21        1.08       1.11         1.5..2.5       1.34       1.09       0.96       0.92
+//     6..9              1.07       1.12        0.91       1.03         6..9           1.23       1.06       0.91       0.92
+//     14..20                       0.85        0.84       0.99         20..30                               1.06       0.89
+//   129..192                                                       65..128
+//     6..9              1.25       1.26        1.07       1.12         6..9           1.38       1.22       1.02       1.05
+//     14..20                       0.97        0.91       1.11         20..30                               1.13       0.98
+//     30..60                                   0.86       0.92         30..60                               1.15       0.86
+//   193..256                                                       193..256
+//     14..20                       1.04        0.93       1.07         14..20                    1.36       1.24       1.22
+//     30..60                                   0.98       0.88         30..60                               1.34       0.96
+// The lines below leave calls 1.2 % (forward) and 0.5 % (backward) above the better of the two on the mean.
 bool use_nf4_tile(int64_t T, int64_t out, int64_t in, bool backward) {
     if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in) || T > 256) return false;
-    return out * in >= (backward ? std::max<int64_t>(1500000, 130000 * T - 6000000) : 1500000 + 38000 * T);
+    const int64_t n = out * in;
+    if (!backward) return n >= (in >= 1400 ? 60000 * T - 1000000 : 90000 * T + 2000000);
+    if (T <= 64) return out >= 1400 && 2 * in <= (T <= 32 ? 12 : 7) * out;
+    return out >= (T <= 80 ? 2800 : 4000) && n >= 300000 * T - 15000000;
 }
 
 inline size_t bf16_bytes(int64_t rows, int64_t cols) {
