@@ -135,27 +135,26 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
 // (38000 calls, 1 to 60 million elements, ranks 16 to 512), by millions of elements:
 //   forward, in       512..724  1024..1448  2048..2896  5800..      backward, out   512..724  1024..1448  2048..2896  5800..
 //   33..64 tokens                                                  up to 32 tokens
-//     1.5..2.5          1.22       1.08        1.02       1.02         1.5..2.5       1.23       1.02       0.93       0.90
-//     6..9              0.94       0.97        0.87       0.91         6..9           1.11       0.96       0.85       0.85
-//     20..30                                   0.79       0.84         20..30                               0.97       0.88
+//     1.5..2.5          1.22       1.08        1.02       1.02         1.5..2.5       1.25       1.03       0.94       0.89
+//     6..9              0.94       0.88        0.82       0.80         6..9           1.13       0.97       0.81       0.82
+//     20..30                                   0.71       0.72         20..30                               0.98       0.78
 //   65..128                                                        33..64
-//     2.5..4            1.36       1.21        1.08       1.11         1.5..2.5       1.34       1.09       0.96       0.92
-//     6..9              1.07       1.12        0.91       1.03         6..9           1.23       1.06       0.91       0.92
-//     14..20                       0.85        0.84       0.99         20..30                               1.06       0.89
+//     2.5..4            1.36       1.21        1.09       1.11         1.5..2.5       1.36       1.10       0.96       0.93
+//     6..9              1.07       1.07        0.92       0.95         6..9           1.23       1.06       0.88       0.89
+//     14..20                       0.85        0.81       0.81         20..30                               1.07       0.81
 //   129..192                                                       65..128
-//     6..9              1.25       1.26        1.07       1.12         6..9           1.38       1.22       1.02       1.05
-//     14..20                       0.97        0.91       1.11         20..30                               1.13       0.98
-//     30..60                                   0.86       0.92         30..60                               1.15       0.86
-//   193..256                                                       193..256
-//     14..20                       1.04        0.93       1.07         14..20                    1.36       1.24       1.22
-//     30..60                                   0.98       0.88         30..60                               1.34       0.96
-// The lines below leave calls 1.2 % (forward) and 0.5 % (backward) above the better of the two on the mean.
+//     6..9              1.28       1.25        1.06       1.08         6..9           1.38       1.22       1.00       1.01
+//     14..20                       0.97        0.89       0.89         20..30                               1.14       0.89
+//   193..256                                                       129..256
+//     14..20                       1.03        0.92       0.89         14..20                    1.33       1.23       1.06
+//     30..60                                   0.95       0.75         30..60                               1.30       0.93
+// The lines below leave calls 0.3 % above the better of the two on the mean, one in fifty by more than 5 %.
 bool use_nf4_tile(int64_t T, int64_t out, int64_t in, bool backward) {
     if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in) || T > 256) return false;
     const int64_t n = out * in;
     if (!backward) return n >= (in >= 1400 ? 60000 * T - 1000000 : 90000 * T + 2000000);
     if (T <= 64) return out >= 1400 && 2 * in <= (T <= 32 ? 12 : 7) * out;
-    return out >= (T <= 80 ? 2800 : 4000) && n >= 300000 * T - 15000000;
+    return out >= (T <= 80 ? 2800 : 4000) && n >= 200000 * T - 12000000;
 }
 
 inline size_t bf16_bytes(int64_t rows, int64_t cols) {

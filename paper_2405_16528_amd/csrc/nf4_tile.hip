@@ -63,6 +63,14 @@ __device__ __forceinline__ void wait_loads(int c) {
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// slices of the contraction, and the one of the second segment
+template <bool BRC>
+__host__ __device__ __forceinline__ int slices_of(const GemmParams& p) {
+    return p.splits + (BRC && p.A[1].K > 0 ? 1 : 0);
+}
+// an eighth of the tiles with all their slices on the 32 compute units of an XCD
+__host__ __device__ __forceinline__ bool one_round(int tiles, int slices) { return ((tiles + 7) >> 3) * slices <= 32; }
+
 // BRC: the weight is stored K x rows (its blocks run along the output columns), else rows x K
 template <int BM, bool BRC>
 __global__ __launch_bounds__(Cfg<BM>::THREADS, Cfg<BM>::THREADS / 256) void nf4_tile_kernel(const GemmParams p) {
@@ -74,16 +82,22 @@ __global__ __launch_bounds__(Cfg<BM>::THREADS, Cfg<BM>::THREADS / 256) void nf4_
     const bool feeds = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) != 0;
     const int tid = feeds ? threadIdx.x - 256 : threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-    // contiguous ranges of tiles per XCD; row tiles of one column run next to each other and share its codes
-    const int L = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (L >= tiles_m * tiles_n) return;
+    // An XCD takes a contiguous range of tiles, row tiles of one column next to each other (they share its codes), with all their slices
+    // where that is one round, else of the tiles of all slices: an eighth of the tiles, rounded up, leaves XCDs idle while others
+    // take two rounds (forward, 192 tokens, 10335 x 2548 in three slices 64.3 -> 44.2 us, 96 tokens, 1131 x 5689 34.7 -> 27.1), but where one round holds them the spread has nothing to give, and backward calls of a few
+    // tokens were 1 to 2 us slower with their slices spread (7872 x 636, one token, 26.2 -> 28.1).
+    const int tiles = tiles_m * tiles_n, slices = slices_of<BRC>(p), per_x = (tiles + 7) >> 3, x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const bool fits = one_round(tiles, slices);
+    const int all = fits ? j : x * (gridDim.x >> 3) + j, of = fits ? per_x : tiles;
+    const int slice = all / of, L = all - slice * of + (fits ? x * per_x : 0);
+    if (L >= tiles || slice >= slices) return;
     const int m0 = (L % tiles_m) * BM, n0 = (L / tiles_m) * BN;
 
     // K x rows: the second segment is the bf16 one, a slice of its own after the others
-    const bool extra = BRC && (int)blockIdx.y == p.splits;
+    const bool extra = BRC && slice == p.splits;
     const int nkt0 = (p.A[0].K + BK - 1) / BK, nkt1 = (p.A[1].K + BK - 1) / BK;
     const int per = ((BRC ? nkt0 : nkt0 + nkt1) + p.splits - 1) / p.splits;
-    const int kt_begin = extra ? nkt0 : blockIdx.y * per;
+    const int kt_begin = extra ? nkt0 : slice * per;
     const int kt_end = extra ? nkt0 + nkt1 : min(BRC ? nkt0 : nkt0 + nkt1, kt_begin + per);
     const int n = kt_end - kt_begin;  // k-tiles of this work-group
     const int tail0 = (p.A[0].K % BK) ? nkt0 - 1 : -1, tail1 = (p.A[1].K % BK) ? nkt0 + nkt1 - 1 : -1;
@@ -449,7 +463,7 @@ __global__ __launch_bounds__(Cfg<BM>::THREADS, Cfg<BM>::THREADS / 256) void nf4_
     }
 
     // lane: row 16 i + (lane & 15), columns 16 j + 4 (lane >> 4) .. +3
-    float* out = reinterpret_cast<float*>(p.C) + (int64_t)blockIdx.y * p.M * p.ldc;
+    float* out = reinterpret_cast<float*>(p.C) + (int64_t)slice * p.M * p.ldc;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int m = m0 + wm * C::WTM + i * 16 + frow;
@@ -479,7 +493,8 @@ hipError_t launch(const GemmParams& p, hipStream_t st) {
     hipError_t e = ensure_attr<BM, BRC>();
     if (e != hipSuccess) return e;
     const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
-    hipLaunchKernelGGL((nf4_tile_kernel<BM, BRC>), dim3((tiles + 7) / 8 * 8, p.splits + (BRC && p.A[1].K > 0 ? 1 : 0)), dim3(Cfg<BM>::THREADS), Cfg<BM>::SMEM, st, p);
+    const int slices = slices_of<BRC>(p), per_xcd = one_round(tiles, slices) ? (tiles + 7) / 8 * slices : (tiles * slices + 7) / 8;
+    hipLaunchKernelGGL((nf4_tile_kernel<BM, BRC>), dim3(per_xcd * 8), dim3(Cfg<BM>::THREADS), Cfg<BM>::SMEM, st, p);
     return hipGetLastError();
 }
 

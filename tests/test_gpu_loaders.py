@@ -40,11 +40,13 @@ def test_contractions_around_the_stages(tile, K):
     assert G.max_err_over_rms(dB.cpu().numpy().astype(np.float64), dB_ref) <= TOL + few
 
 
-@pytest.mark.parametrize("T,out,inp,r", [(33, 300, 64 * n - cut, 24) for n in range(1, 7) for cut in (0, 40) if n > 1 or not cut] +
-                         [(64, 13900, 1100, 72), (64, 13824, 1024, 64), (256, 13900, 1720, 136), (128, 13824, 1536, 128)])
+@pytest.mark.parametrize("T,out,inp,r", [(33, 5100000 // (64 * n - cut) + 1, 64 * n - cut, 24) for n in range(1, 7) for cut in (0, 40) if n > 1 or not cut] +
+                         [(64, 13900, 1100, 72), (64, 13824, 1024, 64), (256, 13900, 1720, 136), (128, 13824, 1536, 128)] +
+                         [(40, 4200, 1100, 72), (96, 1100, 6400, 40), (192, 10335, 2548, 120)])
 def test_fed_by_the_expansion(T, out, inp, r):
     """Products that expand the codes (a few hundred tokens): slices of one to seven k-tiles, and of ten to fourteen, where the feeding
-    waves have a form without branches for k-tiles that are neither cut nor the first of a segment.  Against the products on expanded
+    waves have a form without branches for k-tiles that are neither cut nor the first of a segment; and tiles that are no multiple of
+    eight (9, 9 and 81), whose slices are dealt to the XCDs together.  Against the products on expanded
     weights, which round the same operands: sums in another order, so a bf16 result moves by one step at most, and rarely."""
     from tests import gpu_util as G
     from paper_2405_16528_amd import binding as L
@@ -73,3 +75,23 @@ def test_fed_by_the_expansion(T, out, inp, r):
     for (a, b), own, rest in zip(zip(*got), (2.0 ** -7, 2.0 ** -7, 0.0), (2.0 ** -9, 2.0 ** -9, 2.0 ** -8 * 4.5 ** 2 / T ** 0.5)):
         assert torch.isfinite(a).all()
         assert ((a - b).abs() <= own * b.abs() + rest * b.pow(2).mean().sqrt()).all()
+
+
+def test_merges_in_one_launch_on_256x256():
+    """A list of large weights of rank 512 and more (1024 tiles of 256x256 and more) is one launch on those tiles; a weight alone takes 128x128
+    where they would leave the chip idle.  Same products, same encoder: the same bits."""
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    layers = []
+    for out, inp in [(2048, 2048)] * 15 + [(2041, 2040)]:
+        Wq = L.nf4_quantize(torch.randn((out, inp), generator=g, device="cuda") * 0.02)
+        Pq = L.nf4_quantize(torch.randn((out, 512), generator=g, device="cuda") * out ** -0.5)
+        B = (torch.randn((512, G.rup(inp, 8)), generator=g, device="cuda") * 2e-2).bfloat16()[:, :inp]
+        layers.append((Wq, L.NF4Tensor.empty(out, inp), Pq, B, 0.5))
+    descs = L.make_merge_descs(layers)
+    L.loqt_merge_requant_batched(descs, torch.empty(L.merge_descs_workspace_bytes(descs), dtype=torch.uint8, device="cuda"))
+    for Wq, dst, Pq, B, s in layers:
+        ref = L.loqt_merge_requant(Wq, Pq, B, s, out=L.NF4Tensor.empty(Wq.rows, Wq.cols))
+        assert torch.equal(dst.codes, ref.codes) and torch.equal(dst.absmax, ref.absmax)
