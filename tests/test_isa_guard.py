@@ -117,6 +117,32 @@ def test_direct_loads_wait_for_M0(assembly_of, source):
     assert loads > 0
 
 
+def test_barriers_that_let_lds_reads_pass_come_behind_the_writes(assembly_of):
+    """nf4_tile.hip: a wave that feeds goes to its barrier with up to 15 LDS operations outstanding.  They complete in order, so the
+    tile it has written is in place only if 16 reads or more follow the last write; the compiler could move them ahead of it."""
+    barriers = 0
+    for part in ("ILi%dELb%dE" % (rows, k_rows) for rows in (64, 128, 256) for k_rows in (0, 1)):
+        asm = assembly_of("nf4_tile.hip")
+        start = asm.index("\n", asm.index("nf4_tile_kernel" + part))
+        reads, written, waits = 0, False, ""
+        for line in asm[start:asm.index(".Lfunc_end", start)].split("\n"):
+            x = line.split(";")[0].strip()
+            if re.match(r"\.LBB", x):
+                reads, written = 0, False  # (the blocks before: the loop's own end, checked there, or a wait for everything)
+            elif x.startswith("ds_write"):
+                reads, written = 0, True
+            elif x.startswith("ds_read"):
+                reads += 1
+            elif x.startswith("s_waitcnt"):
+                waits = x
+            elif x.startswith(("s_barrier", "s_branch", "s_cbranch")) and written:
+                if x.startswith("s_barrier") and waits == "s_waitcnt lgkmcnt(15)":
+                    assert reads >= 16, (part, reads)
+                    barriers += 1
+                reads, written = 0, False
+    assert barriers >= 4 * 6
+
+
 def test_few_token_kernels_keep_to_their_registers(few_assembly):
     """16 waves leave 128 registers to a lane.  Only 64 rows of NF4 codes with two token tiles may spill (one round of those is
     still ahead of two rounds of 48 rows), and not more than they do.  Every variant that a launch selects, and no other."""
