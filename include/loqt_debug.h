@@ -31,7 +31,7 @@ extern "C" {
  *                      (2 T r (in + out) flop per pass) from T = out in / (in + out) tokens up.
  *   LOQT_PATH_AUTO   : forward calls with at most 32 tokens (loqt_linear_fwd, loqt_linear_fwd_nq) stream the weight
  *                      once and expand its codes in registers (a kernel of its own; reported as FUSED); calls with up
- *                      to 64 tokens, or T up to 256 on weights of 2.5 million + 50000 T elements or more, that do not fold keep the
+ *                      to 256 tokens that do not fold, on weights large enough for the tokens and with contractions long enough, keep the
  *                      rank-r term beside the weight (reported as PREPASS) but expand the codes inside the products;
  *                      otherwise
  *                      forward and backward take the pre-pass family (measured ahead of the
