@@ -29,6 +29,9 @@ extern "C" {
  *                      y = x W_eff^T and dx = dy W_eff.  The intermediate U is not formed; Z still is
  *                      (dB = Z^T x).  Cheaper than carrying the rank-r term through every token
  *                      (2 T r (in + out) flop per pass) from T = out in / (in + out) tokens up.
+ *   LOQT_PATH_CODES  : as PREPASS, but loqt_linear_fwd and loqt_linear_bwd of up to 256 tokens expand the codes of W_q (and,
+ *                      where a product reads them, of P_q) inside the products, whatever the sizes, as AUTO does on the sizes for
+ *                      which that is faster.
  *   LOQT_PATH_AUTO   : forward calls with at most 32 tokens (loqt_linear_fwd, loqt_linear_fwd_nq) stream the weight
  *                      once and expand its codes in registers (a kernel of its own; reported as FUSED); calls with up
  *                      to 256 tokens that do not fold, on weights large enough for the tokens and with contractions long enough, keep the
@@ -46,10 +49,17 @@ extern "C" {
  * All compute the same quantities; results differ only in rounding order, within the stated
  * tolerance.
  */
-enum { LOQT_PATH_AUTO = 0, LOQT_PATH_FUSED = 1, LOQT_PATH_PREPASS = 2, LOQT_PATH_FOLDED = 3 };
+enum { LOQT_PATH_AUTO = 0, LOQT_PATH_FUSED = 1, LOQT_PATH_PREPASS = 2, LOQT_PATH_FOLDED = 3, LOQT_PATH_CODES = 4 };
 loqt_status loqt_set_path(int path);
 /* The implementation (FUSED, PREPASS or FOLDED) the current option selects for these sizes. */
 int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in);
+/*
+ * Diagnostic (host only): 1 if loqt_linear_fwd (op LOQT_OP_FWD) or loqt_linear_bwd (LOQT_OP_BWD) of these sizes, with a workspace
+ * of loqt_workspace_bytes, expands the codes inside the products of a few hundred tokens under the current option, else 0 (the
+ * kernel for a handful of tokens is another one).  Which of the two a call takes follows from its sizes alone, so a test that is
+ * there for that kernel asks here whether it still reaches it.
+ */
+int loqt_expands_codes(int op, int64_t T, int64_t out, int64_t in);
 
 /*
  * Tile-shape option (process-wide, not thread-safe; for tests and tuning).  The products of the

@@ -25,7 +25,7 @@ F32, BF16 = 0, 1
 OP_FWD, OP_BWD, OP_MERGE, OP_INIT, OP_FWD_RIGHT, OP_BWD_RIGHT, OP_MERGE_RIGHT = 0, 1, 2, 3, 4, 5, 6
 OP_FWD_NQ, OP_BWD_NQ = 7, 8
 OP_FWD_SAVE, OP_BWD_SAVED = 9, 10
-PATH_AUTO, PATH_FUSED, PATH_PREPASS, PATH_FOLDED = 0, 1, 2, 3
+PATH_AUTO, PATH_FUSED, PATH_PREPASS, PATH_FOLDED, PATH_CODES = 0, 1, 2, 3, 4
 TILE_AUTO, TILE_256x256, TILE_256x128, TILE_128x128 = 0, 1, 2, 3
 STATUS_NAMES = {0: "LOQT_OK", 1: "LOQT_INVALID_ARG", 2: "LOQT_BAD_SHAPE", 3: "LOQT_MISALIGNED",
                 4: "LOQT_WORKSPACE_TOO_SMALL", 5: "LOQT_LAUNCH_FAILED", 6: "LOQT_STATIC_SCRATCH_TOO_SMALL"}
@@ -120,6 +120,8 @@ lib.loqt_set_tile.restype = _i
 lib.loqt_set_tile.argtypes = [_i]
 lib.loqt_resolved_path.restype = _i
 lib.loqt_resolved_path.argtypes = [_i, _i64, _i64, _i64]
+lib.loqt_expands_codes.restype = _i
+lib.loqt_expands_codes.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_timing_enable.restype = None
 lib.loqt_timing_enable.argtypes = [_i]
 lib.loqt_timing_slots.restype = _i
@@ -416,7 +418,7 @@ def loqt_prepare() -> None:
 
 
 def set_path(path: int) -> None:
-    """PATH_AUTO, PATH_FUSED or PATH_PREPASS (process-wide)."""
+    """PATH_AUTO, PATH_FUSED, PATH_PREPASS, PATH_FOLDED or PATH_CODES (process-wide)."""
     _check(lib.loqt_set_path(path), "loqt_set_path")
 
 
@@ -442,6 +444,11 @@ def set_tile(tile: int) -> None:
 
 def resolved_path(op: int, T: int, out: int, inp: int) -> int:
     return int(lib.loqt_resolved_path(op, T, out, inp))
+
+
+def expands_codes(op: int, T: int, out: int, inp: int) -> bool:
+    """Whether OP_FWD or OP_BWD of these sizes expands the codes inside the products of a few hundred tokens -- host only."""
+    return bool(lib.loqt_expands_codes(op, T, out, inp))
 
 
 def timing_enable(on: bool) -> None:

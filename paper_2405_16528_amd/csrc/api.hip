@@ -103,7 +103,7 @@ bool use_few_tokens(int64_t tokens) { return g_path == LOQT_PATH_AUTO && tokens 
 // one takes it if the caller brought the workspace (narrow_merge_prepass).
 bool use_prepass_merge(int64_t in) {
     if (g_path == LOQT_PATH_FUSED) return false;
-    if (g_path == LOQT_PATH_PREPASS || g_path == LOQT_PATH_FOLDED) return true;
+    if (g_path != LOQT_PATH_AUTO) return true;
     return in >= 1024;
 }
 
@@ -150,7 +150,9 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
 //     30..60                                   0.95       0.75         30..60                               1.30       0.93
 // The lines below leave calls 0.3 % above the better of the two on the mean, one in fifty by more than 5 %.
 bool use_nf4_tile(int64_t T, int64_t out, int64_t in, bool backward) {
-    if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in) || T > 256) return false;
+    if (T > 256) return false;
+    if (g_path == LOQT_PATH_CODES) return true;
+    if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in)) return false;
     const int64_t n = out * in;
     if (!backward) return n >= (in >= 1400 ? 60000 * T - 1000000 : 90000 * T + 2000000);
     if (T <= 64) return out >= 1400 && 2 * in <= (T <= 32 ? 12 : 7) * out;
@@ -1124,6 +1126,12 @@ int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in) {
     return use_folded(T, out, in) ? LOQT_PATH_FOLDED : LOQT_PATH_PREPASS;
 }
 
+int loqt_expands_codes(int op, int64_t T, int64_t out, int64_t in) {
+    if (T <= 0 || out <= 0 || in <= 0) return 0;
+    if (op == LOQT_OP_FWD) return !use_few_tokens(T) && use_nf4_tile(T, out, in, false);
+    return op == LOQT_OP_BWD && use_nf4_tile(T, out, in, true);
+}
+
 loqt_status loqt_init_compensate(const float* W, int64_t ld_w, const float* P, int64_t ld_p, int64_t out,
                                  int64_t in, int64_t r, float s, int iters, int warm_start, uint8_t* codes_out,
                                  float* absmax_out, int64_t ld_q, loqt_bf16* B, int64_t ld_B, void* ws,
@@ -1634,7 +1642,7 @@ loqt_status loqt_prepare(void) {
 }
 
 loqt_status loqt_set_path(int path) {
-    if (path < LOQT_PATH_AUTO || path > LOQT_PATH_FOLDED) return LOQT_INVALID_ARG;
+    if (path < LOQT_PATH_AUTO || path > LOQT_PATH_CODES) return LOQT_INVALID_ARG;
     g_path = path;
     return LOQT_OK;
 }

@@ -253,6 +253,24 @@ def test_auto_rule_on_the_paper_workloads(lib):
     assert r(L.OP_FWD, 2048, 4096, 4096) == L.PATH_FOLDED and r(L.OP_FWD, 2047, 4096, 4096) == L.PATH_PREPASS
 
 
+def test_query_of_the_form_that_expands_codes_inside_the_products(lib):
+    from paper_2405_16528_amd import binding as L
+
+    def ask(T, out, inp):
+        return L.expands_codes(L.OP_FWD, T, out, inp), L.expands_codes(L.OP_BWD, T, out, inp)
+    assert ask(256, 13824, 5120) == (True, True) and ask(257, 13824, 5120) == (False, False)
+    assert ask(16, 13824, 5120) == (False, True)  # (forward: the kernel for a handful of tokens)
+    assert ask(64, 1024, 1024) == (False, False) and ask(200, 1280, 1024) == (False, False)
+    assert not L.expands_codes(L.OP_MERGE, 64, 4096, 4096) and ask(0, 4096, 4096) == (False, False)
+    try:
+        for path, want in ((L.PATH_CODES, True), (L.PATH_PREPASS, False), (L.PATH_FOLDED, False), (L.PATH_FUSED, False)):
+            L.set_path(path)
+            assert ask(256, 13824, 5120) == ask(16, 40, 24) == (want, want) and ask(257, 13824, 5120) == (False, False)
+    finally:
+        L.set_path(L.PATH_AUTO)
+    assert lib.loqt_set_path(5) == 1
+
+
 @pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
 def test_stream_without_torch_private_names(lib, monkeypatch, missing):
     """The stream handle comes from two private functions of torch; without one of them, from the public call."""

@@ -44,10 +44,11 @@ def test_contractions_around_the_stages(tile, K):
                          [(64, 13900, 1100, 72), (64, 13824, 1024, 64), (256, 13900, 1720, 136), (128, 13824, 1536, 128)] +
                          [(40, 4200, 1100, 72), (96, 1100, 6400, 40), (192, 10335, 2548, 120)])
 def test_fed_by_the_expansion(T, out, inp, r):
-    """Products that expand the codes (a few hundred tokens): slices of one to seven k-tiles, and of ten to fourteen, where the feeding
-    waves have a form without branches for k-tiles that are neither cut nor the first of a segment; and tiles that are no multiple of
-    eight (9, 9 and 81), whose slices are dealt to the XCDs together.  Against the products on expanded
-    weights, which round the same operands: sums in another order, so a bf16 result moves by one step at most, and rarely."""
+    """Products that expand the codes (a few hundred tokens), both directions: slices of one to seven k-tiles, and of ten to
+    fourteen, where the feeding waves have a form without branches for k-tiles that are neither cut nor the first of a segment; and
+    tiles that are no multiple of eight (33, 9 and 81 forward, 9, 50 and 20 backward), whose slices are dealt to the XCDs together.
+    Against the products on expanded weights, which round the same operands: sums in another order, so a bf16 result moves by one step
+    at most, and rarely."""
     from tests import gpu_util as G
     from paper_2405_16528_amd import binding as L
     g = torch.Generator(device="cuda")
@@ -60,8 +61,9 @@ def test_fed_by_the_expansion(T, out, inp, r):
     x, dy, B = bf16(T, inp, 1.0), bf16(T, out, 1e-2), bf16(r, inp, 2e-2)
     got = []
     try:
-        for path in (L.PATH_AUTO, L.PATH_PREPASS):
+        for path in (L.PATH_CODES, L.PATH_PREPASS):
             L.set_path(path)
+            assert all(L.expands_codes(op, T, out, inp) == (path == L.PATH_CODES) for op in (L.OP_FWD, L.OP_BWD))
             y, dx = G.bf16_empty(T, out, fill=float("nan")), G.bf16_empty(T, inp, fill=float("nan"))
             dB = torch.full((r, inp), float("nan"), device="cuda")
             L.loqt_linear_fwd(x, Wq, Pq, B, 0.5, y, G.workspace(L.OP_FWD, T, out, inp, r))

@@ -1,5 +1,7 @@
 """Forward and backward calls with a few hundred tokens, whose products expand the codes themselves: sizes that end inside
 tiles, k-tiles and blocks, slices of the contraction, padding that holds NaN, against the oracle."""
+import contextlib
+
 import numpy as np
 import pytest
 import torch
@@ -22,11 +24,35 @@ CASES = [
     (129, 3500, 4100, 200),   # tiles of 256 tokens
     (256, 3840, 3712, 192),
 ]
+# sizes that come here by themselves, in both directions
+BY_RULE = [
+    (40, 2100, 1500, 72),     # tiles of 64 tokens
+    (100, 4100, 3500, 72),    # of 128
+    (129, 4100, 3500, 200),   # of 256
+]
+
+
+@contextlib.contextmanager
+def _path(path):
+    from paper_2405_16528_amd import binding as L
+    L.set_path(path)
+    try:
+        yield
+    finally:
+        L.set_path(L.PATH_AUTO)
 
 
 @pytest.mark.parametrize("grad", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("T,out,inp,r", CASES)
-def test_fwd_bwd_parity(T, out, inp, r, grad):
+@pytest.mark.parametrize("path,T,out,inp,r", [("codes", *c) for c in CASES] + [("auto", *c) for c in BY_RULE])
+def test_fwd_bwd_parity(path, T, out, inp, r, grad):
+    from tests import gpu_util as G
+    from paper_2405_16528_amd import binding as L
+    with _path(L.PATH_CODES if path == "codes" else L.PATH_AUTO):
+        assert L.expands_codes(L.OP_FWD, T, out, inp) and L.expands_codes(L.OP_BWD, T, out, inp)
+        _parity(T, out, inp, r, grad)
+
+
+def _parity(T, out, inp, r, grad):
     from tests import gpu_util as G
     from paper_2405_16528_amd import binding as L
     rng = synth.rng_for(T, "tile", out, inp)
@@ -51,20 +77,19 @@ def test_fwd_bwd_parity(T, out, inp, r, grad):
     assert G.max_err_over_rms(dB.float().cpu().numpy().astype(np.float64), dB_ref) <= tol
     # the expanded-weight form rounds the same operands: it differs by the order of fp32 sums only, which moves a bf16
     # result by at most one step, and only rarely
-    L.set_path(L.PATH_PREPASS)
-    try:
+    with _path(L.PATH_PREPASS):
+        assert not L.expands_codes(L.OP_FWD, T, out, inp) and not L.expands_codes(L.OP_BWD, T, out, inp)
         y2, dx2 = G.bf16_empty(T, out), G.bf16_empty(T, inp)
         L.loqt_linear_fwd(_nan_padded(x, 8), *q, _nan_padded(B, 16), s, y2, G.workspace(L.OP_FWD, T, out, inp, r))
         L.loqt_linear_bwd(_nan_padded(dy, 0), _nan_padded(x, 8), *q, _nan_padded(B, 16), s, dx2, dB, False, ws)
         torch.cuda.synchronize()
-    finally:
-        L.set_path(L.PATH_AUTO)
     for a, b in ((y, y2), (dx, dx2)):
         a, b = a.double(), b.double()
         assert float((a != b).double().mean()) < 0.02 and float((a - b).norm() / b.norm()) < 3e-4
 
 
-def test_without_dx_and_with_the_smallest_workspace():
+@pytest.mark.parametrize("path", ["codes", "auto"])
+def test_without_dx_and_with_the_smallest_workspace(path):
     from tests import gpu_util as G
     from paper_2405_16528_amd import binding as L
     T, out, inp, r, s = 40, 1000, 1500, 72, 0.5
@@ -85,12 +110,19 @@ def test_without_dx_and_with_the_smallest_workspace():
     for with_dx in (True, False):
         dx = G.bf16_empty(T, inp, fill=float("nan")) if with_dx else None
         dB = torch.full((r, inp), float("nan"), dtype=torch.float32, device="cuda")
-        L.loqt_linear_bwd(*d, dx, dB, False, torch.empty(least, dtype=torch.uint8, device="cuda"))
-        torch.cuda.synchronize()
+        with _path(L.PATH_CODES if path == "codes" else L.PATH_AUTO):
+            L.timing_enable(True)
+            try:
+                L.loqt_linear_bwd(*d, dx, dB, False, torch.empty(least, dtype=torch.uint8, device="cuda"))
+                torch.cuda.synchronize()
+            finally:
+                L.timing_enable(False)
+        # (the least workspace has room for the slices of Z and dx where the copies of W and P would be, so no copy is made)
+        assert (L.timing_read()["prepass"][0] == 0) == (path == "codes")
         assert G.max_err_over_rms(dB.cpu().numpy().astype(np.float64), dB_ref) <= tol
         if with_dx:
             G.bf16_output_report(G.bf16_host(dx), dx_ref)
-    with pytest.raises(L.LoqtError):
+    with pytest.raises(L.LoqtError), _path(L.PATH_CODES if path == "codes" else L.PATH_AUTO):
         L.loqt_linear_bwd(*d, None, dB, False, torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
 
 
@@ -108,8 +140,7 @@ def test_timers_cover_the_sum_of_the_slices():
     dB, ws = torch.empty((r, inp), dtype=torch.float32, device="cuda"), G.workspace(L.OP_BWD, T, out, inp, r)
 
     def untimed_per_launch(path):
-        L.set_path(path)
-        try:
+        with _path(path):
             best = float("inf")
             for _ in range(6):
                 begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -127,8 +158,6 @@ def test_timers_cover_the_sum_of_the_slices():
                 launches, ms = (sum(v) for v in zip(*L.timing_read().values()))
                 best = min(best, (begin.elapsed_time(end) - ms) * 1e3 / launches)
             return best
-        finally:
-            L.set_path(L.PATH_AUTO)
-    tile, plain = untimed_per_launch(L.PATH_AUTO), untimed_per_launch(L.PATH_PREPASS)
+    tile, plain = untimed_per_launch(L.PATH_CODES), untimed_per_launch(L.PATH_PREPASS)
     print(f"outside of the timers, us per launch: {tile:.1f}, with a launch per product {plain:.1f}")
     assert tile <= plain + 1.0
