@@ -224,7 +224,7 @@ __global__ __launch_bounds__(Cfg<BM>::THREADS, Cfg<BM>::THREADS / 256) void nf4_
             for (int i = 0; i < NBL; ++i) direct_load(offB[i], baseB, dst, (uint32_t)(BM * ROWB + i * PASS));
         };
         // tile t has landed: clears A past the end of the contraction (codes past it are finite weights, or k rows repeated).  A thread
-        // clears the chunks it has loaded itself.
+        // clears the chunks it has loaded itself, and waits for that: the next barrier may be one that lets LDS operations pass.
         auto cut = [&](int t) {
             const int kt = kt_begin + t;
             if (t >= n || !is_tail(kt)) return;
@@ -242,6 +242,7 @@ __global__ __launch_bounds__(Cfg<BM>::THREADS, Cfg<BM>::THREADS / 256) void nf4_
                     *q = make_uint4(v.x & keep[0], v.y & keep[1], v.z & keep[2], v.w & keep[3]);
                 }
             }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         };
         // ---- expansion of the thread's codes: byte offsets into the table of levels, look-ups, products with the scale, two to a dword,
         // four dwords to a chunk of 16 bytes.  All look-ups of a k-tile are under way before the first product.
