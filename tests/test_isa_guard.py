@@ -209,6 +209,26 @@ def test_few_token_kernels_keep_to_their_registers(few_assembly):
     assert not any(spills.values()), spills
 
 
+@pytest.mark.parametrize("source", ["gemm_nt.hip", "gemm_pair.hip", "gemm_weight.hip", "nf4_tile.hip"])
+def test_main_loops_keep_to_their_registers(assembly_of, source):
+    """The blocks of every product's main loop, also of the eight-wave forms (256 registers to a lane): nothing goes to scratch memory
+    and no accumulator moves.  Outside of them the 256x256 tiles alone spill, set-up and change of segment, and not more than they
+    do: with eight waves up to 19 registers (fold, merge, unquantised merge, grouped merge), 2 with four."""
+    asm = assembly_of(source)
+    spills = {name: int(count) for name, count in re.findall(r"\.name: +(_Z\S+)\n(?:.*\n)*?.*\.vgpr_spill_count: +(\d+)", asm)}
+    kernels = 0
+    for name, count in spills.items():
+        loops = _loop_blocks(asm, "\n" + name + ":")
+        if not loops:
+            continue
+        kernels += 1
+        moved = [x.strip() for _, lines in loops for x in lines if "scratch_" in x or "v_accvgpr" in x]
+        assert not moved, (name, moved[:3])
+        eight = "grouped_kernelILi256E" in name or re.search(r"nt_gemm_kernelILi256ELi256E.*ELi8EEE", name)
+        assert count <= (19 if eight else 2 if "nt_gemm_kernelILi256ELi256E" in name else 0), (name, count)
+    assert kernels >= 6
+
+
 @pytest.mark.parametrize("source,kernel", [("codec.hip", "nf4_dequantize_kernel"), ("gemm_pair.hip", "nt_copy_kernel")])
 def test_streaming_kernels_keep_out_of_scratch_memory(assembly_of, source, kernel):
     """The expansions of codes with rows that end inside a group of eight, and their neighbours: an array indexed at run time
