@@ -108,7 +108,7 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
     constexpr bool WEIGHT = ENCODES || CODES || EPI == EPI_ACC_BF16;
     static_assert(!WEIGHT || WTN % 64 == 0, "");
     static_assert(!ANF4 || (CODES && !ARC && NS == 2), "");
-    static_assert(!LOADERS || (!WEIGHT && NS > 2), "");
+    static_assert(!LOADERS || (!WEIGHT && (NS == 3 || NS == 4)), "");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     // (LOADERS: the second four waves load, with the indexes of the first four)
@@ -489,7 +489,6 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
         auto landed = [&](int later) {
             if (later >= NS - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * NCH) : "memory");
             else if (NS > 3 && later == NS - 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NCH) : "memory");
-            else if (NS > 4 && later == NS - 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 3) * NCH) : "memory");
             else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCH) : "memory");
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         };
