@@ -229,6 +229,24 @@ def test_main_loops_keep_to_their_registers(assembly_of, source):
     assert kernels >= 6
 
 
+@pytest.mark.parametrize("source", ["gemm_nt.hip", "gemm_pair.hip", "gemm_weight.hip", "nf4_tile.hip"])
+def test_main_loops_wait_for_loads_by_hand_only(assembly_of, source):
+    """The direct loads of a k-tile are counted and waited for by hand.  Where a kernel also has loads into registers, on another
+    branch, the compiler may take it that they are still on their way and wait for all loads in every k-tile."""
+    asm, kernels = assembly_of(source), 0
+    for m in re.finditer(r"^(_Z\S+):", asm, re.M):
+        loops = _loop_blocks(asm, "\n" + m[1] + ":")
+        if not loops:
+            continue
+        kernels += 1
+        for _, lines in loops:
+            by_hand = False
+            for x in lines:
+                by_hand = "#ASMSTART" in x or (by_hand and "#ASMEND" not in x)
+                assert by_hand or not ("s_waitcnt" in x and "vmcnt" in x), (m[1], x.strip())
+    assert kernels >= 6
+
+
 @pytest.mark.parametrize("source,kernel", [("codec.hip", "nf4_dequantize_kernel"), ("gemm_pair.hip", "nt_copy_kernel")])
 def test_streaming_kernels_keep_out_of_scratch_memory(assembly_of, source, kernel):
     """The expansions of codes with rows that end inside a group of eight, and their neighbours: an array indexed at run time
