@@ -779,45 +779,50 @@ __device__ __forceinline__ void nt_gemm_tile(const GemmParams& p, const int L, c
 
     if constexpr (EPI == EPI_BF16 || EPI == EPI_FOLD || EPI == EPI_ACC_BF16) {
         // 32 rows at a time are staged through the wave's private LDS region and leave as whole 16-byte row segments (LDS operations
-        // of one wave complete in order, so no barrier), the stores of one block under way while the next one is computed.  A tile
-        // that lies inside the matrix (wave-uniform) asks for all segments of a block at once and walks a pointer; with the bounds of
+        // of one wave complete in order, so no barrier), the stores of one block under way while the next one is computed.  All segments
+        // of a block are asked for at once, and a wave that lies inside the matrix (wave-uniform) walks a pointer; with the bounds of
         // every segment tested beside its read, each store waited for its own read and for a 64-bit product (256x256, bf16: the
-        // epilogue 13300 cycles before, 6400 to 7900 now).
+        // epilogue 13300 cycles before, 6400 to 7900 now).  The same at the edges, by which a launch of one round is held up (y of
+        // 2816 x 5862 x 768 36.8 us with one segment after the other there, 33.2 this way).
         constexpr int EPITCH = Cfg::EPITCH;
-        char* ebuf = ebase + wave * (32 * EPITCH);
+        char* ebuf = ebase + wave_s * (32 * EPITCH);
         constexpr int CPR = WTN / 8, RPI = 64 / CPR, NIT = 32 / RPI;  // 16-byte chunks per row; rows per store of the wave; stores per block
         uint16_t* C = reinterpret_cast<uint16_t*>(part1 ? p.Cx : p.C);
         const int64_t ldc = part1 ? p.ldcx : p.ldc;
-        const int srow = lane / CPR, sch = lane % CPR;
+        int slane;  // the lane, asked for anew: nothing of the stores has to be kept through the loop
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(slane));
+        const int swm = wave_s / Cfg::WAVES_N, swn = wave_s % Cfg::WAVES_N;
+        const int srow = slane / CPR, sch = slane % CPR;
         const char* const sread = ebuf + srow * EPITCH + sch * 16;
-        const bool inside = m0 + BM <= p.M && n0 + BN <= N;
-        uint16_t* sdst = C + (int64_t)(m0 + wm * WTM + srow) * ldc + (n0 + wn * WTN + sch * 8);
+        const bool inside = m0 + (swm + 1) * WTM <= p.M && n0 + (swn + 1) * WTN <= N;
+        uint16_t* sdst = C + (int64_t)(m0 + swm * WTM + srow) * ldc + (n0 + swn * WTN + sch * 8);
         const int64_t sstep = RPI * ldc;
         // rows row0 .. row0+31 of the wave tile
         auto store_rows = [&](int row0) {
-            if (inside) {
-                u32x4 v[NIT];
+            u32x4 v[NIT];
 #pragma unroll
-                for (int it = 0; it < NIT; ++it) v[it] = *reinterpret_cast<const u32x4*>(sread + it * RPI * EPITCH);
+            for (int it = 0; it < NIT; ++it) v[it] = *reinterpret_cast<const u32x4*>(sread + it * RPI * EPITCH);
+            if (inside) {
 #pragma unroll
                 for (int it = 0; it < NIT; ++it, sdst += sstep) __builtin_nontemporal_store(v[it], reinterpret_cast<u32x4*>(sdst));
                 return;
             }
-#pragma unroll 1
-            for (int it = 0; it < NIT; ++it, sdst += sstep) {
-                const int m = m0 + wm * WTM + row0 + it * RPI + srow, n = n0 + wn * WTN + sch * 8;
-                const uint4 v = *reinterpret_cast<const uint4*>(sread + it * RPI * EPITCH);
-                if (m < p.M) {
-                    if (n + 8 <= N) {
-                        __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(sdst));
-                    } else {
-                        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            const int rows = p.M - (m0 + swm * WTM + srow), cols = N - (n0 + swn * WTN + sch * 8);  // left, from the lane's first segment on
+            if (cols >= 8) {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            if (n + e < N) sdst[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
-                    }
+                for (int it = 0; it < NIT; ++it)
+                    if (row0 + it * RPI < rows) __builtin_nontemporal_store(v[it], reinterpret_cast<u32x4*>(sdst + it * sstep));
+            } else if (cols > 0) {  // the end of the rows: four, two and one elements
+#pragma unroll
+                for (int it = 0; it < NIT; ++it) {
+                    if (row0 + it * RPI >= rows) continue;
+                    uint16_t* const d = sdst + it * sstep;
+                    if (cols & 4) *reinterpret_cast<u32x2*>(d) = u32x2{v[it][0], v[it][1]};
+                    if (cols & 2) *reinterpret_cast<uint32_t*>(d + (cols & 4)) = cols & 4 ? v[it][2] : v[it][0];
+                    if (cols & 1) d[cols & 6] = (uint16_t)(cols & 4 ? cols & 2 ? v[it][3] : v[it][2] : cols & 2 ? v[it][1] : v[it][0]);
                 }
             }
+            sdst += NIT * sstep;
         };
         // Unquantised merge (M = out, N = in): the old bf16 weight, 16 bytes per lane (n < N stays inside the row's pitch, a
         // multiple of 8 elements), two rows of tiles ahead of their turn.  (Fetched four columns at a time where they are
