@@ -89,6 +89,12 @@ loqt_status loqt_plan_product(int64_t M, int64_t N, int64_t Nx, int64_t *n_large
  * 3 = 128x128, 5 = 64x128, 6 = 64x64.  Either pointer may be NULL.
  */
 loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max_splits, int *tile, int *splits);
+/*
+ * Diagnostic (host only), 0 for bad sizes.
+ * loqt_plan_codes: slices of the contraction (K elements) of a product T x N that expands the codes, at most max_slices of them;
+ * extra != 0: with a slice of its own for a second, unquantised operand.
+ */
+int loqt_plan_codes(int64_t T, int64_t N, int64_t K, int extra, int max_slices);
 
 /*
  * Optional per-kernel timing (diagnostics for benchmarks; off by default).

@@ -122,6 +122,8 @@ lib.loqt_resolved_path.restype = _i
 lib.loqt_resolved_path.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_expands_codes.restype = _i
 lib.loqt_expands_codes.argtypes = [_i, _i64, _i64, _i64]
+lib.loqt_plan_codes.restype = _i
+lib.loqt_plan_codes.argtypes = [_i64, _i64, _i64, _i, _i]
 lib.loqt_timing_enable.restype = None
 lib.loqt_timing_enable.argtypes = [_i]
 lib.loqt_timing_slots.restype = _i
@@ -449,6 +451,11 @@ def resolved_path(op: int, T: int, out: int, inp: int) -> int:
 def expands_codes(op: int, T: int, out: int, inp: int) -> bool:
     """Whether OP_FWD or OP_BWD of these sizes expands the codes inside the products of a few hundred tokens -- host only."""
     return bool(lib.loqt_expands_codes(op, T, out, inp))
+
+
+def plan_codes(T: int, N: int, K: int, extra: bool = False, max_slices: int = 32) -> int:
+    """Slices of a product that expands the codes -- host only."""
+    return int(lib.loqt_plan_codes(T, N, K, 1 if extra else 0, max_slices))
 
 
 def timing_enable(on: bool) -> None:

@@ -1672,6 +1672,11 @@ loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max
     return LOQT_OK;
 }
 
+int loqt_plan_codes(int64_t T, int64_t N, int64_t K, int extra, int max_slices) {
+    if (T <= 0 || N <= 0 || K <= 0 || max_slices < 1 || T > ((int64_t)1 << 30) || N > ((int64_t)1 << 30) || K > ((int64_t)1 << 30)) return 0;
+    return nf4_tile_splits(T, N, (K + 63) / 64, extra != 0, max_slices);
+}
+
 void loqt_timing_enable(int on) {
     if (on) {
         if (!g_timing.begin) {

@@ -1,7 +1,7 @@
 // Products of a few hundred tokens with a 4-bit weight:  C[T x N] = alpha * sum_seg A_seg[T x K_seg] * deq(B_seg)[K_seg x N]
 // in fp32 slices of the contraction, the codes expanded on the way from LDS to LDS.
 //
-// With T <= 512 an expansion of the weight to bf16 costs as much as the product (13824 x 5120: 37 us, 40 MB read and 141 MB
+// With T <= 256 an expansion of the weight to bf16 costs as much as the product (13824 x 5120: 37 us, 40 MB read and 141 MB
 // written, and the product reads the 141 MB back).  Here the codes and block scales of a k-tile come into LDS by direct
 // loads (5 KB instead of 16 KB for 64 x 128 weights), each thread expands its 16 (level table in LDS, one fp32 multiply,
 // round to nearest even bf16: the bits of nf4_dequantize) and stores them where the plain kernels' direct loads would have
@@ -512,10 +512,14 @@ hipError_t prepare_nf4_tile_kernels() {
 }
 
 // Slices of the contraction: microseconds per k-tile with few work-groups and with one on every compute unit, plus the
-// rest of a tile, as in plan_nt
+// rest of a tile, as in plan_nt.  The slices it takes against the best of 1 to 32, over 4500 random products (1 to 256 tokens, 64 to 13824
+// columns and as long a contraction): 1.011 on the mean, one in ninety more than 10 % off.  Tiles of 64 rows are priced above their own
+// 0.45 to 0.58 us per k-tile: with those, dx (whose slice of Z B is short, but counts as another one) came in half as many slices
+// (47 tokens, 6078 x 8448, rank 64, the backward call 46.8 -> 53.8 us; 7 tokens, 3650 x 8453, 35.9 -> 40.5), 1.0113 of the best with
+// them, 1.0099 with these.
 int nf4_tile_splits(int64_t M, int64_t N, int64_t nkt, int extra, int64_t max_splits) {
     const int64_t bm = M <= 64 ? 64 : M <= 128 ? 128 : 256;
-    const double alone = bm == 64 ? 0.45 : bm == 128 ? 0.55 : 0.80, full = bm == 64 ? 0.58 : bm == 128 ? 0.75 : 1.0, rest = bm == 64 ? 6.5 : bm == 128 ? 7.0 : 10.0;
+    const double alone = bm == 128 ? 0.55 : 0.80, full = bm == 64 ? 0.95 : bm == 128 ? 0.75 : 1.0, rest = bm == 64 ? 6.0 : bm == 128 ? 7.0 : 10.0;
     const int64_t tiles = (M + bm - 1) / bm * ((N + BN - 1) / BN);
     int best = 1;
     double best_cost = 0.0;

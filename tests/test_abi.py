@@ -271,6 +271,18 @@ def test_query_of_the_form_that_expands_codes_inside_the_products(lib):
     assert lib.loqt_set_path(5) == 1
 
 
+def test_slices_of_products_that_expand_codes(lib):
+    """dx of a few tokens: with a slice of its own for Z B it came in half as many slices, on half of the chip"""
+    from paper_2405_16528_amd import binding as L
+    assert L.plan_codes(47, 8448, 6078, True) == 6 and L.plan_codes(7, 8453, 3650, True) == 6 and L.plan_codes(14, 6785, 7288, True) == 8
+    for T in (1, 64, 65, 128, 129, 256):
+        for K in (64, 700, 5120):
+            for most in (1, 3, 32):
+                n, kt = L.plan_codes(T, 4096, K, False, most), -(-K // 64)
+                assert 1 <= n <= most and -(-kt // -(-kt // n)) == n  # no slice is empty
+    assert L.plan_codes(0, 4096, 4096) == 0 and L.plan_codes(16, 4096, 4096, max_slices=0) == 0
+
+
 @pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
 def test_stream_without_torch_private_names(lib, monkeypatch, missing):
     """The stream handle comes from two private functions of torch; without one of them, from the public call."""
