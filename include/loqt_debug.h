@@ -90,10 +90,12 @@ loqt_status loqt_plan_product(int64_t M, int64_t N, int64_t Nx, int64_t *n_large
  */
 loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max_splits, int *tile, int *splits);
 /*
- * Diagnostic (host only), 0 for bad sizes.
+ * Diagnostics (host only); a tile is one of loqt_plan_tiles, 0 for bad sizes.
+ * loqt_plan_merge_group: one launch of n (<= 24) merges.
  * loqt_plan_codes: slices of the contraction (K elements) of a product T x N that expands the codes, at most max_slices of them;
  * extra != 0: with a slice of its own for a second, unquantised operand.
  */
+int loqt_plan_merge_group(int n, const int64_t *out, const int64_t *in, const int64_t *r);
 int loqt_plan_codes(int64_t T, int64_t N, int64_t K, int extra, int max_slices);
 
 /*

@@ -122,6 +122,8 @@ lib.loqt_resolved_path.restype = _i
 lib.loqt_resolved_path.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_expands_codes.restype = _i
 lib.loqt_expands_codes.argtypes = [_i, _i64, _i64, _i64]
+lib.loqt_plan_merge_group.restype = _i
+lib.loqt_plan_merge_group.argtypes = [_i, _P(_i64), _P(_i64), _P(_i64)]
 lib.loqt_plan_codes.restype = _i
 lib.loqt_plan_codes.argtypes = [_i64, _i64, _i64, _i, _i]
 lib.loqt_timing_enable.restype = None
@@ -451,6 +453,12 @@ def resolved_path(op: int, T: int, out: int, inp: int) -> int:
 def expands_codes(op: int, T: int, out: int, inp: int) -> bool:
     """Whether OP_FWD or OP_BWD of these sizes expands the codes inside the products of a few hundred tokens -- host only."""
     return bool(lib.loqt_expands_codes(op, T, out, inp))
+
+
+def plan_merge_group(shapes) -> int:
+    """Tile of one launch of merges; shapes: (out, in, r) of each -- host only."""
+    cols = [(_i64 * len(shapes))(*c) for c in zip(*shapes)]
+    return int(lib.loqt_plan_merge_group(len(shapes), *cols))
 
 
 def plan_codes(T: int, N: int, K: int, extra: bool = False, max_slices: int = 32) -> int:

@@ -1672,6 +1672,18 @@ loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max
     return LOQT_OK;
 }
 
+int loqt_plan_merge_group(int n, const int64_t* out, const int64_t* in, const int64_t* r) {
+    if (n < 1 || n > MERGE_GROUP_MAX || !out || !in || !r) return 0;
+    MergeGroupLayer layers[MERGE_GROUP_MAX];
+    memset(layers, 0, sizeof(layers));
+    for (int i = 0; i < n; ++i) {
+        constexpr int64_t LIMIT = (int64_t)1 << 30;
+        if (out[i] <= 0 || in[i] <= 0 || r[i] <= 0 || out[i] > LIMIT || in[i] > LIMIT || r[i] > LIMIT) return 0;
+        layers[i].out = (int)out[i], layers[i].in = (int)in[i], layers[i].r = (int)r[i], layers[i].w_ld = (int64_t)round_up(in[i], 64);
+    }
+    return merge_group_tile(layers, n);
+}
+
 int loqt_plan_codes(int64_t T, int64_t N, int64_t K, int extra, int max_slices) {
     if (T <= 0 || N <= 0 || K <= 0 || max_slices < 1 || T > ((int64_t)1 << 30) || N > ((int64_t)1 << 30) || K > ((int64_t)1 << 30)) return 0;
     return nf4_tile_splits(T, N, (K + 63) / 64, extra != 0, max_slices);

@@ -121,26 +121,16 @@ hipError_t prepare_sized() {
 
 }  // namespace
 
-hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, hipStream_t st) {
-    if (n < 1 || n > MERGE_GROUP_MAX) return hipErrorInvalidValue;
-    TimedLaunch tl(slot, st);
-    MergeGroupParams g;
-    memset(&g, 0, sizeof(g));
-    g.n = n;
-    int64_t tiles = 0, tiles256 = 0, rank = 0;  // of 128x128, of 256x256; the largest
+// The tile of a group that has P in bf16
+int merge_group_tile(const MergeGroupLayer* layers, int n) {
+    int64_t tiles = 0, per_xcd256 = 0, most = 0, least = layers[0].r;  // of 128x128; of 256x256, on an XCD; ranks
     for (int i = 0; i < n; ++i) {
         const MergeGroupLayer& l = layers[i];
-        MergeGroupItem& it = g.it[i];
-        it.A = l.A, it.A_absmax = l.A_absmax, it.lda = l.lda, it.B = l.B, it.ldb = l.ldb;
-        it.w_codes = l.w_codes, it.w_absmax = l.w_absmax, it.out_codes = l.out_codes, it.out_absmax = l.out_absmax;
-        it.w_ld = l.w_ld, it.M = l.out, it.N = (int)l.w_ld, it.K = l.r, it.w_cols = l.in, it.alpha = l.s;
         tiles += ((l.out + 127) / 128) * ((l.w_ld + 127) / 128);
-        tiles256 += ((l.out + 255) / 256) * ((l.w_ld + 255) / 256);
-        rank = std::max<int64_t>(rank, l.r);
-        if (l.A_absmax && (l.r > A_CODES_TILES * BK || !layers[0].A_absmax)) return hipErrorInvalidValue;
-        if (!l.A_absmax && layers[0].A_absmax) return hipErrorInvalidValue;
+        per_xcd256 += (((l.out + 255) / 256) * ((l.w_ld + 255) / 256) + 7) / 8;
+        most = std::max<int64_t>(most, l.r), least = std::min<int64_t>(least, l.r);
     }
-    if (layers[0].A_absmax) return launch_grouped<64, true>(&g, st);
+    if (g_nt_tile_override != 0) return NT_128x128;
     // 64x128 where they take no more rounds, as in weight_tile.  The call for a block of seven weights, us, 128x128 / 64x128 /
     // 64x128 from the codes, by tiles of 128x128 (and of 64x128):
     //         196 (392)           280 (528)             432 (864)             574 (1102)            784 (1552)            1210 (2420)
@@ -156,11 +146,44 @@ hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, 
     //   768   26.0 / 24.0   32.3 / 28.4   41.2 / 37.8   40.9 / 38.4   43.3 / 42.7   43.6 / 42.6   47.1 / 47.4
     //   1024  27.8 / 26.3   36.1 / 32.7   46.6 / 43.5   46.2 / 44.0   49.1 / 49.4   50.2 / 49.7   54.4 / 55.6
     // 768 are two rounds of 64x128, three to a unit; a third one of a few tiles is made up for where the rank is small.
-    // 256x256 where a high rank makes the loop count and the last round of 256 tiles is nearly full.  The call, us, 128x128 / 256x256, by
-    // rounds: 518 / 508 (rank 1024, 12.06), 784 / 723 (1024, 18.9), 289 / 277 (800, 7.8), 238 / 230 (768, 6.75), 140 / 139 (512, 4.7),
-    // 331 / 330 (512, 12.06); 239 / 241 (256, 12.06), 153 / 155 (128, 9.1); 101 / 109 (512, 3.06), 74 / 78 (448, 2.3).
-    if (g_nt_tile_override == 0 && rank >= 512 && tiles256 >= 1024 && tiles256 * 100 >= (tiles256 + 255) / 256 * 256 * 92) return launch_grouped<256, false>(&g, st);
-    return g_nt_tile_override == 0 && (tiles <= 384 || (tiles > 512 && tiles <= (rank <= 384 ? 800 : 768))) ? launch_grouped<64, false>(&g, st) : launch_grouped<128, false>(&g, st);
+    if (tiles <= 384 || (tiles > 512 && tiles <= (most <= 384 ? 800 : 768))) return NT_64x128;
+    // 256x256 where every rank is high and their rounds (tiles of an XCD's 32 units; the last one counts half at least) are hardly
+    // more than the group's 128x128 tiles would fill without a gap or a padded edge: up to 1.02 times at rank 640, 1.05 at 1024.
+    // The call, 256x256 / 128x128, mean and largest, by that quotient (2400 groups of 7 to 24 weights, hidden sizes of 1536 to 5120):
+    //   rank              1.01          1.02          1.03          1.04          1.05          1.06          1.07
+    //   640               1.001 1.024   1.006 1.018   1.000 1.012   1.012 1.052   1.007 1.049   1.028 1.054   1.044 1.069
+    //   700 to 800        0.979 1.000   0.986 1.014   0.992 1.015   1.008 1.057   1.005 1.078   1.014 1.036   1.035 1.072
+    //   800 to 900        0.984 1.001   0.989 1.019   0.988 1.020   1.000 1.047   0.998 1.053   1.005 1.042   1.027 1.059
+    //   900 to 1000       0.971 0.978   0.974 0.999   0.981 1.015   0.984 1.041   0.993 1.046   1.000 1.036   1.017 1.041
+    //   1024              0.970 1.005   0.976 1.010   0.978 1.008   0.985 1.038   0.987 1.056   0.997 1.024   1.015 1.053
+    // (A line by the fill of the last round alone, from rank 512 on, took 256x256 for 14 weights of 1792 x 5016, rank 512, 133 -> 157 us,
+    // and for 21 of 1664 x 3584, whose tiles are padded, rank 635, 181 -> 213: 1.030 of the time on the mean.)
+    const double rounds = std::min((double)((per_xcd256 + 31) / 32), (double)per_xcd256 / 32.0 + 0.5);
+    if (least >= 640 && rounds * 1024.0 <= (0.97 + (double)std::min<int64_t>(least, 1024) / 12800.0) * (double)tiles) return NT_256x256;
+    return NT_128x128;
+}
+
+hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, hipStream_t st) {
+    if (n < 1 || n > MERGE_GROUP_MAX) return hipErrorInvalidValue;
+    TimedLaunch tl(slot, st);
+    MergeGroupParams g;
+    memset(&g, 0, sizeof(g));
+    g.n = n;
+    for (int i = 0; i < n; ++i) {
+        const MergeGroupLayer& l = layers[i];
+        MergeGroupItem& it = g.it[i];
+        it.A = l.A, it.A_absmax = l.A_absmax, it.lda = l.lda, it.B = l.B, it.ldb = l.ldb;
+        it.w_codes = l.w_codes, it.w_absmax = l.w_absmax, it.out_codes = l.out_codes, it.out_absmax = l.out_absmax;
+        it.w_ld = l.w_ld, it.M = l.out, it.N = (int)l.w_ld, it.K = l.r, it.w_cols = l.in, it.alpha = l.s;
+        if (l.A_absmax && (l.r > A_CODES_TILES * BK || !layers[0].A_absmax)) return hipErrorInvalidValue;
+        if (!l.A_absmax && layers[0].A_absmax) return hipErrorInvalidValue;
+    }
+    if (layers[0].A_absmax) return launch_grouped<64, true>(&g, st);
+    switch (merge_group_tile(layers, n)) {
+        case NT_256x256: return launch_grouped<256, false>(&g, st);
+        case NT_64x128: return launch_grouped<64, false>(&g, st);
+        default: return launch_grouped<128, false>(&g, st);
+    }
 }
 
 hipError_t prepare_weight_kernels() {

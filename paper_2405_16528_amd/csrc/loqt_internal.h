@@ -342,7 +342,7 @@ int gradient_tile(int epi, const GemmParams& p);
 hipError_t launch_dx_gradient(int slot_dx, const GemmParams& dx, int slot, int epi, const GemmParams& g, hipStream_t st);
 hipError_t launch_z_fold(int slot_z, const GemmParams& z, int slot, int epi, bool b_rc, const GemmParams& fold, hipStream_t st);
 hipError_t prepare_pair_kernels();
-// several merges as one launch (EPI_MERGE over the tiles of all layers, 64x128 or 128x128); at most MERGE_GROUP_MAX layers per
+// several merges as one launch (EPI_MERGE over the tiles of all layers, 64x128, 128x128 or 256x256); at most MERGE_GROUP_MAX layers per
 // launch.  A: deq(P) in bf16 or the codes of P (out x r, pitch lda); B: the trainable factor, r x in stored K x rows; the rest as in
 // GemmParams.
 constexpr int MERGE_GROUP_MAX = 24;
@@ -371,6 +371,7 @@ hipError_t launch_dequantize_grouped(const DequantGroupItem* items, int n, hipSt
 // copies of two matrices and U = s x B^T (bf16, both operands rows x K), in one launch where U runs on small tiles, timed as U
 // then, else two
 hipError_t launch_u_copies(int slot, const GemmParams& u, const DequantGroupItem* items, hipStream_t st);
+int merge_group_tile(const MergeGroupLayer* layers, int n);  // of such a launch, P in bf16 (host)
 hipError_t launch_merge_grouped(int slot, const MergeGroupLayer* layers, int n, hipStream_t st);
 // raise the LDS size of every kernel configuration of gemm_nt.hip / gemm.hip above the default (otherwise done at the
 // first launch of each), so that a first call can be recorded into a HIP graph

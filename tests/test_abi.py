@@ -271,6 +271,9 @@ def test_query_of_the_form_that_expands_codes_inside_the_products(lib):
     assert lib.loqt_set_path(5) == 1
 
 
+T256x256, T128x128, T64x128 = 1, 3, 5
+
+
 def test_slices_of_products_that_expand_codes(lib):
     """dx of a few tokens: with a slice of its own for Z B it came in half as many slices, on half of the chip"""
     from paper_2405_16528_amd import binding as L
@@ -281,6 +284,21 @@ def test_slices_of_products_that_expand_codes(lib):
                 n, kt = L.plan_codes(T, 4096, K, False, most), -(-K // 64)
                 assert 1 <= n <= most and -(-kt // -(-kt // n)) == n  # no slice is empty
     assert L.plan_codes(0, 4096, 4096) == 0 and L.plan_codes(16, 4096, 4096, max_slices=0) == 0
+
+
+def test_tile_of_grouped_merges(lib):
+    """256x256 only where every rank is high and their rounds are hardly more than the 128x128 tiles fill: us on 256x256 / 128x128"""
+    from paper_2405_16528_amd import binding as L
+
+    def block(h, ffn, r, n=7, low=None):
+        shapes = ([(h, h)] * 4 + [(ffn, h)] * 2 + [(h, ffn)]) * 3
+        return L.plan_merge_group([(o, i, low if low and k == 0 else r) for k, (o, i) in enumerate(shapes[:n])])
+    assert block(4096, 11008, 1024) == T256x256 and block(5120, 13824, 1024) == T256x256  # 480 / 501, 738 / 773
+    assert block(1792, 5016, 512, 14) == T128x128  # 157 / 133
+    assert block(1664, 3584, 635, 21) == T128x128 and block(2688, 6144, 641, 21) == T128x128  # padded: 213 / 181, 541 / 488
+    assert block(4096, 11008, 512) == T128x128 and block(4096, 11008, 1024, low=256) == T128x128
+    assert block(512, 1376, 1024) == T64x128
+    assert L.plan_merge_group([(0, 64, 64)]) == 0 and L.plan_merge_group([(64, 64, 64)] * 25) == 0
 
 
 @pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
