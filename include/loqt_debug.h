@@ -90,11 +90,13 @@ loqt_status loqt_plan_product(int64_t M, int64_t N, int64_t Nx, int64_t *n_large
  */
 loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max_splits, int *tile, int *splits);
 /*
- * Diagnostics (host only); a tile is one of loqt_plan_tiles, 0 for bad sizes.
- * loqt_plan_merge_group: one launch of n (<= 24) merges.
+ * Diagnostics (host only) of the launches that walk the weight; the result is a tile as of loqt_plan_tiles, 0 for bad sizes.
+ * loqt_plan_weight: the fold or merge of one weight out x in with rank r, P expanded: op LOQT_OP_FWD (fold), LOQT_OP_FWD_NQ (unquantised
+ * fold or merge), LOQT_OP_MERGE, LOQT_OP_FWD_RIGHT, LOQT_OP_MERGE_RIGHT.  loqt_plan_merge_group: one launch of n (<= 24) merges.
  * loqt_plan_codes: slices of the contraction (K elements) of a product T x N that expands the codes, at most max_slices of them;
  * extra != 0: with a slice of its own for a second, unquantised operand.
  */
+int loqt_plan_weight(int op, int64_t out, int64_t in, int64_t r);
 int loqt_plan_merge_group(int n, const int64_t *out, const int64_t *in, const int64_t *r);
 int loqt_plan_codes(int64_t T, int64_t N, int64_t K, int extra, int max_slices);
 

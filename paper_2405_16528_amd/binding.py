@@ -122,6 +122,8 @@ lib.loqt_resolved_path.restype = _i
 lib.loqt_resolved_path.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_expands_codes.restype = _i
 lib.loqt_expands_codes.argtypes = [_i, _i64, _i64, _i64]
+lib.loqt_plan_weight.restype = _i
+lib.loqt_plan_weight.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_plan_merge_group.restype = _i
 lib.loqt_plan_merge_group.argtypes = [_i, _P(_i64), _P(_i64), _P(_i64)]
 lib.loqt_plan_codes.restype = _i
@@ -453,6 +455,11 @@ def resolved_path(op: int, T: int, out: int, inp: int) -> int:
 def expands_codes(op: int, T: int, out: int, inp: int) -> bool:
     """Whether OP_FWD or OP_BWD of these sizes expands the codes inside the products of a few hundred tokens -- host only."""
     return bool(lib.loqt_expands_codes(op, T, out, inp))
+
+
+def plan_weight(op: int, out: int, inp: int, r: int) -> int:
+    """Tile of the fold (OP_FWD, OP_FWD_NQ, OP_FWD_RIGHT) or merge (OP_MERGE, OP_MERGE_RIGHT) of one weight -- host only."""
+    return int(lib.loqt_plan_weight(op, out, inp, r))
 
 
 def plan_merge_group(shapes) -> int:

@@ -1672,6 +1672,19 @@ loqt_status loqt_plan_tiles(int64_t M, int64_t N, int64_t K, int sliced, int max
     return LOQT_OK;
 }
 
+int loqt_plan_weight(int op, int64_t out, int64_t in, int64_t r) {
+    constexpr int64_t LIMIT = (int64_t)1 << 30;
+    if (out <= 0 || in <= 0 || r <= 0 || out > LIMIT || in > LIMIT || r > LIMIT) return 0;
+    const bool merge = op == LOQT_OP_MERGE || op == LOQT_OP_MERGE_RIGHT, right = op == LOQT_OP_FWD_RIGHT || op == LOQT_OP_MERGE_RIGHT;
+    if (!merge && !right && op != LOQT_OP_FWD && op != LOQT_OP_FWD_NQ) return 0;
+    GemmParams p;
+    memset(&p, 0, sizeof(p));
+    p.M = (int)out;
+    p.N = (int)(merge ? round_up(in, 64) : in);
+    p.A[0].K = (int)r;
+    return weight_tile(merge ? EPI_MERGE : op == LOQT_OP_FWD_NQ ? EPI_ACC_BF16 : EPI_FOLD, !right, p);
+}
+
 int loqt_plan_merge_group(int n, const int64_t* out, const int64_t* in, const int64_t* r) {
     if (n < 1 || n > MERGE_GROUP_MAX || !out || !in || !r) return 0;
     MergeGroupLayer layers[MERGE_GROUP_MAX];

@@ -203,12 +203,23 @@ hipError_t prepare_weight_kernels() {
     return launch_grouped<128, false>(nullptr, nullptr);
 }
 
+// Rounds of an XCD's 32 compute units, each with one 256x256 tile or two of 128x128; the last one by its fill
+static double rounds_of_256x256(int64_t tiles) {
+    const int64_t x = (tiles + 7) / 8, rest = x & 31;
+    return (double)(x >> 5) + (rest ? 0.7 + 0.3 * (double)rest / 32.0 : 0.0);
+}
+static double rounds_of_128x128(int64_t tiles) {
+    const int64_t x = (tiles + 7) / 8, rest = x & 63;
+    return (double)(x >> 6) + (rest == 0 ? 0.0 : rest <= 32 ? 0.5 + 0.15 * (double)rest / 32.0 : 0.85 + 0.15 * (double)(rest - 32) / 32.0);
+}
+
 int weight_tile(int epi, bool b_rc, const GemmParams& p) {
     auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
     if (g_nt_tile_override != 0) return g_nt_tile_override;
     // One 256x256 tile per compute unit, eight waves, moves the least data per product, but has nothing to hide its first loads and its
-    // last stores behind, which two resident 128x128 work-groups have: it is ahead where its rounds of 256 tiles are nearly full.
-    // Time of the launch, 256x256 / 128x128, by tiles of 256x256 (2048 rows):
+    // last stores behind, which two resident 128x128 work-groups have, and its rounds of 256 tiles are coarser and padded more.  So
+    // the rounds of either are counted, and one of 256x256 takes 1 / `per` of one of 128x128 (two to a unit), a little less the longer
+    // the contraction.  Time of the launch, 256x256 / 128x128, by tiles of 256x256 (2048 rows):
     //                      160    192    224    256    320    384    448    512    640    768
     //   fold, rank 64      1.03   0.97   0.93   0.88   1.23   1.12   1.00   1.16   1.08   0.98
     //         256          0.98   0.97   0.88   0.87   1.21   1.08   0.98   1.07   1.02   0.92
@@ -220,19 +231,24 @@ int weight_tile(int epi, bool b_rc, const GemmParams& p) {
     //         1024         1.00   0.97   0.87   0.86   1.16   1.04   0.94   0.86   0.98   0.86
     //   unquantised merge, rank 256 / 1024
     //                      1.07 / 1.02   0.99 / 0.98   0.96 / 0.89   0.95 / 0.91   1.16   1.10 / 1.06   1.06 / 0.98   1.16 / 0.97   1.07 / 0.96   0.98 / 0.86
-    // With B stored rows x K (the projection on the input side) about 0.03 more each: merge, rank 256, 416 to 704 tiles 0.93 to 1.02, fold,
-    // rank 512, 160 to 192 tiles 1.00, 5461 x 2048 20.6 -> 21.4.  And not where the larger tiles are padded by more than 4 % beyond
-    // the smaller ones (merge, 1152 x 11378, rank 192: 22.8 -> 29.9; 1152 x 12984, rank 896: 50.6 -> 54.1) or the contraction is
-    // shorter than a k-tile (merge, 1600 x 8768, rank 8: 23.4 -> 28.9).
-    // And, us, 11008 x 4096, rank 1024 (688 tiles): fold 114 -> 100, merge 120 -> 111; 4096 x 4096 (256): merge 46 -> 39.8; 2048 x 5461,
-    // rank 512 (176): fold 22.4 -> 21.5.  (With four waves the merge was never ahead, the fold in one round, 36.2 against 35.4.)
-    if (epi == EPI_FOLD || epi == EPI_MERGE || epi == EPI_ACC_BF16) {
-        const int64_t t256 = tiles(256, 256), rounds = (t256 + 255) / 256;
-        const int K = p.A[0].K;
-        int64_t least = rounds * 256 + 1;  // (never: folds of low rank over more than one round are bound by their stores)
-        if (rounds == 1) least = epi == EPI_FOLD && b_rc ? (K >= 256 ? 160 : 192) : K >= 512 && epi != EPI_FOLD ? 192 : 208;
-        else if (epi == EPI_MERGE || K > 768) least = rounds * (K < 256 ? 244 : b_rc || K > 768 ? 208 : 220);
-        if (t256 >= least && K >= 64 && tiles(128, 128) * 26 >= t256 * 100) return NT_256x256;
+    // `per` is from 6000 random launches of 385 tiles of 128x128 and more (512 to 13824 rows and columns, ranks 16 to 1024).  Mean of
+    // its choice against 128x128 everywhere and launches that it makes more than 2 % slower, and the same for lines by the fill of the
+    // 256x256 rounds and a limit on their padding, which it has replaced:
+    //   merge, B K x rows   0.980, 14 of 1705 (0.989, 42: 5632 x 10240, rank 306, 3.4 rounds against 6.9, 82 -> 89 us)
+    //          rows x K     0.990, 13 of 879  (0.994, 16)
+    //   fold,  B K x rows   0.977, 39 of 1695 (0.988, 22)
+    //          rows x K     0.988, 14 of 874  (0.996, 14)
+    //   unquantised merge   0.982, 7 of 870   (0.992, 1, but 1152 x 12288, rank 989, was left on 128x128 for its padding, 36 -> 41 us)
+    // Over more than one round folds and unquantised merges of low rank are bound by their stores (fold, 5376 x 12068, rank 351, 112 us against 98); in one round
+    // folds with B stored K x rows are ahead as soon as 128x128 tiles need a second one (0.93 to 0.99 of the time on the mean).
+    // Contractions shorter than a k-tile leave the epilogue, 1600 x 8768, rank 8, 23.4 -> 28.9.
+    const int K = p.A[0].K;
+    if ((epi == EPI_FOLD || epi == EPI_MERGE || epi == EPI_ACC_BF16) && K >= 64) {
+        const int64_t t = tiles(128, 128), t256 = tiles(256, 256);
+        const bool one = t256 <= 256;
+        const double per = (epi == EPI_FOLD && b_rc && one ? 0.57 : 0.51) + 0.003 * (double)std::min((K + BK - 1) / BK, 16);
+        if ((t > 640 || (t > 384 && t <= 512)) && (epi == EPI_MERGE || one || K >= (epi == EPI_FOLD ? 512 : 256)) && rounds_of_256x256(t256) < per * rounds_of_128x128(t))
+            return NT_256x256;
     }
     // 64x128 tiles on two stages, of which a compute unit holds three: where 128x128, two to a unit, leave room for the 64x128
     // to take no more rounds.  Time of the launch, 64x128 / 128x128, ranks of 96, 300 and 768, by tiles of 128x128:

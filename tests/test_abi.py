@@ -301,6 +301,20 @@ def test_tile_of_grouped_merges(lib):
     assert L.plan_merge_group([(0, 64, 64)]) == 0 and L.plan_merge_group([(64, 64, 64)] * 25) == 0
 
 
+def test_tile_of_folds_and_merges(lib):
+    """256x256 by rounds of either tile: us on 256x256 / 128x128"""
+    from paper_2405_16528_amd import binding as L
+    for op, out, inp, r, want in (
+            (L.OP_MERGE, 5632, 10240, 306, T128x128),  # 3.4 rounds against 6.9: 89 / 82
+            (L.OP_MERGE, 6208, 6400, 463, T128x128), (L.OP_MERGE, 5039, 13184, 512, T128x128),  # 79 / 73, 112 / 105
+            (L.OP_FWD_NQ, 1152, 12288, 989, T256x256),  # one round against two, though padded: 36 / 41
+            (L.OP_MERGE, 1152, 12672, 512, T256x256),
+            (L.OP_FWD, 2048, 5461, 512, T256x256), (L.OP_FWD, 4096, 4096, 1024, T256x256), (L.OP_FWD, 11008, 4096, 1024, T256x256),
+            (L.OP_FWD, 5376, 12068, 351, T128x128), (L.OP_MERGE, 1600, 8768, 8, T128x128), (L.OP_MERGE, 2048, 768, 256, T64x128)):
+        assert L.plan_weight(op, out, inp, r) == want, (op, out, inp, r)
+    assert L.plan_weight(L.OP_BWD, 4096, 4096, 64) == 0 and L.plan_weight(L.OP_FWD, 0, 4096, 64) == 0
+
+
 @pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
 def test_stream_without_torch_private_names(lib, monkeypatch, missing):
     """The stream handle comes from two private functions of torch; without one of them, from the public call."""
