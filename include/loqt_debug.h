@@ -59,7 +59,7 @@ int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in);
  * kernel for a handful of tokens is another one).  Which of the two a call takes follows from its sizes alone, so a test that is
  * there for that kernel asks here whether it still reaches it.
  */
-int loqt_expands_codes(int op, int64_t T, int64_t out, int64_t in);
+int loqt_expands_codes(int op, int64_t T, int64_t out, int64_t in, int64_t r);
 
 /*
  * Tile-shape option (process-wide, not thread-safe; for tests and tuning).  The products of the

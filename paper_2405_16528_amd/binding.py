@@ -121,7 +121,7 @@ lib.loqt_set_tile.argtypes = [_i]
 lib.loqt_resolved_path.restype = _i
 lib.loqt_resolved_path.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_expands_codes.restype = _i
-lib.loqt_expands_codes.argtypes = [_i, _i64, _i64, _i64]
+lib.loqt_expands_codes.argtypes = [_i, _i64, _i64, _i64, _i64]
 lib.loqt_plan_weight.restype = _i
 lib.loqt_plan_weight.argtypes = [_i, _i64, _i64, _i64]
 lib.loqt_plan_merge_group.restype = _i
@@ -452,9 +452,9 @@ def resolved_path(op: int, T: int, out: int, inp: int) -> int:
     return int(lib.loqt_resolved_path(op, T, out, inp))
 
 
-def expands_codes(op: int, T: int, out: int, inp: int) -> bool:
+def expands_codes(op: int, T: int, out: int, inp: int, r: int) -> bool:
     """Whether OP_FWD or OP_BWD of these sizes expands the codes inside the products of a few hundred tokens -- host only."""
-    return bool(lib.loqt_expands_codes(op, T, out, inp))
+    return bool(lib.loqt_expands_codes(op, T, out, inp, r))
 
 
 def plan_weight(op: int, out: int, inp: int, r: int) -> int:

@@ -131,32 +131,34 @@ bool use_folded_bwd(int64_t T, int64_t out, int64_t in) {
 // weight is made.  That pays for a weight whose copy costs more than the slower loop, the more so the more tokens there are, and
 // where the contraction (in; backward out) is long enough for the prologues of a k-tile's pipeline not to count.  In the backward
 // pass the copies win more often: they go out beside nothing else, the products of dx fill the chip (the more the wider the weight)
-// and the gradient shares their launch.  Time of the call with the codes against with copies, means over random weights
-// (38000 calls, 1 to 60 million elements, ranks 16 to 512), by millions of elements:
-//   forward, in       512..724  1024..1448  2048..2896  5800..      backward, out   512..724  1024..1448  2048..2896  5800..
-//   33..64 tokens                                                  up to 32 tokens
-//     1.5..2.5          1.22       1.08        1.02       1.02         1.5..2.5       1.25       1.03       0.94       0.89
-//     6..9              0.94       0.88        0.82       0.80         6..9           1.13       0.97       0.81       0.82
-//     20..30                                   0.71       0.72         20..30                               0.98       0.78
-//   65..128                                                        33..64
-//     2.5..4            1.36       1.21        1.09       1.11         1.5..2.5       1.36       1.10       0.96       0.93
-//     6..9              1.07       1.07        0.92       0.95         6..9           1.23       1.06       0.88       0.89
-//     14..20                       0.85        0.81       0.81         20..30                               1.07       0.81
-//   129..192                                                       65..128
-//     6..9              1.28       1.25        1.06       1.08         6..9           1.38       1.22       1.00       1.01
-//     14..20                       0.97        0.89       0.89         20..30                               1.14       0.89
-//   193..256                                                       129..256
-//     14..20                       1.03        0.92       0.89         14..20                    1.33       1.23       1.06
-//     30..60                                   0.95       0.75         30..60                               1.30       0.93
-// The lines below leave calls 0.3 % above the better of the two on the mean, one in fifty by more than 5 %.
-bool use_nf4_tile(int64_t T, int64_t out, int64_t in, bool backward) {
+// and the gradient shares their launch.  Time of the backward call with the codes against with copies, means over random weights
+// (2700 calls of 0.4 to 80 million elements, ranks 32 to 1024), by out (lines) and in:
+//   up to 32 tokens  512   1024  2048  4096  8192    33..64     512   1024  2048  4096  8192
+//   724..1023        1.37  1.30  1.25  1.17  1.09               1.43  1.38  1.28  1.24  1.18
+//   1024..1447       1.19  1.15  0.95  0.96  1.09               1.19  1.10  1.09  1.10  1.17
+//   1448..2047       1.02  1.01  0.95  0.86  1.01               1.00  0.97  0.96  1.01  1.12
+//   2048..2895       1.08  0.94  0.89  0.81  1.02               0.98  0.96  0.91  0.90  1.06
+//   4096..5791       0.93  0.85  0.80  0.82  0.84               0.87  0.92  0.86  0.83  0.87
+//   65..128                                          129..256
+//   2048..2895       1.12  1.07  0.99  1.11  1.10               1.27  1.25  1.33  1.30  1.26
+//   2896..4095       1.06  1.02  0.99  1.03  1.03               1.21  1.21  1.18  1.17  1.16
+//   4096..5791       1.01  1.00  0.96  0.91  0.92               1.28  1.18  1.13  1.14  1.04
+//   5792..8191       1.02  1.02  0.95  0.86  0.86               1.27  1.20  1.06  0.94  1.06
+//   8192..11584      1.07  0.96  0.89  0.82                     1.22  1.16  1.00  0.93  1.00
+// Forward (2170 calls, 33 tokens and more) it is the size of the weight, in / out counting for little.  A copy of P is made or not
+// with that of W, so a high rank counts towards the codes.  65 tokens take tiles of 128.  The lines below leave calls 0.21 % (forward) and
+// 0.31 % (backward) above the better of the two on the mean, 1.4 % and 2.4 % of them by more than 5 %; lines by steps of T and of one side,
+// which they replace, 0.35 % and 0.49 %, 2.5 % and 3.9 % (forward, 50 tokens, 6080 x 1024, rank 882, 22.2 us with the codes, 25.5 with
+// copies; backward, 10 tokens, 1280 x 4864, rank 807, 27.4 and 32.3).
+bool use_nf4_tile(int64_t T, int64_t out, int64_t in, int64_t r, bool backward) {
     if (T > 256) return false;
     if (g_path == LOQT_PATH_CODES) return true;
     if (g_path != LOQT_PATH_AUTO || use_folded(T, out, in)) return false;
-    const int64_t n = out * in;
-    if (!backward) return n >= (in >= 1400 ? 60000 * T - 1000000 : 90000 * T + 2000000);
-    if (T <= 64) return out >= 1400 && 2 * in <= (T <= 32 ? 12 : 7) * out;
-    return out >= (T <= 80 ? 2800 : 4000) && n >= 200000 * T - 12000000;
+    if (!backward)
+        return (double)out * ((double)in + 0.5 * (double)r) >= (double)(2000000 + 50000 * T) * pow((double)out / (double)in, 0.1);
+    const int64_t least = T <= 64 ? 1250 + 7 * T : std::min<int64_t>(5500, 2600 + 40 * (T - 64));
+    return 2 * out + r >= 2 * least && out * in >= std::max<int64_t>(1500000, 200000 * T - 10000000) &&
+           64 * in <= std::max<int64_t>(256, 416 - 3 * T) * out;
 }
 
 inline size_t bf16_bytes(int64_t rows, int64_t cols) {
@@ -735,7 +737,7 @@ static loqt_status fwd_impl(const loqt_bf16* x, int64_t ld_x, int64_t T, const l
     // (the slices go where the copy of the weight would be)
     char* const slices = reinterpret_cast<char*>(ws) + L.Wb;
     const size_t slices_room = ws_bytes - L.Wb;
-    if (!save_weff && use_nf4_tile(T, out, in, false) && slices_that_fit(T, out, slices_room) >= 1) {
+    if (!save_weff && use_nf4_tile(T, out, in, r, false) && slices_that_fit(T, out, slices_room) >= 1) {
         memset(&p, 0, sizeof(p));  // U = s x B^T
         p.A[0] = bf16_operand(x, ld_x, (int)T, (int)in);
         p.B[0] = bf16_operand(B, ld_B, (int)r, (int)in);
@@ -882,7 +884,7 @@ static loqt_status bwd_impl(const loqt_bf16* dy, int64_t ld_dy, const loqt_bf16*
         const int64_t ldw = saved ? ld_saved : L.ldw;
         // a few hundred tokens: Z and dx straight from the codes, their slices where the copies of W and P would be
         const size_t room = ws_bytes - L.Wb;
-        const bool tile = !saved && use_nf4_tile(T, out, in, true) && slices_that_fit(T, r, room) >= 1 &&
+        const bool tile = !saved && use_nf4_tile(T, out, in, r, true) && slices_that_fit(T, r, room) >= 1 &&
                           slices_that_fit(T, in, room) >= 2;
         if (tile) {
             memset(&p, 0, sizeof(p));
@@ -1126,10 +1128,10 @@ int loqt_resolved_path(int op, int64_t T, int64_t out, int64_t in) {
     return use_folded(T, out, in) ? LOQT_PATH_FOLDED : LOQT_PATH_PREPASS;
 }
 
-int loqt_expands_codes(int op, int64_t T, int64_t out, int64_t in) {
-    if (T <= 0 || out <= 0 || in <= 0) return 0;
-    if (op == LOQT_OP_FWD) return !use_few_tokens(T) && use_nf4_tile(T, out, in, false);
-    return op == LOQT_OP_BWD && use_nf4_tile(T, out, in, true);
+int loqt_expands_codes(int op, int64_t T, int64_t out, int64_t in, int64_t r) {
+    if (T <= 0 || out <= 0 || in <= 0 || r <= 0) return 0;
+    if (op == LOQT_OP_FWD) return !use_few_tokens(T) && use_nf4_tile(T, out, in, r, false);
+    return op == LOQT_OP_BWD && use_nf4_tile(T, out, in, r, true);
 }
 
 loqt_status loqt_init_compensate(const float* W, int64_t ld_w, const float* P, int64_t ld_p, int64_t out,

@@ -256,12 +256,12 @@ def test_auto_rule_on_the_paper_workloads(lib):
 def test_query_of_the_form_that_expands_codes_inside_the_products(lib):
     from paper_2405_16528_amd import binding as L
 
-    def ask(T, out, inp):
-        return L.expands_codes(L.OP_FWD, T, out, inp), L.expands_codes(L.OP_BWD, T, out, inp)
+    def ask(T, out, inp, r=16):
+        return L.expands_codes(L.OP_FWD, T, out, inp, r), L.expands_codes(L.OP_BWD, T, out, inp, r)
     assert ask(256, 13824, 5120) == (True, True) and ask(257, 13824, 5120) == (False, False)
     assert ask(16, 13824, 5120) == (False, True)  # (forward: the kernel for a handful of tokens)
     assert ask(64, 1024, 1024) == (False, False) and ask(200, 1280, 1024) == (False, False)
-    assert not L.expands_codes(L.OP_MERGE, 64, 4096, 4096) and ask(0, 4096, 4096) == (False, False)
+    assert not L.expands_codes(L.OP_MERGE, 64, 4096, 4096, 16) and ask(0, 4096, 4096) == ask(64, 4096, 4096, 0) == (False, False)
     try:
         for path, want in ((L.PATH_CODES, True), (L.PATH_PREPASS, False), (L.PATH_FOLDED, False), (L.PATH_FUSED, False)):
             L.set_path(path)
@@ -272,6 +272,25 @@ def test_query_of_the_form_that_expands_codes_inside_the_products(lib):
 
 
 T256x256, T128x128, T64x128 = 1, 3, 5
+
+
+def test_codes_or_copies_where_lines_by_steps_had_slowed_calls(lib):
+    """Calls beside the corners of lines by steps of T and of one side, us with the codes and with copies"""
+    from paper_2405_16528_amd import binding as L
+    for T, out, inp, r, codes, copies in ((50, 6080, 1024, 882, 22.2, 25.5), (37, 6144, 820, 699, 20.2, 22.8), (142, 10903, 1212, 256, 36.6, 40.0),
+                                          (56, 5760, 1195, 640, 23.3, 24.8), (80, 1024, 3712, 115, 22.5, 20.9), (41, 5775, 768, 128, 17.6, 16.2),
+                                          (34, 3072, 1152, 64, 17.2, 15.2)):
+        assert L.expands_codes(L.OP_FWD, T, out, inp, r) == (codes < copies), (T, out, inp)
+    for T, out, inp, r, codes, copies in ((10, 1280, 4864, 807, 27.4, 32.3), (1, 1377, 2560, 667, 24.6, 28.4), (4, 1306, 6400, 640, 29.2, 33.7),
+                                          (33, 1280, 1280, 128, 24.5, 19.8), (65, 1792, 1920, 64, 27.9, 23.4)):
+        assert L.expands_codes(L.OP_BWD, T, out, inp, r) == (codes < copies), (T, out, inp)
+    # no jumps: one token more moves the least square weight by 80 columns at most, but at 65 (backward, tiles of 128)
+    for op in (L.OP_FWD, L.OP_BWD):
+        for T in range(33, 257):
+            least = min((n for n in range(1000, 14000, 8) if L.expands_codes(op, T, n, n, 256)), default=14000)
+            if T > 33 and T != 65:
+                assert 0 <= least - before <= 80, (op, T)
+            before = least
 
 
 def test_slices_of_products_that_expand_codes(lib):

@@ -119,13 +119,13 @@ assert _COLD_SIZES in _COLD_CAPTURE
     (16, 4200, 4096, 256, "registers", "codes"),  # ... from codes expanded inside the products
     (200, 1280, 1024, 128, "copies", "copies"),  # small tiles and slices
     (200, 4200, 4096, 256, "codes", "copies"),
-    (200, 7000, 4096, 256, "codes", "codes"),
+    (200, 7600, 4096, 256, "codes", "codes"),
 ])
 def test_first_call_with_few_tokens_can_be_captured_after_prepare(T, out, inp, r, fwd, bwd):
     """The same for the forms that calls of a few or a few hundred tokens take."""
     from paper_2405_16528_amd import binding as L
     assert (L.resolved_path(L.OP_FWD, T, out, inp) == L.PATH_FUSED) == (fwd == "registers")
-    assert L.expands_codes(L.OP_FWD, T, out, inp) == (fwd == "codes") and L.expands_codes(L.OP_BWD, T, out, inp) == (bwd == "codes")
+    assert L.expands_codes(L.OP_FWD, T, out, inp, r) == (fwd == "codes") and L.expands_codes(L.OP_BWD, T, out, inp, r) == (bwd == "codes")
     import os
     import subprocess
     import sys

@@ -63,7 +63,7 @@ def test_fed_by_the_expansion(T, out, inp, r):
     try:
         for path in (L.PATH_CODES, L.PATH_PREPASS):
             L.set_path(path)
-            assert all(L.expands_codes(op, T, out, inp) == (path == L.PATH_CODES) for op in (L.OP_FWD, L.OP_BWD))
+            assert all(L.expands_codes(op, T, out, inp, r) == (path == L.PATH_CODES) for op in (L.OP_FWD, L.OP_BWD))
             y, dx = G.bf16_empty(T, out, fill=float("nan")), G.bf16_empty(T, inp, fill=float("nan"))
             dB = torch.full((r, inp), float("nan"), device="cuda")
             L.loqt_linear_fwd(x, Wq, Pq, B, 0.5, y, G.workspace(L.OP_FWD, T, out, inp, r))
