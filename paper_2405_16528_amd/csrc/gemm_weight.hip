@@ -239,7 +239,8 @@ int weight_tile(int epi, bool b_rc, const GemmParams& p) {
     //   fold,  B K x rows   0.977, 39 of 1695 (0.988, 22)
     //          rows x K     0.988, 14 of 874  (0.996, 14)
     //   unquantised merge   0.982, 7 of 870   (0.992, 1, but 1152 x 12288, rank 989, was left on 128x128 for its padding, 36 -> 41 us)
-    // Over more than one round folds and unquantised merges of low rank are bound by their stores (fold, 5376 x 12068, rank 351, 112 us against 98); in one round
+    // Over more than one round folds and unquantised merges of low rank are bound by their stores (fold, 5376 x 12068, rank 351, 112 us against 98;
+    // merge, 8192 x 8192, rank 256, 75 against 68); in one round
     // folds with B stored K x rows are ahead as soon as 128x128 tiles need a second one (0.93 to 0.99 of the time on the mean).
     // Contractions shorter than a k-tile leave the epilogue, 1600 x 8768, rank 8, 23.4 -> 28.9.
     const int K = p.A[0].K;
@@ -247,7 +248,7 @@ int weight_tile(int epi, bool b_rc, const GemmParams& p) {
         const int64_t t = tiles(128, 128), t256 = tiles(256, 256);
         const bool one = t256 <= 256;
         const double per = (epi == EPI_FOLD && b_rc && one ? 0.57 : 0.51) + 0.003 * (double)std::min((K + BK - 1) / BK, 16);
-        if ((t > 640 || (t > 384 && t <= 512)) && (epi == EPI_MERGE || one || K >= (epi == EPI_FOLD ? 512 : 256)) && rounds_of_256x256(t256) < per * rounds_of_128x128(t))
+        if ((t > 640 || (t > 384 && t <= 512)) && (epi == EPI_MERGE || one || K >= 512) && rounds_of_256x256(t256) < per * rounds_of_128x128(t))
             return NT_256x256;
     }
     // 64x128 tiles on two stages, of which a compute unit holds three: where 128x128, two to a unit, leave room for the 64x128
