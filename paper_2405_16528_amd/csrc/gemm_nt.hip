@@ -34,17 +34,17 @@ BF16Plan plan_bf16_product(int64_t M, int64_t N, int64_t Nx) {
 // an estimate in microseconds.  Per shape: work-groups per compute unit, the time of one k-tile when a few work-groups
 // have memory to themselves (a serial chain of barrier, fragment reads and matrix instructions), when every compute unit runs
 // one and when it runs two (shared LDS, L2, fabric and power), and the rest of a tile (first loads, epilogue).
-// Over 15300 random products of all three operand orders, every tile and 1 to 32 slices timed by themselves, the plan takes 1.03 of the
-// time of the best choice (y 1.032, dx and Z 1.027, gradients 1.030).  In whole calls (33700 products of
-// forward and backward calls of random sizes, each on the tiles and slices that come near the best, the others as planned) the plan
-// makes the call 1.017 times as long as the best choice.  Two things come from there.  A tile of 256x128 costs 5.0 beside its loop:
-// with 4.0 they were taken, often in two or three slices, where 256x256 or 128x128 in one are ahead (y of 7817 x 13467 x 1856 350 us
+// Over 6000 random products (y, dx and Z, gradients; every tile, 1 to 32 slices, timed by themselves) the plan takes 1.023 of the time of the
+// best choice, 1.033 over those of 9 us and more, one in eight of which is more than 10 % off (1.025, 1.037 and one in seven with 128x128 at
+// the price of the two-stage loop everywhere).  Constants fitted to products by themselves (1.016) don't hold in whole calls, so two
+// come from 33700 products of forward and backward calls of random sizes (timed with loops in which every wave loaded).  A tile of
+// 256x128 costs 5.0 beside its loop: with 4.0 they were taken, often in two or three slices, where 256x256 or 128x128 in one are ahead (y of 7817 x 13467 x 1856 350 us
 // against 308).  And `cold`: operands of more than 128 MB do not stay in the Infinity Cache, and the smaller the tile the more often they
 // are read (y of 4417 x 2135 x 12381 329 us on 256x128 in three slices and 216 on 256x256, of 7621 x 1465 x 9856 234 in two and 177).
 // With both, 122 of those products make their call 1.05 times as fast or more, 15 as slow.  The 64-row tiles have rings of
 // three and four stages (256 x 128 x 4096 on 64x64, us: 17.8 with three, 18.0 with four, 21.6 with eight; 1024 x 1024 x 4096
-// 21.1, 18.8 and 23.3).  128x128 tiles have two, which lets a compute unit hold two of them; alone on it, three or four are no
-// faster (1024 x 2048 x 2048: 20.5 us with two and with four).
+// 21.1, 18.8 and 23.3).  128x128 tiles have two, which lets a compute unit hold two of them; where it gets one at most they have three and
+// waves of their own for the loads, and a price of their own (kLone128).
 struct TileSpec {
     int id, bm, bn, per_cu;
     double alone, full, both, fix, cold;
@@ -56,6 +56,15 @@ constexpr TileSpec kTiles[] = {
     {NT_256x128, 256, 128, 1, 0.60, 0.78, 0.78, 5.0, 1.25},
     {NT_256x256, 256, 256, 1, 1.20, 1.49, 1.49, 7.95, 1.0},
 };
+// 128x128 tiles in a launch that gives a compute unit one of them at most (one_to_a_unit).  At the price of the two-stage loop (0.47 to
+// 0.61) they lost to 64x128 and to slices of 256x128 that are slower (forward + backward of 746 tokens, 3234 x 3234, rank 64, unquantised,
+// 106.7 -> 85.9 us; 640, 3970 x 3970, rank 32, 126.8 -> 111.5).  Of 1444 random calls of more than 256 tokens 157 change, to 0.970 of
+// the time on the mean, two by more than 4 % for the worse.  By themselves these products take 0.35 to 0.51 us per k-tile, but at 0.57
+// they also take one slice where 256x128 in two is ahead in the call (y of 7808 x 384 x 7296, 161.6 -> 171.1): 274 change then, eight
+// for the worse.  (Another 919 calls of 45 us and more: 0.994 over all, 47 of them 4 % faster or more, one slower, 1152 x 5760, rank 69,
+// 2176 tokens, 113.5 -> 119.3.)  Not for gradients: on 64-row tiles they share the launch of dx (451 tokens, 1792 x 3035, rank 768, 77 us; 86 with
+// the gradient on 128x128).
+constexpr TileSpec kLone128{NT_128x128, 128, 128, 1, 0.27, 0.62, 0.62, 2.8, 1.1};
 
 // `tiles` of the output in `splits` slices of at most `per` k-tiles: the time of the fullest compute unit.  Each XCD takes an
 // eighth of the tiles, rounded up, of every slice: 84 tiles in three slices are 33 work-groups for each of seven XCDs with 32
@@ -63,8 +72,10 @@ constexpr TileSpec kTiles[] = {
 // And the first unit with a second work-group holds up the launch, though less than when all have two and share what is beyond
 // the unit: of the way from `full` to `both`, 0.3 at once (1024 x 5120 x 13824: 320 tiles of 128x128 231, 160 of 256x128 165;
 // 437 x 5062 x 5384: 280 of 64x128 82, 80 of 256x128 in three slices 48).
-double tile_cost(const TileSpec& t, int64_t tiles, int per, int splits, bool cold) {
+// lone: 128x128 may take the price of kLone128.
+double tile_cost(const TileSpec& shape, int64_t tiles, int per, int splits, bool cold, bool lone) {
     const int64_t wgs = (tiles + 7) / 8 * splits;  // of the fullest XCD
+    const TileSpec& t = lone && shape.id == NT_128x128 && wgs <= 32 ? kLone128 : shape;
     const int log2_round = t.per_cu == 2 ? 6 : 5;  // ... and in one round of its 32 compute units
     const int64_t rounds = wgs >> log2_round, rest = wgs & ((1 << log2_round) - 1);
     const double kt = (double)per * (cold ? t.cold : 1.0);
@@ -111,7 +122,7 @@ NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, i
             if (crowds && (tiles + 7) / 8 * splits > 32) break;
             const double extra = sliced || splits > 1 ? slices_cost(M, N, splits) : 0.0;
             if (best.tile != 0 && extra >= best.cost) break;  // and more slices cost more still
-            const double cost = tile_cost(t, tiles, per, splits, cold) + extra;
+            const double cost = tile_cost(t, tiles, per, splits, cold, !sliced) + extra;
             if (best.tile == 0 || cost < best.cost) best = NtPlan{t.id, splits, cost};
         }
     }
@@ -122,7 +133,7 @@ NtPlan plan_nt(int64_t M, int64_t N, int64_t nkt, bool sliced, int min_splits, i
 double joint_cost_128(int64_t M, int64_t N, int64_t Nx, int64_t nkt) {
     auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     for (const TileSpec& t : kTiles)
-        if (t.id == NT_128x128) return tile_cost(t, cdiv(M, 128) * (cdiv(N, 128) + cdiv(Nx, 128)), (int)nkt, 1, cold_operands(M + N + Nx, nkt));
+        if (t.id == NT_128x128) return tile_cost(t, cdiv(M, 128) * (cdiv(N, 128) + cdiv(Nx, 128)), (int)nkt, 1, cold_operands(M + N + Nx, nkt), true);
     return 0.0;
 }
 

@@ -66,6 +66,16 @@ def test_plan_counts_work_groups_by_xcd(M, N, K):
     assert (tile, n) != (T256x128, 3)
 
 
+@pytest.mark.parametrize("M,N,K,sliced,want", [
+    (746, 3234, 3328, False, (T128x128, 1)), (640, 3970, 4096, False, (T128x128, 1)), (1408, 768, 5248, False, (T128x128, 3)),
+    (7808, 384, 7296, False, (T256x128, 2)), (544, 4608, 13760, False, (T256x128, 2)),  # a unit to itself, but slices are ahead
+    (768, 3035, 451, True, (T64x128, 1)), (2304, 512, 1878, True, (T64x128, 2)),        # gradients that share the launch of dx
+])
+def test_plan_prices_128x128_with_a_unit_to_itself(M, N, K, sliced, want):
+    from paper_2405_16528_amd import binding as L
+    assert L.plan_tiles(M, N, K, sliced) == want
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,out,inp,r,want", CASES)
 def test_fwd_bwd_parity(T, out, inp, r, want):
