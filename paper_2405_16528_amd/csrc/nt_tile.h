@@ -8,12 +8,13 @@
 // GEMM and keeps every VALU and LDS cycle of the inner loop for feeding the matrix cores.  The exception is the A of
 // a small weight's fold or merge (ANF4), whose whole cost is its launches.
 //
-// Work-group: 256 threads = 4 waves (2 x 2), tile BM x BN x 64, v_mfma_f32_16x16x32_bf16: the same flops per cycle and the
-// same LDS bytes as v_mfma_f32_32x32x16_bf16, the same bits, but a quarter of the accumulator registers read and written per
-// instruction (a few per cent of clock on this power-limited part) and independent accumulators for the small tiles.
+// Work-group: 4 waves that multiply (2 x 2), or 8 (2 x 4, NW), or 4 and as many that only load (LOADERS); tile BM x BN x 64,
+// v_mfma_f32_16x16x32_bf16: the same flops per cycle and the same LDS bytes as v_mfma_f32_32x32x16_bf16, the same bits, but a
+// quarter of the accumulator registers read and written per instruction (a few per cent of clock on this power-limited part) and
+// independent accumulators for the small tiles.
 //  * operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no registers, no
-//    ds_write) into a ring of NS stages.  The loads of a tile are issued one by one between the MFMAs, spread over
-//    the slots, never in a burst (the memory pipeline of a compute unit limits the requests in flight, and a
+//    ds_write) into a ring of NS stages.  Where every wave loads, the loads of a tile are issued one by one between the MFMAs, spread
+//    over the slots, never in a burst (the memory pipeline of a compute unit limits the requests in flight, and a
 //    stalled load holds back the MFMAs behind it in the in-order wave).  Loads past the end of the range fetch the last
 //    tile once more, into a stage nobody reads.  A k-tile that is not full (the last one of a K segment that is not a
 //    multiple of 64) is loaded like any other, lanes past the end fetching a valid chunk, and what lies past the end is
